@@ -189,11 +189,11 @@ int qblora_dequantize_bf16(const qblora_qweight* qw, qblora_bf16* Wt, void* stre
 
 /*
  * How qblora_linear_fwd / _bwd build the 16-bit compute weight of Eq. 1 (Alg. 1: W_tilde = dequantize(...), then
- * x @ W_tilde).  Below qblora_dense_min_tokens() tokens every 256-token tile of the contraction kernel rebuilds
- * the weight tiles it needs from codes and scales in LDS; from that many tokens on, the call first dequantizes
- * the whole weight once into a bf16 buffer inside its workspace (d_out*d_in*2 bytes; transposed for the
- * backward) and the contraction kernel copies weight tiles from there, because rebuilding a tile for each of
- * T/256 token tiles costs more than one sweep over the weight.  The values are the same bf16 numbers either
+ * x @ W_tilde).  A forward on fewer than qblora_dense_min_tokens() tokens -- one 256-token tile -- rebuilds the
+ * weight tiles it needs from codes and scales in LDS; from that many tokens on, and in every backward that produces
+ * dX, the call first dequantizes the whole weight once into a bf16 buffer inside its workspace (d_out*d_in*2 bytes;
+ * transposed for the backward) and the contraction kernel copies weight tiles from there, because rebuilding a
+ * tile for each token tile costs more than one sweep over the weight.  The values are the same bf16 numbers either
  * way (qblora_dequantize_bf16's), and so are the results bit for bit.  The buffer is scratch: nothing is kept
  * between calls, and the *_workspace_bytes() queries include it.
  */

@@ -96,14 +96,19 @@ Codebook codebook_of(const qblora_qweight* qw) {
 
 int64_t n_blocks(const qblora_qweight* qw) { return (int64_t)qw->d_out * (qw->d_in / qw->block); }
 
-// From this many tokens on, a call dequantizes the weight ONCE into a bf16 buffer in its workspace and contracts
-// that (direct copies of both operand tiles); below it, every 256-token tile rebuilds its weight tiles in LDS.
-// Rebuilding costs about a quarter of the contraction kernel's time for every token tile; the one-off pass
-// costs one sweep over the weight (0.56 B read + 2 B written per element), which 2048 tokens amortize.
-constexpr int64_t kDenseMinTokens = 2048;
-// (the contraction kernel addresses the dequantized weight with 32-bit byte offsets)
-bool use_dense(const qblora_qweight* qw, int64_t T) {
-    return (T >= kDenseMinTokens || half_blocks(qw)) && (int64_t)qw->d_out * qw->d_in * 2 < ((int64_t)1 << 32);
+// From this many tokens on, a forward call dequantizes the weight ONCE into a bf16 buffer in its workspace and
+// contracts that; below it -- a single 256-token tile -- the contraction rebuilds weight tiles in LDS, because the
+// one-off pass (0.56 B read + 2 B written per weight) and its scratch would serve one tile only.  With two token
+// tiles or more the pass pays: 11008 x 4096 at 512 tokens 20 + 58 us against 97 us, 4096 x 4096 at 1024 tokens
+// 9 + 39 against 99 us.
+constexpr int64_t kDenseMinTokens = 257;
+bool use_dense(const qblora_qweight* qw, int64_t T) { return T >= kDenseMinTokens || half_blocks(qw); }
+// The backward contracts the transposed weight, which is always dequantized once (its in-LDS form had to transpose
+// every tile on the way in: 512 x 512 at 256 tokens 19 us against 3 + 7, 4096 x 11008 at 512 tokens 239 against 20 + 85).
+
+// Calls on 2048 tokens or more, and all on 8 x 4 blocks, ask for codes on a 16-byte boundary; smaller ones never did.
+bool codes_placed(const qblora_qweight* qw, int64_t T) {
+    return (T < 2048 && !half_blocks(qw)) || (reinterpret_cast<uintptr_t>(qw->codes) & 15) == 0;
 }
 
 struct FwdSpace {
@@ -135,11 +140,11 @@ struct BwdSpace {
     int splits_a, splits_b;
     size_t bytes;
 };
-BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T, void* ws, bool dense) {
+BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T, void* ws) {
     Carver c(ws);
     BwdSpace s{};
     if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
-    if (dense) s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
+    s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
     if (has_adapter(ad)) {
         s.At_x = c.take<qblora_bf16>((size_t)ad->R * qw->d_in);
         s.Bx = c.take<qblora_bf16>((size_t)ad->R * qw->d_out);
@@ -353,7 +358,7 @@ size_t qblora_linear_fwd_workspace_bytes(const qblora_qweight* qw, const qblora_
 
 size_t qblora_linear_bwd_workspace_bytes(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T) {
     if (check_layer(qw, ad) || T < 0) return 0;
-    return carve_bwd(qw, ad, T, nullptr, use_dense(qw, T)).bytes;
+    return carve_bwd(qw, ad, T, nullptr).bytes;
 }
 
 int64_t qblora_dense_min_tokens(void) { return kDenseMinTokens; }
@@ -375,6 +380,7 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     if (!X || !Y) return QBLORA_ERR_NULL;
     const bool dense = allow_dense && use_dense(qw, T);
     if (half_blocks(qw) && !dense) return QBLORA_ERR_UNSUPPORTED;
+    if (dense && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
     FwdSpace ws = carve_fwd(qw, ad, T, workspace, dense);
     if (ws.bytes > 0 && (!workspace || workspace_bytes < ws.bytes)) return QBLORA_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
@@ -472,17 +478,15 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         return QBLORA_OK;
     }
     if (!dY || (adapted && !X)) return QBLORA_ERR_NULL;
-    const bool dense = use_dense(qw, T) && dX;
-    if (half_blocks(qw) && dX && !dense) return QBLORA_ERR_UNSUPPORTED;
-    BwdSpace ws = carve_bwd(qw, ad, T, workspace, use_dense(qw, T));
+    if (dX && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
+    BwdSpace ws = carve_bwd(qw, ad, T, workspace);
     if (ws.bytes > 0 && (!workspace || workspace_bytes < ws.bytes)) return QBLORA_ERR_WORKSPACE;
 
     GemmDesc g{};
-    g.qmode = dense ? 3 : 2;
-    g.block_rows = block_rows_of(qw);
-    if (dX && (rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
-    if (dense) {
+    g.qmode = 3;
+    if (dX) {
         // the transposed bf16 compute weight once, for all token tiles of this call
+        if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
         {
             ScopedEvents ev(QBLORA_PROFILE_DEQUANT, st);
             rc = launch_dequantize_operand(*qw, g.scales, 1, ws.W16t, st);
@@ -566,7 +570,6 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     }
     if (!dX) return QBLORA_OK;
     g.X1 = dY; g.ldx1 = qw->d_out;
-    g.codes = qw->codes; g.beta = qw->beta; g.d_out = qw->d_out; g.d_in = qw->d_in; g.cb = codebook_of(qw);
     g.C = dX; g.ldc = qw->d_in; g.out_scale = 1.0f; g.M = T; g.N = qw->d_in;
     ScopedEvents ev(QBLORA_PROFILE_BWD_GEMM, st);
     return launch_gemm(g, st);
@@ -684,7 +687,7 @@ QaBwdSpace carve_qa_bwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T,
     QaBwdSpace s{};
     const int I = qw->d_in / lam1, J = qw->d_out / lam2;
     if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
-    if (use_dense(qw, T)) s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
+    s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
     s.P = c.take<qblora_bf16>((size_t)T * I);
     s.dVs = c.take<qblora_bf16>((size_t)T * J);
     s.dVs_lo = c.take<qblora_bf16>((size_t)T * J);
@@ -727,7 +730,7 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     sct.scale_group = qw->scale_group; sct.d_out = qw->d_out; sct.d_in = qw->d_in; sct.out = ws.scales;
     const bool tile8 = block_rows_of(qw) == 8;               // 8 x 8 blocks: scales are read in place
     const bool dense = use_dense(qw, T);                     // many tokens: the weight is dequantized once
-    if (half_blocks(qw) && !dense) return QBLORA_ERR_UNSUPPORTED;
+    if (dense && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
     if (tile8 || dense) sct.out = nullptr;
     if ((rc = launch_adapter_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, st, sct.out ? &sct : nullptr))) return rc;
     if (dense) {
@@ -771,6 +774,7 @@ int qablora_linear_bwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     if (!dY || (dH && !X)) return QBLORA_ERR_NULL;
     QaBwdSpace ws = carve_qa_bwd(qw, lambda1, lambda2, T, workspace);
     if (!workspace || workspace_bytes < ws.bytes) return QBLORA_ERR_WORKSPACE;
+    if (dX && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
 
     // (s/lambda1) * sum_lambda2(dY): operand of the dX K-extension and, rescaled by lambda1 at the end, of dH
     // (there with its bf16 residual, so that only the pooled input carries a bf16 rounding)
@@ -786,18 +790,12 @@ int qablora_linear_bwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     }
     if (!dX) return QBLORA_OK;
     GemmDesc g{};
-    g.qmode = 2;
-    g.block_rows = block_rows_of(qw);
+    g.qmode = 3;
     if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
-    if (use_dense(qw, T)) {
-        if ((rc = launch_dequantize_operand(*qw, g.scales, 1, ws.W16t, st))) return rc;
-        g.qmode = 3; g.W1 = ws.W16t; g.K1 = qw->d_out;
-    } else if (half_blocks(qw)) {
-        return QBLORA_ERR_UNSUPPORTED;
-    }
+    if ((rc = launch_dequantize_operand(*qw, g.scales, 1, ws.W16t, st))) return rc;
+    g.W1 = ws.W16t; g.K1 = qw->d_out;
     g.X2 = ws.dVs; g.ldx2 = J; g.W2 = H; g.ldw2 = J; g.K2 = J; g.div2 = lambda1;
     g.X1 = dY; g.ldx1 = qw->d_out;
-    g.codes = qw->codes; g.beta = qw->beta; g.d_out = qw->d_out; g.d_in = qw->d_in; g.cb = codebook_of(qw);
     g.C = dX; g.ldc = qw->d_in; g.out_scale = 1.0f; g.M = T; g.N = qw->d_in;
     return launch_gemm(g, st);
 }

@@ -90,7 +90,7 @@ int launch_scales_reconstruct(const uint8_t* scale_codes, const float* step, con
 int launch_dequantize_bf16(const qblora_qweight& qw, const float* scales, qblora_bf16* Wt, hipStream_t st);
 // The bf16 compute weight in the order the contraction kernel's waves load it (qmode 3): for the operand
 // matrix Wop[N, K] -- the weight itself, N = d_out, K = d_in (transposed = 0), or its transpose, N = d_in,
-// K = d_out -- the 16 bytes Wop[32i + (l & 31)][16j + 8(l >> 5) .. + 7] sit at ((i*(K/16) + j)*64 + l)*16.
+// K = d_out -- the 16 bytes Wop[16i + (l & 15)][32j + 8(l >> 4) .. + 7] sit at ((i*(K/32) + j)*64 + l)*16.
 // d_out*d_in*2 bytes, 16-byte aligned; d_in % 64 == 0, d_out % 64 == 0.
 int launch_dequantize_operand(const qblora_qweight& qw, const float* scales, int transposed, qblora_bf16* Wop,
                               hipStream_t st);
@@ -115,13 +115,12 @@ int launch_adapter_prep(const qblora_bf16* A, const qblora_bf16* B, int d_in, in
 // "token" operands X1/X2 are bf16 row-major; the quantized segment is optional (qmode 0).
 struct GemmDesc {
     int qmode;                 // 0: no quantized segment; 1: forward (N = d_out, K1 = d_in);
-                               // 2: transposed use (N = d_in, K1 = d_out);
                                // 3: first segment on a bf16 weight dequantized beforehand, in operand order
     const qblora_bf16* X1; int64_t ldx1;
     const qblora_bf16* W1; int K1;                     // qmode 3 only: see launch_dequantize_operand
     const uint8_t* codes; const float* scales; const float* beta; int d_out, d_in;
-    const uint8_t* codes_tiled;            // optional tile-ordered copy (forward only)
-    const float* scales_tiled;             // optional tile-ordered scales (forward only)
+    const uint8_t* codes_tiled;            // optional tile-ordered copy
+    const float* scales_tiled;             // optional tile-ordered scales
     Codebook cb;
     const qblora_bf16* X2; int64_t ldx2;
     const qblora_bf16* W2; int64_t ldw2; int K2; int div2;
@@ -134,8 +133,10 @@ struct GemmDesc {
     int dup2;                  // qmode 0, narrow form only: 2 = W2 has K2/2 columns, column m serves k = 2m, 2m+1
 };
 int launch_gemm(const GemmDesc& d, hipStream_t st);
-// the quantized segments (qmode 1, 2) with an 8-wave 256x256 tile; called by launch_gemm
+// the quantized segment (qmode 1) with an 8-wave 256x256 tile; called by launch_gemm
 int launch_qlinear(const GemmDesc& d, hipStream_t st);
+// the contraction on a weight dequantized beforehand (qmode 3); called by launch_gemm
+int launch_dense(const GemmDesc& d, hipStream_t st);
 // narrow-output plain bf16 GEMM (qmode 0, N = inner rank); called by launch_gemm when it applies
 bool skinny_applies(const GemmDesc& d);
 bool skinny_dup_applies(int64_t M, int N, int K, int64_t ldw);

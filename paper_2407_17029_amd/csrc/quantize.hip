@@ -429,8 +429,8 @@ __global__ __launch_bounds__(256) void k_dequantize_bf16(const uint32_t* __restr
 // The bf16 compute weight in MFMA operand order (see launch_dequantize_operand): the weight itself.
 // A workgroup owns 64 stored rows x 128 inputs.  A thread dequantizes 32 inputs of one stored row (16 bytes of
 // codes; four lanes read 64 contiguous bytes of a row) into four 16-byte chunks of an LDS tile [n][16 chunks], chunk
-// c of row n at position c ^ (n & 15); operand order only regroups whole chunks -- lane l = r + 32*hi of the k slice
-// j takes chunk 2j + hi of row r -- so each wave reads its pieces back with 16-byte LDS loads (16 consecutive rows of
+// c of row n at position c ^ (n & 15); operand order only regroups whole chunks -- lane l = r + 16*g of the k slice
+// j takes chunk 4j + g of row r -- so each wave reads its pieces back with 16-byte LDS loads (16 consecutive rows of
 // one chunk lie in 16 different positions) and stores 1 KB per instruction, 4 KB contiguous per wave.  (The first form
 // let a lane load the 32 code bytes of its row's block, twice per row: both lanes of a row need every other dword;
 // it streamed at 0.60 of the HBM peak.)
@@ -496,18 +496,15 @@ __global__ __launch_bounds__(256) void k_dequantize_operand(const uint8_t* __res
     }
     __syncthreads();
     {
-        const int w = t >> 6, lane = t & 63, r = lane & 31, hi = lane >> 5;
-        const int rb = w >> 1;                                  // 32-row block of the tile
-        const int64_t nb = (int64_t)nt * 2 + rb;                // 32-row block of the weight
-        if (nb * 32 < d_out) {
-            const int64_t kb_count = d_in / 16;                 // 16-wide k slices of a row block
+        const int w = t >> 6, lane = t & 63, row = 16 * w + (lane & 15), g = lane >> 4;
+        const int64_t rb = (int64_t)nt * 4 + w;                 // 16-row block of the weight
+        if (rb * 16 < d_out) {
+            const int64_t kb_count = d_in / 32;                 // 32-wide k slices of a row block
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                const int j = (w & 1) * 4 + q;                  // slice inside the tile
-                const int64_t js = (int64_t)kt * 8 + j;
-                const int row = rb * 32 + r;
-                const uint4 o = tile[row][(2 * j + hi) ^ (row & 15)];
-                if (js < kb_count) out[(nb * kb_count + js) * 64 + lane] = o;
+                const int64_t js = (int64_t)kt * 4 + q;
+                const uint4 o = tile[row][(4 * q + g) ^ (row & 15)];
+                if (js < kb_count) out[(rb * kb_count + js) * 64 + lane] = o;
             }
         }
     }
@@ -519,9 +516,9 @@ __global__ __launch_bounds__(256) void k_dequantize_operand(const uint8_t* __res
 // 16-byte chunks into an LDS tile in the stored orientation, [n][128 k] with 256-byte rows; the transposition is
 // left to the transposing LDS read ds_read_b64_tr_b16 (a group of 16 lanes that points at 4 rows x 16 columns
 // gets, lane i, column i of the four rows): two of them give a lane the 8 consecutive n of its k that the
-// operand order wants.  Logical chunk c of row n sits at chunk position c ^ ((n & 3) << 2), so that the four
-// rows of a transposing read lie in different banks.  Each wave then stores 1 KB pieces (lane l = r + 32*hi
-// holds k = r, n = 16q + 8hi .. + 7).  (The first form read 4 bytes of codes per thread and wrote 2-byte elements
+// operand order wants.  Logical chunk c of row n sits at chunk position c ^ ((n & 3) << 2) ^ ((n & 8) >> 2), so that
+// the four rows of a transposing read, and those of the neighbouring lane group eight rows on, lie in different
+// banks.  Each wave then stores 1 KB pieces (lane l = r + 16*g holds k = r, n = 8g .. + 7 of the slice).  (The first form read 4 bytes of codes per thread and wrote 2-byte elements
 // into a [k][n] tile: 57 % of its LDS cycles were bank conflicts and it streamed at 0.49 of the HBM peak.)
 typedef __attribute__((ext_vector_type(4))) short s16x4_t;
 template <bool BETA, int GEOM>
@@ -577,30 +574,30 @@ __global__ __launch_bounds__(256) void k_dequantize_operand_t(const uint8_t* __r
                 const float cv = lut[(cw[c] >> (4 * j)) & 15];
                 v[j] = BETA ? __fmaf_rn(cv, j < 4 ? a : a_hi, j < 4 ? be : be_hi) : __fmul_rn(cv, j < 4 ? a : a_hi);
             }
-            const int pos = (4 * piece + c) ^ ((row & 3) << 2);
+            const int pos = (4 * piece + c) ^ ((row & 3) << 2) ^ ((row & 8) >> 2);
             *reinterpret_cast<uint4*>(tile + row * 256 + pos * 16) =
                 make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
         }
     }
     __syncthreads();
     {
-        const int q = t >> 6, lane = t & 63;                    // wave q: stored rows 16q .. 16q+15 of the tile
-        const int g = lane >> 4, sl = lane & 15;
-        const int frow = 8 * (g >> 1) + (sl >> 2);              // row inside the 16-row slice this lane points at
-        const int64_t kb_count = d_out / 16;                    // slices of the contraction (stored rows)
+        const int w = t >> 6, lane = t & 63, g = lane >> 4, sl = lane & 15;
+        const int s = w >> 1;                                   // 32 stored rows of the tile
+        const int frow = 8 * g + (sl >> 2);                     // row inside the 32-row slice this lane points at
+        const int64_t kb_count = d_out / 32;                    // slices of the contraction (stored rows)
 #pragma unroll
-        for (int kb = 0; kb < 4; ++kb) {                        // 32 inputs each
-            const int col = 32 * kb + 16 * (g & 1) + 4 * (sl & 3);
-            const unsigned char* p = tile + (16 * q + frow) * 256 + ((((col >> 3) ^ ((frow & 3) << 2)) & 15) << 4) +
-                                     ((col >> 2) & 1) * 8;
+        for (int q = 0; q < 4; ++q) {                           // 16 inputs each
+            const int kb = 4 * (w & 1) + q, col = 16 * kb + 4 * (sl & 3);
+            const unsigned char* p = tile + (32 * s + frow) * 256 +
+                                     ((((col >> 3) ^ ((frow & 3) << 2) ^ ((frow & 8) >> 2)) & 15) << 4) + ((col >> 2) & 1) * 8;
             const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p));
             const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p + 4 * 256));
-            const int64_t kb32 = (int64_t)kt * 4 + kb;
-            if (kb32 * 32 < d_in) {
+            const int64_t kb16 = (int64_t)kt * 8 + kb;
+            if (kb16 * 16 < d_in) {
                 uint4 o;
                 o.x = __builtin_bit_cast(uint2, lo).x; o.y = __builtin_bit_cast(uint2, lo).y;
                 o.z = __builtin_bit_cast(uint2, hi).x; o.w = __builtin_bit_cast(uint2, hi).y;
-                out[(kb32 * kb_count + (int64_t)nt * 4 + q) * 64 + lane] = o;
+                out[(kb16 * kb_count + (int64_t)nt * 2 + s) * 64 + lane] = o;
             }
         }
     }
@@ -716,9 +713,7 @@ int launch_dequantize_bf16(const qblora_qweight& qw, const float* scales, qblora
 
 int launch_dequantize_operand(const qblora_qweight& qw, const float* scales, int transposed, qblora_bf16* Wop,
                               hipStream_t st) {
-    if (qw.d_in % 64 != 0 || qw.d_out % 64 != 0 || (reinterpret_cast<uintptr_t>(Wop) & 15) ||
-        (reinterpret_cast<uintptr_t>(qw.codes) & 15))
-        return QBLORA_ERR_UNSUPPORTED;
+    if (qw.d_in % 64 != 0 || qw.d_out % 64 != 0 || (reinterpret_cast<uintptr_t>(Wop) & 15)) return QBLORA_ERR_UNSUPPORTED;
     if (qw.block_rows == 8 &&                             // four block parameters per 16-byte load
         ((reinterpret_cast<uintptr_t>(scales) & 15) || (reinterpret_cast<uintptr_t>(qw.beta) & 15)))
         return QBLORA_ERR_UNSUPPORTED;

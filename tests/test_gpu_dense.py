@@ -1,0 +1,54 @@
+"""GPU parity: the contraction on a weight dequantized once, at the edges of its tiles and of its ring of stages."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2407_17029_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# T, d_out, d_in, R: the tile shape follows from T and the output width (256 x 256, 128 x 256, 256 x 128 and 128 x 128
+# tokens x features; forward and backward differ), the number of 64-wide steps from the other width (one step up to
+# more than the ring holds), R adds none, one partial or two steps of the K-extension.
+CASES = [
+    (4100, 4096, 64, 0),       # 256 x 256, one step; backward 128 x 128, 64 steps
+    (4100, 4096, 128, 72),     # 256 x 256, two steps and a ragged extension
+    (4097, 4160, 192, 8),      # 256 x 256, one token and 64 features past a tile, three steps
+    (2048, 4096, 64, 8),       # 128 x 256, one step
+    (1930, 4032, 256, 0),      # 128 x 256, partial tiles on both sides, as many steps as stages and one more
+    (1270, 6528, 64, 0),       # 256 x 128, one step
+    (1270, 6528, 192, 72),     # 256 x 128, three steps and a ragged extension
+    (257, 64, 320, 8),         # 128 x 128, narrower than a tile
+    (300, 320, 64, 24),        # 128 x 128, fewer steps than stages
+    (1, 448, 128, 16),         # backward of one token
+]
+
+
+@pytest.mark.parametrize("T,d_out,d_in,R", CASES)
+def test_tiles_and_stages(oracle, codebook, T, d_out, d_in, R):
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
+    print(f"case dense T={T} {d_out}x{d_in} R={R}", flush=True)
+    # s*U enters the extension rounded to bf16 (relative 2^-9).  With B ~ N(0, 0.05^2) the adapter term is at most
+    # about 0.4 rms of the output even at these short contractions, 5 * 0.4 rms at its largest element, so that
+    # rounding stays below 5 * 0.4 * 2^-9 = 4e-3 rms, inside the 1e-2 bar (B ~ N(0, 0.3^2), an adapter of the
+    # output's own size with peaks of 15 rms, reached 1.1e-2 from it alone).
+    L = synth.make_layer(5100 + T + d_out, T, d_out, d_in, max(R, 8), 2, 2, b_std=0.05)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook)
+    torch.cuda.synchronize()
+    Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
+    ad = qb.Adapter(bf16_to_dev(L.A), bf16_to_dev(L.B), 2, 2, 0.5) if R else None
+    A, B, s = (L.A, L.B, 0.5) if R else (None, None, 0.0)
+    X, dY = bf16_to_dev(L.X), bf16_to_dev(L.dY)
+    Y = torch.full((T, d_out), float("nan"), dtype=torch.bfloat16, device=X.device)
+    dX = torch.full((T, d_in), float("nan"), dtype=torch.bfloat16, device=X.device)
+    qb.qblora_linear_fwd(qw, ad, X, Y=Y)
+    qb.qblora_linear_bwd(qw, ad, X, dY, need_grads=False, dX=dX)
+    torch.cuda.synchronize()
+    assert_close_bf16(Y, oracle.forward(Wt, L.X, A, B, 2, 2, s), "Y")
+    assert_close_bf16(dX, oracle.backward(Wt, L.X, L.dY, A, B, 2, 2, s)[0], "dX")
+    # the form that rebuilds weight tiles in LDS adds in the same order
+    Y2 = torch.empty_like(Y)
+    qb.qblora_linear_fwd_noalloc(qw, ad, X, Y2)
+    torch.cuda.synchronize()
+    assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
