@@ -27,8 +27,16 @@ struct Carver {
 
 bool has_adapter(const qblora_adapter* ad) { return ad && ad->A && ad->B && ad->R > 0; }
 // Whether the narrow GEMM over `width` features takes the unexpanded adapter operand (pool / repeat factor 2)
-bool pooled_pair_operand(int64_t T, int R, int width, int lam) {
-    return lam == 2 && skinny_dup_applies(T, R, width, width / 2);
+bool pooled_pair_operand(int R, int width, int lam) {
+    return lam == 2 && skinny_dup_applies(R, width, width / 2);
+}
+// Slices of s*U = s*X*At_x.  The partial sums of the forward live in Y, which the contraction behind them overwrites,
+// so that the call needs no further scratch; the backward that recomputes s*U takes the same number for the same bits.
+int su_splits(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T) {
+    return skinny_splits(T, ad->R, qw->d_in, T * qw->d_out * (int64_t)sizeof(qblora_bf16) - 16);
+}
+int du_splits(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T) {
+    return skinny_splits(T, ad->R, qw->d_out, INT64_MAX);
 }
 int scale_op_of(const qblora_adapter* ad) { return has_adapter(ad) ? ad->scale_op : QBLORA_OP_AVGPOOL_REPEAT; }
 // index map of an expanded operand for the compress / expand operator `op`
@@ -155,7 +163,10 @@ BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T
         s.dUs = c.take<qblora_bf16>((size_t)T * ad->R);
         s.splits_a = grad_splits(T, qw->d_in);
         s.splits_b = grad_splits(T, qw->d_out);
-        size_t pa = (size_t)s.splits_a * qw->d_in * ad->R, pb = (size_t)s.splits_b * qw->d_out * ad->R;
+        size_t pa = (size_t)s.splits_a * qw->d_in * ad->R;
+        // (the narrow GEMMs' partial sums share the buffer: they are added up before the gradients start)
+        pa = std::max(pa, (size_t)T * ad->R * std::max(su_splits(qw, ad, T), du_splits(qw, ad, T)));
+        size_t pb = (size_t)s.splits_b * qw->d_out * ad->R;
         s.part = c.take<float>(pa);             // dA and dB are computed in one launch: a buffer each
         s.part_b = c.take<float>(pb);
         if (scale_op_of(ad)) s.A_op = c.take<qblora_bf16>((size_t)qw->d_in * ad->R);
@@ -413,7 +424,7 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     const int op = scale_op_of(ad);
     const bool prep_adapter = adapted && op == QBLORA_OP_AVGPOOL_REPEAT;
     // lambda1 = 2: A^T stays unexpanded and the narrow GEMM uses each of its columns for two adjacent k
-    const bool dup_a = prep_adapter && pooled_pair_operand(T, ad->R, qw->d_in, ad->lambda1);
+    const bool dup_a = prep_adapter && pooled_pair_operand(ad->R, qw->d_in, ad->lambda1);
     {
         ScopedEvents ev(QBLORA_PROFILE_PREP, st);
         rc = launch_adapter_prep(prep_adapter ? ad->A : nullptr, prep_adapter ? ad->B : nullptr,
@@ -439,6 +450,7 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         qblora_bf16* su = saved ? saved : ws.U;               // kept for the backward: high part, then residual
         u.C = su; u.C_lo = saved ? saved + T * ad->R : nullptr;
         u.ldc = ad->R; u.out_scale = op ? ad->s : ad->s / (float)ad->lambda1; u.M = T; u.N = ad->R;
+        u.part = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(Y) + 15) & ~(uintptr_t)15); u.splits = su_splits(qw, ad, T);
         {
             ScopedEvents ev(QBLORA_PROFILE_ADAPTER_FWD, st);
             rc = launch_gemm(u, st);
@@ -499,9 +511,9 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         const int op = scale_op_of(ad);
         const int na = qw->d_in / ad->lambda1, nb = qw->d_out / ad->lambda2;
         // lambda = 2: the narrow GEMMs read B (and A^T) unexpanded, each column serving two adjacent features
-        const bool dup_b = op == QBLORA_OP_AVGPOOL_REPEAT && pooled_pair_operand(T, R, qw->d_out, ad->lambda2) &&
+        const bool dup_b = op == QBLORA_OP_AVGPOOL_REPEAT && pooled_pair_operand(R, qw->d_out, ad->lambda2) &&
                            (reinterpret_cast<uintptr_t>(ad->B) & 15) == 0;      // B is copied in 16-byte chunks
-        const bool dup_a = op == QBLORA_OP_AVGPOOL_REPEAT && pooled_pair_operand(T, R, qw->d_in, ad->lambda1);
+        const bool dup_a = op == QBLORA_OP_AVGPOOL_REPEAT && pooled_pair_operand(R, qw->d_in, ad->lambda1);
         if (op == QBLORA_OP_AVGPOOL_REPEAT) {
             if ((rc = launch_adapter_prep(ad->A, ad->B, dup_a ? qw->d_in / 2 : qw->d_in, qw->d_out, R,
                                           dup_a ? 1 : ad->lambda1, ad->lambda2,
@@ -524,7 +536,7 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         if (dup_b) { du.W2 = ad->B; du.ldw2 = nb; du.dup2 = 2; }
         du.C = ws.dU; du.ldc = R; du.out_scale = ad->s; du.C2 = ws.dUs; du.c2_scale = op ? 1.0f : 1.0f / (float)ad->lambda1;
         du.C_lo = want_grads ? ws.dU_lo : nullptr;
-        du.M = T; du.N = R;
+        du.M = T; du.N = R; du.part = ws.part; du.splits = du_splits(qw, ad, T);
         {
             ScopedEvents ev(QBLORA_PROFILE_ADAPTER_BWD, st);
             rc = launch_gemm(du, st);
@@ -538,6 +550,7 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
                 u.X2 = X; u.ldx2 = qw->d_in; u.W2 = ws.At_x; u.ldw2 = qw->d_in; u.K2 = qw->d_in; u.div2 = 1;
                 if (dup_a) { u.ldw2 = qw->d_in / 2; u.dup2 = 2; }
                 u.C = ws.U; u.ldc = R; u.out_scale = op ? ad->s : ad->s / (float)ad->lambda1; u.M = T; u.N = R; u.C_lo = ws.U_lo;
+                u.part = ws.part; u.splits = su_splits(qw, ad, T);
                 if ((rc = launch_gemm(u, st))) return rc;
                 su = ws.U; su_lo = ws.U_lo;
             }

@@ -16,6 +16,13 @@
 // workgroup on every CU; the two workgroups that share a token tile sit on the same XCD and the second
 // finds X in L2.  Tiles are [row][64 k] bf16 with the 16-byte chunks XOR-swizzled by
 // (row ^ row>>3) & 7, applied by choosing which global chunk a lane fetches.
+//
+// Few tokens leave most of the chip idle (512 tokens x 128 columns: 16 workgroups) while each workgroup is a serial
+// chain of barriers and LDS round trips (1000 cycles per 128 k, the matrix pipe busy for a quarter of them).  The
+// contraction is then cut into slices, one workgroup each, whose fp32 partial tiles k_skinny_reduce adds in slice
+// order.
+#include <algorithm>
+
 #include "common.h"
 
 namespace qblora {
@@ -73,12 +80,14 @@ __global__ __launch_bounds__(kThreads) void k_skinny(GemmDesc d) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     // blockIdx.x % 8 is the XCD: the column tiles of one token tile are 8 apart
     const int tiles_n = (N + BN - 1) / BN;
-    const int grp = blockIdx.x / (8 * tiles_n), within = blockIdx.x % (8 * tiles_n);
+    const int splits = d.splits > 1 ? d.splits : 1, z = blockIdx.x % splits, bid = blockIdx.x / splits;
+    const int grp = bid / (8 * tiles_n), within = bid % (8 * tiles_n);
     const int64_t m0 = ((int64_t)grp * 8 + (within & 7)) * BM;
     const int n0 = (within >> 3) * BN;
     if (m0 >= M) return;                          // the grid is rounded up to whole groups of 8 token tiles
     const int wave_n = wave % WN, wave_m = wave / WN;
-    const int nsteps = K / (kBK * kSub);
+    const int all_steps = K / (kBK * kSub), step0 = (int)((int64_t)all_steps * z / splits);
+    const int nsteps = (int)((int64_t)all_steps * (z + 1) / splits) - step0;      // at least one: splits <= all_steps
 
     // per-lane byte offsets of the copies, relative to the first row of the tile
     const int crow = lane >> 3;
@@ -95,8 +104,8 @@ __global__ __launch_bounds__(kThreads) void k_skinny(GemmDesc d) {
         if (n0 + lrow > N - 1) lrow = N - 1 - n0;
         woff[i] = (uint32_t)((int64_t)lrow * ldw * 2) + (((lane & 7) ^ crow ^ ((WC * wave + i) & 7)) << 4);
     }
-    const qblora_bf16* const x_tile = X + m0 * ldx;
-    const qblora_bf16* const w_tile = W + (int64_t)n0 * ldw;
+    const qblora_bf16* const x_tile = X + m0 * ldx + (int64_t)step0 * kSub * kBK;
+    const qblora_bf16* const w_tile = W + (int64_t)n0 * ldw + (int64_t)step0 * kSub * (kBK / kDup);
     const uint32_t lds_x = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * (8 * XC) * 128);
     const uint32_t lds_w = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * (8 * WC) * 128);
     auto issue = [&](int step) __attribute__((always_inline)) {
@@ -198,6 +207,11 @@ __global__ __launch_bounds__(kThreads) void k_skinny(GemmDesc d) {
         for (int q = 0; q < 4; ++q) {
             const int n = n0 + out_n + q * 8 + hi * 4;
             if (n >= N) continue;
+            if (splits > 1) {                     // N % 4 == 0: whole 16-byte words
+                *reinterpret_cast<float4*>(d.part + ((int64_t)z * M + m) * N + n) =
+                    make_float4(v[q * 4 + 0], v[q * 4 + 1], v[q * 4 + 2], v[q * 4 + 3]);
+                continue;
+            }
             const float v0 = v[q * 4 + 0] * out_scale, v1 = v[q * 4 + 1] * out_scale;
             const float v2 = v[q * 4 + 2] * out_scale, v3 = v[q * 4 + 3] * out_scale;
             uint2 h;
@@ -256,11 +270,38 @@ __global__ __launch_bounds__(kThreads) void k_skinny(GemmDesc d) {
 
 }  // namespace
 
+// The slices' partial tiles added in slice order, four columns of one token per thread; the same outputs as the
+// unsplit kernel's epilogue.
+__global__ __launch_bounds__(256) void k_skinny_reduce(GemmDesc d) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, plane = d.M * d.N;
+    if (i >= plane) return;
+    float4 sum = *reinterpret_cast<const float4*>(d.part + i);
+    for (int z0 = 1; z0 < d.splits; z0 += 8) {
+        float4 v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = *reinterpret_cast<const float4*>(d.part + min(z0 + u, d.splits - 1) * plane + i);
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (z0 + u < d.splits) { sum.x += v[u].x; sum.y += v[u].y; sum.z += v[u].z; sum.w += v[u].w; }
+    }
+    const int64_t m = i / d.N, o = m * d.ldc + (i - m * d.N);
+    const float v0 = sum.x * d.out_scale, v1 = sum.y * d.out_scale, v2 = sum.z * d.out_scale, v3 = sum.w * d.out_scale;
+    const uint2 h = make_uint2(pack_bf16(v0, v1), pack_bf16(v2, v3));
+    *reinterpret_cast<uint2*>(reinterpret_cast<qblora_bf16*>(d.C) + o) = h;
+    if (d.C_lo)
+        *reinterpret_cast<uint2*>(d.C_lo + o) =
+            make_uint2(pack_bf16(v0 - bf16_bits_to_float(h.x & 0xffffu), v1 - bf16_bits_to_float(h.x >> 16)),
+                       pack_bf16(v2 - bf16_bits_to_float(h.y & 0xffffu), v3 - bf16_bits_to_float(h.y >> 16)));
+    if (d.C2)
+        *reinterpret_cast<uint2*>(d.C2 + o) =
+            make_uint2(pack_bf16(v0 * d.c2_scale, v1 * d.c2_scale), pack_bf16(v2 * d.c2_scale, v3 * d.c2_scale));
+}
+
 // Whether the narrow GEMM can take W with K/2 columns, each serving two adjacent k (GemmDesc::dup2 = 2): the
 // problem must be one the k-split form with two k-steps per stage handles (at every token count: with 512 or more
 // tiles of 64 x 128 the plain form on the expanded operand measured slower, 13B layer at rank 128 21.0 -> 20.8 ms).
-bool skinny_dup_applies(int64_t /*M*/, int N, int K, int64_t ldw) {
-    return N > 64 && N % 4 == 0 && N <= 512 && K % (2 * kBK) == 0 && ldw % 8 == 0;
+bool skinny_dup_applies(int N, int K, int64_t ldw) {
+    return N >= 16 && N % 4 == 0 && N <= 512 && K % (2 * kBK) == 0 && ldw % 8 == 0;
 }
 
 // Whether launch_skinny can take this problem (otherwise the general tile kernel does).
@@ -279,15 +320,32 @@ int launch_skinny_cfg(const GemmDesc& d, hipStream_t st) {
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
     if (!attr_ok) return QBLORA_ERR_LAUNCH;
     const int64_t tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
-    dim3 grid((unsigned)((tiles_m + 7) / 8 * 8 * tiles_n));
+    const int splits = kSplitK && d.splits > 1 ? d.splits : 1;
+    dim3 grid((unsigned)((tiles_m + 7) / 8 * 8 * tiles_n * splits));
     hipLaunchKernelGGL(kern, grid, dim3(kThreads), smem, st, d);
+    if (splits > 1)
+        hipLaunchKernelGGL(k_skinny_reduce, dim3((unsigned)((d.M * d.N / 4 + 255) / 256)), dim3(256), 0, st, d);
     return launch_status();
+}
+
+// A slice keeps at least four steps of 128 k (prologue and epilogue cost about five), and the split has to save twelve
+// steps of about 0.44 us to pay for the second launch (4-5 us).  512 tokens, 128 columns: K = 4096 14.2 -> 5.5 + 4.6 us
+// in 8 slices, K = 11008 32.5 -> 6.8 + 4.6 us in 16; 1337 tokens, 64 columns, K = 5120: 22 -> 6.8 + 4.2 us in 10.
+int skinny_splits(int64_t M, int N, int K, int64_t max_part_bytes) {
+    if (M <= 0 || N <= 0 || N % 4 != 0 || N > 512 || K % (2 * kBK) != 0) return 1;
+    const int64_t wgs = ((M + 63) / 64) * ((N + 63) / 64), steps = K / (2 * kBK);
+    const int64_t s = std::min(std::min<int64_t>(256 / wgs, 16), std::min(steps / 4, max_part_bytes / (M * N * 4)));
+    return s >= 2 && steps - steps / s >= 12 ? (int)s : 1;
 }
 
 int launch_skinny(const GemmDesc& d, hipStream_t st) {
     // 64 x 128 tiles once they alone fill the chip twice over; below that 64 x 64 tiles with a deep
     // ring (a narrower output has nothing to split: 32-token tiles, 128 columns)
     const int64_t wgs = ((d.M + 63) / 64) * ((d.N + 127) / 128);
+    if (d.splits > 1) {                                                            // see skinny_splits
+        if (d.dup2 == 2) return launch_skinny_cfg<64, 64, 3, 2, true, 2>(d, st);
+        return launch_skinny_cfg<64, 64, 4, 2, true>(d, st);
+    }
     if (d.dup2 == 2) {                                                             // see skinny_dup_applies
         // 128 columns per workgroup once that still puts a workgroup on every CU: the token tile is then fetched by
         // two workgroups instead of four (65B gate projection, inner rank 256: 2.16 -> 1.44 GB through the CUs,

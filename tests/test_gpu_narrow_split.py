@@ -1,0 +1,46 @@
+"""GPU parity: the adapter's narrow GEMMs cut into slices of their contraction (few tokens, wide layers)."""
+import pytest
+import torch
+
+from paper_2407_17029_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# T, d_out, d_in, R, lambda: slices of four and more steps of 128 on both sides, steps that do not divide evenly
+CASES = [
+    (64, 2304, 2560, 16, 2),       # one token tile, 20 and 18 steps, unexpanded operand
+    (130, 2688, 2176, 24, 1),      # expanded operand, ragged tokens and columns
+    (300, 4096, 2048, 136, 4),     # three column tiles; the forward's partial sums fill part of Y only
+    (1, 2048, 3072, 8, 2),         # one token
+]
+
+
+@pytest.mark.parametrize("T,d_out,d_in,R,lam", CASES)
+def test_sliced_narrow_gemms(oracle, codebook, T, d_out, d_in, R, lam):
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, assert_close_f32, OracleWeight
+    print(f"case narrow split T={T} {d_out}x{d_in} R={R} lam={lam}", flush=True)
+    L = synth.make_layer(6100 + T + R, T, d_out, d_in, R, lam, lam)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook)
+    torch.cuda.synchronize()
+    Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
+    ad = qb.Adapter(bf16_to_dev(L.A), bf16_to_dev(L.B), lam, lam, 0.5)
+    X, dY = bf16_to_dev(L.X), bf16_to_dev(L.dY)
+    Y = qb.qblora_linear_fwd(qw, ad, X)
+    dX, dA, dB = qb.qblora_linear_bwd(qw, ad, X, dY)
+    torch.cuda.synchronize()
+    rX, rA, rB = oracle.backward(Wt, L.X, L.dY, L.A, L.B, lam, lam, 0.5)
+    assert_close_bf16(Y, oracle.forward(Wt, L.X, L.A, L.B, lam, lam, 0.5), "Y")
+    assert_close_bf16(dX, rX, "dX")
+    assert_close_f32(dA, rA, "dA")
+    assert_close_f32(dB, rB, "dB")
+    # kept and recomputed s*U, an output that is not 16-byte aligned, and the forward on the library's own scratch
+    saved = torch.empty(qb.qblora_saved_bytes(ad, T), dtype=torch.uint8, device=X.device)
+    Y2 = torch.empty(T * d_out + 2, dtype=torch.bfloat16, device=X.device)[2:].view(T, d_out)
+    qb.qblora_linear_fwd(qw, ad, X, Y=Y2, saved=saved)
+    dX2, dA2, dB2 = qb.qblora_linear_bwd(qw, ad, X, dY, saved=saved)
+    Y3 = torch.empty_like(Y)
+    qb.qblora_linear_fwd_noalloc(qw, ad, X, Y3)
+    torch.cuda.synchronize()
+    assert torch.equal(Y, Y2) and torch.equal(Y, Y3)
+    assert torch.equal(dX, dX2) and torch.equal(dA, dA2) and torch.equal(dB, dB2)
