@@ -145,7 +145,7 @@ FwdSpace carve_fwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T
 
 struct BwdSpace {
     float* scales; qblora_bf16 *At_x, *Bx, *U, *U_lo, *dU, *dU_lo, *dUs, *A_op, *Xs, *dYs, *W16t; float *part, *part_b;
-    int splits_a, splits_b;
+    int splits_a, splits_b, splits_x;
     size_t bytes;
 };
 BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T, void* ws) {
@@ -153,6 +153,10 @@ BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T
     BwdSpace s{};
     if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
     s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
+    // slices of the dX contraction: their partial sums share the gradients' buffer, which is free by then
+    s.splits_x = dense_splits(T, qw->d_in, qw->d_out, has_adapter(ad) ? ad->R : 0);
+    const size_t px = s.splits_x > 1 ? (size_t)s.splits_x * T * qw->d_in : 0;
+    if (!has_adapter(ad) && px) s.part = c.take<float>(px);
     if (has_adapter(ad)) {
         s.At_x = c.take<qblora_bf16>((size_t)ad->R * qw->d_in);
         s.Bx = c.take<qblora_bf16>((size_t)ad->R * qw->d_out);
@@ -163,7 +167,7 @@ BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T
         s.dUs = c.take<qblora_bf16>((size_t)T * ad->R);
         s.splits_a = grad_splits(T, qw->d_in);
         s.splits_b = grad_splits(T, qw->d_out);
-        size_t pa = (size_t)s.splits_a * qw->d_in * ad->R;
+        size_t pa = std::max(px, (size_t)s.splits_a * qw->d_in * ad->R);
         // (the narrow GEMMs' partial sums share the buffer: they are added up before the gradients start)
         pa = std::max(pa, (size_t)T * ad->R * std::max(su_splits(qw, ad, T), du_splits(qw, ad, T)));
         size_t pb = (size_t)s.splits_b * qw->d_out * ad->R;
@@ -584,6 +588,7 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     if (!dX) return QBLORA_OK;
     g.X1 = dY; g.ldx1 = qw->d_out;
     g.C = dX; g.ldc = qw->d_in; g.out_scale = 1.0f; g.M = T; g.N = qw->d_in;
+    g.part = ws.part; g.splits = ws.splits_x;
     ScopedEvents ev(QBLORA_PROFILE_BWD_GEMM, st);
     return launch_gemm(g, st);
 }
@@ -694,7 +699,7 @@ QaFwdSpace carve_qa_fwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T,
     return s;
 }
 
-struct QaBwdSpace { float* scales; qblora_bf16 *P, *dVs, *dVs_lo, *W16t; float* part; int splits; size_t bytes; };
+struct QaBwdSpace { float* scales; qblora_bf16 *P, *dVs, *dVs_lo, *W16t; float* part; int splits, splits_x; size_t bytes; };
 QaBwdSpace carve_qa_bwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T, void* ws) {
     Carver c(ws);
     QaBwdSpace s{};
@@ -705,7 +710,8 @@ QaBwdSpace carve_qa_bwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T,
     s.dVs = c.take<qblora_bf16>((size_t)T * J);
     s.dVs_lo = c.take<qblora_bf16>((size_t)T * J);
     s.splits = grad_splits(T, I, J);
-    s.part = c.take<float>((size_t)s.splits * I * J);
+    s.splits_x = dense_splits(T, qw->d_in, qw->d_out, J);
+    s.part = c.take<float>(std::max((size_t)s.splits * I * J, s.splits_x > 1 ? (size_t)s.splits_x * T * qw->d_in : 0));
     s.bytes = c.off;
     return s;
 }
@@ -810,6 +816,7 @@ int qablora_linear_bwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     g.X2 = ws.dVs; g.ldx2 = J; g.W2 = H; g.ldw2 = J; g.K2 = J; g.div2 = lambda1;
     g.X1 = dY; g.ldx1 = qw->d_out;
     g.C = dX; g.ldc = qw->d_in; g.out_scale = 1.0f; g.M = T; g.N = qw->d_in;
+    g.part = ws.part; g.splits = ws.splits_x;
     return launch_gemm(g, st);
 }
 

@@ -131,14 +131,16 @@ struct GemmDesc {
     int64_t M; int N;
     int block_rows;            // rows of a quantization block: 0/1 = 64 inputs of one row, 8 = 8 rows x 8 inputs
     int dup2;                  // qmode 0, narrow form only: 2 = W2 has K2/2 columns, column m serves k = 2m, 2m+1
-    float* part; int splits;   // qmode 0, narrow form only: splits > 1 = the contraction in that many workgroup slices,
-                               // fp32 [splits][M][N] partial sums in `part` (skinny_splits, 16-byte aligned)
+    float* part; int splits;   // qmode 0 (narrow form) and 3: splits > 1 = the contraction in that many workgroup slices,
+                               // fp32 [splits][M][N] partial sums in `part` (skinny_splits, dense_splits; 16-byte aligned)
 };
 int launch_gemm(const GemmDesc& d, hipStream_t st);
 // the quantized segment (qmode 1) with an 8-wave 256x256 tile; called by launch_gemm
 int launch_qlinear(const GemmDesc& d, hipStream_t st);
 // the contraction on a weight dequantized beforehand (qmode 3); called by launch_gemm
 int launch_dense(const GemmDesc& d, hipStream_t st);
+// slices of the contraction that pay for an [M, N] output over k1 + k2 (GemmDesc::splits; 1 = none)
+int dense_splits(int64_t M, int N, int k1, int k2);
 // narrow-output plain bf16 GEMM (qmode 0, N = inner rank); called by launch_gemm when it applies
 bool skinny_applies(const GemmDesc& d);
 bool skinny_dup_applies(int N, int K, int64_t ldw);

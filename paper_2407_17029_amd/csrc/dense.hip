@@ -81,7 +81,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
     const int64_t M = d.M;
     const int N = d.N, K2 = d.K2, div2 = d.div2;
-    const int steps1 = d.K1 / kBK, n = steps1 + (K2 + kBK - 1) / kBK;
+    const int all_steps = d.K1 / kBK + (K2 + kBK - 1) / kBK;
     const int64_t ldx2 = d.ldx2, ldw2 = d.ldw2;
     const qblora_bf16* const X2 = d.X2;
     const qblora_bf16* const W2 = d.W2;
@@ -94,11 +94,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // Tile assignment: workgroup ids go to the XCDs round-robin; each XCD gets a contiguous range of tiles, grouped
     // along tokens so that the tiles it runs at a time share token and weight panels in its L2.
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN, ntiles = tiles_m * tiles_n;
+    const int splits = d.splits > 1 ? d.splits : 1;
     int L;
     {
-        const int xcd = blockIdx.x & 7, q = ntiles >> 3, rem = ntiles & 7;
+        const int units = ntiles * splits, xcd = blockIdx.x & 7, q = units >> 3, rem = units & 7;
         L = xcd * q + min(xcd, rem) + (blockIdx.x >> 3);
     }
+    // slice z of the contraction (all tiles of a slice are neighbours): n steps from step0 on, at least one
+    int z = 0, step0 = 0, n = all_steps;
+    if (splits > 1) {
+        z = L / ntiles;
+        step0 = all_steps * z / splits;
+        n = all_steps * (z + 1) / splits - step0;
+        L -= z * ntiles;
+    }
+    const int steps1 = d.K1 / kBK - step0;        // steps from here on that belong to the first segment (may be negative)
     constexpr int GM = 4;
     const int in_group = GM * tiles_n, first_m = (L / in_group) * GM, gsize = min(tiles_m - first_m, GM);
     const int64_t m0 = (int64_t)(first_m + (L % in_group) % gsize) * BM;
@@ -113,7 +123,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // collide in pairs: 19 % of the kernel's cycles.)
     uint32_t xoff[MB / 2][2];
     int xchunk[2];
-    const qblora_bf16* const x_tile = d.X1 + m0 * d.ldx1;
+    const qblora_bf16* const x_tile = d.X1 + m0 * d.ldx1 + (int64_t)step0 * kBK;
 #pragma unroll
     for (int i = 0; i < 2; ++i) xchunk[i] = (lane & 7) ^ (4 * i + (lane >> 4));
     auto token_row = [&](int p, int i) __attribute__((always_inline)) {          // tile row, clamped to the last token
@@ -131,7 +141,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int a = 0; a < NB; ++a) {
         wblk[a] = min(n0 / 32 + (wave >> 1) * NB + a, blocks32 - 1);    // rows past N: any block, results never stored
-        wbase[a] = reinterpret_cast<const unsigned char*>(d.W1) + (int64_t)(2 * wblk[a] + (wave & 1)) * (d.K1 / 32) * 1024;
+        wbase[a] = reinterpret_cast<const unsigned char*>(d.W1) + (int64_t)(2 * wblk[a] + (wave & 1)) * (d.K1 / 32) * 1024 + (int64_t)step0 * 2048;
     }
     const uint32_t lane16 = (uint32_t)lane * 16u;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
@@ -342,6 +352,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // LDS is free: no copy under way, no wave reading
 
     // ---- epilogue -----------------------------------------------------------------------------------------
+    if (splits > 1) {                                                // partial sums: 4 features of one token per lane
+        float* const part = d.part + (int64_t)z * M * N;
+#pragma unroll
+        for (int b = 0; b < 2 * MB; ++b) {
+            const int64_t m = m0 + wm * 32 * MB + 16 * b + r;
+#pragma unroll
+            for (int a = 0; a < 2 * NB; ++a) {
+                const int nn = n0 + wn * 32 * NB + 16 * a + 4 * g;
+                if (m < M && nn < N) *reinterpret_cast<f32x4*>(part + m * N + nn) = acc[a][b];
+            }
+        }
+        return;
+    }
     // A lane holds features n..n+3 of one token per accumulator.  The wave lays its part out in LDS as bf16
     // rows and reads it back 16 bytes a lane, so that a store instruction writes whole row segments.
     {
@@ -371,6 +394,29 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
+// The slices' partial sums added in slice order, eight features of one token per thread.
+__global__ __launch_bounds__(256) void k_dense_reduce(GemmDesc d) {
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 8, plane = d.M * d.N;
+    if (i >= plane) return;
+    f32x4 lo = {0.0f, 0.0f, 0.0f, 0.0f}, hi = lo;
+    for (int z0 = 0; z0 < d.splits; z0 += 4) {
+        f32x4 v[4][2];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const f32x4* src = reinterpret_cast<const f32x4*>(d.part + min(z0 + u, d.splits - 1) * plane + i);
+            v[u][0] = src[0]; v[u][1] = src[1];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (z0 + u < d.splits) { lo += v[u][0]; hi += v[u][1]; }
+    }
+    const int64_t m = i / d.N;
+    const float s = d.out_scale;
+    *reinterpret_cast<uint4*>(reinterpret_cast<qblora_bf16*>(d.C) + m * d.ldc + (i - m * d.N)) =
+        make_uint4(pack_bf16(lo[0] * s, lo[1] * s), pack_bf16(lo[2] * s, lo[3] * s),
+                   pack_bf16(hi[0] * s, hi[1] * s), pack_bf16(hi[2] * s, hi[3] * s));
+}
+
 template <int MB, int NB>
 int launch_cfg(const GemmDesc& d, hipStream_t st) {
     auto kern = k_dense<MB, NB>;
@@ -380,11 +426,48 @@ int launch_cfg(const GemmDesc& d, hipStream_t st) {
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
     if (!attr_ok) return QBLORA_ERR_LAUNCH;
     const int64_t tiles = ((d.M + 64 * MB - 1) / (64 * MB)) * ((d.N + 128 * NB - 1) / (128 * NB));
-    hipLaunchKernelGGL(kern, dim3((unsigned)tiles), dim3(kThreads), smem, st, d);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * (d.splits > 1 ? d.splits : 1))), dim3(kThreads), smem, st, d);
+    if (d.splits > 1)
+        hipLaunchKernelGGL(k_dense_reduce, dim3((unsigned)((d.M * d.N / 8 + 255) / 256)), dim3(256), 0, st, d);
     return launch_status();
 }
 
+// Tile shape (and slices) by the estimated time.  `full` is the measured time of a k-step with every CU busy, `few`
+// with a few (the clock is power-limited: 1.5-1.7 GHz with all matrix pipes busy, 2.4 with few), both in ns; a last
+// round of workgroups (256, one per CU) that is not full lies in between.  Larger tiles move fewer bytes per MFMA
+// (256 x 256 runs at 0.82-0.89 of the matrix pipe, 128 x 128 at 0.42: copies into LDS are its limit) and need more
+// tiles to fill the chip.  T x N x K, us for 256x256 / 128x256 / 256x128 / 128x128: 512 x 4096 x 11008 179 / 130 /
+// 131 / 87; 512 x 11008 x 4096 77 / 61 / 60 / 76; 1337 x 5120 x 5120 94 / 71 / 74 / 90; 2500 x 5120 x 13824 263 / 350 /
+// 358 / 439; 8192 x 4096 x 4096 192 / 233 / 238 / 285.  A slice adds its fp32 partial tile, written and read once, and
+// all of them the second launch: 512 x 4096 x 11008 91 -> 54 + 7 us (128 x 256, four slices), 300 x 2048 x 6144 51 ->
+// 19 + 4 (five), 128 x 4096 x 4096 35 -> 14 + 5 (five).
+struct Plan { int shape, splits; };
+Plan plan(int64_t M, int N, int k1, int k2, int max_splits) {
+    struct Shape { int bm, bn; int64_t few, full; };
+    static constexpr Shape shapes[4] = {{256, 256, 940, 1460}, {128, 256, 800, 920}, {256, 128, 800, 930}, {128, 128, 490, 570}};
+    const int64_t steps = k1 / kBK + (k2 + kBK - 1) / kBK;
+    Plan best{0, 1};
+    int64_t best_ns = INT64_MAX;
+    for (int i = 0; i < 4; ++i) {
+        const int64_t tiles = ((M + shapes[i].bm - 1) / shapes[i].bm) * ((N + shapes[i].bn - 1) / shapes[i].bn);
+        for (int s = 1; s <= max_splits && (s == 1 || (tiles * s <= 256 && steps >= 4 * s)); ++s) {
+            const int64_t units = tiles * s, last = units % 256;
+            const int64_t step_ns = units / 256 * shapes[i].full +
+                                    (last ? shapes[i].few + (shapes[i].full - shapes[i].few) * last / 256 : 0);
+            int64_t ns = step_ns * ((steps + s - 1) / s);
+            if (s > 1) ns += 5000 + M * N * 8 * s / 4000;        // bytes at 4 TB/s
+            if (ns < best_ns) { best_ns = ns; best = Plan{i, s}; }
+        }
+    }
+    return best;
+}
+
 }  // namespace
+
+int dense_splits(int64_t M, int N, int k1, int k2) {
+    if (M <= 0 || N <= 0 || N % 8 != 0) return 1;
+    return plan(M, N, k1, k2, 8).splits;
+}
 
 int launch_dense(const GemmDesc& d, hipStream_t st) {
     if (d.M <= 0 || d.N <= 0) return QBLORA_OK;
@@ -392,25 +475,9 @@ int launch_dense(const GemmDesc& d, hipStream_t st) {
     if (d.out_f32 || d.C2 || d.C_lo || !d.W1 || d.K1 <= 0 || d.K1 % kBK != 0 || d.N % 32 != 0 ||
         (reinterpret_cast<uintptr_t>(d.W1) & 15))
         return QBLORA_ERR_UNSUPPORTED;
-    // Tile shape by the estimated time of a k-step over all rounds of 256 workgroups (one per CU).  `full` is the
-    // measured time of a step with every CU busy, `few` with a few (the clock is power-limited: 1.5-1.7 GHz with all
-    // matrix pipes busy, 2.4 with few), both in ns; a last round that is not full lies in between.  Larger tiles move
-    // fewer bytes per MFMA (256 x 256 runs at 0.82-0.89 of the matrix pipe, 128 x 128 at 0.42: 64 B/clk into LDS is
-    // its limit) and need more tiles to fill the chip.  T x N x K, us for 256x256 / 128x256 / 256x128 / 128x128:
-    // 512 x 4096 x 11008 179 / 130 / 131 / 87; 512 x 11008 x 4096 77 / 61 / 60 / 76; 1337 x 5120 x 5120 94 / 71 / 74 / 90;
-    // 2500 x 5120 x 13824 263 / 350 / 358 / 439; 8192 x 4096 x 4096 192 / 233 / 238 / 285.
-    struct Shape { int bm, bn; int64_t few, full; };
-    static constexpr Shape shapes[4] = {{256, 256, 940, 1460}, {128, 256, 800, 920}, {256, 128, 800, 930}, {128, 128, 490, 570}};
-    int best = 0;
-    int64_t best_cost = INT64_MAX;
-    for (int i = 0; i < 4; ++i) {
-        const int64_t tiles = ((d.M + shapes[i].bm - 1) / shapes[i].bm) * ((d.N + shapes[i].bn - 1) / shapes[i].bn);
-        const int64_t last = tiles % 256;
-        const int64_t cost = tiles / 256 * shapes[i].full +
-                             (last ? shapes[i].few + (shapes[i].full - shapes[i].few) * last / 256 : 0);
-        if (cost < best_cost) { best_cost = cost; best = i; }
-    }
-    switch (best) {
+    const Plan p = plan(d.M, d.N, d.K1, d.K2, d.splits > 1 ? 8 : 1);
+    if (d.splits > 1 && p.splits != d.splits) return QBLORA_ERR_UNSUPPORTED;       // not what dense_splits said
+    switch (p.shape) {
         case 0: return launch_cfg<4, 2>(d, st);
         case 1: return launch_cfg<2, 2>(d, st);
         case 2: return launch_cfg<4, 1>(d, st);

@@ -21,6 +21,9 @@ CASES = [
     (257, 64, 320, 8),         # 128 x 128, narrower than a tile
     (300, 320, 64, 24),        # 128 x 128, fewer steps than stages
     (1, 448, 128, 16),         # backward of one token
+    (200, 2112, 192, 72),      # backward in slices of 128 x 128 tiles, the last one with the ragged extension
+    (1000, 4160, 448, 0),      # backward in slices, no adapter, partial tiles on both sides
+    (513, 8256, 2048, 8),      # backward in slices of 128 x 256 tiles
 ]
 
 
