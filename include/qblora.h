@@ -252,7 +252,7 @@ int qblora_linear_bwd_saved(const qblora_qweight* qw, const qblora_adapter* ad, 
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, checks and results (bit
  * for bit) as qblora_linear_fwd, but the scratch is an array of QBLORA_NOALLOC_SCRATCH_BYTES bytes inside the
  * library's device image (each GPU the library runs on holds it until the process ends) instead of a caller
- * workspace; the call allocates nothing.  It always takes the form that rebuilds weight tiles in LDS (whose
+ * workspace; the call allocates nothing.  It always takes a form that rebuilds weights from the codes (whose
  * scratch is the adapter operands, s*U and the re-ordered block scales: 4.5 MiB for the LLaMA-7B attention
  * projection at T = 8192, rank 64); a problem whose scratch in that form exceeds qblora_noalloc_scratch_bytes()
  * is rejected with QBLORA_ERR_WORKSPACE and nothing is enqueued.  All calls on one GPU share that GPU's array:

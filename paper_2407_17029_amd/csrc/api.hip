@@ -402,7 +402,8 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     const bool adapted = has_adapter(ad);
 
     GemmDesc g{};
-    g.qmode = dense ? 3 : 1;
+    const bool few = !dense && few_applies(T, qw->d_out, qw->d_in);
+    g.qmode = dense ? 3 : few ? 2 : 1;
     // one launch re-orders the block scales for the forward kernel (reconstructing grouped ones) and,
     // with an adapter, builds its K-contiguous operands
     ScaleTiling sct{};
@@ -413,6 +414,10 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     g.scales = nullptr; g.scales_tiled = ws.scales;
     g.block_rows = block_rows_of(qw);
     if (g.block_rows == 8) { sct.out = nullptr; g.scales = qw->scales; g.scales_tiled = nullptr; }   // read in place
+    if (few) {                                            // reads the scales where they are
+        sct.out = nullptr; g.scales_tiled = nullptr;
+        if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
+    }
     if (dense) {
         // the weight once, as the bf16 compute weight of Eq. 1, for all token tiles of this call
         sct.out = nullptr;
@@ -749,8 +754,9 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     sct.scale_group = qw->scale_group; sct.d_out = qw->d_out; sct.d_in = qw->d_in; sct.out = ws.scales;
     const bool tile8 = block_rows_of(qw) == 8;               // 8 x 8 blocks: scales are read in place
     const bool dense = use_dense(qw, T);                     // many tokens: the weight is dequantized once
+    const bool few = !dense && few_applies(T, qw->d_out, qw->d_in);
     if (dense && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
-    if (tile8 || dense) sct.out = nullptr;
+    if (tile8 || dense || few) sct.out = nullptr;
     if ((rc = launch_adapter_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, st, sct.out ? &sct : nullptr))) return rc;
     if (dense) {
         const float* plain = nullptr;
@@ -765,6 +771,10 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     g.scales = nullptr; g.scales_tiled = ws.scales;
     if (tile8) { g.scales = qw->scales; g.scales_tiled = nullptr; g.block_rows = 8; }
     if (dense) { g.qmode = 3; g.W1 = ws.W16; g.K1 = qw->d_in; }
+    if (few) {
+        g.qmode = 2; g.scales_tiled = nullptr;
+        if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
+    }
     g.X2 = ws.P; g.ldx2 = I; g.W2 = ws.Ht; g.ldw2 = I; g.K2 = I; g.div2 = lambda2;
     g.X1 = X; g.ldx1 = qw->d_in;
     g.codes = qw->codes; g.beta = qw->beta; g.d_out = qw->d_out; g.d_in = qw->d_in; g.cb = codebook_of(qw);

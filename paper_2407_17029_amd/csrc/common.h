@@ -115,6 +115,7 @@ int launch_adapter_prep(const qblora_bf16* A, const qblora_bf16* B, int d_in, in
 // "token" operands X1/X2 are bf16 row-major; the quantized segment is optional (qmode 0).
 struct GemmDesc {
     int qmode;                 // 0: no quantized segment; 1: forward (N = d_out, K1 = d_in);
+                               // 2: the same for at most kFewTokens tokens;
                                // 3: first segment on a bf16 weight dequantized beforehand, in operand order
     const qblora_bf16* X1; int64_t ldx1;
     const qblora_bf16* W1; int K1;                     // qmode 3 only: see launch_dequantize_operand
@@ -137,6 +138,10 @@ struct GemmDesc {
 int launch_gemm(const GemmDesc& d, hipStream_t st);
 // the quantized segment (qmode 1) with an 8-wave 256x256 tile; called by launch_gemm
 int launch_qlinear(const GemmDesc& d, hipStream_t st);
+// the quantized segment for few tokens (qmode 2), from row-major codes and fp32 scales; called by launch_gemm
+constexpr int kFewTokens = 256;
+bool few_applies(int64_t M, int N, int K);
+int launch_few(const GemmDesc& d, hipStream_t st);
 // the contraction on a weight dequantized beforehand (qmode 3); called by launch_gemm
 int launch_dense(const GemmDesc& d, hipStream_t st);
 // slices of the contraction that pay for an [M, N] output over k1 + k2 (GemmDesc::splits; 1 = none)

@@ -1,0 +1,44 @@
+"""GPU parity: the forward for at most 256 tokens whose waves split the contraction, at the edges of its tiles."""
+import pytest
+import torch
+
+from paper_2407_17029_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# T, d_out, d_in, R, format: 32 x 32, 32 x 64 and 64 x 64 tiles; fewer steps than waves, one, and a ragged last round
+CASES = [
+    (1, 64, 64, 0, "nf4"),
+    (33, 128, 576, 8, "nf4"),           # ragged tokens, nine steps, extension in the tenth
+    (256, 576, 448, 136, "grouped"),    # seven steps, three extension steps, the last one partial
+    (31, 8256, 1088, 72, "minmax"),     # 32 x 64
+    (130, 4160, 704, 24, "tile8"),      # 64 x 64, ragged tokens
+    (130, 4160, 640, 0, "tile8_nf4"),
+]
+
+
+@pytest.mark.parametrize("T,d_out,d_in,R,fmt", CASES)
+def test_waves_split_the_contraction(oracle, codebook, T, d_out, d_in, R, fmt):
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
+    print(f"case few T={T} {d_out}x{d_in} R={R} {fmt}", flush=True)
+    L = synth.make_layer(7100 + T + d_out, T, d_out, d_in, max(R, 8), 2, 2)
+    br = 8 if fmt.startswith("tile8") else 1
+    minmax, grouped = fmt in ("minmax", "tile8"), fmt == "grouped"
+    if minmax:
+        qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_MINMAX_INT4, block_rows=br)
+    else:
+        qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook,
+                                          qb.SCALES_E4M3_GROUPED if grouped else qb.SCALES_FP32, block_rows=br)
+    torch.cuda.synchronize()
+    Wt = OracleWeight(oracle, L.W, codebook, minmax, grouped, br).assert_same(qw).dequantize(oracle, 2)
+    ad = qb.Adapter(bf16_to_dev(L.A), bf16_to_dev(L.B), 2, 2, 0.5) if R else None
+    A, B, s = (L.A, L.B, 0.5) if R else (None, None, 0.0)
+    X = bf16_to_dev(L.X)
+    Y = torch.full((T, d_out), float("nan"), dtype=torch.bfloat16, device=X.device)
+    qb.qblora_linear_fwd(qw, ad, X, Y=Y)
+    Y2 = torch.empty_like(Y)
+    qb.qblora_linear_fwd_noalloc(qw, ad, X, Y2)
+    torch.cuda.synchronize()
+    assert_close_bf16(Y, oracle.forward(Wt, L.X, A, B, 2, 2, s), "Y")
+    assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
