@@ -352,10 +352,10 @@ int qblora_merge_bf16(const qblora_qweight* base, const float* H, int32_t lambda
  * 16 bits; for the integer codebook of INT4 models bf16(c) = c and the result is Eq. 1 contracted in
  * fp32.  It differs from qblora_linear_fwd without adapter (which contracts the bf16-rounded weight)
  * by that rounding only.
- * 16 < T <= 256 (mid batch: prefill chunks, batched decode), in chunks of at most 128 tokens:
+ * 16 < T <= 256 (mid batch: prefill chunks, batched decode):
  *   Y[t,n] = sum_k X[t,k] * bf16( c[code[n,k]] * alpha (+ beta) ),
  * the arithmetic of qblora_linear_fwd without adapter (Eq. 1 rounded once to the bf16 compute weight, fp32
- * accumulation), on token tiles of 32 / 64 / 128 with the input dimension split over workgroups; the fp32
+ * accumulation), on token tiles of 32 / 64 / 128 / 192 / 256 with the input dimension split over workgroups; the fp32
  * partial tiles of the splits are added in a fixed order (reproducible bit for bit).
  *   X bf16 [T, d_in], 16-byte aligned; Y bf16 [T, d_out], fully overwritten.
  *   workspace: T <= 16: qblora_linear_decode_workspace_bytes() bytes (non-zero only for grouped scales, and

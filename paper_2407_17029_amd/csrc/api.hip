@@ -932,8 +932,7 @@ namespace {
 
 struct DecodePack { uint8_t* codes; float* scales; float* beta; size_t bytes; };
 constexpr int32_t kDecodeMaxTokens = 16;     // up to here: the streaming kernel that scales block sums
-constexpr int32_t kMidChunk = 128;           // above: the bf16 compute weight, at most this many tokens per launch
-constexpr int32_t kMidMaxTokens = 256;
+constexpr int32_t kMidMaxTokens = 256;       // up to here: the bf16 compute weight, one launch
 
 // An INT4 model in 64-blocks (codebook exactly 0, 1, ..., 15 and offsets present): its pack holds the codes
 // with the nibbles of every dword regrouped for the table-free decode kernel.  Pack and decode both decide
@@ -996,9 +995,9 @@ size_t qblora_linear_decode_workspace_bytes(const qblora_qweight* qw) {
 }
 size_t qblora_linear_decode_tokens_workspace_bytes(const qblora_qweight* qw, int32_t T) {
     if (check_qweight(qw, false, true)) return 0;
-    size_t part = 0;
-    for (int32_t t0 = (kDecodeMaxTokens < T || half_blocks(qw)) ? 0 : T; t0 < T; t0 += kMidChunk)   // chunks of the mid-batch form
-        part = std::max(part, w4_mid_part_bytes(qw->d_out, qw->d_in, std::min(kMidChunk, T - t0)));
+    // (queries beyond the largest batch answer for the largest)
+    const bool mid = T > kDecodeMaxTokens || (T > 0 && half_blocks(qw));
+    const size_t part = mid ? w4_mid_part_bytes(qw->d_out, qw->d_in, std::min(T, kMidMaxTokens)) : 0;
     return qblora_linear_decode_workspace_bytes(qw) + align_up(part);
 }
 int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblora_bf16* X, int32_t T, qblora_bf16* Y,
@@ -1036,15 +1035,9 @@ int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblor
         return launch_w4_decode(codes, scales, beta, codebook_of(qw), pack ? 1 : 0, qw->d_out, qw->d_in, X, T, Y, st,
                                 block_rows_of(qw), regrouped);
     float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + scale_bytes);
-    for (int32_t t0 = 0; t0 < T; t0 += kMidChunk) {
-        const int32_t tc = std::min(kMidChunk, T - t0);
-        if ((rc = launch_w4_mid(codes, scales, beta, codebook_of(qw), pack ? 1 : 0, qw->d_out, qw->d_in,
-                                X + (int64_t)t0 * qw->d_in, tc, Y + (int64_t)t0 * qw->d_out,
-                                w4_mid_part_bytes(qw->d_out, qw->d_in, tc) ? part : nullptr, st, block_rows_of(qw), regrouped,
-                                block_rows_of(qw) == 8 ? block_cols_of(qw) : 8)))
-            return rc;
-    }
-    return QBLORA_OK;
+    return launch_w4_mid(codes, scales, beta, codebook_of(qw), pack ? 1 : 0, qw->d_out, qw->d_in, X, T, Y,
+                         w4_mid_part_bytes(qw->d_out, qw->d_in, T) ? part : nullptr, st, block_rows_of(qw), regrouped,
+                         block_rows_of(qw) == 8 ? block_cols_of(qw) : 8);
 }
 
 }  // extern "C"

@@ -1,5 +1,5 @@
 // Mid-batch forward of a 4-bit block-quantized layer without adapter (merged-model inference, Sec. 3.3, with
-// a few dozen to 128 tokens in flight; larger batches are cut into chunks of 128 by the caller):
+// a few dozen to 256 tokens in flight):
 //
 //   Y[t, n] = sum_k X[t, k] * w~[n, k],   w~ = bf16( c[code] * alpha (+ beta) )   (Eq. 1, the bf16 compute
 //                                                                                  weight of the training forward)
@@ -8,7 +8,7 @@
 // of codes + the block parameters per weight) sets the time and at 128 tokens the MFMAs do.  A token tile of
 // 256 (the training kernel) would waste most of its MFMAs here and, with one workgroup per 256 output rows,
 // leave most of the chip idle.  Here a workgroup of 4 waves owns 128 output rows (32 per wave), ALL tokens
-// (32 * TB of them, TB = 1, 2, 4) and one slice of the input dimension; the slices of a row tile (split-K, as
+// (32 * TB of them, TB = 1, 2, 4, 6, 8) and one slice of the input dimension; the slices of a row tile (split-K, as
 // many as it takes to put two workgroups on every CU) write fp32 partial tiles that a second kernel adds in
 // slice order (deterministic).
 //
@@ -22,6 +22,11 @@
 // operations of the loop are issued from assembly statements three steps ahead (codes: four) and counted by
 // hand (the compiler would tie every LDS access to them): a step waits until only the two youngest batches are
 // outstanding.  The operands of step s+1 are built between the MFMAs of step s.
+//
+// Above 128 tokens one launch reads and dequantizes every weight once for all of them (two chunks of 128 did it twice;
+// token fragments are read two MFMAs ahead: with one wave per SIMD one was not enough, 62 -> 47 us).  us of the
+// contraction and the sum of the slices, before (two chunks) / now: 201 tokens 5120 x 13824 63 + 10 / 47 + 5, 256 tokens
+// 11008 x 4096 46 + 15 / 41 + 6, 256 tokens 22016 x 8192 133 + 13 / 136, 130 tokens 4096 x 4096 23 + 9 / 18 + 4.
 //
 // A lane ends up with 4 consecutive output rows of one token per accumulator quad and stores them as one
 // 8-byte word (bf16) or one 16-byte word (fp32 partials).
@@ -242,28 +247,28 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     };
     // One step: the 4 * TB MFMAs on this step's operands `wf`, and between them the units that build the next
     // step's operands `wn` from slot `sl` -- written in issue order and fenced after every MFMA: a wave issues in
-    // order, so vector work has to sit between the MFMAs to run in their shadow.  LDS reads are issued one MFMA
+    // order, so vector work has to sit between the MFMAs to run in their shadow.  LDS reads are issued kAhead MFMAs
     // (token fragment) or one unit (table pair) ahead of their use.
     auto step = [&](const bf16x8 (&wf)[4], int stage, const Slot<BR>& sl, bf16x8 (&wn)[4]) __attribute__((always_inline)) {
-        constexpr int M = 4 * TB, U = 16 / M;
+        constexpr int M = 4 * TB, kAhead = 2;
         const unsigned char* xs = sX + stage * kStageBytes;
         const Params p = params(sl);
         uint32_t o[16];
         float2 tv[2] = {make_float2(0.f, 0.f), make_float2(0.f, 0.f)};
-        bf16x8 xf[2];
+        bf16x8 xf[kAhead];
         auto read_x = [&](int m) __attribute__((always_inline)) {
             return *reinterpret_cast<const bf16x8*>(xs + (f_off[m % TB] ^ ((m / TB) << 4)));
         };
         unit_a(p, 0, tv[0]);
-        xf[0] = read_x(0);
+#pragma unroll
+        for (int m = 0; m < kAhead; ++m) xf[m] = read_x(m);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-            if (m + 1 < M) xf[(m + 1) & 1] = read_x(m + 1);
-            acc[m % TB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[m / TB], xf[m & 1], acc[m % TB], 0, 0, 0);
+            acc[m % TB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[m / TB], xf[m % kAhead], acc[m % TB], 0, 0, 0);
+            if (m + kAhead < M) xf[m % kAhead] = read_x(m + kAhead);
 #pragma unroll
-            for (int q = 0; q < U; ++q) {
-                const int k = m * U + q;
+            for (int k = m * 16 / M; k < (m + 1) * 16 / M; ++k) {
                 if (k + 1 < 16) unit_a(p, k + 1, tv[(k + 1) & 1]);
                 o[k] = unit_b(p, k, tv[k & 1]);
                 asm volatile("" : "+v"(o[k]));                  // computed here
@@ -336,21 +341,27 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     }
 }
 
-// Y = bf16( sum_z part[z] ), slices added in ascending order
+// Y = bf16( sum_z part[z] ), slices added in ascending order, four outputs per thread (Y is 8-byte aligned)
 __global__ __launch_bounds__(256) void k_w4_mid_reduce(const float* __restrict__ part, int splits, int64_t count,
                                                        qblora_bf16* __restrict__ Y) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 2;
+    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= count) return;
-    float a = 0.0f, b = 0.0f;
-    const bool two = i + 1 < count;
-    for (int zz = 0; zz < splits; ++zz) {
-        a += part[zz * count + i];
-        if (two) b += part[zz * count + i + 1];
+    if ((count & 3) == 0) {                                     // every slice's words are aligned
+        f32x4 v[8];                                             // at most 8 slices, all loads issued together
+#pragma unroll
+        for (int zz = 0; zz < 8; ++zz) v[zz] = *reinterpret_cast<const f32x4*>(part + min(zz, splits - 1) * count + i);
+        f32x4 s = v[0];
+#pragma unroll
+        for (int zz = 1; zz < 8; ++zz)
+            if (zz < splits) s += v[zz];
+        *reinterpret_cast<uint2*>(Y + i) = make_uint2(pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3]));
+        return;
     }
-    const uint32_t p = pack_bf16(a, b);
-    uint16_t* y = reinterpret_cast<uint16_t*>(Y) + i;
-    if (two) *reinterpret_cast<uint32_t*>(y) = p;               // i is even: 4-byte aligned
-    else y[0] = (uint16_t)(p & 0xffffu);
+    for (int e = 0; e < 4 && i + e < count; ++e) {
+        float a = 0.0f;
+        for (int zz = 0; zz < splits; ++zz) a += part[zz * count + i + e];
+        reinterpret_cast<uint16_t*>(Y)[i + e] = (uint16_t)(pack_bf16(a, a) & 0xffffu);
+    }
 }
 
 template <int TB>
@@ -385,18 +396,19 @@ int launch_tb(const MidDesc& d, unsigned blocks, hipStream_t st, int block_rows,
 
 }  // namespace
 
-int w4_mid_token_blocks(int T) { return T <= 32 ? 1 : T <= 64 ? 2 : 4; }
+int w4_mid_token_blocks(int T) { return T <= 32 ? 1 : T <= 64 ? 2 : T <= 128 ? 4 : T <= 192 ? 6 : 8; }
 
-// Slices of the input dimension for T <= 128 tokens.  Measured over 2 / 3 / 4 waves per workgroup and 1 .. 8 slices on
+// Slices of the input dimension.  Up to 128 tokens:  Measured over 2 / 3 / 4 waves per workgroup and 1 .. 8 slices on
 // 4096 x 4096, 11008 x 4096 and 22016 x 8192: what counts is the number of workgroups -- about 700 up to 64 tokens
 // (the weight stream wants loads in flight), about 400 at 128 (two resident per CU; more slices only add partial
 // tiles) -- while 64- or 96-row workgroups differ from 128-row ones by a few percent at most; one slice per row tile,
-// which the balance of matrix work alone would choose at 128 tokens, is 20 % slower than two.  At least 4 steps per
-// slice, at most 8 slices, no empty slice.
+// which the balance of matrix work alone would choose at 128 tokens, is 20 % slower than two.  Above 128 tokens a
+// workgroup's ring of token tiles takes a CU's LDS: as many slices as one round of 256 workgroups holds.  At least 4
+// steps per slice, at most 8 slices, no empty slice.
 int w4_mid_splits(int d_out, int d_in, int T) {
     const int tiles_n = (d_out + kMidRows - 1) / kMidRows, steps = d_in / kBlock;
     const int target = w4_mid_token_blocks(T) == 4 ? 400 : 700;
-    int want = (target + tiles_n / 2) / tiles_n;
+    int want = T > 128 ? 256 / tiles_n : (target + tiles_n / 2) / tiles_n;
     if (want > steps / 4) want = steps / 4;
     if (want > 8) want = 8;
     if (want < 1) want = 1;
@@ -412,7 +424,7 @@ size_t w4_mid_part_bytes(int d_out, int d_in, int T) {
 int launch_w4_mid(const uint8_t* codes, const float* scales, const float* beta, const Codebook& cb, int tiled, int d_out,
                   int d_in, const qblora_bf16* X, int T, qblora_bf16* Y, float* part, hipStream_t st, int block_rows,
                   int regrouped, int block_cols) {
-    if (T < 1 || T > 128 || d_in % kBlock != 0 || d_out < 1) return QBLORA_ERR_SHAPE;
+    if (T < 1 || T > 256 || d_in % kBlock != 0 || d_out < 1) return QBLORA_ERR_SHAPE;
     // 32-bit lane offsets: the arrays of one weight and the token rows must stay below 4 GiB
     if ((int64_t)((d_out + 255) / 256) * 256 * (d_in / 2) >= ((int64_t)1 << 32) || (int64_t)T * d_in * 2 >= ((int64_t)1 << 32))
         return QBLORA_ERR_SHAPE;
@@ -425,11 +437,13 @@ int launch_w4_mid(const uint8_t* codes, const float* scales, const float* beta, 
     switch (w4_mid_token_blocks(T)) {
         case 1: rc = launch_tb<1>(d, blocks, st, block_rows, regrouped, block_cols); break;
         case 2: rc = launch_tb<2>(d, blocks, st, block_rows, regrouped, block_cols); break;
-        default: rc = launch_tb<4>(d, blocks, st, block_rows, regrouped, block_cols); break;
+        case 4: rc = launch_tb<4>(d, blocks, st, block_rows, regrouped, block_cols); break;
+        case 6: rc = launch_tb<6>(d, blocks, st, block_rows, regrouped, block_cols); break;
+        default: rc = launch_tb<8>(d, blocks, st, block_rows, regrouped, block_cols); break;
     }
     if (rc || splits == 1) return rc;
     const int64_t count = (int64_t)T * d_out;
-    hipLaunchKernelGGL(k_w4_mid_reduce, dim3((unsigned)((count / 2 + 256) / 256)), dim3(256), 0, st, part, splits, count, Y);
+    hipLaunchKernelGGL(k_w4_mid_reduce, dim3((unsigned)((count + 1023) / 1024)), dim3(256), 0, st, part, splits, count, Y);
     return launch_status();
 }
 

@@ -42,3 +42,18 @@ def test_waves_split_the_contraction(oracle, codebook, T, d_out, d_in, R, fmt):
     torch.cuda.synchronize()
     assert_close_bf16(Y, oracle.forward(Wt, L.X, A, B, 2, 2, s), "Y")
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
+
+
+@pytest.mark.parametrize("T,d_out,d_in", [(21, 37, 1024), (150, 37, 2048), (250, 130, 1088)])
+def test_mid_batch_slices_of_odd_outputs(oracle, codebook, T, d_out, d_in):
+    """Inference above 16 tokens on layers whose outputs are no whole words: the slices' sum takes its scalar path."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
+    print(f"case mid batch, odd outputs T={T} {d_out}x{d_in}", flush=True)
+    L = synth.make_layer(7300 + T, T, d_out, d_in, 8, 1, 1)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook)
+    Y = torch.full((T, d_out), float("nan"), dtype=torch.bfloat16, device=qw.codes.device)
+    qb.qblora_linear_decode(qw, bf16_to_dev(L.X), Y=Y)
+    torch.cuda.synchronize()
+    Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
+    assert_close_bf16(Y, oracle.forward(Wt, L.X, None, None, 1, 1, 0.0), "Y")
