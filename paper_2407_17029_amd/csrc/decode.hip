@@ -9,7 +9,7 @@
 // are constant inside a 64-block, so they are applied to the block's partial sums, not to the weights,
 // and a code byte becomes two bf16 operand values with one LDS read.
 //
-// A workgroup of 4 waves (8 on layers with few rows) owns 16 output rows (32 on tall layers); the waves split
+// A workgroup of 4 waves (8 or 16 on layers with few rows) owns 16 output rows (32 on tall layers); the waves split
 // the input dimension (wave w takes the groups of 4 or 2 consecutive blocks j = w, w+4, ...) and add their partial
 // tiles through LDS at the end.
 // Inside a wave, lane l works on row (l & 15): for block b it loads 8 of the block's 32 code bytes
@@ -85,8 +85,8 @@ constexpr int kBufferWord3 = 0x00020000;    // buffer descriptor, last word: unt
 template <bool BETA, int BR, bool DIRECT, int XMODE, int G = 4, int R = 1, int NE = 4, int NW = 4>
 __device__ __forceinline__ void w4_decode(const DecodeDesc& d);
 
-template <bool BETA, int BR, bool DIRECT = false, int XMODE = 0, int G = 4, int R = 1, int NE = 4>
-__global__ __launch_bounds__(256) void k_w4_decode(DecodeDesc d) { w4_decode<BETA, BR, DIRECT, XMODE, G, R, NE>(d); }
+template <bool BETA, int BR, bool DIRECT = false, int XMODE = 0, int G = 4, int R = 1, int NE = 4, int NW = 4>
+__global__ __launch_bounds__(NW * 64) void k_w4_decode(DecodeDesc d) { w4_decode<BETA, BR, DIRECT, XMODE, G, R, NE, NW>(d); }
 
 // G: blocks per register set.  Four keep the most bytes in flight per wave and use 108 registers (four waves per
 // SIMD, 1024 workgroups resident); two use 76, six waves per SIMD, so that the 1376 workgroups of a 22016-row layer
@@ -485,8 +485,8 @@ int launch_w4_decode(const uint8_t* codes, const float* scales, const float* bet
     const dim3 grid2((unsigned)(((d_out + 31) / 32 + 15) / 16 * 16));      // 32 rows (two row groups)
     const size_t per_cu = (grid.x + 255) / 256, per_cu2 = (grid2.x + 255) / 256;
     const bool tall = grid2.x > 512;            // more than 16384 rows: the forms with two row groups pay
-    auto launch = [&](auto kernel, dim3 g) -> int {
-        hipLaunchKernelGGL(kernel, g, dim3(256), 0, st, d);
+    auto launch = [&](auto kernel, dim3 g, unsigned waves = 4) -> int {
+        hipLaunchKernelGGL(kernel, g, dim3(waves * 64), 0, st, d);
         return launch_status();
     };
     // All of X in LDS: when it is small enough, and when the workgroups of the launch still fit the CUs together with
@@ -526,7 +526,10 @@ int launch_w4_decode(const uint8_t* codes, const float* scales, const float* bet
                                      : launch_xall<true, true, 4, 1, 1, 1>(d, grid, x_all_bytes, st);
             return grid.x > 768 ? launch(k_w4_decode<true, 1, true, 0, 2, 1, 1>, grid) : launch(k_w4_decode<true, 1, true, 0, 4, 1, 1>, grid);
         }
-        if (per_cu <= 1 && T <= 8) return launch(k_w4_decode<true, 1, true, 0>, grid);
+        // one workgroup per CU: sixteen waves with one-block sets (4096 x 11008 / 4096 x 13824 / 4096 x 4096 at eight tokens
+        // 11.3 / 16.0 / 6.8 us with four waves and four-block sets, 10.9 / 14.2 / 6.0 with sixteen; at 16 tokens the
+        // staged form is ahead, 13.8 against 14.0, and so it is with two workgroups per CU, 13.3 against 15.4)
+        if (per_cu <= 1 && T <= 8) return launch(k_w4_decode<true, 1, true, 0, 1, 1, 4, 16>, grid, 16);
         // staged: two row groups and two-block sets on tall layers (22016 x 8192 at 8 / 16 tokens 22.8 / 24.7 us; with
         // one row group and four-block sets 52 / 54 us before the staging was pipelined), else one and four
         if (tall) return launch(k_w4_decode<true, 1, true, 1, 2, 2>, grid2);
@@ -548,10 +551,13 @@ int launch_w4_decode(const uint8_t* codes, const float* scales, const float* bet
             return beta ? launch_xall<true, true, 4, 8>(d, grid, x_all_bytes, st) : launch_xall<false, true, 4, 8>(d, grid, x_all_bytes, st);
         }
         // otherwise staged (22016 x 8192 at 2 / 4 / 8 / 16 tokens 26.4 / 26.5 / 27.9 / 30.8 us; 8192 x 8192 at one token
-        // 13.8 against 14.7 us plain), unless the layer has at most one workgroup per CU (4096 rows)
+        // 13.8 against 14.7 us plain), unless the layer has at most one workgroup per CU (4096 rows): there sixteen
+        // waves with one-block sets split the row group's inputs (4096 x 11008 at 1 / 4 / 8 / 16 tokens 11.7 / 12.6 /
+        // 13.8 / 17.1 us with four waves and four-block sets, 10.6 / 11.7 / 13.2 / 16.8 with sixteen)
         if (tall) return beta ? launch(k_w4_decode<true, 8, true, 1, 2, 2>, grid2) : launch(k_w4_decode<false, 8, true, 1, 2, 2>, grid2);
         if (grid.x > 256) return beta ? launch(k_w4_decode<true, 8, true, 1>, grid) : launch(k_w4_decode<false, 8, true, 1>, grid);
-        return beta ? launch(k_w4_decode<true, 8, true, 0>, grid) : launch(k_w4_decode<false, 8, true, 0>, grid);
+        return beta ? launch(k_w4_decode<true, 8, true, 0, 1, 1, 4, 16>, grid, 16)
+                    : launch(k_w4_decode<false, 8, true, 0, 1, 1, 4, 16>, grid, 16);
     }
 
     // ---- 64-blocks with a code table (any codebook; row-major or tile-ordered arrays) ------------------------------------

@@ -57,3 +57,19 @@ def test_mid_batch_slices_of_odd_outputs(oracle, codebook, T, d_out, d_in):
     torch.cuda.synchronize()
     Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
     assert_close_bf16(Y, oracle.forward(Wt, L.X, None, None, 1, 1, 0.0), "Y")
+
+
+@pytest.mark.parametrize("T,d_out,d_in", [(8, 40, 4160), (5, 4096, 8128), (8, 256, 6080)])
+def test_sixteen_wave_decode_of_a_packed_model(oracle, codebook, T, d_out, d_in):
+    """Packed INT4 model whose activations exceed the LDS copy, few rows: sixteen waves share a row group, with
+    block counts (65, 127, 95) that no wave count divides."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
+    print(f"case sixteen waves T={T} {d_out}x{d_in}", flush=True)
+    L = synth.make_layer(7400 + d_in, T, d_out, d_in, 8, 1, 1)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_MINMAX_INT4)
+    Y = torch.full((T, d_out), float("nan"), dtype=torch.bfloat16, device=qw.codes.device)
+    qb.qblora_linear_decode(qw, bf16_to_dev(L.X), Y=Y, pack=qb.qblora_decode_pack(qw))
+    torch.cuda.synchronize()
+    Wt = OracleWeight(oracle, L.W, codebook, True).assert_same(qw).dequantize(oracle, 2)
+    assert_close_bf16(Y, oracle.forward(Wt, L.X, None, None, 1, 1, 0.0), "Y")
