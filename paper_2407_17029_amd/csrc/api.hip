@@ -341,8 +341,8 @@ int qblora_quantize_blockwise(const float* W, int32_t d_out, int32_t d_in, int32
     }
     if (rc) return rc;
     if (scale_mode == QBLORA_SCALES_E4M3_GROUPED)
-        rc = launch_scales_double_quantize(out->scales, n_blocks(out), out->scale_group, out->scale_codes,
-                                           out->scale_step, out->scale_mid, st);
+        rc = launch_scales_double_quantize(out->scales, n_blocks(out), out->scale_codes, out->scale_step,
+                                           out->scale_mid, st);
     return rc;
 }
 

@@ -83,8 +83,9 @@ int launch_prepack_codes(const uint8_t* codes, int d_out, int d_in, uint8_t* til
 __host__ __device__ inline int64_t tiled_run_offset(int64_t n, int64_t b, int64_t blocks_per_row) {
     return (((n >> 8) * blocks_per_row + b) * 256 + (n & 255)) * 32;
 }
-int launch_scales_double_quantize(const float* scales, int64_t n, int group, uint8_t* scale_codes,
-                                  float* step, float* mid, hipStream_t st);
+// in groups of 256 scales
+int launch_scales_double_quantize(const float* scales, int64_t n, uint8_t* scale_codes, float* step, float* mid,
+                                  hipStream_t st);
 int launch_scales_reconstruct(const uint8_t* scale_codes, const float* step, const float* mid, int64_t n,
                               int group, float* scales, hipStream_t st);
 int launch_dequantize_bf16(const qblora_qweight& qw, const float* scales, qblora_bf16* Wt, hipStream_t st);
