@@ -323,8 +323,8 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
         return d
 
     proj_name = f"{bp.name} [{bp.d_out}x{bp.d_in}]"
-    kname = ("k_qlinear<0> (forward contraction on the weight dequantized once per call)" if dense
-             else "k_qlinear<1> (forward dequantize-and-contract)")
+    kname = ("k_dense (forward contraction on the weight dequantized once per call)" if dense
+             else "k_few (forward dequantize-and-contract)")
     out = {
         "value": round(value, 2), "unit": "TFLOP/s", "steps": steps, "warmup": warmup,
         "ms_per_step": round(ms_per_step, 4), "step_ms": stats(step_ms),

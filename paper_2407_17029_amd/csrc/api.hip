@@ -664,7 +664,7 @@ int qblora_linear_fwd_noalloc(const qblora_qweight* qw, const qblora_adapter* ad
     if (T < 0) return QBLORA_ERR_SHAPE;
     if (T == 0) return QBLORA_OK;
     if (!X || !Y) return QBLORA_ERR_NULL;
-    // always the form that rebuilds weight tiles in LDS: its scratch does not grow with the weight
+    // always a form that rebuilds the weight from its codes (in registers or in LDS): the scratch does not grow with it
     if (carve_fwd(qw, ad, T, nullptr, false).bytes > kStaticScratchBytes) return QBLORA_ERR_WORKSPACE;
     void* ptr = nullptr;
     if ((rc = static_scratch(&ptr))) return rc;

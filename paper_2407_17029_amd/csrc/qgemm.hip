@@ -1,21 +1,10 @@
-// Dequantize-and-contract GEMM for gfx950 (Alg. 1 qblora_forward: W_tilde = dequantize(...),
-// x @ W_tilde, plus the adapter term; and its transpose for the backward pass).
+// Plain bf16 GEMM of the adapter path for outputs that are neither narrow (skinny.hip) nor a base contraction, and the
+// dispatch of all contractions (gfx950):
 //
-//   C[M,N] = X1[M,K1] * Wq^T  +  X2[M,K2] * W2[N/div2, K2]^T
-//
-// Segment 1 reads the 4-bit codes and block scales of the frozen base weight from HBM,
-// rebuilds bf16 weights (Eq. 1: c[code]*alpha (+beta), fp32 then round-to-nearest-even) straight
-// into an LDS tile and feeds them to v_mfma_f32_32x32x16_bf16 with fp32 accumulation; the
-// dequantized weight never exists in HBM.  qmode 1 contracts along d_in (forward), qmode 2
-// uses the same stored tile transposed and contracts along d_out (backward w.r.t. activations);
-// in qmode 2 the scale varies along the contraction index, which is why it is applied while
-// building the tile and not to the accumulator.
-// Segment 2 is a plain bf16 K-extension: the adapter's rank-R product rides in the same
-// accumulators as R extra contraction steps (forward: X2 = s*U, W2 = B^T with output row n using
-// row n/lambda2, i.e. repeat_interleave; backward: X2 = dU/lambda1, W2 = A with row k/lambda1).
+//   C[M,N] = X2[M,K2] * W2[N/div2, K2]^T          (tile products of ragged shapes)
 //
 // Tiling: one workgroup of 512 threads (8 wave64) owns a BM x BN output tile and walks K in steps
-// of 64 (one quantization block).  Both operand tiles live in LDS as [row][64 k] bf16 with the
+// of 64.  Both operand tiles live in LDS as [row][64 k] bf16 with the
 // 16-byte chunks of a row XOR-swizzled by (row ^ row>>3) & 7, double buffered, one barrier per
 // step; global loads for step i+1 are issued before the MFMAs of step i.  The weight tile is the
 // MFMA A operand and the token tile the B operand, so a lane ends up with 4 consecutive output
@@ -33,21 +22,17 @@ __device__ __forceinline__ int swz(int row, int chunk) {
     return row * 128 + (((chunk ^ row ^ (row >> 3)) & 7) << 4);
 }
 
-template <int BM, int BN, int WM, int WN, int QMODE>
+template <int BM, int BN, int WM, int WN>
 __global__ __launch_bounds__(kThreads) void k_qgemm(GemmDesc d) {
     static_assert(WM * WN == 8, "8 waves");
     constexpr int TM = BM / WM, TN = BN / WN;       // wave tile: tokens x features
     constexpr int FM = TM / 32, FN = TN / 32;
     constexpr int XV = BM / 64;                      // 16-byte loads per thread for a token tile
     constexpr int WV = BN / 64;                      // ... for a plain bf16 weight tile
-    constexpr int PER_ROW = kThreads / BN;           // qmode 1: threads sharing one weight row
-    constexpr int CW = 8 / PER_ROW;                  // qmode 1: dwords of codes per thread
-    constexpr int BWD_ITEMS = (BN / 4) * 8;          // qmode 2: (4 columns x 8 rows) work items
 
     extern __shared__ __align__(16) unsigned char smem[];
     unsigned char* sX = smem;                                   // 2 * BM*128 bytes
     unsigned char* sW = smem + 2 * BM * 128;                    // 2 * BN*128 bytes
-    float* lut = reinterpret_cast<float*>(smem + 2 * (BM + BN) * 128);
 
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const int wm0 = (wave % WM) * TM, wn0 = (wave / WM) * TN;
@@ -65,12 +50,7 @@ __global__ __launch_bounds__(kThreads) void k_qgemm(GemmDesc d) {
     const int64_t m0 = (int64_t)mt * BM;
     const int n0 = nt * BN;
 
-    if (t < 16) lut[t] = d.cb.c[t];
-
-    const int K1 = QMODE == 0 ? 0 : (QMODE == 1 ? d.d_in : d.d_out);
-    const int steps1 = K1 / kBK, steps2 = (d.K2 + kBK - 1) / kBK;
-    const int nsteps = steps1 + steps2;
-    const int bpr = d.d_in / kBlock;                // blocks per stored weight row
+    const int nsteps = (d.K2 + kBK - 1) / kBK;
 
     f32x16 acc[FN][FM];
 #pragma unroll
@@ -82,129 +62,34 @@ __global__ __launch_bounds__(kThreads) void k_qgemm(GemmDesc d) {
 
     // ---- prefetch registers ----------------------------------------------------------------------
     uint4 xr[XV];
-    uint4 wr[WV];                   // plain bf16 weight tile (segment 2)
-    uint32_t cw[QMODE == 1 ? CW : 1];
-    float sc1 = 0.f, be1 = 0.f;     // qmode 1 scale / beta of this thread's row and step
-    uint16_t c16[8];
-    float sc2[8], be2[8];           // qmode 2
+    uint4 wr[WV];
 
     const int lrow = t >> 3, lchunk = t & 7;        // plain tile loader coordinates
 
-    auto load_tokens = [&](const qblora_bf16* X, int64_t ld, int K, int k0) {
-        int k = k0 + lchunk * 8;
+    auto load_global = [&](int step) {
+        const int k = step * kBK + lchunk * 8;
 #pragma unroll
         for (int i = 0; i < XV; ++i) {
             int64_t row = m0 + lrow + 64 * i;
             if (row > d.M - 1) row = d.M - 1;
-            xr[i] = (k < K) ? *reinterpret_cast<const uint4*>(X + row * ld + k) : make_uint4(0, 0, 0, 0);
+            xr[i] = (k < d.K2) ? *reinterpret_cast<const uint4*>(d.X2 + row * d.ldx2 + k) : make_uint4(0, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < WV; ++i) {
+            int row = n0 + lrow + 64 * i;
+            if (row > d.N - 1) row = d.N - 1;
+            row /= d.div2;
+            wr[i] = (k < d.K2) ? *reinterpret_cast<const uint4*>(d.W2 + (int64_t)row * d.ldw2 + k) : make_uint4(0, 0, 0, 0);
         }
     };
 
-    auto load_global = [&](int step) {
-        if (step < steps1) {
-            const int k0 = step * kBK;
-            load_tokens(d.X1, d.ldx1, K1, k0);
-            if constexpr (QMODE == 1) {
-                int row = n0 + t / PER_ROW;
-                if (row > d.N - 1) row = d.N - 1;
-                const int part = t % PER_ROW;
-                const uint32_t* p = reinterpret_cast<const uint32_t*>(d.codes + (int64_t)row * (d.d_in / 2) +
-                                                                      k0 / 2 + part * (CW * 4));
-                if constexpr (CW == 4) {
-                    uint4 v = *reinterpret_cast<const uint4*>(p);
-                    cw[0] = v.x; cw[1] = v.y; cw[2] = v.z; cw[3] = v.w;
-                } else if constexpr (CW == 2) {
-                    uint2 v = *reinterpret_cast<const uint2*>(p);
-                    cw[0] = v.x; cw[1] = v.y;
-                } else {
-                    cw[0] = *p;
-                }
-                int64_t blk = (int64_t)row * bpr + step;
-                sc1 = d.scales[blk];
-                if (d.beta) be1 = d.beta[blk];
-            } else if constexpr (QMODE == 2) {
-                if (t < BWD_ITEMS) {
-                    int c = n0 + 4 * (t % (BN / 4));
-                    if (c > d.N - 4) c = d.N - 4;
-                    const int nb = k0 + 8 * (t / (BN / 4));
-#pragma unroll
-                    for (int i = 0; i < 8; ++i) {
-                        int64_t n = nb + i;
-                        c16[i] = *reinterpret_cast<const uint16_t*>(d.codes + n * (d.d_in / 2) + c / 2);
-                        int64_t blk = n * bpr + c / kBlock;
-                        sc2[i] = d.scales[blk];
-                        if (d.beta) be2[i] = d.beta[blk];
-                    }
-                }
-            }
-        } else {
-            const int k0 = (step - steps1) * kBK;
-            load_tokens(d.X2, d.ldx2, d.K2, k0);
-            int k = k0 + lchunk * 8;
-#pragma unroll
-            for (int i = 0; i < WV; ++i) {
-                int row = n0 + lrow + 64 * i;
-                if (row > d.N - 1) row = d.N - 1;
-                row /= d.div2;
-                wr[i] = (k < d.K2) ? *reinterpret_cast<const uint4*>(d.W2 + (int64_t)row * d.ldw2 + k)
-                                   : make_uint4(0, 0, 0, 0);
-            }
-        }
-    };
-
-    auto store_lds = [&](int step, int buf) {
+    auto store_lds = [&](int buf) {
         unsigned char* bx = sX + buf * BM * 128;
         unsigned char* bw = sW + buf * BN * 128;
 #pragma unroll
-        for (int i = 0; i < XV; ++i) {
-            int row = lrow + 64 * i;
-            *reinterpret_cast<uint4*>(bx + swz(row, lchunk)) = xr[i];
-        }
-        if (step < steps1) {
-            if constexpr (QMODE == 1) {
-                const int row = t / PER_ROW, part = t % PER_ROW;
-                const bool hb = d.beta != nullptr;
+        for (int i = 0; i < XV; ++i) *reinterpret_cast<uint4*>(bx + swz(lrow + 64 * i, lchunk)) = xr[i];
 #pragma unroll
-                for (int w = 0; w < CW; ++w) {
-                    float v[8];
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) {
-                        float c = lut[(cw[w] >> (4 * j)) & 15];
-                        v[j] = hb ? __fmaf_rn(c, sc1, be1) : __fmul_rn(c, sc1);
-                    }
-                    uint4 o;
-                    o.x = pack_bf16(v[0], v[1]); o.y = pack_bf16(v[2], v[3]);
-                    o.z = pack_bf16(v[4], v[5]); o.w = pack_bf16(v[6], v[7]);
-                    *reinterpret_cast<uint4*>(bw + swz(row, part * CW + w)) = o;
-                }
-            } else if constexpr (QMODE == 2) {
-                if (t < BWD_ITEMS) {
-                    const int cg = t % (BN / 4), ng = t / (BN / 4);
-                    const bool hb = d.beta != nullptr;
-                    float v[8][4];
-#pragma unroll
-                    for (int i = 0; i < 8; ++i)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            float c = lut[(c16[i] >> (4 * j)) & 15];
-                            v[i][j] = hb ? __fmaf_rn(c, sc2[i], be2[i]) : __fmul_rn(c, sc2[i]);
-                        }
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        uint4 o;
-                        o.x = pack_bf16(v[0][j], v[1][j]); o.y = pack_bf16(v[2][j], v[3][j]);
-                        o.z = pack_bf16(v[4][j], v[5][j]); o.w = pack_bf16(v[6][j], v[7][j]);
-                        *reinterpret_cast<uint4*>(bw + swz(4 * cg + j, ng)) = o;
-                    }
-                }
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < WV; ++i) {
-                int row = lrow + 64 * i;
-                *reinterpret_cast<uint4*>(bw + swz(row, lchunk)) = wr[i];
-            }
-        }
+        for (int i = 0; i < WV; ++i) *reinterpret_cast<uint4*>(bw + swz(lrow + 64 * i, lchunk)) = wr[i];
     };
 
     auto compute = [&](int buf) {
@@ -231,15 +116,14 @@ __global__ __launch_bounds__(kThreads) void k_qgemm(GemmDesc d) {
     // ---- main loop ---------------------------------------------------------------------------------
     if (nsteps > 0) {
         load_global(0);
-        __syncthreads();            // lut visible
-        store_lds(0, 0);
+        store_lds(0);
         __syncthreads();
         for (int step = 0; step < nsteps; ++step) {
             const int buf = step & 1;
             const bool more = step + 1 < nsteps;
             if (more) load_global(step + 1);
             compute(buf);
-            if (more) store_lds(step + 1, buf ^ 1);
+            if (more) store_lds(buf ^ 1);
             __syncthreads();
         }
     }
@@ -284,10 +168,10 @@ __global__ __launch_bounds__(kThreads) void k_qgemm(GemmDesc d) {
         }
 }
 
-template <int BM, int BN, int WM, int WN, int QMODE>
+template <int BM, int BN, int WM, int WN>
 int launch_cfg(const GemmDesc& d, hipStream_t st) {
-    constexpr size_t smem = 2 * (BM + BN) * 128 + 64;
-    auto kern = k_qgemm<BM, BN, WM, WN, QMODE>;
+    constexpr size_t smem = 2 * (BM + BN) * 128;
+    auto kern = k_qgemm<BM, BN, WM, WN>;
     // set once per instantiation; the initialisation of a function-local static is thread safe
     static const bool attr_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
@@ -308,8 +192,8 @@ int launch_gemm(const GemmDesc& d, hipStream_t st) {
     // plain bf16 GEMMs of the adapter path that are not narrow (the tile product): 128 x 128 tiles unless
     // 256 x 256 tiles alone give every CU at least two workgroups
     const int64_t big_tiles = ((d.M + 255) / 256) * ((d.N + 255) / 256);
-    if (d.N <= 128 || big_tiles < 512) return launch_cfg<128, 128, 2, 4, 0>(d, st);
-    return launch_cfg<256, 256, 2, 4, 0>(d, st);
+    if (d.N <= 128 || big_tiles < 512) return launch_cfg<128, 128, 2, 4>(d, st);
+    return launch_cfg<256, 256, 2, 4>(d, st);
 }
 
 }  // namespace qblora
