@@ -137,8 +137,10 @@ struct GemmDesc {
                                // fp32 [splits][M][N] partial sums in `part` (skinny_splits, dense_splits; 16-byte aligned)
 };
 int launch_gemm(const GemmDesc& d, hipStream_t st);
-// the quantized segment (qmode 1) with an 8-wave 256x256 tile; called by launch_gemm
+// the quantized segment (qmode 1) with 8-wave tiles of 256 tokens; called by launch_gemm
 int launch_qlinear(const GemmDesc& d, hipStream_t st);
+// its estimated time for [M, N] over K
+int64_t qlinear_ns(int64_t M, int N, int K);
 // the quantized segment for few tokens (qmode 2), from row-major codes and fp32 scales; called by launch_gemm
 constexpr int kFewTokens = 256;
 bool few_applies(int64_t M, int N, int K);

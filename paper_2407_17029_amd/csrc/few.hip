@@ -5,7 +5,7 @@
 // with the compute weight of Eq. 1 (c[code]*alpha (+beta) in fp32, rounded to bf16) built in registers, bf16 MFMAs,
 // fp32 accumulation; the second segment is the adapter's K-extension (qlinear.hip).
 //
-// The 256 x 256 output tile of qlinear.hip leaves the chip idle here: 256 tokens x 4096 features are 16 workgroups,
+// The 256-token tiles of qlinear.hip leave the chip idle here: 256 tokens x 4096 features are 32 workgroups,
 // and each walks all of K.  A workgroup here owns 16*TB tokens x 16*FB features and its 8 waves split K: wave w takes
 // the 64-wide steps w, w + 8, ...  A lane dequantizes exactly its MFMA operand (row l & 15 of each 16-row block, 16
 // consecutive k: 8 bytes of codes) through a byte-indexed pair table in LDS and loads its token operand (the same 16 k
@@ -13,9 +13,9 @@
 // partial tiles are added in wave order at the end.
 //
 // Bound: the address path.  Neighbouring lanes of an operand load are different rows, so a load of tokens or codes
-// looks up 64 pieces of cache lines; a round of 8 steps costs 2.4 us with 32 x 32 tiles, 3.3 with 32 x 64 and 4.5 with
-// 64 x 64.  us against the 256 x 256 tile: 256 tokens 512 x 512 6.2 / 19, 4096 x 4096 37 / 96; 64 tokens 1024 x 1024
-// 8.1 / 30; 200 tokens 4096 x 11008 75 / 240; 100 tokens 16384 x 8192 in 8 x 8 blocks 115 / 433.
+// looks up 64 pieces of cache lines; a round of 8 steps costs 2.0 us with 32 x 32 tiles, 2.7 with 32 x 64 and 3.6 with
+// 64 x 64.  us against qlinear.hip: 256 tokens 512 x 512 5.6 / 17, 4096 x 4096 34 / 60; 64 tokens 1024 x 1024
+// 7.7 / 23; 200 tokens 4096 x 11008 70 / 166; 100 tokens 16384 x 8192 in 8 x 8 blocks 107 / 115.
 #include "common.h"
 
 namespace qblora {
@@ -220,14 +220,15 @@ int launch_tile(const GemmDesc& d, hipStream_t st) {
 
 namespace {
 
-// Tile (0: 32 x 32, 1: 32 x 64, 2: 64 x 64 tokens x features) by the estimated time in 100 ns: rounds of workgroups
-// (one per CU) x rounds of 8 steps x the measured time of such a round; -1 where the 256 x 256 tile, at 1.5 us a step,
-// is the faster one (256 tokens, 11008 x 4096: 106 us against 123).
+// Tile (0: 32 x 32, 1: 32 x 64, 2: 64 x 64 tokens x features) by the estimated time in ns: rounds of workgroups (one per
+// CU) x rounds of 8 steps x the measured time of such a round; -1 where the 256-token tiles are the faster ones.  us here /
+// there: 11008 x 4096 at 128 / 160 tokens 66 / 72 and 87 / 71; 13824 x 5120 at 128 / 160 79 / 87 and 112 / 86; 22016 x 8192
+// at 64 / 65 121 / 128 and 180 / 133; 8192 x 8192 at 256 tokens 121 / 123.
 int few_tile(int64_t M, int N, int K) {
-    static constexpr int tb[3] = {32, 32, 64}, fb[3] = {32, 64, 64}, cost[3] = {24, 33, 45};
+    static constexpr int tb[3] = {32, 32, 64}, fb[3] = {32, 64, 64}, cost[3] = {2000, 2700, 3600};
     const int64_t steps = K / kBK;
     int best = -1;
-    int64_t best_t = steps * 15 * ((((M + 255) / 256) * ((N + 255) / 256) + 255) / 256);
+    int64_t best_t = qlinear_ns(M, N, K) + 3000;         // its longer start (512 inputs: 4 to 11 us behind)
     for (int i = 0; i < 3; ++i) {
         const int64_t wgs = ((M + tb[i] - 1) / tb[i]) * (N / fb[i]);
         const int64_t t = (wgs + 255) / 256 * ((steps + 7) / 8) * cost[i];

@@ -1,6 +1,6 @@
 // Dequantize-and-contract kernel of the adapted layer's forward for gfx950 (Alg. 1 qblora_forward:
-// W_tilde = dequantize(...), x @ W_tilde, plus the adapter term), for calls whose scratch cannot hold the
-// dequantized weight (few tokens; the forward that allocates nothing).
+// W_tilde = dequantize(...), x @ W_tilde, plus the adapter term), for calls that do not dequantize the weight
+// beforehand: on at most 256 tokens where few.hip is not faster, and the forward that allocates nothing.
 //
 //   C[M,N] = X1[M,K1] * Wq^T  +  X2[M,K2] * W2[N/div2, K2]^T
 //
@@ -12,17 +12,28 @@
 // n/lambda2, i.e. repeat_interleave).  k is accumulated in the order and by the instruction of dense.hip, so both
 // give the same bits.
 //
-// Shape of the computation on a CU: one workgroup of 512 threads (8 wave64, two per SIMD) owns a
-// 256 x 256 output tile; a wave owns 128 tokens x 64 features (128 accumulator registers).  Two waves per SIMD
-// matter: the dequantization arithmetic of one wave issues in the shadow of the other wave's MFMAs.  Both operand
-// tiles live in LDS as [row][64 k] bf16 (128 bytes per row) with the 16-byte chunks of a row XOR-swizzled by
-// (row >> 1) & 7, double buffered, one barrier per k-step.  Activation tiles (and both bf16 tiles of segment 2)
-// go from global memory directly into LDS (global_load_lds, 16 bytes per lane; the swizzle is applied by choosing
-// which global chunk a lane fetches).  Codes and scales are fetched two k-steps ahead into registers and
-// dequantized between the MFMAs of the step before they are needed, through a byte-indexed table
-// in LDS that turns one byte of codes into two fp32 code values.
+// Shape of the computation on a CU: one workgroup of 512 threads (8 wave64, two per SIMD) owns 256 tokens x 256 or 128
+// features; a wave owns 128 x 64 or 64 x 64 of them (128 or 64 accumulator registers).  Two waves per SIMD matter: the
+// dequantization arithmetic of one wave issues in the shadow of the other wave's MFMAs.  Both operand tiles live in LDS
+// as [row][64 k] bf16 (128 bytes per row) with the 16-byte chunks of a row XOR-swizzled by (row >> 1) & 7, double
+// buffered, one barrier per k-step.  Activation tiles (and both bf16 tiles of segment 2) go from global memory directly
+// into LDS (global_load_lds, 16 bytes per lane; the swizzle is applied by choosing which global chunk a lane fetches).
+// Codes and block parameters are fetched two or three k-steps ahead into registers and dequantized between the MFMAs of
+// the step before they are needed, through a byte-indexed table in LDS that turns one byte of codes into two fp32
+// code values.
+//
+// Bound: LDS.  A 64-wide step of the 256 x 256 tile reads 192 KB of fragments and 64 KB of table values and writes 64 KB,
+// about 2600 cycles of LDS against 2048 of MFMAs; it takes 1.5 us with few workgroups and 1.85 us (power) with all CUs
+// busy, the 256 x 128 tile 0.95 and 1.08.  No form may spill: with accumulators, fragments, table values and the codes
+// in flight the wide tile needs nearly all 256 registers, and a version that kept the code row pointers, the
+// K-extension's addresses and four scales a thread in them spilled inside its loop (8 x 8 blocks with offsets 217 us at
+// 512 tokens, 4096 x 4096, where this one takes 61).  Hence 32-bit lane offsets from uniform bases, addresses made again
+// where they are used, and with 8 x 8 blocks a thread that owns one column of one block: one scale, one offset.
+//
 // The weight tile is the MFMA A operand and the token tile the B operand, so a lane ends up with 4
 // consecutive output features of one token and stores them as one 8-byte word.
+#include <type_traits>
+
 #include "common.h"
 
 namespace qblora {
@@ -30,8 +41,8 @@ namespace qblora {
 namespace {
 
 constexpr int kThreads = 512;
-constexpr int BM = 256, BN = 256, kBK = 64;
-constexpr int kTileBytes = 256 * 128;                       // one operand tile: 256 rows x 128 bytes
+constexpr int BM = 256, kBK = 64;
+constexpr int kTileX = BM * 128;                            // a token tile: rows of 128 bytes
 constexpr int kTableBytes = 256 * 128;                      // byte-indexed pair table, 16 replicas
 
 __device__ __align__(16) const uint32_t g_zero_chunk[4] = {0u, 0u, 0u, 0u};
@@ -57,21 +68,44 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 
-// codes / scales of one k-step held in registers, 32 weights per thread: half a stored row (16 bytes of codes) and
-// one scale -- or, with 8 x 8 quantization blocks (BR = 8), one scale per code dword (8 inputs = one block column)
-template <int BR>
+// codes and block parameters of one k-step held in registers: D dwords of 8 codes per thread, all in one block --
+// consecutive ones of a stored row, or, with 8 x 8 quantization blocks, the same 8 inputs of D adjacent rows
+template <int D>
 struct Staged {
-    uint32_t cw[4];
-    float sc[BR == 8 ? 4 : 1];
-    float be[BR == 8 ? 4 : 1];
+    uint32_t cw[D];
+    float sc, be;
 };
 
-template <bool BETA, int BR>
+// The lane, read again where it is used: a value that need not be kept in a register across the loop.
+__device__ __forceinline__ int lane_id() {
+    int l = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    asm volatile("" : "+v"(l));
+    return l;
+}
+
+typedef __attribute__((ext_vector_type(2))) float f32x2;
+
+template <int N> using Int = std::integral_constant<int, N>;
+
+// Waits until at most N of this wave's loads and copies are in flight and its LDS accesses are done, then the
+// workgroup's barrier.  The builtin tells the compiler that its own loads up to there have arrived; the statement keeps
+// every memory access on its side of the barrier.
+template <int N>
+__device__ __forceinline__ void publish(Int<N>) {
+    static_assert(N >= 0 && N < 16, "one field of the wait");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_waitcnt(0x0070 | N);
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" :: "n"(N) : "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int BN, bool BETA, int BR>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_qlinear(GemmDesc d) {
+    constexpr int kTileW = BN * 128, D = BN / 64;    // bytes of a weight tile, code dwords per thread and step
+    constexpr int MB = BN / 32;                      // 16-token blocks of a wave
     extern __shared__ __align__(16) unsigned char smem[];
-    unsigned char* sX = smem;                                   // 2 tiles
-    unsigned char* sW = sX + 2 * kTileBytes;                    // 2 tiles
-    unsigned char* sT = smem + 4 * kTileBytes;                  // pair table, see below
+    unsigned char* const sW = smem + 2 * kTileX;                // 2 token tiles in front, then 2 weight tiles
+    unsigned char* const sT = sW + 2 * kTileW;                  // pair table, see below
 
     // Every field of the descriptor the loop touches is copied into a local first: the copies in
     // the loop are assembly statements that clobber memory, and values must not be re-read around them.
@@ -80,21 +114,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const qblora_bf16* const X1 = d.X1; const int64_t ldx1 = d.ldx1;
     const qblora_bf16* const X2 = d.X2; const int64_t ldx2 = d.ldx2;
     const qblora_bf16* const W2 = d.W2; const int64_t ldw2 = d.ldw2;
-    const uint8_t* const codes = d.codes;
-    const float* const scales = d.scales;
     const float* const beta = d.beta;
     qblora_bf16* const C = reinterpret_cast<qblora_bf16*>(d.C);
     const int64_t ldc = d.ldc;
     const float out_scale = d.out_scale;
 
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int wm0 = (wave & 1) * 128, wn0 = (wave >> 1) * 64;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    // a wave owns 16*MB tokens x 64 features
+    const int wm0 = BN == 256 ? (wave & 1) * 128 : (wave & 3) * 64, wn0 = BN == 256 ? (wave >> 1) * 64 : (wave >> 2) * 64;
 
     // ---- tile assignment: XCD-contiguous, grouped along tokens ---------------------------------
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN;
     const int ntiles = tiles_m * tiles_n;
-    int L = blockIdx.x;
-    if ((ntiles & 7) == 0) L = (blockIdx.x & 7) * (ntiles >> 3) + (blockIdx.x >> 3);
+    int L;
+    {
+        const int xcd = blockIdx.x & 7, q = ntiles >> 3, rem = ntiles & 7;
+        L = xcd * q + min(xcd, rem) + (blockIdx.x >> 3);
+    }
     constexpr int GM = 4;
     const int in_group = GM * tiles_n;
     const int first_m = (L / in_group) * GM;
@@ -103,6 +139,233 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int64_t m0 = (int64_t)mt * BM;
     const int n0 = nt * BN;
 
+    const int steps1 = d_in / kBK, steps2 = (K2 + kBK - 1) / kBK;
+    const int nsteps = steps1 + steps2;
+    const int bpr = d_in / kBlock;                // blocks per stored weight row
+
+    f32x4 acc[4][MB];                             // [16 features][16 tokens]
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < MB; ++b) acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+    // ---- direct global -> LDS copies -------------------------------------------------------------
+    // Wave w fills rows 32w .. 32w+31 of a token tile (BN/8 rows of a weight tile) with copies of 8 rows each.  In
+    // copy i, lane l lands on row 8i + (l>>3) of those, physical chunk l&7, which must hold logical chunk
+    // (l&7) ^ (row>>1)&7 = (l&7) ^ (4(i&1) + (l>>4)).
+    const int crow = lane >> 3;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
+    // a tile of the K-extension: chunks at or beyond K2 are fetched from a zero constant instead
+    auto copy_tile = [&](auto rows_per_wave, const qblora_bf16* src, int64_t ld, int64_t row_base, int64_t row_max,
+                         int div, int k0, uint32_t tile_off) __attribute__((always_inline)) {
+        const int l = lane_id();                     // row addresses are made again at every call, not held across the loop
+#pragma unroll
+        for (int i = 0; i < rows_per_wave.value / 8; ++i) {
+            int64_t row = row_base + wave * rows_per_wave.value + i * 8 + (l >> 3);
+            row = row > row_max ? row_max : row;
+            if (div != 1) row = (int64_t)((uint32_t)row / (uint32_t)div);      // only weight rows (< 2^31) are divided
+            const int k = k0 + (((l & 7) ^ (4 * (i & 1) + (l >> 4))) << 3);
+            const qblora_bf16* p = k < K2 ? src + row * ld + k : reinterpret_cast<const qblora_bf16*>(g_zero_chunk);
+            copy16_to_lds(p, lds0 + tile_off + (wave * rows_per_wave.value + i * 8) * 128);
+        }
+    };
+    // Segment-1 activation tiles: per-lane byte offsets relative to the tile's first row are fixed for
+    // the whole kernel, the uniform base walks along k.
+    uint32_t xoff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        int64_t lrow = wave * 32 + i * 8 + crow;
+        if (m0 + lrow > M - 1) lrow = M - 1 - m0;
+        xoff[i] = (uint32_t)(lrow * ldx1 * 2) + (((lane & 7) ^ (4 * (i & 1) + (lane >> 4))) << 4);
+    }
+    const qblora_bf16* const x1_tile = X1 + m0 * ldx1;
+    auto issue_x1 = [&](int step) __attribute__((always_inline)) {
+        const qblora_bf16* base = x1_tile + (int64_t)step * kBK;
+        const uint32_t to = lds0 + (step & 1) * kTileX + wave * 32 * 128;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) copy16_to_lds(base, xoff[i], to + i * 8 * 128);
+    };
+    auto issue_copies = [&](int step) __attribute__((always_inline)) {
+        if (step < steps1) {
+            issue_x1(step);
+        } else {
+            const int k0 = (step - steps1) * kBK, buf = step & 1;
+            copy_tile(Int<32>{}, X2, ldx2, m0, M - 1, 1, k0, buf * kTileX);
+            copy_tile(Int<BN / 8>{}, W2, ldw2, n0, N - 1, div2, k0, 2 * kTileX + buf * kTileW);
+        }
+    };
+
+    // ---- codes / scales -> registers -------------------------------------------------------------
+    // 64-blocks: a thread owns 1/(512/BN) of a stored row.  8 x 8 blocks: the dword t & 7 of D rows of one block row.
+    constexpr int kPerRow = 512 / BN;
+    const int wrow = BR == 8 ? D * (t >> 3) : t / kPerRow, wchunk = BR == 8 ? (t & 7) : D * (t % kPerRow);
+    const int qrow = min(n0 + wrow, N - (BR == 8 ? D : 1));      // rows past N: any valid ones, results never stored
+    // (uniform bases, which walk along k, and 32-bit lane offsets from the tile's first row)
+    const int lrow = qrow - n0;
+    const uint8_t* codes_at; int codes_step = 32;
+    uint32_t codes_off = (uint32_t)lrow * (uint32_t)(d_in / 2), codes_row = (uint32_t)(d_in / 2);
+    if (d.codes_tiled) { codes_at = d.codes_tiled + tiled_run_offset(n0, 0, bpr); codes_step = 256 * 32; codes_row = 32; codes_off = (uint32_t)lrow * 32u; }
+    else codes_at = d.codes + (int64_t)n0 * (d_in / 2);
+    codes_off += (uint32_t)wchunk * 4u;
+    const int64_t blk0 = BR == 8 ? (int64_t)(n0 >> 3) * (d_in >> 3) : (int64_t)n0 * bpr;
+    const uint32_t blk_off = BR == 8 ? (uint32_t)(lrow >> 3) * (uint32_t)(d_in >> 3) + (uint32_t)wchunk : (uint32_t)lrow * (uint32_t)bpr;
+    // 64-blocks: the scales come in tile order
+    const float* const scales_at = BR == 8 ? d.scales + blk0 : d.scales_tiled + tiled_run_offset(n0, 0, bpr) / 32;
+    const uint32_t scales_off = BR == 8 ? blk_off : (uint32_t)lrow;
+    const float* const beta_at = BETA ? beta + blk0 : nullptr;
+    constexpr int kLoads = (BR == 8 ? D : 1) + 1 + (BETA ? 1 : 0);   // load instructions of a step
+    typedef typename std::conditional<D == 4, uint4, uint2>::type Row;
+    auto load_staged = [&](Staged<D>& s, int step) __attribute__((always_inline)) {
+        const uint8_t* const p = codes_at + (int64_t)step * codes_step;
+        if constexpr (BR == 8) {
+#pragma unroll
+            for (int i = 0; i < D; ++i) s.cw[i] = *reinterpret_cast<const uint32_t*>(p + codes_row * i + codes_off);
+        } else {
+            const Row v = *reinterpret_cast<const Row*>(p + codes_off);
+            s.cw[0] = v.x; s.cw[1] = v.y;
+            if constexpr (D == 4) { s.cw[2] = v.z; s.cw[3] = v.w; }
+        }
+        s.sc = (scales_at + (int64_t)step * (BR == 8 ? 8 : 256))[scales_off];
+        if constexpr (BETA) s.be = (beta_at + (int64_t)step * (BR == 8 ? 8 : 1))[blk_off];
+        asm volatile("" ::: "memory");               // the loads stay in front of what follows
+    };
+
+    // ---- dequantization of a staged k-step, in units of one byte of codes; four of them fill a 16-byte chunk ----------
+    const uint32_t table_lane = lds_address(sT) + ((lane & 15) << 3);
+    auto look_up = [&](uint32_t w, int i) __attribute__((always_inline)) {                 // byte i of dword w
+        const uint32_t at = ((i == 0 ? (w << 7) : (w >> (8 * i - 7))) & 0x7f80u) | table_lane;
+        return *reinterpret_cast<const __attribute__((address_space(3))) f32x2*>(at);
+    };
+    auto scale = [&](const Staged<D>& s, f32x2 c) __attribute__((always_inline)) {         // two adjacent k
+        return BETA ? pack_bf16(__fmaf_rn(c[0], s.sc, s.be), __fmaf_rn(c[1], s.sc, s.be))
+                    : pack_bf16(__fmul_rn(c[0], s.sc), __fmul_rn(c[1], s.sc));
+    };
+    uint32_t store_at = (uint32_t)swz(wrow, wchunk);
+    auto store_chunk = [&](int p, const uint32_t (&o)[4], unsigned char* tile) __attribute__((always_inline)) {
+        // swz(wrow, wchunk + p), or swz(wrow + p, wchunk) with 8 x 8 blocks: wchunk and wrow are multiples of D
+        const uint32_t at = BR == 8 ? (store_at ^ (uint32_t)((p >> 1) << 4)) + p * 128 : store_at ^ (uint32_t)(p << 4);
+        *reinterpret_cast<uint4*>(tile + at) = make_uint4(o[0], o[1], o[2], o[3]);
+    };
+
+    // ---- fragments ----------------------------------------------------------------------------------
+    // 16-row block b, slice ks of 32 k: row base + 16b + r, chunk 4ks + g sits at (base + r)*128 + 2048b +
+    // 16*[(g ^ r>>1) & 7 ^ 4ks] -- one per-lane value XOR a constant plus an immediate;
+    // the empty asm in a step keeps the variants from being hoisted and held in registers.
+    const int r = lane & 15, g = lane >> 4;
+    uint32_t frag_w = 2 * kTileX + (uint32_t)((wn0 + r) * 128 + ((g ^ (r >> 1)) << 4));
+    uint32_t frag_x = (uint32_t)((wm0 + r) * 128 + ((g ^ (r >> 1)) << 4));
+    auto read_w = [&](int buf, int ks, bf16x8 (&f)[4]) __attribute__((always_inline)) {
+        const unsigned char* const p = smem + ((frag_w ^ (uint32_t)(ks << 6)) + buf * kTileW);
+#pragma unroll
+        for (int a = 0; a < 4; ++a) f[a] = *reinterpret_cast<const bf16x8*>(p + a * 2048);
+    };
+    auto read_x = [&](int buf, int ks, int half, bf16x8 (&f)[4]) __attribute__((always_inline)) {
+        const unsigned char* const p = smem + ((frag_x ^ (uint32_t)(ks << 6)) + buf * kTileX) + half * 8192;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) f[b] = *reinterpret_cast<const bf16x8*>(p + b * 2048);
+    };
+    auto mfma = [&](const bf16x8& w, const bf16x8& x, f32x4& c) __attribute__((always_inline)) {
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x, c, 0, 0, 0);
+    };
+
+    // ---- one k-step ----------------------------------------------------------------------------------
+    // Buffer s & 1 of both tiles holds step s when it starts, and the copies of step s+1's tokens are in flight.  Its
+    // barrier publishes tile s+1 and frees the buffers of step s.  A wave issues in order, so the dequantization is
+    // written between the MFMAs in whose shadow it runs, and fenced there.
+    // kMode 1: steps s+1 and s+2 are quantized, no conditions (codes are fetched ahead from a clamped step); 0: the last
+    // quantized steps; 2: the K-extension, nothing to dequantize.
+    constexpr int kSets = BN == 256 ? 2 : 4;
+    Staged<D> st[kSets];                             // by step % kSets
+    bf16x8 wf[BN == 256 ? 1 : 2][4], xf[BN == 256 ? 1 : 2][4];
+    f32x2 lv[2][4];                                  // table values of two chunks
+    auto step = [&](auto mode, auto phase, int s) __attribute__((always_inline)) {
+        constexpr int kMode = mode.value, P = phase.value;
+        const int cur = s & 1, nxt = cur ^ 1;
+        const bool dq = kMode == 1 || (kMode == 0 && s + 1 < steps1), look = kMode == 1 || (kMode == 0 && s + 2 < steps1);
+        const bool more = kMode == 1 || s + 1 < nsteps;
+        unsigned char* const w_next = sW + nxt * kTileW;
+        uint32_t o[4];
+        asm volatile("" : "+v"(frag_w), "+v"(frag_x), "+v"(store_at));
+        if constexpr (BN == 128) {
+            // First slice: its MFMAs, weight tile s+1 scaled and stored (looked up in the step before), the second slice's
+            // fragments read.  Second slice: 6 MFMAs, the barrier, then the other 10 beside the reads of tile s+1's
+            // first fragments, the copies of step s+2 and its lookups.  Codes are fetched three steps ahead; those of
+            // this step stay in flight across the barrier.
+            if (kMode == 1 || (kMode == 0 && s + 3 < steps1)) load_staged(st[(P + 3) & 3], min(s + 3, steps1 - 1));
+            read_w(cur, 1, wf[1]);
+            read_x(cur, 1, 0, xf[1]);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                mfma(wf[0][i >> 2], xf[0][i & 3], acc[i >> 2][i & 3]);
+                if (i < 8 && dq) {
+                    o[i & 3] = scale(st[(P + 1) & 3], lv[i >> 2][i & 3]);
+                    if ((i & 3) == 3) store_chunk(i >> 2, o, w_next);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int i = 0; i < 6; ++i) mfma(wf[1][i >> 2], xf[1][i & 3], acc[i >> 2][i & 3]);
+            if constexpr (kMode == 1) publish(Int<kLoads>{}); else publish(Int<0>{});
+            if (more) { read_w(nxt, 0, wf[0]); read_x(nxt, 0, 0, xf[0]); }
+            if (kMode == 1) issue_x1(s + 2);
+            else if (s + 2 < nsteps) issue_copies(s + 2);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int i = 6; i < 16; ++i) {
+                mfma(wf[1][i >> 2], xf[1][i & 3], acc[i >> 2][i & 3]);
+                const int u = i - 6;
+                if (u < 8 && look) lv[u >> 2][u & 3] = look_up(st[(P + 2) & 3].cw[u >> 2], u & 3);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        } else {
+            // Four quarters of 16 MFMAs: a 32-wide slice of k, half of the wave's tokens.  There are no registers for a
+            // second set of fragments: the MFMAs of a quarter run along the antidiagonals of [feature block][token
+            // block], so that every fragment is replaced by the next quarter's behind its last use and has five or more
+            // MFMAs to arrive.  The next weight tile is scaled and stored over the first three quarters, its table values
+            // read four units ahead; the barrier stands behind 6 MFMAs of the last quarter, in front of the first read
+            // of the next tiles.  Codes are fetched two steps ahead.
+            if (kMode == 1 || (kMode == 0 && s + 2 < steps1)) load_staged(st[P & 1], min(s + 2, steps1 - 1));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t slice = q == 1 || q == 2 ? 64 : 0;          // of quarter q + 1
+                const unsigned char* const xs = smem + ((frag_x ^ slice) + (q < 3 ? cur : nxt) * kTileX) + ((q + 1) & 1) * 8192;
+                const unsigned char* const ws = smem + ((frag_w ^ slice) + (q < 3 ? cur : nxt) * kTileW);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int j = 0, n = 0; j < 7; ++j) {
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) {
+                        const int b = j - a;
+                        if (b < 0 || b > 3) continue;
+                        mfma(wf[0][a], xf[0][b], acc[a][(4 * (q & 1) + b) % MB]);
+                        const int m = 16 * q + n, u = m / 3;
+                        if (q < 3 && m % 3 == 0 && dq) {
+                            o[u & 3] = scale(st[(P + 1) & 1], lv[(u >> 2) & 1][u & 3]);
+                            if (u < 12) lv[((u >> 2) + 1) & 1][u & 3] = look_up(st[(P + 1) & 1].cw[((u >> 2) + 1) % D], u & 3);
+                            if ((u & 3) == 3) store_chunk(u >> 2, o, w_next);
+                        }
+                        if (q == 3 && n == 5) {
+                            publish(Int<0>{});
+                            if (kMode == 1) issue_x1(s + 2);
+                            else if (s + 2 < nsteps) issue_copies(s + 2);
+                        }
+                        if (q == 3 && n > 5 && n % 2 == 1 && n < 15 && look) lv[0][(n - 7) / 2] = look_up(st[P & 1].cw[0], (n - 7) / 2);
+                        if (b == 3 && (q & 1) && (q < 3 || more)) wf[0][a] = *reinterpret_cast<const bf16x8*>(ws + a * 2048);
+                        if (a == 3 && (q < 3 || more)) xf[0][b] = *reinterpret_cast<const bf16x8*>(xs + b * 2048);
+                        __builtin_amdgcn_sched_barrier(0);
+                        ++n;
+                    }
+                }
+            }
+        }
+    };
+
+    // ---- main loop ---------------------------------------------------------------------------------
+    issue_copies(0);
+#pragma unroll
+    for (int i = 0; i < (BN == 256 ? 2 : 3); ++i) load_staged(st[i], min(i, steps1 - 1));
+    if (nsteps > 1) issue_copies(1);
     // Pair table: a byte of codes (two adjacent k, low nibble first) selects the 8-byte entry
     // (c[lo], c[hi]) -- one LDS read dequantizes two weights.  The 256 entries are replicated 16 times,
     // entry b of replica q at b*128 + q*8, and lane l reads replica l & 15, so that lanes of one
@@ -116,296 +379,70 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const float4 e = make_float4(c_lo, c_hi, c_lo, c_hi);
 #pragma unroll
         for (int q = 0; q < 4; ++q) *reinterpret_cast<float4*>(sT + b * 128 + (t >> 8) * 64 + q * 16) = e;
-    }
-
-    const int steps1 = d_in / kBK, steps2 = (K2 + kBK - 1) / kBK;
-    const int nsteps = steps1 + steps2;
-    const int bpr = d_in / kBlock;                // blocks per stored weight row
-
-    f32x4 acc[4][8];                              // [16 features][16 tokens]
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 8; ++b) acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-
-    // ---- direct global -> LDS copies -------------------------------------------------------------
-    // Wave w fills rows 32w .. 32w+31 of a tile with 4 copies of 8 rows each.  In copy i, lane l
-    // lands on row 32w + 8i + (l>>3), physical chunk l&7, which must hold logical chunk
-    // (l&7) ^ (row>>1)&7 = (l&7) ^ (4(i&1) + (l>>4)).
-    const int crow = lane >> 3;
-    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem) + wave * 32 * 128);
-    // check_k: chunks at or beyond K are fetched from a zero constant instead (K-extension only)
-    auto copy_tile = [&](const bool check_k, const qblora_bf16* src, int64_t ld, int64_t row_base, int64_t row_max,
-                         int div, int K, int k0, uint32_t tile_off) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            int64_t row = row_base + wave * 32 + i * 8 + crow;
-            row = row > row_max ? row_max : row;
-            if (div != 1) row = (int64_t)((uint32_t)row / (uint32_t)div);      // only weight rows (< 2^31) are divided
-            const int k = k0 + (((lane & 7) ^ (4 * (i & 1) + (lane >> 4))) << 3);
-            const qblora_bf16* p = src + row * ld + k;
-            if (check_k)
-                p = (k < K) ? p : reinterpret_cast<const qblora_bf16*>(g_zero_chunk);
-            copy16_to_lds(p, lds0 + tile_off + i * 8 * 128);
-        }
-    };
-    // Segment-1 activation tiles: per-lane byte offsets relative to the tile's first row are fixed for
-    // the whole kernel, the uniform base walks along k.
-    uint32_t xoff[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        int64_t lrow = wave * 32 + i * 8 + crow;
-        if (m0 + lrow > M - 1) lrow = M - 1 - m0;
-        xoff[i] = (uint32_t)(lrow * ldx1 * 2) + (((lane & 7) ^ (4 * (i & 1) + (lane >> 4))) << 4);
-    }
-    const qblora_bf16* const x1_tile = X1 + m0 * ldx1;
-    auto issue_x1 = [&](int step, int buf) __attribute__((always_inline)) {
-        const qblora_bf16* base = x1_tile + step * kBK;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) copy16_to_lds(base, xoff[i], lds0 + buf * kTileBytes + i * 8 * 128);
-    };
-    auto issue_copies = [&](int step, int buf) __attribute__((always_inline)) {
-        if (step < steps1) {
-            issue_x1(step, buf);
-        } else {
-            const int k0 = (step - steps1) * kBK;
-            copy_tile(true, X2, ldx2, m0, M - 1, 1, K2, k0, buf * kTileBytes);
-            copy_tile(true, W2, ldw2, n0, N - 1, div2, K2, k0, (2 + buf) * kTileBytes);
-        }
-    };
-
-    // ---- codes / scales -> registers -------------------------------------------------------------
-    const uint8_t* fwd_codes = nullptr; int fwd_stride = 32;
-    const float* fwd_scales = nullptr; int fwd_scale_stride = 1;
-    int qrow = n0 + (t >> 1);                        // this thread's stored weight row (it owns half of it)
-    if (qrow > N - 1) qrow = N - 1;
-    if (d.codes_tiled) { fwd_codes = d.codes_tiled + tiled_run_offset(n0 + (t >> 1), 0, bpr) + (t & 1) * 16; fwd_stride = 256 * 32; }
-    else fwd_codes = codes + (int64_t)qrow * (d_in / 2) + (t & 1) * 16;
-    if (d.scales_tiled) { fwd_scales = d.scales_tiled + tiled_run_offset(n0 + (t >> 1), 0, bpr) / 32; fwd_scale_stride = 256; }
-    else fwd_scales = scales + (int64_t)qrow * bpr;
-    auto load_staged = [&](Staged<BR>& s, int step) __attribute__((always_inline)) {
-        const uint4 v = *reinterpret_cast<const uint4*>(fwd_codes + (int64_t)step * fwd_stride);
-        s.cw[0] = v.x; s.cw[1] = v.y; s.cw[2] = v.z; s.cw[3] = v.w;
-        if constexpr (BR == 8) {
-            // block columns 8*step + 4*half .. +3 of block row qrow/8: one scale per code dword
-            const int64_t b0 = (int64_t)(qrow >> 3) * (d_in >> 3) + 8 * step + 4 * (t & 1);
-            const float4 a4 = *reinterpret_cast<const float4*>(scales + b0);
-            s.sc[0] = a4.x; s.sc[1] = a4.y; s.sc[2] = a4.z; s.sc[3] = a4.w;
-            if constexpr (BETA) {
-                const float4 b4 = *reinterpret_cast<const float4*>(beta + b0);
-                s.be[0] = b4.x; s.be[1] = b4.y; s.be[2] = b4.z; s.be[3] = b4.w;
-            }
-        } else {
-            s.sc[0] = fwd_scales[(int64_t)step * fwd_scale_stride];
-            if constexpr (BETA) s.be[0] = beta[(int64_t)qrow * bpr + step];
-        }
-    };
-
-    // ---- dequantization of a staged k-step: 4 pieces of 8 weights (4 table reads each) per thread ----------
-    // Piece p = code dword p of this thread's half row -> chunk 4*half+p of LDS row t>>1.
-    constexpr int kPieces = 4, kReads = 4;
-    const uint32_t table_lane = lds_address(sT) - lds_address(smem) + ((lane & 15) << 3);
-    auto table_offsets = [&](const Staged<BR>& s, int p, uint32_t (&li)[kReads]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < kReads; ++i) {           // byte i of dword p
-            const uint32_t w = s.cw[p];
-            const uint32_t sh = i == 0 ? (w << 7) : (w >> (8 * i - 7));
-            li[i] = (sh & 0x7f80u) | table_lane;
-        }
-    };
-    auto table_reads = [&](const uint32_t (&li)[kReads], float2 (&lv)[kReads]) __attribute__((always_inline)) {
-#pragma unroll
-        for (int i = 0; i < kReads; ++i) lv[i] = *reinterpret_cast<const float2*>(smem + li[i]);
-    };
-    auto finish_piece = [&](const Staged<BR>& s, int p, const float2 (&lv)[kReads], unsigned char* tile)
-        __attribute__((always_inline)) {
-        float lo[kReads], hi[kReads];
-#pragma unroll
-        for (int i = 0; i < kReads; ++i) {
-            const float sc = s.sc[BR == 8 ? p : 0], be = BETA ? s.be[BR == 8 ? p : 0] : 0.0f;
-            lo[i] = BETA ? __fmaf_rn(lv[i].x, sc, be) : __fmul_rn(lv[i].x, sc);
-            hi[i] = BETA ? __fmaf_rn(lv[i].y, sc, be) : __fmul_rn(lv[i].y, sc);
-        }
-        // byte i holds elements 2i, 2i+1 of the 8: adjacent k, packed as they come
-        uint4 o0;
-        o0.x = pack_bf16(lo[0], hi[0]); o0.y = pack_bf16(lo[1], hi[1]);
-        o0.z = pack_bf16(lo[2], hi[2]); o0.w = pack_bf16(lo[3], hi[3]);
-        *reinterpret_cast<uint4*>(tile + swz(t >> 1, 4 * (t & 1) + p)) = o0;
-    };
-    auto dequant_store = [&](const Staged<BR>& s, unsigned char* tile) __attribute__((always_inline)) {
-#pragma unroll
-        for (int p = 0; p < kPieces; ++p) {
-            uint32_t li[kReads];
-            float2 lv[kReads];
-            table_offsets(s, p, li);
-            table_reads(li, lv);
-            finish_piece(s, p, lv, tile);
-        }
-    };
-
-    // ---- one k-step ----------------------------------------------------------------------------------
-    // Four quarters of 16 MFMAs: a 32-wide slice of k, half of the wave's tokens.  Token fragments of quarter q+1
-    // are read during quarter q (two sets), the slice's weight fragments at its start; the dequantization of the
-    // next weight tile is spread over the first three quarters (table reads one quarter before the values are
-    // scaled and stored); the barrier that publishes the next tiles sits in front of the last quarter, whose MFMAs
-    // cover it and the first fragment reads of the next step.
-    const int r = lane & 15, g = lane >> 4;
-    bf16x8 wf[4], xf[2][4];         // token set 0 holds quarter 0 when a step starts
-    // Fragment addresses: 16-row block b, slice ks: row base + 16b + r, chunk 4ks + g sits at (base + r)*128 +
-    // 2048b + 16*[(g ^ r>>1) & 7 ^ 4ks] -- one per-lane value XOR a constant plus an immediate;
-    // the empty asm in run_step keeps the variants from being hoisted and held in registers.
-    uint32_t frag_w = (uint32_t)(sW - smem) + (uint32_t)((wn0 + r) * 128 + ((g ^ (r >> 1)) << 4));
-    uint32_t frag_x = (uint32_t)(sX - smem) + (uint32_t)((wm0 + r) * 128 + ((g ^ (r >> 1)) << 4));
-    auto read_x = [&](const unsigned char* bx, int q, bf16x8 (&fx)[4]) __attribute__((always_inline)) {
-        const uint32_t xo = (uint32_t)(bx - sX);
-#pragma unroll
-        for (int b = 0; b < 4; ++b)
-            fx[b] = *reinterpret_cast<const bf16x8*>(smem + ((frag_x ^ (uint32_t)((q >> 1) << 6)) + (xo + (4 * (q & 1) + b) * 2048)));
-    };
-    auto read_w = [&](const unsigned char* bw, int ks) __attribute__((always_inline)) {
-        const uint32_t wo = (uint32_t)(bw - sW);
-#pragma unroll
-        for (int a = 0; a < 4; ++a) wf[a] = *reinterpret_cast<const bf16x8*>(smem + ((frag_w ^ (uint32_t)(ks << 6)) + (wo + a * 2048)));
-    };
-    // dq: dequantize `sdq` into bw_next during this step; has_next: a step follows (its tiles are in
-    // bx_next / bw_next once the barrier is passed); dq_next: the following step dequantizes `sdq_next`, whose
-    // first piece is looked up behind this step's barrier (lv0 carries the values across the step boundary).
-    // All flags are literal `true` in the steady state.
-    float2 lv0[kReads];
-    auto run_step = [&](const unsigned char* bx, const unsigned char* bw, const unsigned char* bx_next,
-                        unsigned char* bw_next, const bool dq, const Staged<BR>& sdq, const bool has_next,
-                        const bool refill, const int step2, const int buf2, const bool dq_next,
-                        const Staged<BR>& sdq_next) __attribute__((always_inline)) {
-        float2 lv[2][kReads];
-        uint32_t li[kReads];
-        asm volatile("" : "+v"(frag_w), "+v"(frag_x));
-        if (dq) {
-#pragma unroll
-            for (int i = 0; i < kReads; ++i) lv[0][i] = lv0[i];
-        }
-#pragma unroll
-        for (int ks = 0; ks < 4; ++ks) {
-            const int cur = ks & 1, nxt = cur ^ 1;
-            // the last piece is stored in front of the barrier that publishes the tile
-            if (ks == 3 && dq) finish_piece(sdq, 3, lv[1], bw_next);
-            if (ks == 3 && has_next) {
-                __builtin_amdgcn_s_waitcnt(0x0F70);        // vmcnt(0): direct copies and staged codes
-                __syncthreads();                           // next tiles published; this step's tiles free
-                read_x(bx_next, 0, xf[0]);
-                if (refill) issue_x1(step2, buf2);         // this step's token buffer is free: refill it
-            }
-            if (ks % 2 == 0) read_w(bw, ks / 2);
-            if (ks < 3) read_x(bx, ks + 1, xf[nxt]);
-            if (dq && ks < 3) {
-                // piece ks+1 is looked up while piece ks is scaled and stored
-                table_offsets(sdq, ks + 1, li);
-                table_reads(li, lv[nxt]);
-            }
-            if (ks == 3 && dq_next) {                      // the staged codes of the next step's tile have arrived
-                // (the empty statement pins the address arithmetic behind the barrier: hoisted to the top of
-                // the step it would wait for the code loads issued there)
-                Staged<BR> nx = sdq_next;
-#pragma unroll
-                for (int i = 0; i < 4; ++i) asm volatile("" : "+v"(nx.cw[i]));
-                table_offsets(nx, 0, li);
-                table_reads(li, lv0);
-            }
-            __builtin_amdgcn_sched_barrier(0);             // LDS reads of the next quarter go out before this quarter's MFMAs
-            if (dq && ks < 3) finish_piece(sdq, ks, lv[cur], bw_next);
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b)
-                    acc[a][4 * (ks & 1) + b] =
-                        __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[a], xf[cur][b], acc[a][4 * (ks & 1) + b], 0, 0, 0);
-            // the scaling arithmetic of the piece goes into the shadow of the MFMAs, one vector instruction each
-#pragma unroll
-            for (int i = 0; i < 15; ++i) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
-            }
-            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    };
-
-    // ---- main loop ---------------------------------------------------------------------------------
-    // Invariant at the top of step s: tile buffers s&1 hold step s and fragment set 0 holds its first
-    // quarter; st[(s+1)&1] holds the codes of step s+1 (if that is a quantized step).
-    Staged<BR> st[2];
-    if (nsteps > 0) {
-        issue_copies(0, 0);
-        int issued = 0;                                    // copies are in flight or done for steps <= issued
-        if (steps1 > 1) { issue_copies(1, 1); issued = 1; }
-        if (steps1 > 0) load_staged(st[0], 0);
-        if (steps1 > 1) load_staged(st[1], 1);
-        __syncthreads();                                   // pair table visible
-        if (steps1 > 0) dequant_store(st[0], sW);
-        __builtin_amdgcn_s_waitcnt(0x0F70);
         __syncthreads();
-        read_x(sX, 0, xf[0]);
-        if (steps1 > 1) {                                  // first piece of the tile the first step dequantizes
-            uint32_t li[kReads];
-            table_offsets(st[1], 0, li);
-            table_reads(li, lv0);
+    }
+#pragma unroll
+    for (int p = 0; p < D; ++p) {
+        uint32_t o[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) o[i] = scale(st[0], look_up(st[0].cw[p], i));
+        store_chunk(p, o, sW);
+    }
+    publish(Int<0>{});
+    read_w(0, 0, wf[0]);
+    read_x(0, 0, 0, xf[0]);
+    if (steps1 > 1) {
+#pragma unroll
+        for (int u = 0; u < (BN == 256 ? 4 : 8); ++u) lv[u >> 2][u & 3] = look_up(st[1].cw[u >> 2], u & 3);
+    }
+    int s = 0;
+    // (s is a multiple of the number of sets behind the first loop)
+    if constexpr (BN == 128) {
+        for (; s + 5 < steps1; s += 4) {
+            step(Int<1>{}, Int<0>{}, s);
+            step(Int<1>{}, Int<1>{}, s + 1);
+            step(Int<1>{}, Int<2>{}, s + 2);
+            step(Int<1>{}, Int<3>{}, s + 3);
         }
-        int s = 0;
-        // Quantized steps whose successor is quantized too (the successor's tile is dequantized during
-        // the step), unrolled by two so that the staging registers and the tile buffers have fixed
-        // names.  Codes are fetched two steps ahead; past the end the last quantized step is fetched
-        // again (in bounds, unused) so that the body has no conditions.  A step refills its own token
-        // buffer with the copies of the step after next (when that is a quantized step) behind its
-        // barrier, under its last 8 MFMAs.
-        const int last_q = steps1 - 1;
-        for (; s + 2 < steps1; s += 2) {
-            load_staged(st[0], min(s + 2, last_q));
-            run_step(sX, sW, sX + kTileBytes, sW + kTileBytes, true, st[1], true, true, s + 2, 0, true, st[0]);
-            load_staged(st[1], min(s + 3, last_q));
-            const bool more = s + 3 < steps1;
-            // (past the last dequantizing step the looked-up piece is simply not used)
-            run_step(sX + kTileBytes, sW + kTileBytes, sX, sW, true, st[0], true, more, s + 3, 1, true, st[1]);
-            issued = more ? s + 3 : s + 2;
+        for (; s < steps1; ++s) {
+            step(Int<0>{}, Int<0>{}, s);
+            st[1] = st[2]; st[2] = st[3];
         }
-        if (s + 1 < steps1) {
-            run_step(sX, sW, sX + kTileBytes, sW + kTileBytes, true, st[1], true, false, 0, 0, false, st[0]);
-            ++s;
+    } else {
+        for (; s + 3 < steps1; s += 2) {
+            step(Int<1>{}, Int<0>{}, s);
+            step(Int<1>{}, Int<1>{}, s + 1);
         }
-        // the last quantized step and the K-extension steps: nothing to dequantize; copies of the next
-        // step are issued at the top of a step when no earlier step has done it
-        for (; s < nsteps; ++s) {
-            const int buf = s & 1;
-            const bool has_next = s + 1 < nsteps;
-            if (has_next && issued < s + 1) { issue_copies(s + 1, buf ^ 1); issued = s + 1; }
-            run_step(sX + buf * kTileBytes, sW + buf * kTileBytes, sX + (buf ^ 1) * kTileBytes,
-                     sW + (buf ^ 1) * kTileBytes, false, st[0], has_next, false, 0, 0, false, st[0]);
+        for (; s < steps1; ++s) {
+            step(Int<0>{}, Int<0>{}, s);
+            st[1] = st[0];
         }
     }
-
-    __builtin_amdgcn_s_waitcnt(0x0F70);                    // nothing may still be writing this workgroup's LDS
+    for (; s < nsteps; ++s) step(Int<2>{}, Int<0>{}, s);
+    publish(Int<0>{});                                     // every wave is done reading the tiles
 
     // ---- epilogue ---------------------------------------------------------------------------------------
     // A lane holds features n..n+3 of one token per accumulator, i.e. 8 bytes of an output row.
-    // The wave first lays its 128 x 64 quadrant out in LDS (the tiles are dead by now) as bf16 rows of
+    // The wave first lays its part out in LDS (the tiles are dead by now) as bf16 rows of
     // 128 bytes (pitch 144), then reads it back 16 bytes per lane so that every global store
     // instruction writes eight complete 128-byte row segments.
-    __syncthreads();                                       // every wave is done reading the tiles
     {
         constexpr int kPitch = 144;
-        unsigned char* eb = smem + wave * (128 * kPitch);
+        const int el = lane_id(), er = el & 15, eg = el >> 4;
+        unsigned char* eb = smem + wave * (16 * MB * kPitch);
 #pragma unroll
         for (int a = 0; a < 4; ++a)
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
+            for (int b = 0; b < MB; ++b) {
                 uint2 o;
                 o.x = pack_bf16(acc[a][b][0] * out_scale, acc[a][b][1] * out_scale);
                 o.y = pack_bf16(acc[a][b][2] * out_scale, acc[a][b][3] * out_scale);
-                *reinterpret_cast<uint2*>(eb + (b * 16 + r) * kPitch + (a * 16 + g * 4) * 2) = o;
+                *reinterpret_cast<uint2*>(eb + (b * 16 + er) * kPitch + (a * 16 + eg * 4) * 2) = o;
             }
-        const int erow = lane >> 3, echunk = lane & 7;
+        const int erow = el >> 3, echunk = el & 7;
         const int n = n0 + wn0 + echunk * 8;
 #pragma unroll 8
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < 2 * MB; ++i) {
             const int row = i * 8 + erow;
             const uint4 v = *reinterpret_cast<const uint4*>(eb + row * kPitch + echunk * 16);
             const int64_t m = m0 + wm0 + row;
@@ -418,10 +455,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-template <bool BETA, int BR>
+template <int BN, bool BETA, int BR>
 int launch_cfg(const GemmDesc& d, hipStream_t st) {
-    constexpr size_t smem = 4 * kTileBytes + kTableBytes;
-    auto kern = k_qlinear<BETA, BR>;
+    constexpr size_t smem = 2 * (kTileX + BN * 128) + kTableBytes;
+    auto kern = k_qlinear<BN, BETA, BR>;
     // set once per instantiation; the initialisation of a function-local static is thread safe
     static const bool attr_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
@@ -431,20 +468,44 @@ int launch_cfg(const GemmDesc& d, hipStream_t st) {
     return launch_status();
 }
 
+// Time of a launch in ns, by tile width: a k-step with every CU busy and with a few (a last round of workgroups, one per
+// CU, lies in between).  256 x 128 tiles take 0.65 of the 256 x 256 tiles' time for half the work, so they pay where the
+// wide ones leave more than a third of the CUs idle or start a round for a few tiles.  us on 256 x 256 / 256 x 128 tiles:
+// 1024 x 4096 x 4096 105 / 71, 4096 x 4096 x 4096 124 / 141, 700 x 11008 x 4096 106 / 132, 512 x 11008 x 4096 105 / 69,
+// 700 x 22016 x 8192 398 / 369, 2047 x 16384 x 8192 440 / 532, 4096 x 5120 x 13824 673 / 630.
+struct Plan { bool wide; int64_t ns; };
+Plan plan(int64_t M, int N, int64_t steps) {
+    auto step_ns = [&](int bn, int64_t few, int64_t full) {
+        const int64_t tiles = (M + BM - 1) / BM * ((N + bn - 1) / bn), last = tiles % 256;
+        return tiles / 256 * full + (last ? few + (full - few) * last / 256 : 0);
+    };
+    const int64_t wide = step_ns(256, 1490, 1840), narrow = step_ns(128, 950, 1080);
+    return wide < narrow ? Plan{true, wide * steps} : Plan{false, narrow * steps};
+}
+
+template <bool BETA, int BR>
+int launch_tile(const GemmDesc& d, hipStream_t st) {
+    if (plan(d.M, d.N, 1).wide) return launch_cfg<256, BETA, BR>(d, st);
+    return launch_cfg<128, BETA, BR>(d, st);
+}
+
 }  // namespace
+
+int64_t qlinear_ns(int64_t M, int N, int K) { return plan(M, N, K / kBK).ns; }
 
 // The quantized GEMM of the layer's forward (qmode 1, bf16 output, no auxiliary outputs).
 int launch_qlinear(const GemmDesc& d, hipStream_t st) {
     if (d.M <= 0 || d.N <= 0) return QBLORA_OK;
     if (d.out_f32 || d.C2 || d.C_lo) return QBLORA_ERR_UNSUPPORTED;
     if (d.block_rows == 8) {
-        // scales / offsets are read as 16-byte groups of 4 block columns; tile-ordered scales do not exist
+        // 8 x 8 blocks ask for block parameters on a 16-byte boundary, here as everywhere; tile-ordered scales do not exist
         if (d.scales_tiled || !d.scales || d.d_out % 8 != 0 || (reinterpret_cast<uintptr_t>(d.scales) & 15) ||
             (reinterpret_cast<uintptr_t>(d.beta) & 15))
             return QBLORA_ERR_UNSUPPORTED;
-        return d.beta ? launch_cfg<true, 8>(d, st) : launch_cfg<false, 8>(d, st);
+        return d.beta ? launch_tile<true, 8>(d, st) : launch_tile<false, 8>(d, st);
     }
-    return d.beta ? launch_cfg<true, 1>(d, st) : launch_cfg<false, 1>(d, st);
+    if (!d.scales_tiled) return QBLORA_ERR_UNSUPPORTED;
+    return d.beta ? launch_tile<true, 1>(d, st) : launch_tile<false, 1>(d, st);
 }
 
 }  // namespace qblora
