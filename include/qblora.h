@@ -182,20 +182,23 @@ int qblora_prepack_codes(const qblora_qweight* qw, void* stream);
 /*
  * Dequantize (Eq. 1) to the 16-bit compute weight: Wt[n,k] = bf16(c[code]*alpha) or
  * bf16(fma(c[code], alpha, beta)), fp32 arithmetic then round-to-nearest-even.  This is the
- * weight the forward/backward kernels build on the fly in LDS; the standalone call exists
+ * weight the forward/backward kernels build (see below); the standalone call exists
  * for inspection and tests.  Wt is bf16 [d_out, d_in], device.
  */
 int qblora_dequantize_bf16(const qblora_qweight* qw, qblora_bf16* Wt, void* stream);
 
 /*
  * How qblora_linear_fwd / _bwd build the 16-bit compute weight of Eq. 1 (Alg. 1: W_tilde = dequantize(...), then
- * x @ W_tilde).  A forward on fewer than qblora_dense_min_tokens() tokens -- one 256-token tile -- rebuilds the
- * weight tiles it needs from codes and scales in LDS; from that many tokens on, and in every backward that produces
- * dX, the call first dequantizes the whole weight once into a bf16 buffer inside its workspace (d_out*d_in*2 bytes;
- * transposed for the backward) and the contraction kernel copies weight tiles from there, because rebuilding a
- * tile for each token tile costs more than one sweep over the weight.  The values are the same bf16 numbers either
- * way (qblora_dequantize_bf16's), and so are the results bit for bit.  The buffer is scratch: nothing is kept
- * between calls, and the *_workspace_bytes() queries include it.
+ * x @ W_tilde).  A forward on fewer than qblora_dense_min_tokens() tokens rebuilds the weights it needs from codes and
+ * scales, in registers or in LDS.  From that many tokens on the workspace has room for the whole weight as a bf16
+ * buffer (d_out*d_in*2 bytes); the call dequantizes it once into that and contracts it, because rebuilding it for
+ * each token tile costs more than one sweep over the weight -- or still contracts the codes on wide layers, where it
+ * does not.  A backward that produces dX always dequantizes, transposed.  The weights are the same bf16 numbers every
+ * way (qblora_dequantize_bf16's).  Results: a forward has the same bits on either way it may take at its token count
+ * (qblora_linear_fwd and qblora_linear_fwd_noalloc agree), and a repeated call repeats its bits.  Across token counts
+ * the order of the fp32 sums may differ -- below the limit it depends on the tile that the count selects, and so does
+ * the number of slices whose partial sums a backward adds -- so one token's row need not have the same bits in
+ * two batches.  The buffer is scratch: nothing is kept between calls, and the *_workspace_bytes() queries include it.
  */
 int64_t qblora_dense_min_tokens(void);
 

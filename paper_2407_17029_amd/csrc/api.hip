@@ -104,13 +104,16 @@ Codebook codebook_of(const qblora_qweight* qw) {
 
 int64_t n_blocks(const qblora_qweight* qw) { return (int64_t)qw->d_out * (qw->d_in / qw->block); }
 
-// From this many tokens on, a forward call dequantizes the weight ONCE into a bf16 buffer in its workspace and
-// contracts that; below it -- a single 256-token tile -- the contraction rebuilds weight tiles in LDS, because the
-// one-off pass (0.56 B read + 2 B written per weight) and its scratch would serve one tile only.  With two token
-// tiles or more the pass pays: 11008 x 4096 at 512 tokens 20 + 58 us against 97 us, 4096 x 4096 at 1024 tokens
-// 9 + 39 against 99 us.
+// From this many tokens on, a forward call has scratch for the weight as a bf16 buffer and dequantizes it ONCE into that
+// where this pays (dense_pays); below it the contraction rebuilds the weight from its codes, because the one-off pass
+// (0.56 B read + 2 B written per weight) and its scratch would serve one token tile only.  Both give the same bits from
+// here on.
 constexpr int64_t kDenseMinTokens = 257;
 bool use_dense(const qblora_qweight* qw, int64_t T) { return T >= kDenseMinTokens || half_blocks(qw); }
+// ... and whether a forward with K2 steps of adapter behind the contraction does
+bool dequantize_first(const qblora_qweight* qw, int64_t T, int K2) {
+    return half_blocks(qw) || (T >= kDenseMinTokens && dense_pays(T, qw->d_out, qw->d_in, K2));
+}
 // The backward contracts the transposed weight, which is always dequantized once (its in-LDS form had to transpose
 // every tile on the way in: 512 x 512 at 256 tokens 19 us against 3 + 7, 4096 x 11008 at 512 tokens 239 against 20 + 85).
 
@@ -393,9 +396,9 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     if (T < 0) return QBLORA_ERR_SHAPE;
     if (T == 0) return QBLORA_OK;
     if (!X || !Y) return QBLORA_ERR_NULL;
-    const bool dense = allow_dense && use_dense(qw, T);
-    if (half_blocks(qw) && !dense) return QBLORA_ERR_UNSUPPORTED;
-    if (dense && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
+    if (half_blocks(qw) && !allow_dense) return QBLORA_ERR_UNSUPPORTED;
+    if (allow_dense && use_dense(qw, T) && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
+    const bool dense = allow_dense && dequantize_first(qw, T, has_adapter(ad) ? ad->R : 0);
     FwdSpace ws = carve_fwd(qw, ad, T, workspace, dense);
     if (ws.bytes > 0 && (!workspace || workspace_bytes < ws.bytes)) return QBLORA_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
@@ -689,10 +692,10 @@ int check_qa(const qblora_qweight* qw, const qblora_bf16* H, int32_t lam1, int32
 }
 
 struct QaFwdSpace { float* scales; qblora_bf16 *Ht, *P, *W16; size_t bytes; };
-QaFwdSpace carve_qa_fwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T, void* ws) {
+QaFwdSpace carve_qa_fwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T, void* ws, bool dense) {
     Carver c(ws);
     QaFwdSpace s{};
-    if (use_dense(qw, T)) {
+    if (dense) {
         s.W16 = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
         if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
     } else {
@@ -725,7 +728,7 @@ QaBwdSpace carve_qa_bwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T,
 
 size_t qablora_linear_fwd_workspace_bytes(const qblora_qweight* qw, int32_t lambda1, int32_t lambda2, int64_t T) {
     if (check_qweight(qw, false, true) || lambda1 <= 0 || lambda2 <= 0 || T < 0) return 0;
-    return carve_qa_fwd(qw, lambda1, lambda2, T, nullptr).bytes;
+    return carve_qa_fwd(qw, lambda1, lambda2, T, nullptr, use_dense(qw, T)).bytes;
 }
 
 size_t qablora_linear_bwd_workspace_bytes(const qblora_qweight* qw, int32_t lambda1, int32_t lambda2, int64_t T) {
@@ -741,7 +744,8 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     if (T < 0) return QBLORA_ERR_SHAPE;
     if (T == 0) return QBLORA_OK;
     if (!X || !Y) return QBLORA_ERR_NULL;
-    QaFwdSpace ws = carve_qa_fwd(qw, lambda1, lambda2, T, workspace);
+    const bool dense = dequantize_first(qw, T, qw->d_in / lambda1);   // many tokens: the weight is dequantized once
+    QaFwdSpace ws = carve_qa_fwd(qw, lambda1, lambda2, T, workspace, dense);
     if (!workspace || workspace_bytes < ws.bytes) return QBLORA_ERR_WORKSPACE;
     hipStream_t st = as_stream(stream);
     const int I = qw->d_in / lambda1, J = qw->d_out / lambda2;
@@ -753,9 +757,8 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     if (grouped) { sct.scale_codes = qw->scale_codes; sct.scale_step = qw->scale_step; sct.scale_mid = qw->scale_mid; }
     sct.scale_group = qw->scale_group; sct.d_out = qw->d_out; sct.d_in = qw->d_in; sct.out = ws.scales;
     const bool tile8 = block_rows_of(qw) == 8;               // 8 x 8 blocks: scales are read in place
-    const bool dense = use_dense(qw, T);                     // many tokens: the weight is dequantized once
     const bool few = !dense && few_applies(T, qw->d_out, qw->d_in);
-    if (dense && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
+    if (use_dense(qw, T) && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
     if (tile8 || dense || few) sct.out = nullptr;
     if ((rc = launch_adapter_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, st, sct.out ? &sct : nullptr))) return rc;
     if (dense) {

@@ -147,6 +147,11 @@ bool few_applies(int64_t M, int N, int K);
 int launch_few(const GemmDesc& d, hipStream_t st);
 // the contraction on a weight dequantized beforehand (qmode 3); called by launch_gemm
 int launch_dense(const GemmDesc& d, hipStream_t st);
+// its tile shape (0 .. 3: 256 x 256, 128 x 256, 256 x 128, 128 x 128 tokens x features), slices and estimated time
+struct DensePlan { int shape, splits; int64_t ns; };
+DensePlan dense_plan(int64_t M, int N, int k1, int k2, int max_splits);
+// whether dequantizing the weight first is faster than contracting straight from the codes (qmode 3 against qmode 1)
+bool dense_pays(int64_t M, int N, int k1, int k2);
 // slices of the contraction that pay for an [M, N] output over k1 + k2 (GemmDesc::splits; 1 = none)
 int dense_splits(int64_t M, int N, int k1, int k2);
 // narrow-output plain bf16 GEMM (qmode 0, N = inner rank); called by launch_gemm when it applies

@@ -432,6 +432,8 @@ int launch_cfg(const GemmDesc& d, hipStream_t st) {
     return launch_status();
 }
 
+}  // namespace
+
 // Tile shape (and slices) by the estimated time.  `full` is the measured time of a k-step with every CU busy, `few`
 // with a few (the clock is power-limited: 1.5-1.7 GHz with all matrix pipes busy, 2.4 with few), both in ns; a last
 // round of workgroups (256, one per CU) that is not full lies in between.  Larger tiles move fewer bytes per MFMA
@@ -441,13 +443,11 @@ int launch_cfg(const GemmDesc& d, hipStream_t st) {
 // 358 / 439; 8192 x 4096 x 4096 192 / 233 / 238 / 285.  A slice adds its fp32 partial tile, written and read once, and
 // all of them the second launch: 512 x 4096 x 11008 91 -> 54 + 7 us (128 x 256, four slices), 300 x 2048 x 6144 51 ->
 // 19 + 4 (five), 128 x 4096 x 4096 35 -> 14 + 5 (five).
-struct Plan { int shape, splits; };
-Plan plan(int64_t M, int N, int k1, int k2, int max_splits) {
+DensePlan dense_plan(int64_t M, int N, int k1, int k2, int max_splits) {
     struct Shape { int bm, bn; int64_t few, full; };
     static constexpr Shape shapes[4] = {{256, 256, 940, 1460}, {128, 256, 800, 920}, {256, 128, 800, 930}, {128, 128, 490, 570}};
     const int64_t steps = k1 / kBK + (k2 + kBK - 1) / kBK;
-    Plan best{0, 1};
-    int64_t best_ns = INT64_MAX;
+    DensePlan best{0, 1, INT64_MAX};
     for (int i = 0; i < 4; ++i) {
         const int64_t tiles = ((M + shapes[i].bm - 1) / shapes[i].bm) * ((N + shapes[i].bn - 1) / shapes[i].bn);
         for (int s = 1; s <= max_splits && (s == 1 || (tiles * s <= 256 && steps >= 4 * s)); ++s) {
@@ -456,17 +456,25 @@ Plan plan(int64_t M, int N, int k1, int k2, int max_splits) {
                                     (last ? shapes[i].few + (shapes[i].full - shapes[i].few) * last / 256 : 0);
             int64_t ns = step_ns * ((steps + s - 1) / s);
             if (s > 1) ns += 5000 + M * N * 8 * s / 4000;        // bytes at 4 TB/s
-            if (ns < best_ns) { best_ns = ns; best = Plan{i, s}; }
+            if (ns < best.ns) best = DensePlan{i, s, ns};
         }
     }
     return best;
 }
 
-}  // namespace
+// The one-off pass takes 0.46 us per million weights and a launch, which the forward's kernel from the codes does not
+// spend; that one wins on wide layers with few tokens.  us from the codes / dequantized first: 512 x 22016 x 8192 190 / 265,
+// 512 x 16384 x 8192 138 / 194, 512 x 11008 x 4096 72 / 77, 1024 x 16384 x 8192 233 / 257, 512 x 4096 x 4096 70 / 46,
+// 2048 x 22016 x 8192 632 / 610.  The margin of 5 % is for the estimates' errors: without it 72 of 1134 measured calls
+// lose up to 9 % of their time, with it three lose 3 % (and 207 gain 17 % on average).
+bool dense_pays(int64_t M, int N, int k1, int k2) {
+    const int64_t first = dense_plan(M, N, k1, k2, 1).ns + (int64_t)N * k1 * 46 / 100000 + 2000;
+    return qlinear_ns(M, N, k1 + (k2 + kBK - 1) / kBK * kBK) + 2000 >= first - first * 5 / 100;
+}
 
 int dense_splits(int64_t M, int N, int k1, int k2) {
     if (M <= 0 || N <= 0 || N % 8 != 0) return 1;
-    return plan(M, N, k1, k2, 8).splits;
+    return dense_plan(M, N, k1, k2, 8).splits;
 }
 
 int launch_dense(const GemmDesc& d, hipStream_t st) {
@@ -475,7 +483,7 @@ int launch_dense(const GemmDesc& d, hipStream_t st) {
     if (d.out_f32 || d.C2 || d.C_lo || !d.W1 || d.K1 <= 0 || d.K1 % kBK != 0 || d.N % 32 != 0 ||
         (reinterpret_cast<uintptr_t>(d.W1) & 15))
         return QBLORA_ERR_UNSUPPORTED;
-    const Plan p = plan(d.M, d.N, d.K1, d.K2, d.splits > 1 ? 8 : 1);
+    const DensePlan p = dense_plan(d.M, d.N, d.K1, d.K2, d.splits > 1 ? 8 : 1);
     if (d.splits > 1 && p.splits != d.splits) return QBLORA_ERR_UNSUPPORTED;       // not what dense_splits said
     switch (p.shape) {
         case 0: return launch_cfg<4, 2>(d, st);

@@ -469,7 +469,7 @@ int launch_cfg(const GemmDesc& d, hipStream_t st) {
 }
 
 // Time of a launch in ns, by tile width: a k-step with every CU busy and with a few (a last round of workgroups, one per
-// CU, lies in between).  256 x 128 tiles take 0.65 of the 256 x 256 tiles' time for half the work, so they pay where the
+// CU, lies in between: the clock holds up to about 3/4 of them).  256 x 128 tiles take 0.65 of the 256 x 256 tiles' time for half the work, so they pay where the
 // wide ones leave more than a third of the CUs idle or start a round for a few tiles.  us on 256 x 256 / 256 x 128 tiles:
 // 1024 x 4096 x 4096 105 / 71, 4096 x 4096 x 4096 124 / 141, 700 x 11008 x 4096 106 / 132, 512 x 11008 x 4096 105 / 69,
 // 700 x 22016 x 8192 398 / 369, 2047 x 16384 x 8192 440 / 532, 4096 x 5120 x 13824 673 / 630.
@@ -477,7 +477,7 @@ struct Plan { bool wide; int64_t ns; };
 Plan plan(int64_t M, int N, int64_t steps) {
     auto step_ns = [&](int bn, int64_t few, int64_t full) {
         const int64_t tiles = (M + BM - 1) / BM * ((N + bn - 1) / bn), last = tiles % 256;
-        return tiles / 256 * full + (last ? few + (full - few) * last / 256 : 0);
+        return tiles / 256 * full + (last ? few + (full - few) * last * last / 65536 : 0);
     };
     const int64_t wide = step_ns(256, 1490, 1840), narrow = step_ns(128, 950, 1080);
     return wide < narrow ? Plan{true, wide * steps} : Plan{false, narrow * steps};
