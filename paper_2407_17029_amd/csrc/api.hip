@@ -998,9 +998,14 @@ size_t qblora_linear_decode_workspace_bytes(const qblora_qweight* qw) {
 }
 size_t qblora_linear_decode_tokens_workspace_bytes(const qblora_qweight* qw, int32_t T) {
     if (check_qweight(qw, false, true)) return 0;
-    // (queries beyond the largest batch answer for the largest)
+    // The size covers every smaller batch too: the slices depend on the token tile, and the largest batch of a smaller
+    // tile may have more partial sums (22016 x 8192: none from 129 tokens on, 22 MB at 128).  Queries beyond the largest
+    // batch answer for the largest.
     const bool mid = T > kDecodeMaxTokens || (T > 0 && half_blocks(qw));
-    const size_t part = mid ? w4_mid_part_bytes(qw->d_out, qw->d_in, std::min(T, kMidMaxTokens)) : 0;
+    size_t part = 0;
+    if (mid)
+        for (const int32_t tile : {32, 64, 128, 192, kMidMaxTokens})
+            part = std::max(part, w4_mid_part_bytes(qw->d_out, qw->d_in, std::min(T, tile)));
     return qblora_linear_decode_workspace_bytes(qw) + align_up(part);
 }
 int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblora_bf16* X, int32_t T, qblora_bf16* Y,

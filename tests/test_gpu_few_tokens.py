@@ -59,6 +59,24 @@ def test_mid_batch_slices_of_odd_outputs(oracle, codebook, T, d_out, d_in):
     assert_close_bf16(Y, oracle.forward(Wt, L.X, None, None, 1, 1, 0.0), "Y")
 
 
+def test_mid_batch_on_the_workspace_of_the_largest(oracle, codebook):
+    """A serving loop allocates for 256 tokens once; this layer needs no partial tiles there, and three slices at 100."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
+    d_out, d_in = 19200, 768
+    print(f"case mid batch, one workspace {d_out}x{d_in}", flush=True)
+    L = synth.make_layer(7500, 100, d_out, d_in, 8, 1, 1)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook)
+    q = qw.c_struct()
+    need = int(qb.lib().qblora_linear_decode_tokens_workspace_bytes(qb.C.byref(q), 256))
+    ws = torch.empty(max(need, 256), dtype=torch.uint8, device=qw.codes.device)
+    Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
+    for T in (100, 33, 17, 5):
+        Y = qb.qblora_linear_decode(qw, bf16_to_dev(L.X[:T]), workspace=ws)
+        torch.cuda.synchronize()
+        assert_close_bf16(Y, oracle.forward(Wt, L.X[:T], None, None, 1, 1, 0.0), f"Y, {T} tokens")
+
+
 @pytest.mark.parametrize("T,d_out,d_in", [(8, 40, 4160), (5, 4096, 8128), (8, 256, 6080)])
 def test_sixteen_wave_decode_of_a_packed_model(oracle, codebook, T, d_out, d_in):
     """Packed INT4 model whose activations exceed the LDS copy, few rows: sixteen waves share a row group, with
