@@ -71,7 +71,7 @@ def test_mid_batch_on_the_workspace_of_the_largest(oracle, codebook):
     need = int(qb.lib().qblora_linear_decode_tokens_workspace_bytes(qb.C.byref(q), 256))
     ws = torch.empty(max(need, 256), dtype=torch.uint8, device=qw.codes.device)
     Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
-    for T in (100, 33, 17, 5):
+    for T in (100, 33, 17):                              # (up to 16 tokens the weight is not rounded, and there are no slices)
         Y = qb.qblora_linear_decode(qw, bf16_to_dev(L.X[:T]), workspace=ws)
         torch.cuda.synchronize()
         assert_close_bf16(Y, oracle.forward(Wt, L.X[:T], None, None, 1, 1, 0.0), f"Y, {T} tokens")
