@@ -151,14 +151,21 @@ struct BwdSpace {
     int splits_a, splits_b, splits_x;
     size_t bytes;
 };
-BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T, void* ws) {
+// `dx`: the call produces dX, i.e. dequantizes the weight and contracts it.  `query`: the size that serves every number of
+// tokens up to T -- the slices of the contractions, and with them the partial sums, may be more for fewer tokens.
+BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T, void* ws, bool dx, bool query) {
     Carver c(ws);
     BwdSpace s{};
-    if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
-    s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
-    // slices of the dX contraction: their partial sums share the gradients' buffer, which is free by then
-    s.splits_x = dense_splits(T, qw->d_in, qw->d_out, has_adapter(ad) ? ad->R : 0);
-    const size_t px = s.splits_x > 1 ? (size_t)s.splits_x * T * qw->d_in : 0;
+    size_t px = 0;
+    if (dx) {
+        const int R = has_adapter(ad) ? ad->R : 0;
+        if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
+        s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
+        // slices of the dX contraction: their partial sums share the gradients' buffer, which is free by then
+        s.splits_x = query ? 1 : dense_splits(T, qw->d_in, qw->d_out, R);
+        const int64_t rows = query ? dense_part_rows(T, qw->d_in, qw->d_out, R) : s.splits_x > 1 ? s.splits_x * T : 0;
+        px = (size_t)rows * qw->d_in;
+    }
     if (!has_adapter(ad) && px) s.part = c.take<float>(px);
     if (has_adapter(ad)) {
         s.At_x = c.take<qblora_bf16>((size_t)ad->R * qw->d_in);
@@ -172,7 +179,9 @@ BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T
         s.splits_b = grad_splits(T, qw->d_out);
         size_t pa = std::max(px, (size_t)s.splits_a * qw->d_in * ad->R);
         // (the narrow GEMMs' partial sums share the buffer: they are added up before the gradients start)
-        pa = std::max(pa, (size_t)T * ad->R * std::max(su_splits(qw, ad, T), du_splits(qw, ad, T)));
+        const int64_t narrow = query ? std::max(skinny_part_rows(T, ad->R, qw->d_in), skinny_part_rows(T, ad->R, qw->d_out))
+                                     : T * std::max(su_splits(qw, ad, T), du_splits(qw, ad, T));
+        pa = std::max(pa, (size_t)narrow * ad->R);
         size_t pb = (size_t)s.splits_b * qw->d_out * ad->R;
         s.part = c.take<float>(pa);             // dA and dB are computed in one launch: a buffer each
         s.part_b = c.take<float>(pb);
@@ -376,7 +385,7 @@ size_t qblora_linear_fwd_workspace_bytes(const qblora_qweight* qw, const qblora_
 
 size_t qblora_linear_bwd_workspace_bytes(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T) {
     if (check_layer(qw, ad) || T < 0) return 0;
-    return carve_bwd(qw, ad, T, nullptr).bytes;
+    return carve_bwd(qw, ad, T, nullptr, true, true).bytes;
 }
 
 int64_t qblora_dense_min_tokens(void) { return kDenseMinTokens; }
@@ -503,7 +512,7 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     }
     if (!dY || (adapted && !X)) return QBLORA_ERR_NULL;
     if (dX && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
-    BwdSpace ws = carve_bwd(qw, ad, T, workspace);
+    BwdSpace ws = carve_bwd(qw, ad, T, workspace, dX != nullptr, false);
     if (ws.bytes > 0 && (!workspace || workspace_bytes < ws.bytes)) return QBLORA_ERR_WORKSPACE;
 
     GemmDesc g{};
@@ -708,18 +717,23 @@ QaFwdSpace carve_qa_fwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T,
 }
 
 struct QaBwdSpace { float* scales; qblora_bf16 *P, *dVs, *dVs_lo, *W16t; float* part; int splits, splits_x; size_t bytes; };
-QaBwdSpace carve_qa_bwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T, void* ws) {
+QaBwdSpace carve_qa_bwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T, void* ws, bool dx, bool query) {
     Carver c(ws);
     QaBwdSpace s{};
     const int I = qw->d_in / lam1, J = qw->d_out / lam2;
-    if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
-    s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
+    size_t px = 0;                                            // as in carve_bwd
+    if (dx) {
+        if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
+        s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
+        s.splits_x = query ? 1 : dense_splits(T, qw->d_in, qw->d_out, J);
+        const int64_t rows = query ? dense_part_rows(T, qw->d_in, qw->d_out, J) : s.splits_x > 1 ? s.splits_x * T : 0;
+        px = (size_t)rows * qw->d_in;
+    }
     s.P = c.take<qblora_bf16>((size_t)T * I);
     s.dVs = c.take<qblora_bf16>((size_t)T * J);
     s.dVs_lo = c.take<qblora_bf16>((size_t)T * J);
     s.splits = grad_splits(T, I, J);
-    s.splits_x = dense_splits(T, qw->d_in, qw->d_out, J);
-    s.part = c.take<float>(std::max((size_t)s.splits * I * J, s.splits_x > 1 ? (size_t)s.splits_x * T * qw->d_in : 0));
+    s.part = c.take<float>(std::max((size_t)s.splits * I * J, px));
     s.bytes = c.off;
     return s;
 }
@@ -733,7 +747,7 @@ size_t qablora_linear_fwd_workspace_bytes(const qblora_qweight* qw, int32_t lamb
 
 size_t qablora_linear_bwd_workspace_bytes(const qblora_qweight* qw, int32_t lambda1, int32_t lambda2, int64_t T) {
     if (check_qweight(qw, false, true) || lambda1 <= 0 || lambda2 <= 0 || T < 0) return 0;
-    return carve_qa_bwd(qw, lambda1, lambda2, T, nullptr).bytes;
+    return carve_qa_bwd(qw, lambda1, lambda2, T, nullptr, true, true).bytes;
 }
 
 int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t lambda1, int32_t lambda2, float s,
@@ -804,7 +818,7 @@ int qablora_linear_bwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
         return QBLORA_OK;
     }
     if (!dY || (dH && !X)) return QBLORA_ERR_NULL;
-    QaBwdSpace ws = carve_qa_bwd(qw, lambda1, lambda2, T, workspace);
+    QaBwdSpace ws = carve_qa_bwd(qw, lambda1, lambda2, T, workspace, dX != nullptr, false);
     if (!workspace || workspace_bytes < ws.bytes) return QBLORA_ERR_WORKSPACE;
     if (dX && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
 

@@ -154,11 +154,15 @@ DensePlan dense_plan(int64_t M, int N, int k1, int k2, int max_splits);
 bool dense_pays(int64_t M, int N, int k1, int k2);
 // slices of the contraction that pay for an [M, N] output over k1 + k2 (GemmDesc::splits; 1 = none)
 int dense_splits(int64_t M, int N, int k1, int k2);
+// the most rows of partial sums, slices x tokens, that any number of tokens up to M takes
+int64_t dense_part_rows(int64_t M, int N, int k1, int k2);
 // narrow-output plain bf16 GEMM (qmode 0, N = inner rank); called by launch_gemm when it applies
 bool skinny_applies(const GemmDesc& d);
 bool skinny_dup_applies(int N, int K, int64_t ldw);
 // slices of the contraction that fill the chip when there are few tokens; at most max_part_bytes of partial sums
 int skinny_splits(int64_t M, int N, int K, int64_t max_part_bytes);
+// no fewer rows of partial sums, slices x tokens, than any number of tokens up to M takes
+int64_t skinny_part_rows(int64_t M, int N, int K);
 int launch_skinny(const GemmDesc& d, hipStream_t st);
 
 // Token-contraction GEMM with split-T partials:  part[z][i][j] = sum_{t in slice z} L[t,i] * S[t,j]

@@ -25,6 +25,7 @@
 //
 // k is accumulated in ascending order by v_mfma_f32_16x16x32_bf16, as in the kernel that rebuilds weight tiles
 // in LDS (qlinear.hip), so both give the same bits.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -454,12 +455,40 @@ DensePlan dense_plan(int64_t M, int N, int k1, int k2, int max_splits) {
             const int64_t units = tiles * s, last = units % 256;
             const int64_t step_ns = units / 256 * shapes[i].full +
                                     (last ? shapes[i].few + (shapes[i].full - shapes[i].few) * last / 256 : 0);
-            int64_t ns = step_ns * ((steps + s - 1) / s);
-            if (s > 1) ns += 5000 + M * N * 8 * s / 4000;        // bytes at 4 TB/s
-            if (ns < best.ns) best = DensePlan{i, s, ns};
+            int64_t t = step_ns * ((steps + s - 1) / s) * 4000;  // in ns / 4000: exactly linear in M while the tiles stay
+            if (s > 1) t += 5000 * 4000 + M * N * 8 * s;         // bytes at 4 TB/s
+            if (t < best.ns) best = DensePlan{i, s, t};
         }
     }
+    best.ns /= 4000;
     return best;
+}
+
+// Tiles are counted in 128 or 256 tokens, so between two multiples of 128 every form's time is linear in M, with a slope
+// that grows with its slices: the cheapest form's slices do not increase with M there, and each run of the same number
+// has its most rows at its end.
+int64_t dense_part_rows(int64_t M, int N, int k1, int k2) {
+    if (M <= 0 || N <= 0) return 0;
+    auto splits = [&](int64_t m) { return (int64_t)dense_splits(m, N, k1, k2); };
+    int64_t top = 0;                                             // the largest M whose tiles leave room for two slices
+    for (const int bm : {128, 256})
+        for (const int bn : {128, 256}) top = std::max<int64_t>(top, (int64_t)bm * (128 / ((N + bn - 1) / bn)));
+    int64_t rows = 0;
+    for (int64_t hi = std::min(M, top); hi > 0 && 8 * hi > rows; hi = (hi - 1) / 128 * 128) {
+        const int64_t lo = (hi - 1) / 128 * 128 + 1, most = splits(lo);
+        for (int64_t b = hi, s = splits(b); ; ) {
+            if (s > 1) rows = std::max(rows, s * b);
+            if (most <= s || most * b <= rows) break;
+            int64_t more = lo, same = b;                         // the last M with more slices
+            while (same - more > 1) {
+                const int64_t mid = (more + same) / 2;
+                if (splits(mid) > s) more = mid; else same = mid;
+            }
+            b = more;
+            s = splits(b);
+        }
+    }
+    return rows;
 }
 
 // The one-off pass takes 0.46 us per million weights and a launch, which the forward's kernel from the codes does not

@@ -337,6 +337,10 @@ int skinny_splits(int64_t M, int N, int K, int64_t max_part_bytes) {
     const int64_t s = std::min(std::min<int64_t>(256 / wgs, 16), std::min(steps / 4, max_part_bytes / (M * N * 4)));
     return s >= 2 && steps - steps / s >= 12 ? (int)s : 1;
 }
+int64_t skinny_part_rows(int64_t M, int N, int K) {
+    const int64_t most = std::min(16, K / (2 * kBK) / 4);         // M * slices <= 64 * token tiles * (256 / workgroups)
+    return M <= 0 || N <= 0 ? 0 : std::min(M * std::max<int64_t>(most, 1), std::max<int64_t>(M, 64 * 256 / ((N + 63) / 64)));
+}
 
 int launch_skinny(const GemmDesc& d, hipStream_t st) {
     // 64 x 128 tiles once they alone fill the chip twice over; below that 64 x 64 tiles with a deep

@@ -51,3 +51,37 @@ def test_inference_workspace_serves_smaller_batches(rules, d_out, d_in, kind):
     need = [rules.L.qblora_linear_decode_tokens_workspace_bytes(C.byref(q), T) for T in range(0, 300)]
     assert all(a <= b for a, b in zip(need, need[1:]))
     assert need[256] == need[299]
+
+
+TOKENS = sorted({*range(1, 400), *range(400, 3300, 13), 511, 512, 513, 767, 768, 769, 1024, 2047, 2048, 4096, 8192})
+
+
+@pytest.mark.parametrize("d_out,d_in", SHAPES)
+@pytest.mark.parametrize("R,lam,op", [(0, 1, 0), (16, 2, 0), (136, 4, 0), (512, 8, 0), (24, 2, 2)])
+def test_layer_workspaces_serve_fewer_tokens(rules, d_out, d_in, R, lam, op):
+    """One workspace for the largest batch, then a ragged last one: the slices of a contraction may grow as tokens get
+    fewer, the sizes may not."""
+    qb, L = rules.qb, rules.L
+    d_out = d_out // 64 * 64
+    q = _weight(qb, d_out, d_in, grouped=R == 136)
+    ad = qb.CAdapter()
+    ad.lambda1, ad.lambda2, ad.R, ad.s, ad.scale_op = lam, lam, R, 1.0, op
+    if R:
+        ad.A = ad.B = 0x1000
+    for f in (L.qblora_linear_fwd_workspace_bytes, L.qblora_linear_bwd_workspace_bytes):
+        need = [f(C.byref(q), C.byref(ad), T) for T in TOKENS]
+        assert need[0] > 0 and all(a <= b for a, b in zip(need, need[1:]))
+    for f in (L.qablora_linear_fwd_workspace_bytes, L.qablora_linear_bwd_workspace_bytes):
+        need = [f(C.byref(q), lam, lam, T) for T in TOKENS]
+        assert need[0] > 0 and all(a <= b for a, b in zip(need, need[1:]))
+
+
+@pytest.mark.parametrize("N,k1,k2", [(512, 512, 0), (4096, 11008, 128), (4160, 448, 8), (11008, 4096, 1376), (64, 22016, 0)])
+def test_partial_sum_rows_are_the_most_of_any_count(rules, N, k1, k2):
+    rows = rules.L["_ZN6qblora15dense_part_rowsEliii"]
+    rows.argtypes, rows.restype = [C.c_int64, C.c_int, C.c_int, C.c_int], C.c_int64
+    most = 0
+    for T in range(1, 1500):
+        s = rules.dense_plan(T, N, k1, k2, 8).splits
+        most = max(most, s * T if s > 1 else 0)
+        assert rows(T, N, k1, k2) == most, T

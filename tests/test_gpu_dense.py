@@ -55,3 +55,61 @@ def test_tiles_and_stages(oracle, codebook, T, d_out, d_in, R):
     qb.qblora_linear_fwd_noalloc(qw, ad, X, Y2)
     torch.cuda.synchronize()
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
+
+
+@pytest.mark.parametrize("form", ["none", "two", "single"])
+def test_fewer_tokens_on_the_workspace_of_many(oracle, codebook, form):
+    """A training loop allocates for its largest batch; the backward of a smaller one takes more slices here, and more
+    partial sums than the largest does."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, assert_close_f32, OracleWeight
+    d_out, d_in, most = 1024, 512, 600
+    print(f"case one workspace, {form}", flush=True)
+    L = synth.make_layer(5900, 300, d_out, d_in, 16, 2, 2, b_std=0.05)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook)
+    Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
+    ad = qb.Adapter(bf16_to_dev(L.A), bf16_to_dev(L.B), 2, 2, 0.5) if form == "two" else None
+    Hb = synth.f32_to_bf16_bits(synth.normal_f32(5901, 0, (d_in // 8, d_out // 8)) * np.float32(0.02))
+    q = qw.c_struct()
+    need = (int(qb.lib().qablora_linear_bwd_workspace_bytes(qb.C.byref(q), 8, 8, most)) if form == "single"
+            else qb.qblora_linear_bwd_workspace_bytes(qw, ad, most))
+    ws = torch.empty(need, dtype=torch.uint8, device=qw.codes.device)
+    for T in (300, 200, 100):
+        X, dY = bf16_to_dev(L.X[:T]), bf16_to_dev(L.dY[:T])
+        if form == "single":
+            dX, dH = qb.qablora_linear_bwd(qw, bf16_to_dev(Hb), 8, 8, 0.5, X, dY, workspace=ws)
+            torch.cuda.synchronize()
+            rX, rH = oracle.qa_backward(Wt, L.X[:T], L.dY[:T], Hb, 8, 8, 0.5)
+            assert_close_f32(dH, rH, "dH")
+        else:
+            dX, dA, dB = qb.qblora_linear_bwd(qw, ad, X, dY, need_grads=ad is not None, workspace=ws)
+            torch.cuda.synchronize()
+            A, B, s = (L.A, L.B, 0.5) if ad else (None, None, 0.0)
+            rX, rA, rB = oracle.backward(Wt, L.X[:T], L.dY[:T], A, B, 2, 2, s)
+            if ad:
+                assert_close_f32(dA, rA, "dA")
+                assert_close_f32(dB, rB, "dB")
+        assert_close_bf16(dX, rX, f"dX, {T} tokens")
+
+
+@pytest.mark.parametrize("form", ["two", "single"])
+def test_gradients_alone_need_no_room_for_the_weight(codebook, form):
+    """Without dX nothing is dequantized: the call takes a workspace smaller than the 16-bit weight, same bits."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev
+    T, d_out, d_in = 200, 2048, 1024
+    print(f"case gradients alone, {form}", flush=True)
+    L = synth.make_layer(5950, T, d_out, d_in, 16, 2, 2, b_std=0.05)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook, qb.SCALES_E4M3_GROUPED)
+    X, dY = bf16_to_dev(L.X), bf16_to_dev(L.dY)
+    ws = torch.empty(2 * d_out * d_in - 256, dtype=torch.uint8, device=X.device)
+    if form == "two":
+        ad = qb.Adapter(bf16_to_dev(L.A), bf16_to_dev(L.B), 2, 2, 0.5)
+        _, dA, dB = qb.qblora_linear_bwd(qw, ad, X, dY, need_dx=False, workspace=ws)
+        _, rA, rB = qb.qblora_linear_bwd(qw, ad, X, dY)
+        assert torch.equal(dA, rA) and torch.equal(dB, rB)
+    else:
+        H = torch.zeros((d_in // 8, d_out // 8), dtype=torch.bfloat16, device=X.device)
+        _, dH = qb.qablora_linear_bwd(qw, H, 8, 8, 0.5, X, dY, need_dx=False, workspace=ws)
+        _, rH = qb.qablora_linear_bwd(qw, H, 8, 8, 0.5, X, dY)
+        assert torch.equal(dH, rH)
