@@ -331,10 +331,11 @@ def qblora_linear_bwd_workspace_bytes(qw: QWeight, ad, T: int) -> int:
     return int(lib().qblora_linear_bwd_workspace_bytes(C.byref(s), aref, T))
 
 
-def _workspace(nbytes: int, device, workspace):
+def _workspace(nbytes, device, workspace):
+    """The caller's workspace, or one of nbytes() bytes (a query that is only made when it is needed)."""
     if workspace is not None:
         return workspace
-    return torch.empty(max(nbytes, 256), dtype=torch.uint8, device=device)
+    return torch.empty(max(int(nbytes()), 256), dtype=torch.uint8, device=device)
 
 
 def qblora_saved_bytes(ad, T: int) -> int:
@@ -349,7 +350,7 @@ def qblora_linear_fwd(qw: QWeight, ad, X: torch.Tensor, Y: torch.Tensor = None, 
     T = X.shape[0]
     if Y is None:
         Y = torch.empty((T, qw.d_out), dtype=torch.bfloat16, device=X.device)
-    ws = _workspace(qblora_linear_fwd_workspace_bytes(qw, ad, T), X.device, workspace)
+    ws = _workspace(lambda: qblora_linear_fwd_workspace_bytes(qw, ad, T), X.device, workspace)
     s = qw.c_struct()
     a, aref = _adapter_ref(ad)
     if saved is None:
@@ -396,7 +397,7 @@ def qblora_linear_bwd(qw: QWeight, ad, X: torch.Tensor, dY: torch.Tensor, need_d
             dA = torch.empty((qw.d_in // ad.lambda1, ad.R), dtype=torch.float32, device=dev)
         if dB is None:
             dB = torch.empty((ad.R, qw.d_out // ad.lambda2), dtype=torch.float32, device=dev)
-    ws = _workspace(qblora_linear_bwd_workspace_bytes(qw, ad, T), dev, workspace)
+    ws = _workspace(lambda: qblora_linear_bwd_workspace_bytes(qw, ad, T), dev, workspace)
     s = qw.c_struct()
     a, aref = _adapter_ref(ad)
     if saved is None:
@@ -420,7 +421,7 @@ def qablora_linear_fwd(qw: QWeight, H: torch.Tensor, lambda1: int, lambda2: int,
     if Y is None:
         Y = torch.empty((T, qw.d_out), dtype=torch.bfloat16, device=X.device)
     q = qw.c_struct()
-    ws = _workspace(int(lib().qablora_linear_fwd_workspace_bytes(C.byref(q), lambda1, lambda2, T)), X.device, workspace)
+    ws = _workspace(lambda: lib().qablora_linear_fwd_workspace_bytes(C.byref(q), lambda1, lambda2, T), X.device, workspace)
     rc = lib().qablora_linear_fwd(C.byref(q), _ptr(H), lambda1, lambda2, s, _ptr(X), T, _ptr(Y), _ptr(ws), ws.numel(),
                                   _stream())
     _check(rc, "qablora_linear_fwd")
@@ -439,7 +440,7 @@ def qablora_linear_bwd(qw: QWeight, H: torch.Tensor, lambda1: int, lambda2: int,
     if need_dh and dH is None:
         dH = torch.empty((qw.d_in // lambda1, qw.d_out // lambda2), dtype=torch.float32, device=dev)
     q = qw.c_struct()
-    ws = _workspace(int(lib().qablora_linear_bwd_workspace_bytes(C.byref(q), lambda1, lambda2, T)), dev, workspace)
+    ws = _workspace(lambda: lib().qablora_linear_bwd_workspace_bytes(C.byref(q), lambda1, lambda2, T), dev, workspace)
     rc = lib().qablora_linear_bwd(C.byref(q), _ptr(H), lambda1, lambda2, s, _ptr(X), _ptr(dY), T,
                                   _ptr(dX if need_dx else None), _ptr(dH if need_dh else None), _ptr(ws), ws.numel(),
                                   _stream())
@@ -452,8 +453,7 @@ def qblora_tile_product(ad: Adapter, d_in: int, d_out: int, H: torch.Tensor = No
     if H is None:
         H = torch.empty((d_in // ad.lambda1, d_out // ad.lambda2), dtype=torch.float32, device=dev)
     a = ad.c_struct()
-    need = int(lib().qblora_tile_product_workspace_bytes(C.byref(a), d_in, d_out))
-    ws = _workspace(need, dev, workspace)
+    ws = _workspace(lambda: lib().qblora_tile_product_workspace_bytes(C.byref(a), d_in, d_out), dev, workspace)
     rc = lib().qblora_tile_product(C.byref(a), d_in, d_out, _ptr(H), _ptr(ws), ws.numel(), _stream())
     _check(rc, "qblora_tile_product")
     return H
@@ -535,7 +535,7 @@ def qblora_linear_decode(qw: QWeight, X: torch.Tensor, Y: torch.Tensor = None, w
     if Y is None:
         Y = torch.empty((T, qw.d_out), dtype=torch.bfloat16, device=X.device)
     q = qw.c_struct()
-    ws = _workspace(int(lib().qblora_linear_decode_tokens_workspace_bytes(C.byref(q), T)), X.device, workspace)
+    ws = _workspace(lambda: lib().qblora_linear_decode_tokens_workspace_bytes(C.byref(q), T), X.device, workspace)
     rc = lib().qblora_linear_decode(C.byref(q), _ptr(pack), _ptr(X), T, _ptr(Y), _ptr(ws), ws.numel(), _stream())
     _check(rc, "qblora_linear_decode")
     return Y
