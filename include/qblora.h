@@ -56,7 +56,8 @@ enum { QBLORA_MERGE_BETA_SHIFT = 0, QBLORA_MERGE_REQUANT_MINMAX = 1 };
  *   codebook   16 ascending code values c_j (host values, copied by value into launches).
  *              Absmax/codebook quantizer (the NF4-style base of Sec. 3.2): any 16 ascending
  *              values in [-1,1].  Min-max INT4: 0,1,...,15.
- *   codes      [d_out*d_in/2] bytes.
+ *   codes      [d_out*d_in/2] bytes.  Placement: 16-byte aligned for qblora_linear_decode, for layer calls on 2048
+ *              tokens or more and for 8 x 4 blocks (below); other layer calls take any address.
  *   scales     alpha, fp32 [d_out*d_in/block].
  *   beta       beta,  fp32 [d_out*d_in/block], or NULL meaning beta = 0 (absmax quantizer).
  *   scale_mode QBLORA_SCALES_FP32: `scales` is what consumers read.

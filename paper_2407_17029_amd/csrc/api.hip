@@ -117,9 +117,11 @@ bool dequantize_first(const qblora_qweight* qw, int64_t T, int K2) {
 // The backward contracts the transposed weight, which is always dequantized once (its in-LDS form had to transpose
 // every tile on the way in: 512 x 512 at 256 tokens 19 us against 3 + 7, 4096 x 11008 at 512 tokens 239 against 20 + 85).
 
-// Calls on 2048 tokens or more, and all on 8 x 4 blocks, ask for codes on a 16-byte boundary; smaller ones never did.
+// Calls on 2048 tokens or more (on weights below 2^31 elements), and all on 8 x 4 blocks, ask for codes on a 16-byte
+// boundary: a contract with callers, no kernel behind it needs that.
 bool codes_placed(const qblora_qweight* qw, int64_t T) {
-    return (T < 2048 && !half_blocks(qw)) || (reinterpret_cast<uintptr_t>(qw->codes) & 15) == 0;
+    const bool any = T < 2048 || (int64_t)qw->d_out * qw->d_in >= (int64_t)1 << 31;
+    return (any && !half_blocks(qw)) || (reinterpret_cast<uintptr_t>(qw->codes) & 15) == 0;
 }
 
 struct FwdSpace {

@@ -14,6 +14,13 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
+// Words of codes where they lie: forward and backward calls take codes at any address (calls on many tokens ask for 16
+// bytes, see codes_placed), so their loads must not promise an alignment.  A global load takes any address in one
+// instruction.
+typedef uint32_t u32_any __attribute__((aligned(1)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
+typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
+
 struct Codebook {
     float c[16];
 };

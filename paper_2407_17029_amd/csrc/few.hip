@@ -29,7 +29,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 template <int TB, int FB, bool BETA, int BR>
 struct Step {                                     // one 64-wide step of this lane
-    uint2 cw[FB];                                 // codes of 16 inputs of FB rows
+    u32x2_any cw[FB];                             // codes of 16 inputs of FB rows
     float sc[FB][BR == 8 ? 2 : 1], be[FB][BR == 8 ? 2 : 1];
     bf16x8 xf[TB][2];
 };
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const unsigned char* xb = xbase + (int64_t)step * (kBK * 2);
 #pragma unroll
         for (int h = 0; h < FB; ++h) {
-            st.cw[h] = *reinterpret_cast<const uint2*>(cb + coff[h]);
+            st.cw[h] = *reinterpret_cast<const u32x2_any*>(cb + coff[h]);
 #pragma unroll
             for (int i = 0; i < (BR == 8 ? 2 : 1); ++i) {
                 st.sc[h][i] = sb[soff[h] + i];

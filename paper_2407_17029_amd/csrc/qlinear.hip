@@ -214,16 +214,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const uint32_t scales_off = BR == 8 ? blk_off : (uint32_t)lrow;
     const float* const beta_at = BETA ? beta + blk0 : nullptr;
     constexpr int kLoads = (BR == 8 ? D : 1) + 1 + (BETA ? 1 : 0);   // load instructions of a step
-    typedef typename std::conditional<D == 4, uint4, uint2>::type Row;
+    typedef typename std::conditional<D == 4, u32x4_any, u32x2_any>::type Row;
     auto load_staged = [&](Staged<D>& s, int step) __attribute__((always_inline)) {
         const uint8_t* const p = codes_at + (int64_t)step * codes_step;
         if constexpr (BR == 8) {
 #pragma unroll
-            for (int i = 0; i < D; ++i) s.cw[i] = *reinterpret_cast<const uint32_t*>(p + codes_row * i + codes_off);
+            for (int i = 0; i < D; ++i) s.cw[i] = *reinterpret_cast<const u32_any*>(p + codes_row * i + codes_off);
         } else {
             const Row v = *reinterpret_cast<const Row*>(p + codes_off);
-            s.cw[0] = v.x; s.cw[1] = v.y;
-            if constexpr (D == 4) { s.cw[2] = v.z; s.cw[3] = v.w; }
+#pragma unroll
+            for (int i = 0; i < D; ++i) s.cw[i] = v[i];
         }
         s.sc = (scales_at + (int64_t)step * (BR == 8 ? 8 : 256))[scales_off];
         if constexpr (BETA) s.be = (beta_at + (int64_t)step * (BR == 8 ? 8 : 1))[blk_off];

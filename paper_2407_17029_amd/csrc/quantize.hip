@@ -452,11 +452,11 @@ __global__ __launch_bounds__(256) void k_dequantize_operand(const uint8_t* __res
         const int row = t >> 2, piece = t & 3;                  // stored row in tile, 32 inputs
         const int64_t n = min((int64_t)nt * 64 + row, (int64_t)d_out - 1);    // rows past the end: computed, never stored
         const int k0 = kt * 128 + piece * 32;
-        uint4 cq = make_uint4(0, 0, 0, 0);
+        u32x4_any cq = {0u, 0u, 0u, 0u};
         float a1 = 0.0f, b1 = 0.0f;
         float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f), b4 = make_float4(0.f, 0.f, 0.f, 0.f), a4b = a4, b4b = b4;
         if (k0 < d_in) {                                        // d_in % 64 == 0: the last tile may be half
-            cq = *reinterpret_cast<const uint4*>(codes + n * (d_in / 2) + k0 / 2);
+            cq = *reinterpret_cast<const u32x4_any*>(codes + n * (d_in / 2) + k0 / 2);
             if constexpr (block_rows == 8 && block_cols == 4) {  // eight block columns of 4 inputs
                 const int64_t blk = (n >> 3) * (int64_t)(d_in / 4) + k0 / 4;
                 a4 = *reinterpret_cast<const float4*>(scales + blk);
@@ -536,11 +536,11 @@ __global__ __launch_bounds__(256) void k_dequantize_operand_t(const uint8_t* __r
         const int row = t >> 2, piece = t & 3;                  // stored row in tile, 32 inputs
         const int64_t n = (int64_t)nt * 64 + row;
         const int k0 = kt * 128 + piece * 32;
-        uint4 cq = make_uint4(0, 0, 0, 0);
+        u32x4_any cq = {0u, 0u, 0u, 0u};
         float a1 = 0.0f, b1 = 0.0f;
         float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f), b4 = make_float4(0.f, 0.f, 0.f, 0.f), a4b = a4, b4b = b4;
         if (k0 < d_in) {                                        // d_in % 64 == 0: the last tile may be half
-            cq = *reinterpret_cast<const uint4*>(codes + n * (d_in / 2) + k0 / 2);
+            cq = *reinterpret_cast<const u32x4_any*>(codes + n * (d_in / 2) + k0 / 2);
             if constexpr (block_rows == 8 && block_cols == 4) {  // eight block columns of 4 inputs
                 const int64_t blk = (n >> 3) * (int64_t)(d_in / 4) + k0 / 4;
                 a4 = *reinterpret_cast<const float4*>(scales + blk);

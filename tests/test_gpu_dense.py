@@ -113,3 +113,36 @@ def test_gradients_alone_need_no_room_for_the_weight(codebook, form):
         _, dH = qb.qablora_linear_bwd(qw, H, 8, 8, 0.5, X, dY, need_dx=False, workspace=ws)
         _, rH = qb.qablora_linear_bwd(qw, H, 8, 8, 0.5, X, dY)
         assert torch.equal(dH, rH)
+
+
+@pytest.mark.parametrize("fmt", ["nf4", "tile8"])
+def test_codes_at_any_dword(codebook, fmt):
+    """Codes that start between 16-byte boundaries: calls on fewer than 2048 tokens take them, in every form that reads
+    codes, with the same results; calls on more refuse them."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev
+    d_out, d_in = 2112, 1088
+    print(f"case codes placement {fmt}", flush=True)
+    W = synth.base_weight(5990, 0, d_out, d_in)
+    if fmt == "nf4":
+        qw = qb.qblora_quantize_blockwise(f32_to_dev(W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook, tiled=False)
+    else:
+        qw = qb.qblora_quantize_blockwise(f32_to_dev(W), 64, qb.QUANT_MINMAX_INT4, block_rows=8, tiled=False)
+    buf = torch.empty(qw.codes.numel() + 16, dtype=torch.uint8, device=qw.codes.device)
+    moved = qb.QWeight(d_out, d_in, 64, qw.codebook, buf[4:4 + qw.codes.numel()].view_as(qw.codes), qw.scales, qw.beta,
+                       block_rows=qw.block_rows)
+    moved.codes.copy_(qw.codes)
+    assert moved.codes.data_ptr() % 16 == 4
+    g = torch.Generator(device="cuda").manual_seed(5991)
+    X = torch.randn((2048, d_in), generator=g, device="cuda").to(torch.bfloat16)
+    dY = torch.randn((2048, d_out), generator=g, device="cuda").to(torch.bfloat16)
+    for T in (5, 100, 256, 300, 2047):
+        assert torch.equal(qb.qblora_linear_fwd(moved, None, X[:T]), qb.qblora_linear_fwd(qw, None, X[:T]))
+        dX = [qb.qblora_linear_bwd(w, None, X[:T], dY[:T], need_grads=False)[0] for w in (moved, qw)]
+        assert torch.equal(*dX)
+    Y = [qb.qblora_linear_fwd_noalloc(w, None, X, torch.empty((2048, d_out), dtype=torch.bfloat16, device="cuda")) for w in (moved, qw)]
+    assert torch.equal(*Y)
+    with pytest.raises(RuntimeError):
+        qb.qblora_linear_fwd(moved, None, X)
+    with pytest.raises(RuntimeError):
+        qb.qblora_linear_bwd(moved, None, X, dY, need_grads=False)
