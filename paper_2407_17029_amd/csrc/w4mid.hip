@@ -97,7 +97,8 @@ __device__ __forceinline__ void wait_slot(Slot<BR>& s) {
 
 // TB: 32-token blocks; BETA: offsets present; BR: 1 (64 inputs of one row), 8 (8 rows x 8 inputs) or 84 (8 rows x 4 inputs);
 // REGROUPED: INT4 model whose code dwords were regrouped by the decode pack (codebook 0..15, offsets present)
-template <int TB, bool BETA, int BR, bool REGROUPED>
+// AHEAD: MFMAs between the read of a token fragment and its use (1 or 2)
+template <int TB, bool BETA, int BR, bool REGROUPED, int AHEAD>
 __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     static_assert(!REGROUPED || (BETA && BR == 1), "regrouped codes belong to INT4 models in 64-blocks");
     constexpr int kStageBytes = TB * 32 * 128;
@@ -247,26 +248,27 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     };
     // One step: the 4 * TB MFMAs on this step's operands `wf`, and between them the units that build the next
     // step's operands `wn` from slot `sl` -- written in issue order and fenced after every MFMA: a wave issues in
-    // order, so vector work has to sit between the MFMAs to run in their shadow.  LDS reads are issued kAhead MFMAs
+    // order, so vector work has to sit between the MFMAs to run in their shadow.  LDS reads are issued AHEAD MFMAs
     // (token fragment) or one unit (table pair) ahead of their use.
     auto step = [&](const bf16x8 (&wf)[4], int stage, const Slot<BR>& sl, bf16x8 (&wn)[4]) __attribute__((always_inline)) {
-        constexpr int M = 4 * TB, kAhead = 2;
+        constexpr int M = 4 * TB;
         const unsigned char* xs = sX + stage * kStageBytes;
         const Params p = params(sl);
         uint32_t o[16];
         float2 tv[2] = {make_float2(0.f, 0.f), make_float2(0.f, 0.f)};
-        bf16x8 xf[kAhead];
+        bf16x8 xf[2];
         auto read_x = [&](int m) __attribute__((always_inline)) {
             return *reinterpret_cast<const bf16x8*>(xs + (f_off[m % TB] ^ ((m / TB) << 4)));
         };
         unit_a(p, 0, tv[0]);
 #pragma unroll
-        for (int m = 0; m < kAhead; ++m) xf[m] = read_x(m);
+        for (int m = 0; m < AHEAD; ++m) xf[m] = read_x(m);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-            acc[m % TB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[m / TB], xf[m % kAhead], acc[m % TB], 0, 0, 0);
-            if (m + kAhead < M) xf[m % kAhead] = read_x(m + kAhead);
+            if (AHEAD == 1 && m + 1 < M) xf[(m + 1) & 1] = read_x(m + 1);
+            acc[m % TB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[m / TB], xf[m & 1], acc[m % TB], 0, 0, 0);
+            if (AHEAD == 2 && m + 2 < M) xf[m & 1] = read_x(m + 2);
 #pragma unroll
             for (int k = m * 16 / M; k < (m + 1) * 16 / M; ++k) {
                 if (k + 1 < 16) unit_a(p, k + 1, tv[(k + 1) & 1]);
@@ -347,13 +349,15 @@ __global__ __launch_bounds__(256) void k_w4_mid_reduce(const float* __restrict__
     const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4;
     if (i >= count) return;
     if ((count & 3) == 0) {                                     // every slice's words are aligned
-        f32x4 v[8];                                             // at most 8 slices, all loads issued together
+        f32x4 s = *reinterpret_cast<const f32x4*>(part + i);
+        for (int z0 = 1; z0 < splits; z0 += 4) {                // four slices' loads issued together
+            f32x4 v[4];
 #pragma unroll
-        for (int zz = 0; zz < 8; ++zz) v[zz] = *reinterpret_cast<const f32x4*>(part + min(zz, splits - 1) * count + i);
-        f32x4 s = v[0];
+            for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4*>(part + min(z0 + u, splits - 1) * count + i);
 #pragma unroll
-        for (int zz = 1; zz < 8; ++zz)
-            if (zz < splits) s += v[zz];
+            for (int u = 0; u < 4; ++u)
+                if (z0 + u < splits) s += v[u];
+        }
         *reinterpret_cast<uint2*>(Y + i) = make_uint2(pack_bf16(s[0], s[1]), pack_bf16(s[2], s[3]));
         return;
     }
@@ -375,12 +379,12 @@ bool set_lds(K kernel, size_t smem) {
                                (int)smem) == hipSuccess;
 }
 
-template <int TB, bool BETA, int BR, bool REGROUPED>
+template <int TB, bool BETA, int BR, bool REGROUPED, int AHEAD = 2>
 int launch_one(const MidDesc& d, unsigned blocks, hipStream_t st) {
     constexpr size_t smem = mid_lds<TB>(REGROUPED);
-    static const bool ok = set_lds(k_w4_mid<TB, BETA, BR, REGROUPED>, smem);
+    static const bool ok = set_lds(k_w4_mid<TB, BETA, BR, REGROUPED, AHEAD>, smem);
     if (!ok) return QBLORA_ERR_LAUNCH;
-    hipLaunchKernelGGL((k_w4_mid<TB, BETA, BR, REGROUPED>), dim3(blocks), dim3(kMidThreads), smem, st, d);
+    hipLaunchKernelGGL((k_w4_mid<TB, BETA, BR, REGROUPED, AHEAD>), dim3(blocks), dim3(kMidThreads), smem, st, d);
     return launch_status();
 }
 
@@ -390,7 +394,12 @@ int launch_tb(const MidDesc& d, unsigned blocks, hipStream_t st, int block_rows,
         return d.beta ? launch_one<TB, true, 84, false>(d, blocks, st) : launch_one<TB, false, 84, false>(d, blocks, st);
     if (block_rows == 8)
         return d.beta ? launch_one<TB, true, 8, false>(d, blocks, st) : launch_one<TB, false, 8, false>(d, blocks, st);
-    if (regrouped) return d.beta ? launch_one<TB, true, 1, true>(d, blocks, st) : QBLORA_ERR_UNSUPPORTED;
+    if (regrouped && !d.beta) return QBLORA_ERR_UNSUPPORTED;
+    // Without the table two workgroups of 128 tokens fit a CU's LDS.  Once there are two for a CU, each hides the other's
+    // LDS latency and a fragment is best read one MFMA ahead (T = 96: 22016 x 8192 63.6 -> 59.5 us, 5120 x 13824
+    // 33.4 -> 31.8); with one it takes two (4096 x 4096 17.0 -> 16.3, 4096 x 11008 23.4 -> 21.5).
+    if (TB == 4 && regrouped && blocks > 256) return launch_one<TB, true, 1, true, TB == 4 ? 1 : 2>(d, blocks, st);
+    if (regrouped) return launch_one<TB, true, 1, true>(d, blocks, st);
     return d.beta ? launch_one<TB, true, 1, false>(d, blocks, st) : launch_one<TB, false, 1, false>(d, blocks, st);
 }
 
