@@ -80,14 +80,18 @@ __global__ __launch_bounds__(kThreads) void k_skinny(GemmDesc d) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     // blockIdx.x % 8 is the XCD: the column tiles of one token tile are 8 apart
     const int tiles_n = (N + BN - 1) / BN;
-    const int splits = d.splits > 1 ? d.splits : 1, z = blockIdx.x % splits, bid = blockIdx.x / splits;
+    const int splits = d.splits > 1 ? d.splits : 1, all_steps = K / (kBK * kSub);
+    int z = 0, bid = blockIdx.x, step0 = 0, nsteps = all_steps;    // (unsliced calls spend no divisions on it: 0.3 us)
+    if (splits > 1) {
+        z = bid % splits; bid /= splits;
+        step0 = all_steps * z / splits;           // all_steps < 2^24
+        nsteps = all_steps * (z + 1) / splits - step0;             // at least one: splits <= all_steps
+    }
     const int grp = bid / (8 * tiles_n), within = bid % (8 * tiles_n);
     const int64_t m0 = ((int64_t)grp * 8 + (within & 7)) * BM;
     const int n0 = (within >> 3) * BN;
     if (m0 >= M) return;                          // the grid is rounded up to whole groups of 8 token tiles
     const int wave_n = wave % WN, wave_m = wave / WN;
-    const int all_steps = K / (kBK * kSub), step0 = (int)((int64_t)all_steps * z / splits);
-    const int nsteps = (int)((int64_t)all_steps * (z + 1) / splits) - step0;      // at least one: splits <= all_steps
 
     // per-lane byte offsets of the copies, relative to the first row of the tile
     const int crow = lane >> 3;
