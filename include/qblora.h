@@ -194,7 +194,8 @@ int qblora_dequantize_bf16(const qblora_qweight* qw, qblora_bf16* Wt, void* stre
  * scales, in registers or in LDS.  From that many tokens on the workspace has room for the whole weight as a bf16
  * buffer (d_out*d_in*2 bytes); the call dequantizes it once into that and contracts it, because rebuilding it for
  * each token tile costs more than one sweep over the weight -- or still contracts the codes on wide layers, where it
- * does not.  A backward that produces dX always dequantizes, transposed.  The weights are the same bf16 numbers every
+ * does not.  A backward that produces dX has that room at every token count, for the transposed weight, and chooses
+ * likewise.  The weights are the same bf16 numbers every
  * way (qblora_dequantize_bf16's).  Results: a forward has the same bits on either way it may take at its token count
  * (qblora_linear_fwd and qblora_linear_fwd_noalloc agree), and a repeated call repeats its bits.  Across token counts
  * the order of the fp32 sums may differ -- below the limit it depends on the tile that the count selects, and so does

@@ -114,8 +114,11 @@ bool use_dense(const qblora_qweight* qw, int64_t T) { return T >= kDenseMinToken
 bool dequantize_first(const qblora_qweight* qw, int64_t T, int K2) {
     return half_blocks(qw) || (T >= kDenseMinTokens && dense_pays(T, qw->d_out, qw->d_in, K2));
 }
-// The backward contracts the transposed weight, which is always dequantized once (its in-LDS form had to transpose
-// every tile on the way in: 512 x 512 at 256 tokens 19 us against 3 + 7, 4096 x 11008 at 512 tokens 239 against 20 + 85).
+// The backward contracts the transposed weight, dequantized once where that pays (512 x 512 at 256 tokens 3 + 7 us
+// against 19 from the codes, 4096 x 11008 at 512 tokens 20 + 85 against 239) or from the codes.
+bool dequantize_first_t(const qblora_qweight* qw, int64_t T, int K2) {
+    return half_blocks(qw) || dense_pays_t(T, qw->d_in, qw->d_out, K2);
+}
 
 // Calls on 2048 tokens or more (on weights below 2^31 elements), and all on 8 x 4 blocks, ask for codes on a 16-byte
 // boundary: a contract with callers, no kernel behind it needs that.
@@ -153,15 +156,15 @@ struct BwdSpace {
     int splits_a, splits_b, splits_x;
     size_t bytes;
 };
-// `dx`: the call produces dX, i.e. dequantizes the weight and contracts it.  `query`: the size that serves every number of
+// `dx`: the call produces dX; `dense`: it dequantizes the weight for that.  `query`: the size that serves every number of
 // tokens up to T -- the slices of the contractions, and with them the partial sums, may be more for fewer tokens.
-BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T, void* ws, bool dx, bool query) {
+BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T, void* ws, bool dx, bool dense, bool query) {
     Carver c(ws);
     BwdSpace s{};
     size_t px = 0;
-    if (dx) {
+    if (dx && qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
+    if (dx && dense) {
         const int R = has_adapter(ad) ? ad->R : 0;
-        if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
         s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
         // slices of the dX contraction: their partial sums share the gradients' buffer, which is free by then
         s.splits_x = query ? 1 : dense_splits(T, qw->d_in, qw->d_out, R);
@@ -227,6 +230,12 @@ int resolve_scales(const qblora_qweight* qw, float* scratch, hipStream_t st, con
     *out = scratch;
     return launch_scales_reconstruct(qw->scale_codes, qw->scale_step, qw->scale_mid, n_blocks(qw),
                                      qw->scale_group, scratch, st);
+}
+
+// the weight itself, for the contractions that build it from its codes
+void describe_codes(const qblora_qweight* qw, GemmDesc& g) {
+    g.codes = qw->codes; g.beta = qw->beta; g.d_out = qw->d_out; g.d_in = qw->d_in; g.cb = codebook_of(qw);
+    g.codes_tiled = qw->codes_tiled; g.block_rows = block_rows_of(qw);
 }
 
 // ---- QA-BLoRA merge: validation (touches nothing), description + output header, offset-shift launch ------------
@@ -387,7 +396,7 @@ size_t qblora_linear_fwd_workspace_bytes(const qblora_qweight* qw, const qblora_
 
 size_t qblora_linear_bwd_workspace_bytes(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T) {
     if (check_layer(qw, ad) || T < 0) return 0;
-    return carve_bwd(qw, ad, T, nullptr, true, true).bytes;
+    return carve_bwd(qw, ad, T, nullptr, true, true, true).bytes;
 }
 
 int64_t qblora_dense_min_tokens(void) { return kDenseMinTokens; }
@@ -426,8 +435,7 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     if (grouped) { sct.scale_codes = qw->scale_codes; sct.scale_step = qw->scale_step; sct.scale_mid = qw->scale_mid; }
     sct.scale_group = qw->scale_group; sct.d_out = qw->d_out; sct.d_in = qw->d_in; sct.out = ws.scales;
     g.scales = nullptr; g.scales_tiled = ws.scales;
-    g.block_rows = block_rows_of(qw);
-    if (g.block_rows == 8) { sct.out = nullptr; g.scales = qw->scales; g.scales_tiled = nullptr; }   // read in place
+    if (block_rows_of(qw) == 8) { sct.out = nullptr; g.scales = qw->scales; g.scales_tiled = nullptr; }   // read in place
     if (few) {                                            // reads the scales where they are
         sct.out = nullptr; g.scales_tiled = nullptr;
         if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
@@ -484,8 +492,7 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         g.K2 = 0; g.div2 = 1;
     }
     g.X1 = X; g.ldx1 = qw->d_in;
-    g.codes = qw->codes; g.beta = qw->beta; g.d_out = qw->d_out; g.d_in = qw->d_in; g.cb = codebook_of(qw);
-    g.codes_tiled = qw->codes_tiled;
+    describe_codes(qw, g);
     g.C = Y; g.ldc = qw->d_out; g.out_scale = 1.0f; g.M = T; g.N = qw->d_out;
     ScopedEvents ev(QBLORA_PROFILE_FWD_GEMM, st);
     return launch_gemm(g, st);
@@ -514,20 +521,23 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     }
     if (!dY || (adapted && !X)) return QBLORA_ERR_NULL;
     if (dX && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
-    BwdSpace ws = carve_bwd(qw, ad, T, workspace, dX != nullptr, false);
+    const bool dense = dX && dequantize_first_t(qw, T, adapted ? ad->R : 0);
+    BwdSpace ws = carve_bwd(qw, ad, T, workspace, dX != nullptr, dense, false);
     if (ws.bytes > 0 && (!workspace || workspace_bytes < ws.bytes)) return QBLORA_ERR_WORKSPACE;
 
     GemmDesc g{};
-    g.qmode = 3;
-    if (dX) {
+    g.qmode = dense ? 3 : 4;
+    if (dX && (rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
+    if (dX && dense) {
         // the transposed bf16 compute weight once, for all token tiles of this call
-        if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
         {
             ScopedEvents ev(QBLORA_PROFILE_DEQUANT, st);
             rc = launch_dequantize_operand(*qw, g.scales, 1, ws.W16t, st);
         }
         if (rc) return rc;
         g.W1 = ws.W16t; g.K1 = qw->d_out;
+    } else if (dX) {
+        describe_codes(qw, g);
     }
     if (adapted) {
         const int R = ad->R;
@@ -719,13 +729,13 @@ QaFwdSpace carve_qa_fwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T,
 }
 
 struct QaBwdSpace { float* scales; qblora_bf16 *P, *dVs, *dVs_lo, *W16t; float* part; int splits, splits_x; size_t bytes; };
-QaBwdSpace carve_qa_bwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T, void* ws, bool dx, bool query) {
+QaBwdSpace carve_qa_bwd(const qblora_qweight* qw, int lam1, int lam2, int64_t T, void* ws, bool dx, bool dense, bool query) {
     Carver c(ws);
     QaBwdSpace s{};
     const int I = qw->d_in / lam1, J = qw->d_out / lam2;
     size_t px = 0;                                            // as in carve_bwd
-    if (dx) {
-        if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
+    if (dx && qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));
+    if (dx && dense) {
         s.W16t = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
         s.splits_x = query ? 1 : dense_splits(T, qw->d_in, qw->d_out, J);
         const int64_t rows = query ? dense_part_rows(T, qw->d_in, qw->d_out, J) : s.splits_x > 1 ? s.splits_x * T : 0;
@@ -749,7 +759,7 @@ size_t qablora_linear_fwd_workspace_bytes(const qblora_qweight* qw, int32_t lamb
 
 size_t qablora_linear_bwd_workspace_bytes(const qblora_qweight* qw, int32_t lambda1, int32_t lambda2, int64_t T) {
     if (check_qweight(qw, false, true) || lambda1 <= 0 || lambda2 <= 0 || T < 0) return 0;
-    return carve_qa_bwd(qw, lambda1, lambda2, T, nullptr, true, true).bytes;
+    return carve_qa_bwd(qw, lambda1, lambda2, T, nullptr, true, true, true).bytes;
 }
 
 int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t lambda1, int32_t lambda2, float s,
@@ -788,7 +798,7 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     GemmDesc g{};
     g.qmode = 1;
     g.scales = nullptr; g.scales_tiled = ws.scales;
-    if (tile8) { g.scales = qw->scales; g.scales_tiled = nullptr; g.block_rows = 8; }
+    if (tile8) { g.scales = qw->scales; g.scales_tiled = nullptr; }
     if (dense) { g.qmode = 3; g.W1 = ws.W16; g.K1 = qw->d_in; }
     if (few) {
         g.qmode = 2; g.scales_tiled = nullptr;
@@ -796,8 +806,7 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     }
     g.X2 = ws.P; g.ldx2 = I; g.W2 = ws.Ht; g.ldw2 = I; g.K2 = I; g.div2 = lambda2;
     g.X1 = X; g.ldx1 = qw->d_in;
-    g.codes = qw->codes; g.beta = qw->beta; g.d_out = qw->d_out; g.d_in = qw->d_in; g.cb = codebook_of(qw);
-    g.codes_tiled = qw->codes_tiled;
+    describe_codes(qw, g);
     g.C = Y; g.ldc = qw->d_out; g.out_scale = 1.0f; g.M = T; g.N = qw->d_out;
     return launch_gemm(g, st);
 }
@@ -820,7 +829,8 @@ int qablora_linear_bwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
         return QBLORA_OK;
     }
     if (!dY || (dH && !X)) return QBLORA_ERR_NULL;
-    QaBwdSpace ws = carve_qa_bwd(qw, lambda1, lambda2, T, workspace, dX != nullptr, false);
+    const bool dense = dX && dequantize_first_t(qw, T, J);
+    QaBwdSpace ws = carve_qa_bwd(qw, lambda1, lambda2, T, workspace, dX != nullptr, dense, false);
     if (!workspace || workspace_bytes < ws.bytes) return QBLORA_ERR_WORKSPACE;
     if (dX && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
 
@@ -838,10 +848,14 @@ int qablora_linear_bwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     }
     if (!dX) return QBLORA_OK;
     GemmDesc g{};
-    g.qmode = 3;
+    g.qmode = dense ? 3 : 4;
     if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
-    if ((rc = launch_dequantize_operand(*qw, g.scales, 1, ws.W16t, st))) return rc;
-    g.W1 = ws.W16t; g.K1 = qw->d_out;
+    if (dense) {
+        if ((rc = launch_dequantize_operand(*qw, g.scales, 1, ws.W16t, st))) return rc;
+        g.W1 = ws.W16t; g.K1 = qw->d_out;
+    } else {
+        describe_codes(qw, g);
+    }
     g.X2 = ws.dVs; g.ldx2 = J; g.W2 = H; g.ldw2 = J; g.K2 = J; g.div2 = lambda1;
     g.X1 = dY; g.ldx1 = qw->d_out;
     g.C = dX; g.ldc = qw->d_in; g.out_scale = 1.0f; g.M = T; g.N = qw->d_in;

@@ -124,7 +124,8 @@ int launch_adapter_prep(const qblora_bf16* A, const qblora_bf16* B, int d_in, in
 struct GemmDesc {
     int qmode;                 // 0: no quantized segment; 1: forward (N = d_out, K1 = d_in);
                                // 2: the same for at most kFewTokens tokens;
-                               // 3: first segment on a bf16 weight dequantized beforehand, in operand order
+                               // 3: first segment on a bf16 weight dequantized beforehand, in operand order;
+                               // 4: transposed use of 1 (N = d_in, K1 = d_out)
     const qblora_bf16* X1; int64_t ldx1;
     const qblora_bf16* W1; int K1;                     // qmode 3 only: see launch_dequantize_operand
     const uint8_t* codes; const float* scales; const float* beta; int d_out, d_in;
@@ -144,7 +145,7 @@ struct GemmDesc {
                                // fp32 [splits][M][N] partial sums in `part` (skinny_splits, dense_splits; 16-byte aligned)
 };
 int launch_gemm(const GemmDesc& d, hipStream_t st);
-// the quantized segment (qmode 1) with 8-wave tiles of 256 tokens; called by launch_gemm
+// the quantized segment (qmode 1 and 4) with 8-wave tiles of 256 tokens; called by launch_gemm
 int launch_qlinear(const GemmDesc& d, hipStream_t st);
 // its estimated time for [M, N] over K
 int64_t qlinear_ns(int64_t M, int N, int K);
@@ -159,6 +160,8 @@ struct DensePlan { int shape, splits; int64_t ns; };
 DensePlan dense_plan(int64_t M, int N, int k1, int k2, int max_splits);
 // whether dequantizing the weight first is faster than contracting straight from the codes (qmode 3 against qmode 1)
 bool dense_pays(int64_t M, int N, int k1, int k2);
+// the same for the transposed weight (qmode 3, in slices where they pay, against qmode 4)
+bool dense_pays_t(int64_t M, int N, int k1, int k2);
 // slices of the contraction that pay for an [M, N] output over k1 + k2 (GemmDesc::splits; 1 = none)
 int dense_splits(int64_t M, int N, int k1, int k2);
 // the most rows of partial sums, slices x tokens, that any number of tokens up to M takes

@@ -501,6 +501,15 @@ bool dense_pays(int64_t M, int N, int k1, int k2) {
     return qlinear_ns(M, N, k1 + (k2 + kBK - 1) / kBK * kBK) + 2000 >= first - first * 5 / 100;
 }
 
+// The transposed weight's pass is the same; its contraction may be sliced, which the one from the codes is not.  us from
+// the codes / dequantized first, 8192 x 22016: 64 tokens 122 / 185, 256 122 / 223, 512 195 / 275, 700 376 / 401; 4096 x 11008
+// at 512 67 / 76; 8192 x 8192 at 700 131 / 124.  A margin of 10 %: the slices' time is the less certain (with 5 % two of
+// 480 measured calls lose 6 and 10 %, with 10 % none).
+bool dense_pays_t(int64_t M, int N, int k1, int k2) {
+    const int64_t first = dense_plan(M, N, k1, k2, 8).ns + (int64_t)N * k1 * 46 / 100000 + 2000;
+    return qlinear_ns(M, N, k1 + (k2 + kBK - 1) / kBK * kBK) + 2000 >= first - first * 10 / 100;
+}
+
 int dense_splits(int64_t M, int N, int k1, int k2) {
     if (M <= 0 || N <= 0 || N % 8 != 0) return 1;
     return dense_plan(M, N, k1, k2, 8).splits;

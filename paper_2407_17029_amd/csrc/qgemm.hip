@@ -185,7 +185,7 @@ int launch_cfg(const GemmDesc& d, hipStream_t st) {
 
 int launch_gemm(const GemmDesc& d, hipStream_t st) {
     if (d.M <= 0 || d.N <= 0) return QBLORA_OK;
-    if (d.qmode == 1) return launch_qlinear(d, st);
+    if (d.qmode == 1 || d.qmode == 4) return launch_qlinear(d, st);
     if (d.qmode == 2) return launch_few(d, st);
     if (d.qmode == 3) return launch_dense(d, st);
     if (skinny_applies(d)) return launch_skinny(d, st);

@@ -1,15 +1,15 @@
-// Dequantize-and-contract kernel of the adapted layer's forward for gfx950 (Alg. 1 qblora_forward:
-// W_tilde = dequantize(...), x @ W_tilde, plus the adapter term), for calls that do not dequantize the weight
-// beforehand: on at most 256 tokens where few.hip is not faster, and the forward that allocates nothing.
+// Dequantize-and-contract kernel of the adapted layer for gfx950 (Alg. 1 qblora_forward: W_tilde = dequantize(...),
+// x @ W_tilde, plus the adapter term; and dX of its backward, on the transposed weight), for calls that do not
+// dequantize the weight beforehand: few tokens on wide layers, and the forward that allocates nothing.
 //
-//   C[M,N] = X1[M,K1] * Wq^T  +  X2[M,K2] * W2[N/div2, K2]^T
+//   C[M,N] = X1[M,K1] * Wq^T  +  X2[M,K2] * W2[N/div2, K2]^T     (forward: N = d_out, K1 = d_in; dX: the other way)
 //
 // Segment 1 reads the 4-bit codes and block scales of the frozen base weight from HBM, rebuilds
 // bf16 weights (Eq. 1: c[code]*alpha (+beta), fp32 then round-to-nearest-even) straight into an
 // LDS tile and feeds them to v_mfma_f32_16x16x32_bf16 with fp32 accumulation; the dequantized
 // weight never exists in HBM.  Segment 2 is a plain bf16 K-extension: the adapter's rank-R product
 // rides in the same accumulators as R extra contraction steps (X2 = s*U, W2 = B^T with output row n using row
-// n/lambda2, i.e. repeat_interleave).  k is accumulated in the order and by the instruction of dense.hip, so both
+// n/lambda2, i.e. repeat_interleave; dX: X2 = dU/lambda1, W2 = A with row k/lambda1).  k is accumulated in the order and by the instruction of dense.hip, so both
 // give the same bits.
 //
 // Shape of the computation on a CU: one workgroup of 512 threads (8 wave64, two per SIMD) owns 256 tokens x 256 or 128
@@ -20,7 +20,8 @@
 // into LDS (global_load_lds, 16 bytes per lane; the swizzle is applied by choosing which global chunk a lane fetches).
 // Codes and block parameters are fetched two or three k-steps ahead into registers and dequantized between the MFMAs of
 // the step before they are needed, through a byte-indexed table in LDS that turns one byte of codes into two fp32
-// code values.
+// code values.  The transposed form stages a patch of 4 or 2 stored rows x 8 columns per thread and packs it down the
+// columns; its scales, one a row, are spread inside a quad of lanes.  It takes as long as the other.
 //
 // Bound: LDS.  A 64-wide step of the 256 x 256 tile reads 192 KB of fragments and 64 KB of table values and writes 64 KB,
 // about 2600 cycles of LDS against 2048 of MFMAs; it takes 1.5 us with few workgroups and 1.85 us (power) with all CUs
@@ -47,8 +48,11 @@ constexpr int kTableBytes = 256 * 128;                      // byte-indexed pair
 
 __device__ __align__(16) const uint32_t g_zero_chunk[4] = {0u, 0u, 0u, 0u};
 
-__device__ __forceinline__ int swz(int row, int chunk) {
-    return row * 128 + (((chunk ^ (row >> 1)) & 7) << 4);
+// Byte of a 16-byte chunk in a weight tile.  TR: its columns are written by threads 8 tile rows apart, which the row's low
+// bits alone would send to two chunk positions; the number of the 16-row block spreads them over all eight.
+template <bool TR>
+__device__ __forceinline__ int swz_w(int row, int chunk) {
+    return row * 128 + (((chunk ^ (row >> 1) ^ (TR ? row >> 4 : 0)) & 7) << 4);
 }
 
 // One wave-wide global -> LDS copy: lane i fetches 16 bytes and they land at lds_base + 16*i (M0
@@ -68,13 +72,22 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
 }
 
-// codes and block parameters of one k-step held in registers: D dwords of 8 codes per thread, all in one block --
-// consecutive ones of a stored row, or, with 8 x 8 quantization blocks, the same 8 inputs of D adjacent rows
+// Codes and block parameters of one k-step held in registers: D dwords of 8 codes per thread.  The weight itself: all in
+// one block -- consecutive dwords of a stored row, or, with 8 x 8 quantization blocks, the same 8 inputs of D adjacent
+// rows.  Transposed: the same 8 columns of D adjacent stored rows; the scale is that of row (lane % D) of those, which
+// the lanes of a quad share (they hold 32 consecutive columns), or with 8 x 8 blocks the one of all.
 template <int D>
 struct Staged {
     uint32_t cw[D];
     float sc, be;
 };
+
+// v of lane I of the caller's aligned group of D lanes (D = 2 or 4)
+template <int D, int I>
+__device__ __forceinline__ float group_broadcast(float v) {
+    constexpr int quad = D == 4 ? I * 0x55 : I == 0 ? 0xA0 : 0xF5;        // quad_perm
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), quad, 0xf, 0xf, false));
+}
 
 // The lane, read again where it is used: a value that need not be kept in a register across the loop.
 __device__ __forceinline__ int lane_id() {
@@ -99,7 +112,8 @@ __device__ __forceinline__ void publish(Int<N>) {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int BN, bool BETA, int BR>
+// TR: the transposed weight (output features = stored columns, contraction over stored rows)
+template <int BN, bool BETA, int BR, bool TR>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_qlinear(GemmDesc d) {
     constexpr int kTileW = BN * 128, D = BN / 64;    // bytes of a weight tile, code dwords per thread and step
     constexpr int MB = BN / 32;                      // 16-token blocks of a wave
@@ -139,7 +153,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const int64_t m0 = (int64_t)mt * BM;
     const int n0 = nt * BN;
 
-    const int steps1 = d_in / kBK, steps2 = (K2 + kBK - 1) / kBK;
+    const int steps1 = (TR ? d.d_out : d_in) / kBK, steps2 = (K2 + kBK - 1) / kBK;
     const int nsteps = steps1 + steps2;
     const int bpr = d_in / kBlock;                // blocks per stored weight row
 
@@ -157,14 +171,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
     // a tile of the K-extension: chunks at or beyond K2 are fetched from a zero constant instead
     auto copy_tile = [&](auto rows_per_wave, const qblora_bf16* src, int64_t ld, int64_t row_base, int64_t row_max,
-                         int div, int k0, uint32_t tile_off) __attribute__((always_inline)) {
+                         int div, int k0, uint32_t tile_off, const bool weight) __attribute__((always_inline)) {
         const int l = lane_id();                     // row addresses are made again at every call, not held across the loop
 #pragma unroll
         for (int i = 0; i < rows_per_wave.value / 8; ++i) {
             int64_t row = row_base + wave * rows_per_wave.value + i * 8 + (l >> 3);
             row = row > row_max ? row_max : row;
             if (div != 1) row = (int64_t)((uint32_t)row / (uint32_t)div);      // only weight rows (< 2^31) are divided
-            const int k = k0 + (((l & 7) ^ (4 * (i & 1) + (l >> 4))) << 3);
+            const int high = TR && weight ? ((wave * rows_per_wave.value + i * 8) >> 4) & 7 : 0;    // see swz_w
+            const int k = k0 + (((l & 7) ^ (4 * (i & 1) + (l >> 4)) ^ high) << 3);
             const qblora_bf16* p = k < K2 ? src + row * ld + k : reinterpret_cast<const qblora_bf16*>(g_zero_chunk);
             copy16_to_lds(p, lds0 + tile_off + (wave * rows_per_wave.value + i * 8) * 128);
         }
@@ -190,34 +205,51 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             issue_x1(step);
         } else {
             const int k0 = (step - steps1) * kBK, buf = step & 1;
-            copy_tile(Int<32>{}, X2, ldx2, m0, M - 1, 1, k0, buf * kTileX);
-            copy_tile(Int<BN / 8>{}, W2, ldw2, n0, N - 1, div2, k0, 2 * kTileX + buf * kTileW);
+            copy_tile(Int<32>{}, X2, ldx2, m0, M - 1, 1, k0, buf * kTileX, false);
+            copy_tile(Int<BN / 8>{}, W2, ldw2, n0, N - 1, div2, k0, 2 * kTileX + buf * kTileW, true);
         }
     };
 
     // ---- codes / scales -> registers -------------------------------------------------------------
     // 64-blocks: a thread owns 1/(512/BN) of a stored row.  8 x 8 blocks: the dword t & 7 of D rows of one block row.
-    constexpr int kPerRow = 512 / BN;
-    const int wrow = BR == 8 ? D * (t >> 3) : t / kPerRow, wchunk = BR == 8 ? (t & 7) : D * (t % kPerRow);
-    const int qrow = min(n0 + wrow, N - (BR == 8 ? D : 1));      // rows past N: any valid ones, results never stored
-    // (uniform bases, which walk along k, and 32-bit lane offsets from the tile's first row)
-    const int lrow = qrow - n0;
-    const uint8_t* codes_at; int codes_step = 32;
-    uint32_t codes_off = (uint32_t)lrow * (uint32_t)(d_in / 2), codes_row = (uint32_t)(d_in / 2);
-    if (d.codes_tiled) { codes_at = d.codes_tiled + tiled_run_offset(n0, 0, bpr); codes_step = 256 * 32; codes_row = 32; codes_off = (uint32_t)lrow * 32u; }
-    else codes_at = d.codes + (int64_t)n0 * (d_in / 2);
-    codes_off += (uint32_t)wchunk * 4u;
-    const int64_t blk0 = BR == 8 ? (int64_t)(n0 >> 3) * (d_in >> 3) : (int64_t)n0 * bpr;
-    const uint32_t blk_off = BR == 8 ? (uint32_t)(lrow >> 3) * (uint32_t)(d_in >> 3) + (uint32_t)wchunk : (uint32_t)lrow * (uint32_t)bpr;
-    // 64-blocks: the scales come in tile order
-    const float* const scales_at = BR == 8 ? d.scales + blk0 : d.scales_tiled + tiled_run_offset(n0, 0, bpr) / 32;
-    const uint32_t scales_off = BR == 8 ? blk_off : (uint32_t)lrow;
-    const float* const beta_at = BETA ? beta + blk0 : nullptr;
-    constexpr int kLoads = (BR == 8 ? D : 1) + 1 + (BETA ? 1 : 0);   // load instructions of a step
+    // Transposed: 8 columns of D stored rows.  wrow / wchunk: its place in the tile, of the first of its columns if TR.
+    constexpr int kPerRow = 512 / BN, kGroups = BN / 8;
+    const int wrow = TR ? 8 * (t % kGroups) : BR == 8 ? D * (t >> 3) : t / kPerRow;
+    const int wchunk = TR ? D * (t / kGroups) / 8 : BR == 8 ? (t & 7) : D * (t % kPerRow);
+    // (uniform bases, which walk along k, and 32-bit lane offsets from the tile's first row or column; rows past N: any
+    // valid ones, results never stored)
+    const uint8_t* codes_at; int64_t codes_step = 32;
+    const float *scales_at, *beta_at = nullptr;
+    uint32_t codes_off, codes_row = (uint32_t)(d_in / 2), scales_off, blk_off;
+    if constexpr (TR) {
+        const int row = D * (t / kGroups), col = min(n0 + wrow, N - 8) - n0;
+        codes_at = d.codes + n0 / 2; codes_step = 32 * (int64_t)d_in;
+        codes_off = (uint32_t)row * codes_row + (uint32_t)(col / 2);
+        blk_off = BR == 8 ? (uint32_t)(row >> 3) * (uint32_t)(d_in >> 3) + (uint32_t)(n0 + col) / 8u
+                          : (uint32_t)(row + (t & (D - 1))) * (uint32_t)bpr + (uint32_t)(n0 + col) / kBlock;
+        scales_off = blk_off;
+        scales_at = d.scales;
+        if constexpr (BETA) beta_at = beta;
+    } else {
+        const int lrow = min(n0 + wrow, N - (BR == 8 ? D : 1)) - n0;
+        codes_off = (uint32_t)lrow * codes_row;
+        if (d.codes_tiled) { codes_at = d.codes_tiled + tiled_run_offset(n0, 0, bpr); codes_step = 256 * 32; codes_row = 32; codes_off = (uint32_t)lrow * 32u; }
+        else codes_at = d.codes + (int64_t)n0 * (d_in / 2);
+        codes_off += (uint32_t)wchunk * 4u;
+        const int64_t blk0 = BR == 8 ? (int64_t)(n0 >> 3) * (d_in >> 3) : (int64_t)n0 * bpr;
+        blk_off = BR == 8 ? (uint32_t)(lrow >> 3) * (uint32_t)(d_in >> 3) + (uint32_t)wchunk : (uint32_t)lrow * (uint32_t)bpr;
+        // 64-blocks: the scales come in tile order
+        scales_at = BR == 8 ? d.scales + blk0 : d.scales_tiled + tiled_run_offset(n0, 0, bpr) / 32;
+        scales_off = BR == 8 ? blk_off : (uint32_t)lrow;
+        if constexpr (BETA) beta_at = beta + blk0;
+    }
+    const int64_t scales_step = TR ? d_in : BR == 8 ? 8 : 256, beta_step = TR ? d_in : BR == 8 ? 8 : 1;
+    constexpr bool kRows = TR || BR == 8;                            // a dword of each of D stored rows
+    constexpr int kLoads = (kRows ? D : 1) + 1 + (BETA ? 1 : 0);     // load instructions of a step
     typedef typename std::conditional<D == 4, u32x4_any, u32x2_any>::type Row;
     auto load_staged = [&](Staged<D>& s, int step) __attribute__((always_inline)) {
-        const uint8_t* const p = codes_at + (int64_t)step * codes_step;
-        if constexpr (BR == 8) {
+        const uint8_t* const p = codes_at + step * codes_step;
+        if constexpr (kRows) {
 #pragma unroll
             for (int i = 0; i < D; ++i) s.cw[i] = *reinterpret_cast<const u32_any*>(p + codes_row * i + codes_off);
         } else {
@@ -225,26 +257,63 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
             for (int i = 0; i < D; ++i) s.cw[i] = v[i];
         }
-        s.sc = (scales_at + (int64_t)step * (BR == 8 ? 8 : 256))[scales_off];
-        if constexpr (BETA) s.be = (beta_at + (int64_t)step * (BR == 8 ? 8 : 1))[blk_off];
+        s.sc = (scales_at + step * scales_step)[scales_off];
+        if constexpr (BETA) s.be = (beta_at + step * beta_step)[blk_off];
         asm volatile("" ::: "memory");               // the loads stay in front of what follows
     };
 
-    // ---- dequantization of a staged k-step, in units of one byte of codes; four of them fill a 16-byte chunk ----------
+    // ---- dequantization of a staged k-step, in 4*D units of one byte of codes (two adjacent inputs) -----------------
+    // The weight itself: unit u is byte u & 3 of dword u / 4, and four units fill a 16-byte chunk.  Transposed: byte u / D
+    // of stored row u % D; the D rows of a byte are packed down its two columns.
     const uint32_t table_lane = lds_address(sT) + ((lane & 15) << 3);
-    auto look_up = [&](uint32_t w, int i) __attribute__((always_inline)) {                 // byte i of dword w
+    auto look_up = [&](const Staged<D>& s, int u) __attribute__((always_inline)) {
+        const uint32_t w = s.cw[TR ? u % D : u / 4];
+        const int i = TR ? u / D : u % 4;
         const uint32_t at = ((i == 0 ? (w << 7) : (w >> (8 * i - 7))) & 0x7f80u) | table_lane;
         return *reinterpret_cast<const __attribute__((address_space(3))) f32x2*>(at);
     };
-    auto scale = [&](const Staged<D>& s, f32x2 c) __attribute__((always_inline)) {         // two adjacent k
-        return BETA ? pack_bf16(__fmaf_rn(c[0], s.sc, s.be), __fmaf_rn(c[1], s.sc, s.be))
-                    : pack_bf16(__fmul_rn(c[0], s.sc), __fmul_rn(c[1], s.sc));
+    float rs[D], rb[D];                              // transposed 64-blocks: of the D rows of the tile in work
+    auto spread = [&](const Staged<D>& s) __attribute__((always_inline)) {
+        if constexpr (TR && BR == 1) {
+            rs[0] = group_broadcast<D, 0>(s.sc); rs[1] = group_broadcast<D, 1>(s.sc);
+            if constexpr (BETA) { rb[0] = group_broadcast<D, 0>(s.be); rb[1] = group_broadcast<D, 1>(s.be); }
+            if constexpr (D == 4) {
+                rs[2] = group_broadcast<D, 2>(s.sc); rs[3] = group_broadcast<D, 3>(s.sc);
+                if constexpr (BETA) { rb[2] = group_broadcast<D, 2>(s.be); rb[3] = group_broadcast<D, 3>(s.be); }
+            }
+        }
     };
-    uint32_t store_at = (uint32_t)swz(wrow, wchunk);
-    auto store_chunk = [&](int p, const uint32_t (&o)[4], unsigned char* tile) __attribute__((always_inline)) {
-        // swz(wrow, wchunk + p), or swz(wrow + p, wchunk) with 8 x 8 blocks: wchunk and wrow are multiples of D
-        const uint32_t at = BR == 8 ? (store_at ^ (uint32_t)((p >> 1) << 4)) + p * 128 : store_at ^ (uint32_t)(p << 4);
-        *reinterpret_cast<uint4*>(tile + at) = make_uint4(o[0], o[1], o[2], o[3]);
+    auto scaled = [&](float c, float sc, float be) __attribute__((always_inline)) { return BETA ? __fmaf_rn(c, sc, be) : __fmul_rn(c, sc); };
+    uint32_t store_at = TR ? (uint32_t)(swz_w<TR>(wrow, wchunk) + (D * (t / kGroups) % 8) * 2) : (uint32_t)swz_w<TR>(wrow, wchunk);
+    uint32_t o[4];
+    // lv: the values of units u & ~3 .. | 3
+    auto finish = [&](const Staged<D>& s, int u, const f32x2 (&lv)[4], unsigned char* tile) __attribute__((always_inline)) {
+        if constexpr (!TR) {
+            const f32x2 c = lv[u & 3];
+            o[u & 3] = pack_bf16(scaled(c[0], s.sc, s.be), scaled(c[1], s.sc, s.be));
+            if ((u & 3) != 3) return;
+            // swz(wrow, wchunk + p), or swz(wrow + p, wchunk) with 8 x 8 blocks: wchunk and wrow are multiples of D
+            const int p = u >> 2;
+            const uint32_t at = BR == 8 ? (store_at ^ (uint32_t)((p >> 1) << 4)) + p * 128 : store_at ^ (uint32_t)(p << 4);
+            *reinterpret_cast<uint4*>(tile + at) = make_uint4(o[0], o[1], o[2], o[3]);
+        } else {
+            const int i = u % D, p = u / D;
+            if ((i & 1) == 0) return;
+            const f32x2 c0 = lv[(u - 1) & 3], c1 = lv[u & 3];        // stored rows i - 1 and i
+            const float s0 = BR == 8 ? s.sc : rs[(i - 1) % D], s1 = BR == 8 ? s.sc : rs[i];
+            const float b0 = !BETA ? 0.0f : BR == 8 ? s.be : rb[(i - 1) % D], b1 = !BETA ? 0.0f : BR == 8 ? s.be : rb[i];
+            o[i >> 1] = pack_bf16(scaled(c0[0], s0, b0), scaled(c1[0], s1, b1));            // column 2p
+            o[2 + (i >> 1)] = pack_bf16(scaled(c0[1], s0, b0), scaled(c1[1], s1, b1));      // column 2p + 1
+            if (i != D - 1) return;
+            unsigned char* const at = tile + (store_at ^ (uint32_t)(p << 4)) + p * 256;     // two tile rows share a swizzle
+            if constexpr (D == 2) {
+                *reinterpret_cast<uint32_t*>(at) = o[0];
+                *reinterpret_cast<uint32_t*>(at + 128) = o[2];
+            } else {
+                *reinterpret_cast<uint2*>(at) = make_uint2(o[0], o[1]);
+                *reinterpret_cast<uint2*>(at + 128) = make_uint2(o[2], o[3]);
+            }
+        }
     };
 
     // ---- fragments ----------------------------------------------------------------------------------
@@ -252,12 +321,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // 16*[(g ^ r>>1) & 7 ^ 4ks] -- one per-lane value XOR a constant plus an immediate;
     // the empty asm in a step keeps the variants from being hoisted and held in registers.
     const int r = lane & 15, g = lane >> 4;
-    uint32_t frag_w = 2 * kTileX + (uint32_t)((wn0 + r) * 128 + ((g ^ (r >> 1)) << 4));
+    // (the transposed weight's tile: XOR the number of the 16-row block as well)
+    uint32_t frag_w = 2 * kTileX + (uint32_t)((wn0 + r) * 128 + (((g ^ (r >> 1)) ^ (TR ? (wn0 >> 4) & 7 : 0)) << 4));
     uint32_t frag_x = (uint32_t)((wm0 + r) * 128 + ((g ^ (r >> 1)) << 4));
     auto read_w = [&](int buf, int ks, bf16x8 (&f)[4]) __attribute__((always_inline)) {
-        const unsigned char* const p = smem + ((frag_w ^ (uint32_t)(ks << 6)) + buf * kTileW);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) f[a] = *reinterpret_cast<const bf16x8*>(p + a * 2048);
+        for (int a = 0; a < 4; ++a)
+            f[a] = *reinterpret_cast<const bf16x8*>(smem + ((frag_w ^ (uint32_t)((ks << 6) ^ (TR ? a << 4 : 0))) + buf * kTileW) + a * 2048);
     };
     auto read_x = [&](int buf, int ks, int half, bf16x8 (&f)[4]) __attribute__((always_inline)) {
         const unsigned char* const p = smem + ((frag_x ^ (uint32_t)(ks << 6)) + buf * kTileX) + half * 8192;
@@ -284,7 +354,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         const bool dq = kMode == 1 || (kMode == 0 && s + 1 < steps1), look = kMode == 1 || (kMode == 0 && s + 2 < steps1);
         const bool more = kMode == 1 || s + 1 < nsteps;
         unsigned char* const w_next = sW + nxt * kTileW;
-        uint32_t o[4];
         asm volatile("" : "+v"(frag_w), "+v"(frag_x), "+v"(store_at));
         if constexpr (BN == 128) {
             // First slice: its MFMAs, weight tile s+1 scaled and stored (looked up in the step before), the second slice's
@@ -294,14 +363,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             if (kMode == 1 || (kMode == 0 && s + 3 < steps1)) load_staged(st[(P + 3) & 3], min(s + 3, steps1 - 1));
             read_w(cur, 1, wf[1]);
             read_x(cur, 1, 0, xf[1]);
+            if (dq) spread(st[(P + 1) & 3]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 mfma(wf[0][i >> 2], xf[0][i & 3], acc[i >> 2][i & 3]);
-                if (i < 8 && dq) {
-                    o[i & 3] = scale(st[(P + 1) & 3], lv[i >> 2][i & 3]);
-                    if ((i & 3) == 3) store_chunk(i >> 2, o, w_next);
-                }
+                if (i < 8 && dq) finish(st[(P + 1) & 3], i, lv[i >> 2], w_next);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
@@ -315,7 +382,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             for (int i = 6; i < 16; ++i) {
                 mfma(wf[1][i >> 2], xf[1][i & 3], acc[i >> 2][i & 3]);
                 const int u = i - 6;
-                if (u < 8 && look) lv[u >> 2][u & 3] = look_up(st[(P + 2) & 3].cw[u >> 2], u & 3);
+                if (u < 8 && look) lv[u >> 2][u & 3] = look_up(st[(P + 2) & 3], u);
                 __builtin_amdgcn_sched_barrier(0);
             }
         } else {
@@ -326,11 +393,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             // read four units ahead; the barrier stands behind 6 MFMAs of the last quarter, in front of the first read
             // of the next tiles.  Codes are fetched two steps ahead.
             if (kMode == 1 || (kMode == 0 && s + 2 < steps1)) load_staged(st[P & 1], min(s + 2, steps1 - 1));
+            if (dq) spread(st[(P + 1) & 1]);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const uint32_t slice = q == 1 || q == 2 ? 64 : 0;          // of quarter q + 1
                 const unsigned char* const xs = smem + ((frag_x ^ slice) + (q < 3 ? cur : nxt) * kTileX) + ((q + 1) & 1) * 8192;
-                const unsigned char* const ws = smem + ((frag_w ^ slice) + (q < 3 ? cur : nxt) * kTileW);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int j = 0, n = 0; j < 7; ++j) {
@@ -341,17 +408,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                         mfma(wf[0][a], xf[0][b], acc[a][(4 * (q & 1) + b) % MB]);
                         const int m = 16 * q + n, u = m / 3;
                         if (q < 3 && m % 3 == 0 && dq) {
-                            o[u & 3] = scale(st[(P + 1) & 1], lv[(u >> 2) & 1][u & 3]);
-                            if (u < 12) lv[((u >> 2) + 1) & 1][u & 3] = look_up(st[(P + 1) & 1].cw[((u >> 2) + 1) % D], u & 3);
-                            if ((u & 3) == 3) store_chunk(u >> 2, o, w_next);
+                            finish(st[(P + 1) & 1], u, lv[(u >> 2) & 1], w_next);
+                            if (u < 12) lv[((u >> 2) + 1) & 1][u & 3] = look_up(st[(P + 1) & 1], u + 4);
                         }
                         if (q == 3 && n == 5) {
                             publish(Int<0>{});
                             if (kMode == 1) issue_x1(s + 2);
                             else if (s + 2 < nsteps) issue_copies(s + 2);
                         }
-                        if (q == 3 && n > 5 && n % 2 == 1 && n < 15 && look) lv[0][(n - 7) / 2] = look_up(st[P & 1].cw[0], (n - 7) / 2);
-                        if (b == 3 && (q & 1) && (q < 3 || more)) wf[0][a] = *reinterpret_cast<const bf16x8*>(ws + a * 2048);
+                        if (q == 3 && n > 5 && n % 2 == 1 && n < 15 && look) lv[0][(n - 7) / 2] = look_up(st[P & 1], (n - 7) / 2);
+                        if (b == 3 && (q & 1) && (q < 3 || more)) 
+                            wf[0][a] = *reinterpret_cast<const bf16x8*>(
+                                smem + ((frag_w ^ slice ^ (uint32_t)(TR ? a << 4 : 0)) + (q < 3 ? cur : nxt) * kTileW) + a * 2048);
                         if (a == 3 && (q < 3 || more)) xf[0][b] = *reinterpret_cast<const bf16x8*>(xs + b * 2048);
                         __builtin_amdgcn_sched_barrier(0);
                         ++n;
@@ -381,19 +449,18 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int q = 0; q < 4; ++q) *reinterpret_cast<float4*>(sT + b * 128 + (t >> 8) * 64 + q * 16) = e;
         __syncthreads();
     }
+    spread(st[0]);
 #pragma unroll
-    for (int p = 0; p < D; ++p) {
-        uint32_t o[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) o[i] = scale(st[0], look_up(st[0].cw[p], i));
-        store_chunk(p, o, sW);
+    for (int u = 0; u < 4 * D; ++u) {
+        lv[0][u & 3] = look_up(st[0], u);
+        finish(st[0], u, lv[0], sW);
     }
     publish(Int<0>{});
     read_w(0, 0, wf[0]);
     read_x(0, 0, 0, xf[0]);
     if (steps1 > 1) {
 #pragma unroll
-        for (int u = 0; u < (BN == 256 ? 4 : 8); ++u) lv[u >> 2][u & 3] = look_up(st[1].cw[u >> 2], u & 3);
+        for (int u = 0; u < (BN == 256 ? 4 : 8); ++u) lv[u >> 2][u & 3] = look_up(st[1], u);
     }
     int s = 0;
     // (s is a multiple of the number of sets behind the first loop)
@@ -455,10 +522,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     }
 }
 
-template <int BN, bool BETA, int BR>
+template <int BN, bool BETA, int BR, bool TR>
 int launch_cfg(const GemmDesc& d, hipStream_t st) {
     constexpr size_t smem = 2 * (kTileX + BN * 128) + kTableBytes;
-    auto kern = k_qlinear<BN, BETA, BR>;
+    auto kern = k_qlinear<BN, BETA, BR, TR>;
     // set once per instantiation; the initialisation of a function-local static is thread safe
     static const bool attr_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
@@ -485,18 +552,20 @@ Plan plan(int64_t M, int N, int64_t steps) {
 
 template <bool BETA, int BR>
 int launch_tile(const GemmDesc& d, hipStream_t st) {
-    if (plan(d.M, d.N, 1).wide) return launch_cfg<256, BETA, BR>(d, st);
-    return launch_cfg<128, BETA, BR>(d, st);
+    const bool wide = plan(d.M, d.N, 1).wide;
+    if (d.qmode == 4) return wide ? launch_cfg<256, BETA, BR, true>(d, st) : launch_cfg<128, BETA, BR, true>(d, st);
+    return wide ? launch_cfg<256, BETA, BR, false>(d, st) : launch_cfg<128, BETA, BR, false>(d, st);
 }
 
 }  // namespace
 
 int64_t qlinear_ns(int64_t M, int N, int K) { return plan(M, N, K / kBK).ns; }
 
-// The quantized GEMM of the layer's forward (qmode 1, bf16 output, no auxiliary outputs).
+// The quantized GEMMs of the layer (qmode 1 and 4, bf16 output, no auxiliary outputs).
 int launch_qlinear(const GemmDesc& d, hipStream_t st) {
     if (d.M <= 0 || d.N <= 0) return QBLORA_OK;
     if (d.out_f32 || d.C2 || d.C_lo) return QBLORA_ERR_UNSUPPORTED;
+    if (d.qmode == 4 && (!d.scales || d.N != d.d_in || d.d_out % kBK != 0)) return QBLORA_ERR_UNSUPPORTED;
     if (d.block_rows == 8) {
         // 8 x 8 blocks ask for block parameters on a 16-byte boundary, here as everywhere; tile-ordered scales do not exist
         if (d.scales_tiled || !d.scales || d.d_out % 8 != 0 || (reinterpret_cast<uintptr_t>(d.scales) & 15) ||
@@ -504,7 +573,7 @@ int launch_qlinear(const GemmDesc& d, hipStream_t st) {
             return QBLORA_ERR_UNSUPPORTED;
         return d.beta ? launch_tile<true, 8>(d, st) : launch_tile<false, 8>(d, st);
     }
-    if (!d.scales_tiled) return QBLORA_ERR_UNSUPPORTED;
+    if (d.qmode == 1 && !d.scales_tiled) return QBLORA_ERR_UNSUPPORTED;
     return d.beta ? launch_tile<true, 1>(d, st) : launch_tile<false, 1>(d, st);
 }
 
