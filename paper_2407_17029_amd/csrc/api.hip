@@ -1051,7 +1051,11 @@ int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblor
     hipStream_t st = as_stream(stream);
     const bool mid = T > kDecodeMaxTokens || half_blocks(qw);   // 8 x 4 blocks: the mid-batch kernel at every token count
     const size_t scale_bytes = qblora_linear_decode_workspace_bytes(qw);
-    const size_t need = mid ? qblora_linear_decode_tokens_workspace_bytes(qw, T) : (pack ? 0 : scale_bytes);
+    // the mid-batch kernel's token rows have 32-bit offsets: a batch of 4 GiB goes in two halves
+    const int32_t chunk = (int64_t)T * qw->d_in * (int64_t)sizeof(qblora_bf16) >= (int64_t)1 << 32 ? kMidMaxTokens / 2 : kMidMaxTokens;
+    const size_t part_bytes = mid ? std::max(w4_mid_part_bytes(qw->d_out, qw->d_in, std::min(T, chunk)),
+                                             T > chunk ? w4_mid_part_bytes(qw->d_out, qw->d_in, T - chunk) : 0) : 0;
+    const size_t need = mid ? scale_bytes + align_up(part_bytes) : (pack ? 0 : scale_bytes);
     if (need > 0 && (!workspace || workspace_bytes < need)) return QBLORA_ERR_WORKSPACE;
     if (mid && need > scale_bytes && (reinterpret_cast<uintptr_t>(workspace) & 15)) return QBLORA_ERR_WORKSPACE;
     // the mid-batch kernel stores 8-byte words and, with 8 x 8 blocks, loads four block parameters at a time
@@ -1073,9 +1077,15 @@ int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblor
         return launch_w4_decode(codes, scales, beta, codebook_of(qw), pack ? 1 : 0, qw->d_out, qw->d_in, X, T, Y, st,
                                 block_rows_of(qw), regrouped);
     float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + scale_bytes);
-    return launch_w4_mid(codes, scales, beta, codebook_of(qw), pack ? 1 : 0, qw->d_out, qw->d_in, X, T, Y,
-                         w4_mid_part_bytes(qw->d_out, qw->d_in, T) ? part : nullptr, st, block_rows_of(qw), regrouped,
-                         block_rows_of(qw) == 8 ? block_cols_of(qw) : 8);
+    for (int32_t t0 = 0; t0 < T; t0 += chunk) {
+        const int32_t n = std::min(chunk, T - t0);
+        if ((rc = launch_w4_mid(codes, scales, beta, codebook_of(qw), pack ? 1 : 0, qw->d_out, qw->d_in,
+                                X + (int64_t)t0 * qw->d_in, n, Y + (int64_t)t0 * qw->d_out,
+                                w4_mid_part_bytes(qw->d_out, qw->d_in, n) ? part : nullptr, st, block_rows_of(qw), regrouped,
+                                block_rows_of(qw) == 8 ? block_cols_of(qw) : 8)))
+            return rc;
+    }
+    return QBLORA_OK;
 }
 
 }  // extern "C"

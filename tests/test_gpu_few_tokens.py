@@ -77,6 +77,22 @@ def test_mid_batch_on_the_workspace_of_the_largest(oracle, codebook):
         assert_close_bf16(Y, oracle.forward(Wt, L.X[:T], None, None, 1, 1, 0.0), f"Y, {T} tokens")
 
 
+def test_mid_batch_of_four_gibibytes(codebook):
+    """256 rows of 2^23 inputs: more than the kernel's 32-bit row offsets reach, so the call goes in two halves."""
+    from paper_2407_17029_amd import binding as qb
+    T, d_out, d_in = 256, 8, 1 << 23
+    print(f"case mid batch of 4 GiB T={T} {d_out}x{d_in}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(7600)
+    W = torch.randn((d_out, d_in), generator=g, device="cuda").mul_(0.02)
+    qw = qb.qblora_quantize_blockwise(W, 64, qb.QUANT_ABSMAX_CODEBOOK, codebook, tiled=False)
+    X = torch.empty((T, d_in), dtype=torch.bfloat16, device="cuda")
+    for row in X:
+        row.copy_(torch.randn((d_in,), generator=g, device="cuda"))
+    Y = qb.qblora_linear_decode(qw, X)
+    halves = [qb.qblora_linear_decode(qw, X[t:t + 128]) for t in (0, 128)]
+    assert torch.equal(Y, torch.cat(halves))
+
+
 @pytest.mark.parametrize("T,d_out,d_in", [(8, 40, 4160), (5, 4096, 8128), (8, 256, 6080)])
 def test_sixteen_wave_decode_of_a_packed_model(oracle, codebook, T, d_out, d_in):
     """Packed INT4 model whose activations exceed the LDS copy, few rows: sixteen waves share a row group, with
