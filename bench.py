@@ -7,7 +7,8 @@ projection of the workload, in sequence on one shared workspace,
 then the tile product H = A B and the requantizing INT4 merge of ALL projections back to back (the batch the
 merge is meant to be timed on).  Default workload: the LLaMA-65B-shaped layer (seven projections, T = 8192,
 double-quantized block scales, rank 128), the largest single-GPU configuration.  All inputs are resident in HBM
-before the timed region.  Prints ONE JSON line.
+before the timed region.  Prints ONE JSON line of the headline figures, short enough to be kept whole by whatever
+records the end of a program's output, and writes everything that was measured to --details (bench_details.json):
 
 value        algorithmic fwd+bwd flops of all projections (4*T*d_in*d_out + 6*T*r*(d_in+d_out) each) over the
              wall time of the whole step, TFLOP/s.
@@ -236,7 +237,6 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
              "prep": (qb.PROFILE_PREP, "fwd"), "dequant_fwd": (qb.PROFILE_DEQUANT, "fwd"),
              "dequant_bwd": (qb.PROFILE_DEQUANT, "bwd"), "tile_product": (qb.PROFILE_TILE_PRODUCT, "merge"),
              "merge": (qb.PROFILE_MERGE, "merge")}
-    dense = T >= qb.qblora_dense_min_tokens()           # the calls dequantize once, then contract the bf16 weight
     events = {k: [(new_event(), new_event()) for _ in range(steps if k == "fwd_gemm" else side_steps)] for k in slots}
     marks = [new_event() for _ in range(steps + 1)]
     for pairs in events.values():
@@ -301,8 +301,12 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
     def gemm_ms(k):
         return max(float(np.mean(raw[k])) - empty_pair_ms, 1e-6)
 
-    if not dense:                                       # no one-off dequantize pass in these calls
-        raw["dequant_fwd"] = raw["dequant_bwd"] = [0.0]
+    # Which calls dequantized the weight once and then contracted it (the library decides by the shape): those in which
+    # the dequantize slot's events were recorded after the timed steps, not only when their handles were made.
+    once = {k: marks[steps].elapsed_time(events[k][0][0]) > 0 for k in ("dequant_fwd", "dequant_bwd")}
+    for k, ran in once.items():
+        if not ran:
+            raw[k] = [0.0]
 
     fwd_flops = 2.0 * T * bp.d_in * bp.d_out + 2.0 * T * R * bp.d_out / lam
     bwd_flops = 2.0 * T * bp.d_in * bp.d_out + 2.0 * T * R * bp.d_in / lam
@@ -323,8 +327,8 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
         return d
 
     proj_name = f"{bp.name} [{bp.d_out}x{bp.d_in}]"
-    kname = ("k_dense (forward contraction on the weight dequantized once per call)" if dense
-             else "k_few (forward dequantize-and-contract)")
+    kname = ("k_dense (forward contraction on the weight dequantized once per call)" if once["dequant_fwd"]
+             else "k_qlinear, or k_few up to 256 tokens (forward contraction from the 4-bit codes)")
     out = {
         "value": round(value, 2), "unit": "TFLOP/s", "steps": steps, "warmup": warmup,
         "ms_per_step": round(ms_per_step, 4), "step_ms": stats(step_ms),
@@ -344,9 +348,9 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
                          "frac": round(bwd_flops / (gemm_ms("bwd_gemm") * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4)},
             "quantize": hbm("quantize", quant_bytes),
             "dequantize_once_fwd": (hbm("dequant_fwd", n_w * (0.5 + 4 / 64 + 2), "codes + scales -> bf16 weight in the workspace")
-                                    if dense else None),
+                                    if once["dequant_fwd"] else None),
             "dequantize_once_bwd": (hbm("dequant_bwd", n_w * (0.5 + 4 / 64 + 2), "the same, transposed, for the backward contraction")
-                                    if dense else None),
+                                    if once["dequant_bwd"] else None),
             "adapter_fwd_skinny": hbm("adapter_fwd", 2.0 * T * bp.d_in + 2.0 * T * R * 2, "s*U = (s/lambda) X A_x^T; reads X once"),
             "adapter_bwd_skinny": hbm("adapter_bwd", 2.0 * T * bp.d_out + 2.0 * T * R * 3, "dU = s dY B_x^T; reads dY once"),
             "adapter_grads": hbm("adapter_grads", 2.0 * T * (bp.d_in + bp.d_out) + 8.0 * T * R,
@@ -704,6 +708,20 @@ def side_measurements(which):
     return list(_SIDE)
 
 
+def headline(out):
+    """The line that is printed: the fields of the whole step in full, one figure for each kernel and workload."""
+    line = {k: v for k, v in out.items() if k not in ("roofline", "kernels", "cpu_baseline", "configs", "side")}
+    line["roofline"] = {k: out["roofline"][k] for k in ("kernel", "projection", "bound", "achieved", "peak", "unit", "frac",
+                                                        "traffic", "avg_kernel_ms")}
+    line["kernel_frac"] = {k: v["frac"] for k, v in out["kernels"].items() if isinstance(v, dict) and "frac" in v}
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = {k: v for k, v in out["cpu_baseline"].items() if isinstance(v, (int, float))}
+    if "configs" in out:
+        line["configs"] = {k: {"value": v["value"], "ms_per_step": v["ms_per_step"], "roofline_frac": v["roofline"]["frac"]}
+                           for k, v in out["configs"].items()}
+    return line
+
+
 def main() -> int:
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -722,6 +740,8 @@ def main() -> int:
     ap.add_argument("--calibration-copy", action="store_true",
                     help="also run one plain device copy of 256 MiB before the timed steps, so that a counter "
                          "profile of this command holds a kernel of known traffic to scale FETCH_SIZE/WRITE_SIZE by")
+    ap.add_argument("--details", default=os.path.join(ROOT, "bench_details.json"),
+                    help="file for the full record (every kernel, workload and side measurement); empty string = none")
     args = ap.parse_args()
     if args.gpus != 1 or int(os.environ.get("WORLD_SIZE", "1")) != 1:
         print("bench.py: this build measures one GPU only (no collectives are part of it); run with --gpus 1",
@@ -790,7 +810,10 @@ def main() -> int:
     side = [w for w in args.side.split(",") if w]
     if side:
         out["side"] = side_measurements(side)
-    print(json.dumps(out))
+    if args.details:
+        with open(args.details, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(headline(out)))
     return 0
 
 
