@@ -133,7 +133,7 @@ def test_workspace_sizes(qb):
     qw = qb.CQWeight()
     qw.d_out, qw.d_in, qw.block = 4096, 4096, 64
     qw.codes = qw.scales = 0x1000
-    few = L.qblora_dense_min_tokens() - 1                               # weight tiles rebuilt in LDS per token tile
+    few = L.qblora_dense_min_tokens() - 1                               # weights rebuilt in the contraction
     many = L.qblora_dense_min_tokens()                                  # weight dequantized once into the workspace
     assert few >= 256
     scales_t = 4 * 4096 * 64                                            # tile-ordered fp32 block scales

@@ -4,24 +4,6 @@ import ctypes as C
 import pytest
 
 
-class DensePlan(C.Structure):
-    _fields_ = [("shape", C.c_int), ("splits", C.c_int), ("ns", C.c_int64)]
-
-
-@pytest.fixture(scope="module")
-def rules():
-    """The library's own rules, by their C++ names."""
-    from paper_2407_17029_amd import binding as qb
-    L = qb.lib()
-    pays = L["_ZN6qblora10dense_paysEliii"]
-    pays.argtypes, pays.restype = [C.c_int64, C.c_int, C.c_int, C.c_int], C.c_bool
-    pays_t = L["_ZN6qblora12dense_pays_tEliii"]
-    pays_t.argtypes, pays_t.restype = [C.c_int64, C.c_int, C.c_int, C.c_int], C.c_bool
-    plan = L["_ZN6qblora10dense_planEliiii"]
-    plan.argtypes, plan.restype = [C.c_int64, C.c_int, C.c_int, C.c_int, C.c_int], DensePlan
-    return type("Rules", (), dict(qb=qb, L=L, dense_pays=pays, dense_pays_t=pays_t, dense_plan=plan))
-
-
 @pytest.mark.parametrize("T,d_out,d_in,K2,dense", [
     (300, 22016, 8192, 0, False), (512, 22016, 8192, 128, False), (700, 16384, 8192, 128, False),
     (512, 16384, 8192, 1024, False),

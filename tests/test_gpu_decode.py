@@ -99,7 +99,7 @@ def test_decode_of_the_merged_int4_model(qb, oracle, codebook):
 
 
 MID_CASES = [
-    # T, d_out, d_in: token tiles of 32 / 64 / 128, two chunks above 128, ragged rows, one to many steps
+    # T, d_out, d_in: token tiles of 32 / 64 / 128 / 192 / 256, ragged rows, one to many steps
     (17, 512, 512), (32, 320, 192), (33, 1000, 1088), (64, 256, 2048), (100, 40, 64), (128, 1024, 1024),
     (129, 384, 320), (200, 648, 704), (256, 512, 4096),
 ]
@@ -109,7 +109,7 @@ MID_CASES = [
 @pytest.mark.parametrize("T,d_out,d_in", MID_CASES)
 def test_mid_batch_parity(qb, oracle, codebook, T, d_out, d_in, base):
     """16 < T <= 256: the entry point contracts the bf16 compute weight (Eq. 1 rounded once, as the training
-    forward does) on token tiles of 32 / 64 / 128; from the row-major arrays and from the pack (INT4 models: codes
+    forward does) on token tiles of 32 to 256; from the row-major arrays and from the pack (INT4 models: codes
     regrouped, converted without the table)."""
     from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
     print(f"case mid batch T={T} {d_out}x{d_in} base={base}", flush=True)

@@ -9,7 +9,8 @@ pytestmark = pytest.mark.gpu
 
 # T, d_out, d_in, R: the tile shape follows from T and the output width (256 x 256, 128 x 256, 256 x 128 and 128 x 128
 # tokens x features; forward and backward differ), the number of 64-wide steps from the other width (one step up to
-# more than the ring holds), R adds none, one partial or two steps of the K-extension.
+# more than the ring holds), R adds none, one partial or two steps of the K-extension.  Backward contractions of few
+# output tiles are sliced, most of these in 128 x 128 tiles; the other tiles in slices are below.
 CASES = [
     (4100, 4096, 64, 0),       # 256 x 256, one step; backward 128 x 128, 64 steps
     (4100, 4096, 128, 72),     # 256 x 256, two steps and a ragged extension
@@ -20,10 +21,10 @@ CASES = [
     (1270, 6528, 192, 72),     # 256 x 128, three steps and a ragged extension
     (257, 64, 320, 8),         # 128 x 128, narrower than a tile
     (300, 320, 64, 24),        # 128 x 128, fewer steps than stages
-    (1, 448, 128, 16),         # backward of one token
-    (200, 2112, 192, 72),      # backward in slices of 128 x 128 tiles, the last one with the ragged extension
+    (1, 448, 128, 16),         # backward of one token; forward few
+    (200, 2112, 192, 72),      # backward in slices of 128 x 128 tiles, the last one with the ragged extension; forward few
     (1000, 4160, 448, 0),      # backward in slices, no adapter, partial tiles on both sides
-    (513, 8256, 2048, 8),      # backward in slices of 128 x 256 tiles
+    (513, 8256, 2048, 8),      # backward in slices of 128 x 128 tiles; forward from the codes
 ]
 
 
@@ -50,11 +51,55 @@ def test_tiles_and_stages(oracle, codebook, T, d_out, d_in, R):
     torch.cuda.synchronize()
     assert_close_bf16(Y, oracle.forward(Wt, L.X, A, B, 2, 2, s), "Y")
     assert_close_bf16(dX, oracle.backward(Wt, L.X, L.dY, A, B, 2, 2, s)[0], "dX")
-    # the form that rebuilds weight tiles in LDS adds in the same order
+    # the form that rebuilds weight tiles in LDS adds in the same order (of 1 and 200 tokens both take the one for few,
+    # of 513 both take this one)
     Y2 = torch.empty_like(Y)
     qb.qblora_linear_fwd_noalloc(qw, ad, X, Y2)
     torch.cuda.synchronize()
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
+
+
+SHAPES = ["256 x 256", "128 x 256", "256 x 128", "128 x 128"]
+
+
+@pytest.mark.parametrize("T,d_out,d_in,R,shape,slices", [
+    (513, 4096, 6592, 72, "256 x 256", 3),     # one token past two tiles, 192 features in the last
+    (257, 4096, 5440, 0, "128 x 256", 3),      # one token past two tiles, 64 features in the last
+    (385, 6144, 3136, 24, "256 x 128", 5),     # steps that do not divide evenly
+])
+def test_slices_of_every_tile(oracle, codebook, rules, T, d_out, d_in, R, shape, slices):
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
+    print(f"case dense slices T={T} {d_out}x{d_in} R={R}", flush=True)
+    plan = rules.dense_plan(T, d_in, d_out, R, 8)
+    assert rules.dense_pays_t(T, d_in, d_out, R) and (SHAPES[plan.shape], plan.splits) == (shape, slices)
+    L = synth.make_layer(5200 + T, T, d_out, d_in, max(R, 8), 2, 2, b_std=0.05)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook, tiled=False)
+    Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
+    ad = qb.Adapter(bf16_to_dev(L.A), bf16_to_dev(L.B), 2, 2, 0.5) if R else None
+    A, B, s = (L.A, L.B, 0.5) if R else (None, None, 0.0)
+    dX = torch.full((T, d_in), float("nan"), dtype=torch.bfloat16, device="cuda")
+    qb.qblora_linear_bwd(qw, ad, bf16_to_dev(L.X), bf16_to_dev(L.dY), need_grads=False, dX=dX)
+    torch.cuda.synchronize()
+    assert_close_bf16(dX, oracle.backward(Wt, L.X, L.dY, A, B, 2, 2, s)[0], "dX")
+
+
+def test_slices_with_a_single_matrix_adapter(oracle, codebook, rules):
+    """dX's extension is H^T here, d_out / lambda2 wide: its steps lie in the last slices."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, assert_close_f32, OracleWeight
+    T, d_out, d_in, lam = 300, 2112, 1088, 8
+    print(f"case dense slices, single matrix T={T} {d_out}x{d_in}", flush=True)
+    assert rules.dense_pays_t(T, d_in, d_out, d_out // lam) and rules.dense_plan(T, d_in, d_out, d_out // lam, 8).splits > 1
+    L = synth.make_layer(5300, T, d_out, d_in, 8, lam, lam)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook, tiled=False)
+    Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
+    Hb = synth.f32_to_bf16_bits(synth.normal_f32(5301, 0, (d_in // lam, d_out // lam)) * np.float32(0.02))
+    dX, dH = qb.qablora_linear_bwd(qw, bf16_to_dev(Hb), lam, lam, 0.5, bf16_to_dev(L.X), bf16_to_dev(L.dY))
+    torch.cuda.synchronize()
+    rX, rH = oracle.qa_backward(Wt, L.X, L.dY, Hb, lam, lam, 0.5)
+    assert_close_bf16(dX, rX, "dX")
+    assert_close_f32(dH, rH, "dH")
 
 
 @pytest.mark.parametrize("form", ["none", "two", "single"])

@@ -18,10 +18,11 @@ CASES = [
 
 
 @pytest.mark.parametrize("T,d_out,d_in,R,fmt", CASES)
-def test_waves_split_the_contraction(oracle, codebook, T, d_out, d_in, R, fmt):
+def test_waves_split_the_contraction(oracle, codebook, rules, T, d_out, d_in, R, fmt):
     from paper_2407_17029_amd import binding as qb
     from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
     print(f"case few T={T} {d_out}x{d_in} R={R} {fmt}", flush=True)
+    assert rules.few_applies(T, d_out, d_in)
     L = synth.make_layer(7100 + T + d_out, T, d_out, d_in, max(R, 8), 2, 2)
     br = 8 if fmt.startswith("tile8") else 1
     minmax, grouped = fmt in ("minmax", "tile8"), fmt == "grouped"
@@ -42,6 +43,23 @@ def test_waves_split_the_contraction(oracle, codebook, T, d_out, d_in, R, fmt):
     torch.cuda.synchronize()
     assert_close_bf16(Y, oracle.forward(Wt, L.X, A, B, 2, 2, s), "Y")
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
+
+
+def test_single_matrix_adapter_on_grouped_scales(oracle, codebook, rules):
+    """The single-matrix forward reconstructs the grouped block scales for this kernel; the extension is H's."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
+    T, d_out, d_in, lam = 130, 576, 832, 8
+    print(f"case few, single matrix on grouped scales T={T} {d_out}x{d_in}", flush=True)
+    assert rules.few_applies(T, d_out, d_in)
+    L = synth.make_layer(7200, T, d_out, d_in, 8, lam, lam)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook, qb.SCALES_E4M3_GROUPED)
+    torch.cuda.synchronize()
+    Wt = OracleWeight(oracle, L.W, codebook, False, True).assert_same(qw).dequantize(oracle, 2)
+    Hb = synth.f32_to_bf16_bits(synth.normal_f32(7201, 0, (d_in // lam, d_out // lam)) * 0.02)
+    Y = qb.qablora_linear_fwd(qw, bf16_to_dev(Hb), lam, lam, 0.5, bf16_to_dev(L.X))
+    torch.cuda.synchronize()
+    assert_close_bf16(Y, oracle.qa_forward(Wt, L.X, Hb, lam, lam, 0.5), "Y")
 
 
 @pytest.mark.parametrize("T,d_out,d_in", [(21, 37, 1024), (150, 37, 2048), (250, 130, 1088)])

@@ -211,7 +211,8 @@ def test_adapter_dominant_parity(qb, oracle, codebook, T, d_out, d_in, R, lam1, 
 
 # ---- many tokens: the weight is dequantized once per call ---------------------------------------------
 # From qblora_dense_min_tokens() tokens on, the forward / backward calls first write the bf16 compute weight
-# (transposed for the backward) into their workspace and contract that.  Small widths with ragged token counts
+# (transposed for the backward) into their workspace and contract that, except where the weight is so large and the
+# tokens so few that contracting straight from the codes is faster (not at these sizes; the test asks the rule).  Small widths with ragged token counts
 # keep the oracle fast while the path sees partial tiles, every block geometry and scale format.
 DENSE_CASES = [
     # extra tokens, d_out, d_in, R, lam1, lam2, s, minmax, grouped, block_rows
@@ -223,11 +224,12 @@ DENSE_CASES = [
 ]
 
 
+@pytest.mark.parametrize("start", [0, 2048])         # from the first token count at which they may, and from far above
 @pytest.mark.parametrize("extra,d_out,d_in,R,lam1,lam2,s,minmax,grouped,block_rows", DENSE_CASES)
-def test_many_token_calls_dequantize_once(qb, oracle, codebook, extra, d_out, d_in, R, lam1, lam2, s, minmax, grouped,
-                                          block_rows):
+def test_many_token_calls_dequantize_once(qb, oracle, codebook, rules, extra, d_out, d_in, R, lam1, lam2, s, minmax, grouped,
+                                          block_rows, start):
     from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, assert_close_f32, OracleWeight
-    T = qb.qblora_dense_min_tokens() + extra
+    T = max(start, qb.qblora_dense_min_tokens()) + extra
     print(f"case many tokens T={T} {d_out}x{d_in} R={R} lam=({lam1},{lam2}) minmax={minmax} grouped={grouped} "
           f"block_rows={block_rows}", flush=True)
     L = synth.make_layer(1500 + extra + d_out, T, d_out, d_in, max(R, 8), lam1, lam2, b_std=0.2)
@@ -242,6 +244,7 @@ def test_many_token_calls_dequantize_once(qb, oracle, codebook, extra, d_out, d_
     ad = qb.Adapter(bf16_to_dev(L.A), bf16_to_dev(L.B), lam1, lam2, s) if R > 0 else None
     A, B = (L.A, L.B) if R > 0 else (None, None)
     X, dY = bf16_to_dev(L.X), bf16_to_dev(L.dY)
+    assert rules.dense_pays(T, d_out, d_in, R) and rules.dense_pays_t(T, d_in, d_out, R)
     assert qb.qblora_linear_fwd_workspace_bytes(qw, ad, T) >= 2 * d_out * d_in
     Y = qb.qblora_linear_fwd(qw, ad, X)
     dX, dA, dB = qb.qblora_linear_bwd(qw, ad, X, dY, need_grads=R > 0)

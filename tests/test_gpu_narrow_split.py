@@ -44,3 +44,27 @@ def test_sliced_narrow_gemms(oracle, codebook, T, d_out, d_in, R, lam):
     torch.cuda.synchronize()
     assert torch.equal(Y, Y2) and torch.equal(Y, Y3)
     assert torch.equal(dX, dX2) and torch.equal(dA, dA2) and torch.equal(dB, dB2)
+
+
+@pytest.mark.parametrize("op", [1, 2])
+@pytest.mark.parametrize("T,d_out,d_in,R,lam", [CASES[0], CASES[2]])
+def test_sliced_narrow_gemms_of_the_other_operators(oracle, codebook, rules, T, d_out, d_in, R, lam, op):
+    """Truncation and interval sampling: zero-filled expanded operands in the sliced narrow GEMMs and in a sliced dX."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, assert_close_f32, OracleWeight
+    print(f"case narrow split op={op} T={T} {d_out}x{d_in} R={R} lam={lam}", flush=True)
+    assert rules.dense_pays_t(T, d_in, d_out, R) and rules.dense_plan(T, d_in, d_out, R, 8).splits > 1
+    L = synth.make_layer(6200 + T + R, T, d_out, d_in, R, lam, lam)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook)
+    torch.cuda.synchronize()
+    Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
+    ad = qb.Adapter(bf16_to_dev(L.A), bf16_to_dev(L.B), lam, lam, 0.5, scale_op=op)
+    X, dY = bf16_to_dev(L.X), bf16_to_dev(L.dY)
+    Y = qb.qblora_linear_fwd(qw, ad, X)
+    dX, dA, dB = qb.qblora_linear_bwd(qw, ad, X, dY)
+    torch.cuda.synchronize()
+    rX, rA, rB = oracle.backward_op(Wt, L.X, L.dY, L.A, L.B, lam, lam, 0.5, op)
+    assert_close_bf16(Y, oracle.forward_op(Wt, L.X, L.A, L.B, lam, lam, 0.5, op), "Y")
+    assert_close_bf16(dX, rX, "dX")
+    assert_close_f32(dA, rA, "dA")
+    assert_close_f32(dB, rB, "dB")

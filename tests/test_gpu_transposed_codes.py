@@ -5,7 +5,6 @@ import pytest
 import torch
 
 from paper_2407_17029_amd import synth
-from test_dispatch_rules import rules  # noqa: F401  (fixture)
 
 pytestmark = pytest.mark.gpu
 
