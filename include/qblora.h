@@ -395,10 +395,12 @@ int qblora_decode_pack(const qblora_qweight* qw, void* pack, void* stream);
 
 /*
  * Measurement hook.  Registers a pair of caller-created hipEvent_t (passed as void*) that the next
- * calls record on their stream immediately before and after ONE kernel launch, so that a
- * benchmark can time that kernel alone while running the whole path:
- *   QBLORA_PROFILE_FWD_GEMM   the dequantize-and-contract kernel of qblora_linear_fwd
- *   QBLORA_PROFILE_BWD_GEMM   the transposed dequantize-and-contract kernel of qblora_linear_bwd
+ * calls record on their stream immediately before and after ONE part of the work, so that a
+ * benchmark can time that part alone while running the whole path.  It is one kernel launch, except that a
+ * contraction that is cut into slices is bracketed together with the launch that adds them:
+ *   QBLORA_PROFILE_FWD_GEMM   the base contraction of qblora_linear_fwd, adapter term included, from the codes or on the
+ *                             weight dequantized once (whose pass is then QBLORA_PROFILE_DEQUANT)
+ *   QBLORA_PROFILE_BWD_GEMM   the same on the transposed weight: dX of qblora_linear_bwd
  *   QBLORA_PROFILE_MERGE      the requantizing (or beta-shift) kernel of qablora_merge_quantize
  *   QBLORA_PROFILE_QUANTIZE   the code-selection kernel of qblora_quantize_blockwise
  *   QBLORA_PROFILE_ADAPTER_FWD    the narrow GEMM s*U = s * AvgPool(X) A of the forward
@@ -407,7 +409,8 @@ int qblora_decode_pack(const qblora_qweight* qw, void* pack, void* stream);
  *   QBLORA_PROFILE_GRAD_REDUCE    the fixed-order reduction of those partial sums into dA and dB
  *   QBLORA_PROFILE_PREP           the per-call re-layout launch of the forward (adapter operands, block scales)
  *   QBLORA_PROFILE_TILE_PRODUCT   the kernel of qblora_tile_product
- *   QBLORA_PROFILE_DEQUANT        the one-off dequantize pass of a forward / backward call on many tokens
+ *   QBLORA_PROFILE_DEQUANT        the one-off dequantize pass of a forward / backward call (not recorded by calls
+ *                                 that contract from the codes)
  * Passing NULL for both events unregisters the slot.  The registration is per host thread: it applies to
  * calls made by the thread that registered it, so concurrent callers do not see each other's events.  Has
  * no effect on results.

@@ -23,8 +23,8 @@
 // (lgkmcnt(0)) in front of the barrier that ends their phase, and the other half's same phase ends one barrier
 // earlier than the refill starts.
 //
-// k is accumulated in ascending order by v_mfma_f32_16x16x32_bf16, as in the kernel that rebuilds weight tiles
-// in LDS (qlinear.hip), so both give the same bits.
+// k is accumulated in ascending order by v_mfma_f32_16x16x32_bf16, as in the kernel that contracts from the codes
+// (qlinear.hip), so both give the same bits where this one is not sliced.
 #include <algorithm>
 #include <type_traits>
 

@@ -1,7 +1,7 @@
 // Plain bf16 GEMM of the adapter path for outputs that are neither narrow (skinny.hip) nor a base contraction, and the
 // dispatch of all contractions (gfx950):
 //
-//   C[M,N] = X2[M,K2] * W2[N/div2, K2]^T          (tile products of ragged shapes)
+//   C[M,N] = X2[M,K2] * W2[N/div2, K2]^T          (tile products of ragged shapes; s*U and dU of inner ranks above 512)
 //
 // Tiling: one workgroup of 512 threads (8 wave64) owns a BM x BN output tile and walks K in steps
 // of 64.  Both operand tiles live in LDS as [row][64 k] bf16 with the

@@ -9,8 +9,8 @@
 // LDS tile and feeds them to v_mfma_f32_16x16x32_bf16 with fp32 accumulation; the dequantized
 // weight never exists in HBM.  Segment 2 is a plain bf16 K-extension: the adapter's rank-R product
 // rides in the same accumulators as R extra contraction steps (X2 = s*U, W2 = B^T with output row n using row
-// n/lambda2, i.e. repeat_interleave; dX: X2 = dU/lambda1, W2 = A with row k/lambda1).  k is accumulated in the order and by the instruction of dense.hip, so both
-// give the same bits.
+// n/lambda2, i.e. repeat_interleave; dX: X2 = dU/lambda1, W2 = A with row k/lambda1).  k is accumulated in the order and
+// by the instruction of dense.hip, so both give the same bits.
 //
 // Shape of the computation on a CU: one workgroup of 512 threads (8 wave64, two per SIMD) owns 256 tokens x 256 or 128
 // features; a wave owns 128 x 64 or 64 x 64 of them (128 or 64 accumulator registers).  Two waves per SIMD matter: the
@@ -536,8 +536,9 @@ int launch_cfg(const GemmDesc& d, hipStream_t st) {
 }
 
 // Time of a launch in ns, by tile width: a k-step with every CU busy and with a few (a last round of workgroups, one per
-// CU, lies in between: the clock holds up to about 3/4 of them).  256 x 128 tiles take 0.65 of the 256 x 256 tiles' time for half the work, so they pay where the
-// wide ones leave more than a third of the CUs idle or start a round for a few tiles.  us on 256 x 256 / 256 x 128 tiles:
+// CU, lies in between: the clock holds up to about 3/4 of them).  256 x 128 tiles take 0.65 of the 256 x 256 tiles' time
+// for half the work, so they pay where the wide ones leave more than a third of the CUs idle or start a round for a few
+// tiles.  us on 256 x 256 / 256 x 128 tiles:
 // 1024 x 4096 x 4096 105 / 71, 4096 x 4096 x 4096 124 / 141, 700 x 11008 x 4096 106 / 132, 512 x 11008 x 4096 105 / 69,
 // 700 x 22016 x 8192 398 / 369, 2047 x 16384 x 8192 440 / 532, 4096 x 5120 x 13824 673 / 630.
 struct Plan { bool wide; int64_t ns; };
