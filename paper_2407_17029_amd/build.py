@@ -8,20 +8,15 @@ import subprocess
 _DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_DIR, "csrc")
 LIB = os.path.join(_DIR, "libqblora.so")
-SOURCES = ["api.hip", "quantize.hip", "prep.hip", "qgemm.hip", "qlinear.hip", "dense.hip", "few.hip", "skinny.hip", "grads.hip", "merge.hip", "pool.hip", "decode.hip", "w4mid.hip", "tileprod.hip"]
+SOURCES = ["api.hip", "quantize.hip", "prep.hip", "qgemm.hip", "qlinear.hip", "dense.hip", "few.hip", "skinny.hip", "grads.hip", "merge.hip", "pool.hip", "w4mid.hip", "w4rows.hip", "tileprod.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-ffp-contract=off",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument"]
-
-
-# Per-file additions.  decode.hip scales every block's MFMA result with vector FMAs right away: with the
-# results in ordinary vector registers there is no accumulator-register read in front of each FMA.
-EXTRA_FLAGS = {"decode.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]}
 
 
 def _compile(src: str) -> str:
     obj = os.path.join(_DIR, "_build", src.replace(".hip", ".o"))
     os.makedirs(os.path.dirname(obj), exist_ok=True)
-    cmd = ["hipcc", *FLAGS, *EXTRA_FLAGS.get(src, []), "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = ["hipcc", *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if "packed-fp32-ops" not in l)
     if r.returncode != 0:

@@ -964,8 +964,8 @@ int qblora_merge_bf16(const qblora_qweight* base, const float* H, int32_t lambda
 namespace {
 
 struct DecodePack { uint8_t* codes; float* scales; float* beta; size_t bytes; };
-constexpr int32_t kDecodeMaxTokens = 16;     // up to here: the streaming kernel that scales block sums
-constexpr int32_t kMidMaxTokens = 256;       // up to here: the bf16 compute weight, one launch
+constexpr int32_t kDecodeMaxTokens = 16;     // up to here, with 64-blocks: scales act on block sums
+constexpr int32_t kMidMaxTokens = 256;       // up to here: the bf16 compute weight
 
 // An INT4 model in 64-blocks (codebook exactly 0, 1, ..., 15 and offsets present): its pack holds the codes
 // with the nibbles of every dword regrouped for the table-free decode kernel.  Pack and decode both decide
@@ -1049,7 +1049,8 @@ int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblor
         (reinterpret_cast<uintptr_t>(pack) & 255))
         return QBLORA_ERR_SHAPE;
     hipStream_t st = as_stream(stream);
-    const bool mid = T > kDecodeMaxTokens || half_blocks(qw);   // 8 x 4 blocks: the mid-batch kernel at every token count
+    const bool mid = T > kDecodeMaxTokens || half_blocks(qw);   // contracts the bf16 compute weight whatever the block shape
+    const bool rows = w4_rows_applies(qw->d_out, qw->d_in, T);  // one launch that leaves the workspace's partial sums unused
     const size_t scale_bytes = qblora_linear_decode_workspace_bytes(qw);
     // the mid-batch kernel's token rows have 32-bit offsets: a batch of 4 GiB goes in two halves
     const int32_t chunk = (int64_t)T * qw->d_in * (int64_t)sizeof(qblora_bf16) >= (int64_t)1 << 32 ? kMidMaxTokens / 2 : kMidMaxTokens;
@@ -1073,16 +1074,16 @@ int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblor
     } else if ((rc = resolve_scales(qw, static_cast<float*>(workspace), st, &scales))) {
         return rc;
     }
-    if (!mid)
-        return launch_w4_decode(codes, scales, beta, codebook_of(qw), pack ? 1 : 0, qw->d_out, qw->d_in, X, T, Y, st,
-                                block_rows_of(qw), regrouped);
+    const int block_cols = block_rows_of(qw) == 8 ? block_cols_of(qw) : 8;
+    if (rows)
+        return launch_w4_rows(codes, scales, beta, codebook_of(qw), pack ? 1 : 0, qw->d_out, qw->d_in, X, T, Y, st,
+                              block_rows_of(qw), regrouped, block_cols);
     float* part = reinterpret_cast<float*>(static_cast<unsigned char*>(workspace) + scale_bytes);
     for (int32_t t0 = 0; t0 < T; t0 += chunk) {
         const int32_t n = std::min(chunk, T - t0);
         if ((rc = launch_w4_mid(codes, scales, beta, codebook_of(qw), pack ? 1 : 0, qw->d_out, qw->d_in,
                                 X + (int64_t)t0 * qw->d_in, n, Y + (int64_t)t0 * qw->d_out,
-                                w4_mid_part_bytes(qw->d_out, qw->d_in, n) ? part : nullptr, st, block_rows_of(qw), regrouped,
-                                block_rows_of(qw) == 8 ? block_cols_of(qw) : 8)))
+                                w4_mid_part_bytes(qw->d_out, qw->d_in, n) ? part : nullptr, st, block_rows_of(qw), regrouped, block_cols)))
             return rc;
     }
     return QBLORA_OK;

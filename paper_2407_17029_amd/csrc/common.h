@@ -219,9 +219,13 @@ int launch_merge_requant_batch(const MergeDesc* ds, int count, hipStream_t st);
 int launch_merge_bf16(const MergeDesc& d, hipStream_t st);
 // H = A * B (fp32) for whole 64 x 128 tiles and R % 16 == 0; QBLORA_ERR_UNSUPPORTED otherwise (nothing launched)
 int launch_tile_product(const qblora_bf16* A, const qblora_bf16* B, int rows, int cols, int R, float* H, hipStream_t st);
-int launch_w4_decode(const uint8_t* codes, const float* scales, const float* beta, const Codebook& cb, int tiled,
-                     int d_out, int d_in, const qblora_bf16* X, int T, qblora_bf16* Y, hipStream_t st, int block_rows = 1, int regrouped = 0);
-// The same layer for 1 <= T <= 256 tokens, in one launch, on the bf16 compute weight (w4mid.hip); `part` holds
+// A quantized layer without adapter for 1 <= T <= 64 tokens (w4rows.hip): codes, scales and offsets row-major or in the
+// pack's order (tiled, with regrouped nibbles for INT4 models in 64-blocks)
+bool w4_rows_applies(int d_out, int d_in, int T);
+int launch_w4_rows(const uint8_t* codes, const float* scales, const float* beta, const Codebook& cb, int tiled, int d_out,
+                   int d_in, const qblora_bf16* X, int T, qblora_bf16* Y, hipStream_t st, int block_rows = 1,
+                   int regrouped = 0, int block_cols = 8);
+// The same layer for 33 <= T <= 256 tokens, in one launch, on the bf16 compute weight (w4mid.hip); `part` holds
 // w4_mid_part_bytes() bytes of split-K partial tiles (may be NULL when that is 0)
 int w4_mid_splits(int d_out, int d_in, int T);
 size_t w4_mid_part_bytes(int d_out, int d_in, int T);

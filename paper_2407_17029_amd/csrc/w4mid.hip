@@ -8,7 +8,7 @@
 // of codes + the block parameters per weight) sets the time and at 128 tokens the MFMAs do.  A token tile of
 // 256 (the training kernel) would waste most of its MFMAs here and, with one workgroup per 256 output rows,
 // leave most of the chip idle.  Here a workgroup of 4 waves owns 128 output rows (32 per wave), ALL tokens
-// (32 * TB of them, TB = 1, 2, 4, 6, 8) and one slice of the input dimension; the slices of a row tile (split-K, as
+// (32 * TB of them, TB = 2, 4, 6, 8) and one slice of the input dimension; the slices of a row tile (split-K, as
 // many as it takes to put two workgroups on every CU) write fp32 partial tiles that a second kernel adds in
 // slice order (deterministic).
 //
@@ -405,7 +405,7 @@ int launch_tb(const MidDesc& d, unsigned blocks, hipStream_t st, int block_rows,
 
 }  // namespace
 
-int w4_mid_token_blocks(int T) { return T <= 32 ? 1 : T <= 64 ? 2 : T <= 128 ? 4 : T <= 192 ? 6 : 8; }
+int w4_mid_token_blocks(int T) { return T <= 64 ? 2 : T <= 128 ? 4 : T <= 192 ? 6 : 8; }
 
 // Slices of the input dimension.  Up to 128 tokens:  Measured over 2 / 3 / 4 waves per workgroup and 1 .. 8 slices on
 // 4096 x 4096, 11008 x 4096 and 22016 x 8192: what counts is the number of workgroups -- about 700 up to 64 tokens
@@ -444,7 +444,6 @@ int launch_w4_mid(const uint8_t* codes, const float* scales, const float* beta, 
     const unsigned blocks = (unsigned)(((d_out + kMidRows - 1) / kMidRows) * splits);
     int rc;
     switch (w4_mid_token_blocks(T)) {
-        case 1: rc = launch_tb<1>(d, blocks, st, block_rows, regrouped, block_cols); break;
         case 2: rc = launch_tb<2>(d, blocks, st, block_rows, regrouped, block_cols); break;
         case 4: rc = launch_tb<4>(d, blocks, st, block_rows, regrouped, block_cols); break;
         case 6: rc = launch_tb<6>(d, blocks, st, block_rows, regrouped, block_cols); break;
