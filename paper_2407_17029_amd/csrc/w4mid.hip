@@ -8,8 +8,8 @@
 // of codes + the block parameters per weight) sets the time and at 128 tokens the MFMAs do.  A token tile of
 // 256 (the training kernel) would waste most of its MFMAs here and, with one workgroup per 256 output rows,
 // leave most of the chip idle.  Here a workgroup of 4 waves owns 128 output rows (32 per wave), ALL tokens
-// (32 * TB of them, TB = 2, 4, 6, 8) and one slice of the input dimension; the slices of a row tile (split-K, as
-// many as it takes to put two workgroups on every CU) write fp32 partial tiles that a second kernel adds in
+// (32 * TB of them, TB = 2 .. 8) and one slice of the input dimension; the slices of a row tile (split-K, as
+// many as one round of workgroups holds, see call_splits) write fp32 partial tiles that a second kernel adds in
 // slice order (deterministic).
 //
 // A wave dequantizes its own MFMA operand in registers: lane l owns row (l & 31) and the 32 inputs
@@ -20,16 +20,18 @@
 // (row ^ row>>3) & 7): it is shared by the four waves, arrives by direct global -> LDS copies into a ring of
 // four stages, and is read as the B operand (lane l: token l & 31, the same 8 inputs).  All vector-memory
 // operations of the loop are issued from assembly statements three steps ahead (codes: four) and counted by
-// hand (the compiler would tie every LDS access to them): a step waits until only the two youngest batches are
-// outstanding.  The operands of step s+1 are built between the MFMAs of step s.
+// hand (the compiler would tie every LDS access to them): a step waits until only the two youngest batches (the codes
+// and the token tile of a step each) are outstanding.  The operands of step s+1 are built between the MFMAs of step s.
 //
-// Above 128 tokens one launch reads and dequantizes every weight once for all of them (two chunks of 128 did it twice;
-// token fragments are read two MFMAs ahead: with one wave per SIMD one was not enough, 62 -> 47 us).  us of the
-// contraction and the sum of the slices, before (two chunks) / now: 201 tokens 5120 x 13824 63 + 10 / 47 + 5, 256 tokens
-// 11008 x 4096 46 + 15 / 41 + 6, 256 tokens 22016 x 8192 133 + 13 / 136, 130 tokens 4096 x 4096 23 + 9 / 18 + 4.
+// Above 128 tokens one launch reads and dequantizes every weight once for all of them; two chunks of 128 did it twice (201
+// tokens of 5120 x 13824 63 + 10 us for the contraction and the sum of the slices, one launch 47 + 5).  What bounds it: the
+// partial tiles (256 workgroups of 128 rows x 256 tokens write and read 34 MB, about 14 us of 4096 x 4096's 25), then the
+// matrix pipe at half to two thirds of its rate.
 //
 // A lane ends up with 4 consecutive output rows of one token per accumulator quad and stores them as one
 // 8-byte word (bf16) or one 16-byte word (fp32 partials).
+#include <algorithm>
+
 #include "common.h"
 
 namespace qblora {
@@ -95,12 +97,14 @@ __device__ __forceinline__ void wait_slot(Slot<BR>& s) {
     }
 }
 
-// TB: 32-token blocks; BETA: offsets present; BR: 1 (64 inputs of one row), 8 (8 rows x 8 inputs) or 84 (8 rows x 4 inputs);
-// REGROUPED: INT4 model whose code dwords were regrouped by the decode pack (codebook 0..15, offsets present)
-// AHEAD: MFMAs between the read of a token fragment and its use (1 or 2)
-template <int TB, bool BETA, int BR, bool REGROUPED, int AHEAD>
+// How a code becomes a number: any codebook through a table of byte pairs in LDS, the codebook 0, 1, ..., 15 by byte
+// conversions, and the same with the nibbles of every code dword regrouped by the decode pack (64-blocks).
+enum { TABLE, INT4, REGROUPED };
+
+// TB: 32-token blocks; BETA: offsets present; BR: 1 (64 inputs of one row), 8 (8 rows x 8 inputs) or 84 (8 rows x 4 inputs)
+template <int TB, bool BETA, int BR, int CODES>
 __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
-    static_assert(!REGROUPED || (BETA && BR == 1), "regrouped codes belong to INT4 models in 64-blocks");
+    static_assert(CODES != REGROUPED || (BETA && BR == 1), "regrouped codes belong to INT4 models in 64-blocks");
     constexpr int kStageBytes = TB * 32 * 128;
     static_assert(BR == 1 || BR == 8 || BR == 84, "block shape");
     constexpr int kParamLoads = BR == 84 ? 2 : 1;              // 16-byte (or 4-byte) loads of scales per step; as many of offsets
@@ -120,7 +124,7 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     const int s_begin = z * d.steps_per_split;
     const int s_end = min(steps_total, s_begin + d.steps_per_split);
 
-    if constexpr (!REGROUPED) {
+    if constexpr (CODES == TABLE) {
         const float2 e = make_float2(d.cb.c[t & 15], d.cb.c[t >> 4]);
 #pragma unroll
         for (int q = 0; q < kTableReplicas; ++q) sT[t * kTableReplicas + q] = e;
@@ -159,9 +163,10 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     const unsigned char* const bbase = reinterpret_cast<const unsigned char*>(d.beta);
     const unsigned char* const xbase = reinterpret_cast<const unsigned char*>(d.X);
 
-    // One batch of operations per step, the same count (kOps) whatever the step: the codes and block parameters of
-    // step `sc` into register slot `sl`, and the token tile of step `sx` into ring stage `stage`.  Steps past the
-    // slice are redirected to its last step (fetched, never used).
+    // One batch of operations per step, the same count (kOps) whatever the step: the codes and block parameters of step
+    // `sc` into register slot `sl` in front of the step's MFMAs, and the copies of the token tile of step `sx` into ring
+    // stage `stage`, one behind every fourth of them.  Steps past the slice are redirected to its last step (fetched,
+    // never used).
     auto issue_codes = [&](Slot<BR>& sl, int step) __attribute__((always_inline)) {
         const int64_t sc = min(step, s_end - 1);
         load16(sl.cw, c_off, cbase + sc * c_step);
@@ -177,10 +182,9 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
             if constexpr (BETA) load4(sl.be, s_off, bbase + sc * s_step);
         }
     };
-    auto issue_x = [&](int step, int stage) __attribute__((always_inline)) {
+    auto issue_x = [&](int step, int stage, int i) __attribute__((always_inline)) {
         const int64_t sx = min(step, s_end - 1);
-#pragma unroll
-        for (int i = 0; i < TB; ++i) copy16_to_lds(xbase + sx * 128, x_off[i], lds_x + stage * kStageBytes + i * 1024);
+        copy16_to_lds(xbase + sx * 128, x_off[i], lds_x + stage * kStageBytes + i * 1024);
     };
 
     // fragment addresses of the token tile: token 32*tb + r, logical chunk 4h + j
@@ -202,8 +206,9 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     };
     // Dequantization in 16 units per step: unit k = 4j + i makes dword i (two weights, inputs 2i and 2i+1 of the
     // 8) of the j-th A operand (code dword j).  Table form: unit_a fetches the byte's (c[lo], c[hi]) pair from LDS,
-    // unit_b scales, offsets and rounds; an INT4 model's regrouped dword holds input 0, 2, 4, 6, 1, 3, 5, 7 in its
-    // nibbles, so the bytes of (w & 0x0F0F0F0F) are inputs 0, 4, 1, 5 and those of ((w >> 4) & 0x0F0F0F0F) 2, 6, 3, 7.
+    // unit_b scales, offsets and rounds.  The bytes of an INT4 model's (w & 0x0F0F0F0F) are inputs 0, 2, 4, 6 and those of
+    // ((w >> 4) & 0x0F0F0F0F) 1, 3, 5, 7; a regrouped dword holds input 0, 2, 4, 6, 1, 3, 5, 7 in its nibbles, so there
+    // they are inputs 0, 4, 1, 5 and 2, 6, 3, 7.
     struct Params { uint32_t cw[4]; float a[8], b[8]; };       // scale / offset of inputs 0..3 and 4..7 of each code dword
     auto params = [&](const Slot<BR>& sl) __attribute__((always_inline)) {
         Params p;
@@ -222,15 +227,18 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
         return p;
     };
     auto unit_a = [&](const Params& p, int k, float2& tv) __attribute__((always_inline)) {
-        if constexpr (!REGROUPED) tv = my_table[((p.cw[k >> 2] >> (8 * (k & 3))) & 0xffu) * kTableReplicas];
+        if constexpr (CODES == TABLE) tv = my_table[((p.cw[k >> 2] >> (8 * (k & 3))) & 0xffu) * kTableReplicas];
     };
     auto unit_b = [&](const Params& p, int k, const float2& tv) __attribute__((always_inline)) {
         const int j = k >> 2, i = k & 3;
         float lo, hi;
-        if constexpr (REGROUPED) {
+        if constexpr (CODES == REGROUPED) {
             const uint32_t t = (p.cw[j] >> (4 * (i & 1))) & 0x0F0F0F0Fu;       // i odd: inputs 2, 6, 3, 7
             lo = (float)((t >> (8 * (i >> 1))) & 0xffu);                          // i < 2: bytes 0 and 2, else 1 and 3
             hi = (float)((t >> (16 + 8 * (i >> 1))) & 0xffu);
+        } else if constexpr (CODES == INT4) {
+            lo = (float)((p.cw[j] >> (8 * i)) & 15u);
+            hi = (float)((p.cw[j] >> (8 * i + 4)) & 15u);
         } else {
             lo = tv.x; hi = tv.y;
         }
@@ -248,9 +256,12 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     };
     // One step: the 4 * TB MFMAs on this step's operands `wf`, and between them the units that build the next
     // step's operands `wn` from slot `sl` -- written in issue order and fenced after every MFMA: a wave issues in
-    // order, so vector work has to sit between the MFMAs to run in their shadow.  LDS reads are issued AHEAD MFMAs
-    // (token fragment) or one unit (table pair) ahead of their use.
-    auto step = [&](const bf16x8 (&wf)[4], int stage, const Slot<BR>& sl, bf16x8 (&wn)[4]) __attribute__((always_inline)) {
+    // order, so vector work has to sit between the MFMAs to run in their shadow.  LDS reads are issued two MFMAs (token
+    // fragment; four or eight ahead measured the same) or one unit (table pair) ahead of their use.  The copies of a later
+    // tile are spread over the step: a copy holds the address path for 16 cycles or more, and the waves' bursts of TB of
+    // them in front of the MFMAs left the matrix pipe idle (22016 x 8192 at 256 tokens 120 -> 107 us, 11008 x 4096 42.6 ->
+    // 38.6).
+    auto step = [&](const bf16x8 (&wf)[4], int now, int stage, const Slot<BR>& sl, bf16x8 (&wn)[4]) __attribute__((always_inline)) {
         constexpr int M = 4 * TB;
         const unsigned char* xs = sX + stage * kStageBytes;
         const Params p = params(sl);
@@ -262,13 +273,13 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
         };
         unit_a(p, 0, tv[0]);
 #pragma unroll
-        for (int m = 0; m < AHEAD; ++m) xf[m] = read_x(m);
+        for (int m = 0; m < 2; ++m) xf[m] = read_x(m);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int m = 0; m < M; ++m) {
-            if (AHEAD == 1 && m + 1 < M) xf[(m + 1) & 1] = read_x(m + 1);
             acc[m % TB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[m / TB], xf[m & 1], acc[m % TB], 0, 0, 0);
-            if (AHEAD == 2 && m + 2 < M) xf[m & 1] = read_x(m + 2);
+            if (m + 2 < M) xf[m & 1] = read_x(m + 2);
+            if (m % 4 == 1) issue_x(now + kStages - 1, (stage + kStages - 1) % kStages, m / 4);
 #pragma unroll
             for (int k = m * 16 / M; k < (m + 1) * 16 / M; ++k) {
                 if (k + 1 < 16) unit_a(p, k + 1, tv[(k + 1) & 1]);
@@ -295,7 +306,11 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     // the token tiles: batch b carries the codes of step b+4 and the tile of step b+3.
     issue_codes(slot[0], s_begin);
 #pragma unroll
-    for (int u = 0; u < kStages - 1; ++u) { issue_codes(slot[u + 1], s_begin + u + 1); issue_x(s_begin + u, u); }
+    for (int u = 0; u < kStages - 1; ++u) {
+        issue_codes(slot[u + 1], s_begin + u + 1);
+#pragma unroll
+        for (int i = 0; i < TB; ++i) issue_x(s_begin + u, u, i);
+    }
     wait_slot<(kStages - 1) * kOps, BR, BETA>(slot[0]);
     dequantize(slot[0], wf[0]);
     for (int s = s_begin; s < s_end; s += kStages) {
@@ -304,13 +319,13 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
             // the batch issued three steps ago is in when at most the two after it are outstanding
             wait_slot<(kStages - 2) * kOps, BR, BETA>(slot[(u + 1) % kStages]);
             __syncthreads();                                    // every wave's part of the tile is in; all waves are past
-                                                                // the step before, whose stage is refilled now
+                                                                // the step before, whose stage this step refills
             issue_codes(slot[u], s + u + kStages);              // slot u was turned into operands a step ago
-            issue_x(s + u + kStages - 1, (u + kStages - 1) % kStages);
-            if (s + u < s_end) step(wf[u & 1], u, slot[(u + 1) % kStages], wf[(u + 1) & 1]);
+            if (s + u < s_end) step(wf[u & 1], s + u, u, slot[(u + 1) % kStages], wf[(u + 1) & 1]);
         }
     }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // the redirected look-ahead operations
+#pragma unroll
+    for (int u = 0; u < kStages; ++u) wait_slot<0, BR, BETA>(slot[u]);     // the redirected look-ahead operations
 
     // ---- store: lane = token 32*tb + r; registers 4q .. 4q+3 = rows 8q + 4h .. +3 of the wave's 32 ----------
     const bool whole = (d_out & 3) == 0;
@@ -369,8 +384,8 @@ __global__ __launch_bounds__(256) void k_w4_mid_reduce(const float* __restrict__
 }
 
 template <int TB>
-constexpr size_t mid_lds(bool regrouped) {
-    return (size_t)kStages * TB * 32 * 128 + (regrouped ? 0 : 256 * kTableReplicas * sizeof(float2));
+constexpr size_t mid_lds(int codes) {
+    return (size_t)kStages * TB * 32 * 128 + (codes == TABLE ? 256 * kTableReplicas * sizeof(float2) : 0);
 }
 
 template <typename K>
@@ -379,50 +394,66 @@ bool set_lds(K kernel, size_t smem) {
                                (int)smem) == hipSuccess;
 }
 
-template <int TB, bool BETA, int BR, bool REGROUPED, int AHEAD = 2>
+template <int TB, bool BETA, int BR, int CODES>
 int launch_one(const MidDesc& d, unsigned blocks, hipStream_t st) {
-    constexpr size_t smem = mid_lds<TB>(REGROUPED);
-    static const bool ok = set_lds(k_w4_mid<TB, BETA, BR, REGROUPED, AHEAD>, smem);
+    constexpr size_t smem = mid_lds<TB>(CODES);
+    static const bool ok = set_lds(k_w4_mid<TB, BETA, BR, CODES>, smem);
     if (!ok) return QBLORA_ERR_LAUNCH;
-    hipLaunchKernelGGL((k_w4_mid<TB, BETA, BR, REGROUPED, AHEAD>), dim3(blocks), dim3(kMidThreads), smem, st, d);
+    hipLaunchKernelGGL((k_w4_mid<TB, BETA, BR, CODES>), dim3(blocks), dim3(kMidThreads), smem, st, d);
     return launch_status();
 }
 
+template <int TB, int BR>
+int launch_br(const MidDesc& d, unsigned blocks, hipStream_t st, int form) {
+    if constexpr (BR == 1)
+        if (form == REGROUPED) return launch_one<TB, true, BR, REGROUPED>(d, blocks, st);
+    if (form == INT4) return launch_one<TB, true, BR, INT4>(d, blocks, st);
+    return d.beta ? launch_one<TB, true, BR, TABLE>(d, blocks, st) : launch_one<TB, false, BR, TABLE>(d, blocks, st);
+}
+
 template <int TB>
-int launch_tb(const MidDesc& d, unsigned blocks, hipStream_t st, int block_rows, int regrouped, int block_cols) {
-    if (block_rows == 8 && block_cols == 4)
-        return d.beta ? launch_one<TB, true, 84, false>(d, blocks, st) : launch_one<TB, false, 84, false>(d, blocks, st);
-    if (block_rows == 8)
-        return d.beta ? launch_one<TB, true, 8, false>(d, blocks, st) : launch_one<TB, false, 8, false>(d, blocks, st);
-    if (regrouped && !d.beta) return QBLORA_ERR_UNSUPPORTED;
-    // Without the table two workgroups of 128 tokens fit a CU's LDS.  Once there are two for a CU, each hides the other's
-    // LDS latency and a fragment is best read one MFMA ahead (T = 96: 22016 x 8192 63.6 -> 59.5 us, 5120 x 13824
-    // 33.4 -> 31.8); with one it takes two (4096 x 4096 17.0 -> 16.3, 4096 x 11008 23.4 -> 21.5).
-    if (TB == 4 && regrouped && blocks > 256) return launch_one<TB, true, 1, true, TB == 4 ? 1 : 2>(d, blocks, st);
-    if (regrouped) return launch_one<TB, true, 1, true>(d, blocks, st);
-    return d.beta ? launch_one<TB, true, 1, false>(d, blocks, st) : launch_one<TB, false, 1, false>(d, blocks, st);
+int launch_tb(const MidDesc& d, unsigned blocks, hipStream_t st, int form, int block_rows, int block_cols) {
+    if (block_rows == 8 && block_cols == 4) return launch_br<TB, 84>(d, blocks, st, form);
+    if (block_rows == 8) return launch_br<TB, 8>(d, blocks, st, form);
+    return launch_br<TB, 1>(d, blocks, st, form);
 }
 
 }  // namespace
 
-int w4_mid_token_blocks(int T) { return T <= 64 ? 2 : T <= 128 ? 4 : T <= 192 ? 6 : 8; }
+namespace {
 
-// Slices of the input dimension.  Up to 128 tokens:  Measured over 2 / 3 / 4 waves per workgroup and 1 .. 8 slices on
-// 4096 x 4096, 11008 x 4096 and 22016 x 8192: what counts is the number of workgroups -- about 700 up to 64 tokens
+// 32-token blocks of a workgroup: as many as there are (with two, four, six or eight of them alone 201 tokens of 5120 x
+// 13824 took 48.0 us instead of 45.1, 129 of 22016 x 8192 88.7 instead of 74.5)
+int token_blocks(int T) { return T <= 64 ? 2 : (T + 31) / 32; }
+
+// no empty slice, at least 4 steps each
+int slices_of(int want, int steps) {
+    want = std::max(std::min({want, steps / 4, 8}), 1);
+    const int per = (steps + want - 1) / want;
+    return (steps + per - 1) / per;
+}
+
+// The slices of a call.  A codebook in LDS wants two workgroups on a CU up to 128 tokens, which w4_mid_splits counts on;
+// without one a lone workgroup hides its expansion, and the partial tiles of more slices than one round of workgroups
+// holds only cost time.  us at 65 / 128 tokens with the slices for two workgroups and for one: 5120 x 13824 31.1 / 38.1
+// and 27.5 / 31.8, 8192 x 8192 28.8 / 36.2 and 23.6 / 30.1, 22016 x 8192 59.0 / 70.2 and 58.5 / 64.5; with the table
+// 22016 x 8192 57.6 / 69.1 and 68.1 / 71.4.
+int call_splits(int d_out, int d_in, int T, int form) {
+    const int tiles_n = (d_out + kMidRows - 1) / kMidRows;
+    return T > 64 && form != TABLE ? slices_of(256 / tiles_n, d_in / kBlock) : w4_mid_splits(d_out, d_in, T);
+}
+
+}  // namespace
+
+// The most slices of the input dimension.  Up to 128 tokens, measured over 2 / 3 / 4 waves per workgroup and 1 .. 8 slices
+// on 4096 x 4096, 11008 x 4096 and 22016 x 8192: what counts is the number of workgroups -- about 700 up to 64 tokens
 // (the weight stream wants loads in flight), about 400 at 128 (two resident per CU; more slices only add partial
 // tiles) -- while 64- or 96-row workgroups differ from 128-row ones by a few percent at most; one slice per row tile,
 // which the balance of matrix work alone would choose at 128 tokens, is 20 % slower than two.  Above 128 tokens a
-// workgroup's ring of token tiles takes a CU's LDS: as many slices as one round of 256 workgroups holds.  At least 4
-// steps per slice, at most 8 slices, no empty slice.
+// workgroup's ring of token tiles takes a CU's LDS: as many slices as one round of 256 workgroups holds.
 int w4_mid_splits(int d_out, int d_in, int T) {
-    const int tiles_n = (d_out + kMidRows - 1) / kMidRows, steps = d_in / kBlock;
-    const int target = w4_mid_token_blocks(T) == 4 ? 400 : 700;
-    int want = T > 128 ? 256 / tiles_n : (target + tiles_n / 2) / tiles_n;
-    if (want > steps / 4) want = steps / 4;
-    if (want > 8) want = 8;
-    if (want < 1) want = 1;
-    const int per = (steps + want - 1) / want;
-    return (steps + per - 1) / per;
+    const int tiles_n = (d_out + kMidRows - 1) / kMidRows, target = T > 64 ? 400 : 700;
+    return slices_of(T > 128 ? 256 / tiles_n : (target + tiles_n / 2) / tiles_n, d_in / kBlock);
 }
 
 size_t w4_mid_part_bytes(int d_out, int d_in, int T) {
@@ -438,16 +469,23 @@ int launch_w4_mid(const uint8_t* codes, const float* scales, const float* beta, 
     if ((int64_t)((d_out + 255) / 256) * 256 * (d_in / 2) >= ((int64_t)1 << 32) || (int64_t)T * d_in * 2 >= ((int64_t)1 << 32))
         return QBLORA_ERR_SHAPE;
     if (block_rows == 8 && (d_out % 8 != 0)) return QBLORA_ERR_SHAPE;
-    const int splits = w4_mid_splits(d_out, d_in, T), steps = d_in / kBlock;
+    if (regrouped && (!beta || block_rows == 8)) return QBLORA_ERR_UNSUPPORTED;
+    bool whole_numbers = beta != nullptr;
+    for (int j = 0; j < 16; ++j) whole_numbers &= cb.c[j] == (float)j;
+    const int form = regrouped ? REGROUPED : whole_numbers ? INT4 : TABLE;
+    const int splits = call_splits(d_out, d_in, T, form), steps = d_in / kBlock;
     if (splits > 1 && !part) return QBLORA_ERR_WORKSPACE;
     MidDesc d{codes, scales, beta, cb, tiled, d_out, d_in, X, T, Y, part, splits, (steps + splits - 1) / splits};
     const unsigned blocks = (unsigned)(((d_out + kMidRows - 1) / kMidRows) * splits);
     int rc;
-    switch (w4_mid_token_blocks(T)) {
-        case 2: rc = launch_tb<2>(d, blocks, st, block_rows, regrouped, block_cols); break;
-        case 4: rc = launch_tb<4>(d, blocks, st, block_rows, regrouped, block_cols); break;
-        case 6: rc = launch_tb<6>(d, blocks, st, block_rows, regrouped, block_cols); break;
-        default: rc = launch_tb<8>(d, blocks, st, block_rows, regrouped, block_cols); break;
+    switch (token_blocks(T)) {
+        case 2: rc = launch_tb<2>(d, blocks, st, form, block_rows, block_cols); break;
+        case 3: rc = launch_tb<3>(d, blocks, st, form, block_rows, block_cols); break;
+        case 4: rc = launch_tb<4>(d, blocks, st, form, block_rows, block_cols); break;
+        case 5: rc = launch_tb<5>(d, blocks, st, form, block_rows, block_cols); break;
+        case 6: rc = launch_tb<6>(d, blocks, st, form, block_rows, block_cols); break;
+        case 7: rc = launch_tb<7>(d, blocks, st, form, block_rows, block_cols); break;
+        default: rc = launch_tb<8>(d, blocks, st, form, block_rows, block_cols); break;
     }
     if (rc || splits == 1) return rc;
     const int64_t count = (int64_t)T * d_out;

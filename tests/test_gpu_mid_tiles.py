@@ -1,0 +1,26 @@
+"""Inference on 65 to 256 tokens: every token tile at both of its ends, one to eight slices whose steps leave a remainder in
+the ring, ragged row tiles, and the three ways a code becomes a number (table, INT4, INT4 with regrouped nibbles)."""
+import pytest
+import torch
+
+from test_gpu_w4_rows import FORMATS, _case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("fmt", list(FORMATS))
+@pytest.mark.parametrize("T,d_out,d_in", [
+    (65, 40, 64), (96, 136, 640), (97, 256, 1088), (128, 24, 2048), (129, 264, 448), (160, 8, 320), (161, 136, 192),
+    (192, 128, 704), (193, 72, 2112), (224, 136, 256), (225, 40, 576), (256, 120, 832),
+])
+def test_token_tiles(oracle, codebook, T, d_out, d_in, fmt):
+    from gpu_util import assert_close_bf16
+    print(f"case mid tiles T={T} {d_out}x{d_in} {fmt}", flush=True)
+    qb, qw, X, ref = _case(oracle, codebook, 8200 + T + d_out, T, d_out, d_in, fmt)
+    Y = torch.full((T + 1, d_out), 7.0, dtype=torch.bfloat16, device=X.device)
+    qb.qblora_linear_decode(qw, X, Y=Y[:T])
+    Yp = qb.qblora_linear_decode(qw, X, pack=qb.qblora_decode_pack(qw))
+    torch.cuda.synchronize()
+    assert_close_bf16(Y[:T], ref, "Y")
+    assert torch.equal(Y[:T], Yp)                        # the same weight, contracted in the same order
+    assert torch.all(Y[T:] == 7.0)                       # nothing is written past the last token
