@@ -409,8 +409,9 @@ int qblora_decode_pack(const qblora_qweight* qw, void* pack, void* stream);
  *   QBLORA_PROFILE_GRAD_REDUCE    the fixed-order reduction of those partial sums into dA and dB
  *   QBLORA_PROFILE_PREP           the per-call re-layout launch of the forward (adapter operands, block scales)
  *   QBLORA_PROFILE_TILE_PRODUCT   the kernel of qblora_tile_product
- *   QBLORA_PROFILE_DEQUANT        the one-off dequantize pass of a forward / backward call (not recorded by calls
- *                                 that contract from the codes)
+ *   QBLORA_PROFILE_DEQUANT        the launch with the one-off dequantize pass of a forward / backward call, which the
+ *                                 re-layouts (PREP) or the reduction (GRAD_REDUCE) share (not recorded by calls that
+ *                                 contract from the codes)
  * Passing NULL for both events unregisters the slot.  The registration is per host thread: it applies to
  * calls made by the thread that registered it, so concurrent callers do not see each other's events.  Has
  * no effect on results.

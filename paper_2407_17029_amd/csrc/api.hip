@@ -440,16 +440,11 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         sct.out = nullptr; g.scales_tiled = nullptr;
         if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
     }
+    DequantDesc weight;
     if (dense) {
-        // the weight once, as the bf16 compute weight of Eq. 1, for all token tiles of this call
+        // the weight once, as the bf16 compute weight of Eq. 1, for all token tiles of this call (with the re-layouts)
         sct.out = nullptr;
-        const float* plain = nullptr;
-        if ((rc = resolve_scales(qw, ws.scales, st, &plain))) return rc;
-        {
-            ScopedEvents ev(QBLORA_PROFILE_DEQUANT, st);
-            rc = launch_dequantize_operand(*qw, plain, 0, ws.W16, st);
-        }
-        if (rc) return rc;
+        if ((rc = describe_dequantize(*qw, ws.W16, &weight))) return rc;
         g.W1 = ws.W16; g.K1 = qw->d_in;
     }
     const int op = scale_op_of(ad);
@@ -461,7 +456,7 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         rc = launch_adapter_prep(prep_adapter ? ad->A : nullptr, prep_adapter ? ad->B : nullptr,
                                  dup_a ? qw->d_in / 2 : qw->d_in, qw->d_out,
                                  adapted ? ad->R : 0, adapted ? (dup_a ? 1 : ad->lambda1) : 1, adapted ? ad->lambda2 : 1,
-                                 ws.At_x, ws.Bt, nullptr, st, sct.out ? &sct : nullptr);
+                                 ws.At_x, ws.Bt, nullptr, st, sct.out ? &sct : nullptr, dense ? &weight : nullptr);
     }
     if (rc) return rc;
     if (adapted && op != QBLORA_OP_AVGPOOL_REPEAT) {
@@ -527,16 +522,13 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
 
     GemmDesc g{};
     g.qmode = dense ? 3 : 4;
-    if (dX && (rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
-    if (dX && dense) {
-        // the transposed bf16 compute weight once, for all token tiles of this call
-        {
-            ScopedEvents ev(QBLORA_PROFILE_DEQUANT, st);
-            rc = launch_dequantize_operand(*qw, g.scales, 1, ws.W16t, st);
-        }
-        if (rc) return rc;
+    DequantDesc weight;
+    if (dense) {
+        // the transposed bf16 compute weight once, for all token tiles of this call (with the gradients' reduction)
+        if ((rc = describe_dequantize(*qw, ws.W16t, &weight))) return rc;
         g.W1 = ws.W16t; g.K1 = qw->d_out;
     } else if (dX) {
+        if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
         describe_codes(qw, g);
     }
     if (adapted) {
@@ -606,7 +598,7 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
                     ga.L = ws.Xs; ga.ldl = na; gb.L = ws.dYs; gb.ldl = nb;
                 }
             }
-            if ((rc = launch_grad_pair(ga, gb, st))) return rc;
+            if ((rc = launch_grad_pair(ga, gb, st, dense ? &weight : nullptr))) return rc;
         }
         g.X2 = ws.dUs; g.ldx2 = R; g.K2 = R;
         if (op == QBLORA_OP_AVGPOOL_REPEAT) { g.W2 = ad->A; g.ldw2 = R; g.div2 = ad->lambda1; }
@@ -615,6 +607,7 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         g.K2 = 0; g.div2 = 1;
     }
     if (!dX) return QBLORA_OK;
+    if (dense && !want_grads && (rc = launch_dequantize_t(weight, st))) return rc;
     g.X1 = dY; g.ldx1 = qw->d_out;
     g.C = dX; g.ldc = qw->d_in; g.out_scale = 1.0f; g.M = T; g.N = qw->d_in;
     g.part = ws.part; g.splits = ws.splits_x;
@@ -786,12 +779,10 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     const bool few = !dense && few_applies(T, qw->d_out, qw->d_in);
     if (use_dense(qw, T) && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
     if (tile8 || dense || few) sct.out = nullptr;
-    if ((rc = launch_adapter_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, st, sct.out ? &sct : nullptr))) return rc;
-    if (dense) {
-        const float* plain = nullptr;
-        if ((rc = resolve_scales(qw, ws.scales, st, &plain))) return rc;
-        if ((rc = launch_dequantize_operand(*qw, plain, 0, ws.W16, st))) return rc;
-    }
+    DequantDesc weight;
+    if (dense && (rc = describe_dequantize(*qw, ws.W16, &weight))) return rc;
+    if ((rc = launch_adapter_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, st, sct.out ? &sct : nullptr, dense ? &weight : nullptr)))
+        return rc;
     // s * AvgPool_lambda1(X)
     if ((rc = launch_pool_rows(X, T, qw->d_in, lambda1, s / (float)lambda1, ws.P, nullptr, st))) return rc;
 
@@ -833,6 +824,8 @@ int qablora_linear_bwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     QaBwdSpace ws = carve_qa_bwd(qw, lambda1, lambda2, T, workspace, dX != nullptr, dense, false);
     if (!workspace || workspace_bytes < ws.bytes) return QBLORA_ERR_WORKSPACE;
     if (dX && !codes_placed(qw, T)) return QBLORA_ERR_UNSUPPORTED;
+    DequantDesc weight;
+    if (dense && (rc = describe_dequantize(*qw, ws.W16t, &weight))) return rc;
 
     // (s/lambda1) * sum_lambda2(dY): operand of the dX K-extension and, rescaled by lambda1 at the end, of dH
     // (there with its bf16 residual, so that only the pooled input carries a bf16 rounding)
@@ -844,16 +837,16 @@ int qablora_linear_bwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
         gh.L = ws.P; gh.ldl = I; gh.I = I; gh.S = ws.dVs; gh.S_lo = ws.dVs_lo; gh.lds = J; gh.J = J; gh.T = T;
         gh.part = ws.part; gh.splits = ws.splits; gh.out = dH; gh.pool = 1;
         gh.out_scale = (float)lambda1; gh.transpose_out = 0;
-        if ((rc = launch_grad(gh, st))) return rc;
+        if ((rc = launch_grad(gh, st, dense ? &weight : nullptr))) return rc;
     }
     if (!dX) return QBLORA_OK;
     GemmDesc g{};
     g.qmode = dense ? 3 : 4;
-    if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
     if (dense) {
-        if ((rc = launch_dequantize_operand(*qw, g.scales, 1, ws.W16t, st))) return rc;
+        if (!dH && (rc = launch_dequantize_t(weight, st))) return rc;
         g.W1 = ws.W16t; g.K1 = qw->d_out;
     } else {
+        if ((rc = resolve_scales(qw, ws.scales, st, &g.scales))) return rc;
         describe_codes(qw, g);
     }
     g.X2 = ws.dVs; g.ldx2 = J; g.W2 = H; g.ldw2 = J; g.K2 = J; g.div2 = lambda1;

@@ -97,11 +97,19 @@ int launch_scales_reconstruct(const uint8_t* scale_codes, const float* step, con
                               int group, float* scales, hipStream_t st);
 int launch_dequantize_bf16(const qblora_qweight& qw, const float* scales, qblora_bf16* Wt, hipStream_t st);
 // The bf16 compute weight in the order the contraction kernel's waves load it (qmode 3): for the operand
-// matrix Wop[N, K] -- the weight itself, N = d_out, K = d_in (transposed = 0), or its transpose, N = d_in,
-// K = d_out -- the 16 bytes Wop[16i + (l & 15)][32j + 8(l >> 4) .. + 7] sit at ((i*(K/32) + j)*64 + l)*16.
+// matrix Wop[N, K] -- the weight itself, N = d_out, K = d_in, or its transpose, N = d_in, K = d_out -- the 16 bytes
+// Wop[16i + (l & 15)][32j + 8(l >> 4) .. + 7] sit at ((i*(K/32) + j)*64 + l)*16.
 // d_out*d_in*2 bytes, 16-byte aligned; d_in % 64 == 0, d_out % 64 == 0.
-int launch_dequantize_operand(const qblora_qweight& qw, const float* scales, int transposed, qblora_bf16* Wop,
-                              hipStream_t st);
+enum { ROWS, EIGHT_BY_8, EIGHT_BY_4, ROWS_GROUPED };       // 64-blocks, blocks of 8 rows, 64-blocks with grouped scales
+struct DequantDesc {
+    const uint8_t* codes; const float* scales; const float* beta;
+    const uint8_t* scale_codes; const float* scale_step; const float* scale_mid; int scale_group;
+    Codebook cb; int d_out, d_in;
+    uint4* out;
+    int geom; unsigned blocks;                             // workgroups of the pass
+};
+int describe_dequantize(const qblora_qweight& qw, qblora_bf16* Wop, DequantDesc* d);
+int launch_dequantize_t(const DequantDesc& d, hipStream_t st);         // the transposed weight
 
 // Builds K-contiguous bf16 copies of the adapter matrices for the GEMM kernels:
 //   At_x [R, d_in]        At_x[j,k] = A[k/lam1, j]     (transpose, expand along k)
@@ -117,17 +125,17 @@ struct ScaleTiling {
 };
 int launch_adapter_prep(const qblora_bf16* A, const qblora_bf16* B, int d_in, int d_out, int R, int lam1,
                         int lam2, qblora_bf16* At_x, qblora_bf16* Bt, qblora_bf16* Bx, hipStream_t st,
-                        const ScaleTiling* sc = nullptr);
+                        const ScaleTiling* sc = nullptr, const DequantDesc* dequant = nullptr);   // the weight in the same launch
 
 // One GEMM launch description.  C[M,N] = out_scale1 * ( X1[M,K1] * Wq^T  +  X2[M,K2] * W2[N/div2, K2]^T )
 // "token" operands X1/X2 are bf16 row-major; the quantized segment is optional (qmode 0).
 struct GemmDesc {
     int qmode;                 // 0: no quantized segment; 1: forward (N = d_out, K1 = d_in);
                                // 2: the same for at most kFewTokens tokens;
-                               // 3: first segment on a bf16 weight dequantized beforehand, in operand order;
+                               // 3: first segment on a bf16 weight dequantized beforehand, in operand order (DequantDesc);
                                // 4: transposed use of 1 (N = d_in, K1 = d_out)
     const qblora_bf16* X1; int64_t ldx1;
-    const qblora_bf16* W1; int K1;                     // qmode 3 only: see launch_dequantize_operand
+    const qblora_bf16* W1; int K1;                     // qmode 3 only: see DequantDesc
     const uint8_t* codes; const float* scales; const float* beta; int d_out, d_in;
     const uint8_t* codes_tiled;            // optional tile-ordered copy
     const float* scales_tiled;             // optional tile-ordered scales
@@ -189,9 +197,10 @@ struct GradDesc {
 int grad_splits(int64_t T, int I, int J = 1);    // slices of the token range for an [I, J] gradient
 int launch_pool_rows(const qblora_bf16* in, int64_t T, int d, int lam, float scale, qblora_bf16* out,
                      qblora_bf16* out_lo, hipStream_t st);
-int launch_grad(const GradDesc& d, hipStream_t st);
+// `dequant` (may be NULL): the transposed weight, in the launch that reduces the partial sums
+int launch_grad(const GradDesc& d, hipStream_t st, const DequantDesc* dequant = nullptr);
 // two independent gradients whose partial buffers do not overlap: one launch for both where the shapes allow
-int launch_grad_pair(const GradDesc& a, const GradDesc& b, hipStream_t st);
+int launch_grad_pair(const GradDesc& a, const GradDesc& b, hipStream_t st, const DequantDesc* dequant = nullptr);
 // out[t, c] = in[t, lam*c] for c < d/lam (every lam-th feature of each row), bf16
 int launch_sample_rows(const qblora_bf16* in, int64_t T, int d, int lam, qblora_bf16* out, hipStream_t st);
 

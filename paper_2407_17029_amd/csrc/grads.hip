@@ -15,7 +15,7 @@
 // feature.  k_grad_tr (the fast path) copies token-major tiles straight into an LDS ring and lets
 // the transposing LDS read (ds_read_b64_tr_b16) deliver the operand layout; k_grad_partial (any
 // shape and alignment) transposes in registers on the way into LDS.
-#include "common.h"
+#include "dequant.h"
 
 namespace qblora {
 
@@ -436,19 +436,30 @@ __device__ __forceinline__ void grad_reduce_tile(const GradDesc& d, const unsign
             make_float4(tr[jj][iq], tr[jj][iq + 1], tr[jj][iq + 2], tr[jj][iq + 3]);
 }
 
-__global__ __launch_bounds__(256) void k_grad_reduce(GradDesc d) { grad_reduce_plain(d, blockIdx.x); }
-
-__global__ __launch_bounds__(256) void k_grad_reduce_tile(GradDesc d) {
+// Second stages of a call's gradients in one launch: the first n_a workgroups reduce `a` element-wise, the next n_b `b`
+// by tiles.  TILES: there is a `b`; without it a thread needs half the registers, and the gradient of the single-matrix
+// adapter, 36 MB at 2112 x 4320, is reduced 3 us faster.
+struct ReducePair { GradDesc a, b; int n_a, n_b; };
+template <bool TILES>
+__device__ __forceinline__ void reduce_block(const ReducePair& p, float (&tr)[32][33]) {
+    if (!TILES || (int)blockIdx.x < p.n_a) grad_reduce_plain(p.a, blockIdx.x);
+    else if constexpr (TILES) grad_reduce_tile(p.b, blockIdx.x - p.n_a, tr);
+}
+template <bool TILES>
+__global__ __launch_bounds__(256) void k_grad_reduce(ReducePair p) {
     __shared__ float tr[32][33];
-    grad_reduce_tile(d, blockIdx.x, tr);
+    reduce_block<TILES>(p, tr);
 }
 
-// Both second stages of a layer's gradients in one launch: blocks below n_a reduce `a` element-wise, the
-// others reduce `b` by tiles (transposed output).
-__global__ __launch_bounds__(256) void k_grad_reduce_pair(GradPair p) {
-    __shared__ float tr[32][33];
-    if ((int)blockIdx.x < p.n_a) grad_reduce_plain(p.a, blockIdx.x);
-    else grad_reduce_tile(p.b, blockIdx.x - p.n_a, tr);
+// ... and behind them the transposed weight that dX is contracted from: the reduction waits on loads of partial sums that
+// lie in the caches while the other streams codes from HBM.
+template <bool BETA, int GEOM, bool TILES>
+__global__ __launch_bounds__(256) void k_grad_reduce_dequantize(ReducePair p, DequantDesc q) {
+    __shared__ __align__(16) DequantLds lds;
+    static_assert(sizeof(float[32][33]) <= sizeof(DequantLds), "both jobs share the LDS");
+    const int n = p.n_a + p.n_b;
+    if ((int)blockIdx.x < n) reduce_block<TILES>(p, *reinterpret_cast<float (*)[32][33]>(&lds));
+    else dequantize_t_block<BETA, GEOM>(q, blockIdx.x - n, lds);
 }
 
 }  // namespace
@@ -534,28 +545,54 @@ unsigned reduce_blocks(const GradDesc& d) {
     return (unsigned)(((int64_t)Ip * d.J + 255) / 256);
 }
 
-int launch_reduce(const GradDesc& d, hipStream_t st) {
-    if (reduce_by_tiles(d)) hipLaunchKernelGGL(k_grad_reduce_tile, dim3(reduce_blocks(d)), dim3(256), 0, st, d);
-    else hipLaunchKernelGGL(k_grad_reduce, dim3(reduce_blocks(d)), dim3(256), 0, st, d);
+// up to two reductions, and the transposed weight
+int launch_reduce(const GradDesc* a, const GradDesc* b, const DequantDesc* dequant, hipStream_t st) {
+    ReducePair p{};
+    if (a && b && reduce_by_tiles(*a) == reduce_by_tiles(*b)) {          // two of one kind take a launch each
+        const int rc = launch_reduce(a, nullptr, nullptr, st);
+        if (rc) return rc;
+        a = b; b = nullptr;
+    }
+    for (const GradDesc* d : {a, b}) {
+        if (!d) continue;
+        if (reduce_by_tiles(*d)) { p.b = *d; p.n_b = (int)reduce_blocks(*d); }
+        else { p.a = *d; p.n_a = (int)reduce_blocks(*d); }
+    }
+    const int64_t n = (int64_t)p.n_a + p.n_b;
+    if (dequant) {
+        if (n + dequant->blocks > 0x7fffffff) return QBLORA_ERR_UNSUPPORTED;
+        ProfileScope ev(QBLORA_PROFILE_DEQUANT, st);
+        with_form(*dequant, [&](auto beta, auto geom) {
+            const dim3 grid((unsigned)(n + dequant->blocks));
+            if (p.n_b) hipLaunchKernelGGL((k_grad_reduce_dequantize<beta.value, geom.value, true>), grid, dim3(256), 0, st, p, *dequant);
+            else hipLaunchKernelGGL((k_grad_reduce_dequantize<beta.value, geom.value, false>), grid, dim3(256), 0, st, p, *dequant);
+        });
+    } else if (p.n_b) {
+        hipLaunchKernelGGL(k_grad_reduce<true>, dim3((unsigned)n), dim3(256), 0, st, p);
+    } else {
+        hipLaunchKernelGGL(k_grad_reduce<false>, dim3((unsigned)n), dim3(256), 0, st, p);
+    }
     return launch_status();
 }
 
 }  // namespace
 
-int launch_grad(const GradDesc& d, hipStream_t st) {
+int launch_dequantize_t(const DequantDesc& d, hipStream_t st) { return launch_reduce(nullptr, nullptr, &d, st); }
+
+int launch_grad(const GradDesc& d, hipStream_t st, const DequantDesc* dequant) {
     if (d.T <= 0) return QBLORA_ERR_SHAPE;      // the entry point handles the empty batch itself
     int rc = tr_applies(d) ? launch_tr(d, nullptr, st) : launch_partial(d, st);
     if (rc) return rc;
-    return launch_reduce(d, st);
+    return launch_reduce(&d, nullptr, dequant, st);
 }
 
 // Two independent gradients with partial buffers of their own: one launch of the copy path for both when
 // both qualify, else one after the other.
-int launch_grad_pair(const GradDesc& a, const GradDesc& b, hipStream_t st) {
+int launch_grad_pair(const GradDesc& a, const GradDesc& b, hipStream_t st, const DequantDesc* dequant) {
     if (a.T <= 0 || b.T <= 0) return QBLORA_ERR_SHAPE;
     if (a.part == b.part || !tr_applies(a) || !tr_applies(b) || (a.S_lo == nullptr) != (b.S_lo == nullptr)) {
         int rc = launch_grad(a, st);
-        return rc ? rc : launch_grad(b, st);
+        return rc ? rc : launch_grad(b, st, dequant);
     }
     int rc;
     {
@@ -564,14 +601,7 @@ int launch_grad_pair(const GradDesc& a, const GradDesc& b, hipStream_t st) {
     }
     if (rc) return rc;
     ProfileScope ev(QBLORA_PROFILE_GRAD_REDUCE, st);
-    if (!reduce_by_tiles(a) && reduce_by_tiles(b)) {         // the usual case (dA plain, dB transposed): one launch
-        GradPair p{};
-        p.a = a; p.b = b; p.n_a = (int)reduce_blocks(a);
-        hipLaunchKernelGGL(k_grad_reduce_pair, dim3(reduce_blocks(a) + reduce_blocks(b)), dim3(256), 0, st, p);
-        return launch_status();
-    }
-    if ((rc = launch_reduce(a, st))) return rc;
-    return launch_reduce(b, st);
+    return launch_reduce(&a, &b, dequant, st);
 }
 
 }  // namespace qblora

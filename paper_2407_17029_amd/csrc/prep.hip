@@ -3,7 +3,7 @@
 // AvgPool(lambda1) on the input equals contracting X with A repeated lambda1 times along k and
 // scaling by 1/lambda1; repeat_interleave(lambda2) on the output equals using row n/lambda2 of B^T
 // for output column n (the tiling conditions stated after Eq. 2).
-#include "common.h"
+#include "dequant.h"
 
 namespace qblora {
 
@@ -95,9 +95,8 @@ struct PrepDesc {
 
 // All re-layouts of one call in a single launch: blocks [0,nA) transpose-expand A, the next nB
 // transpose B, the last nX expand B along its columns.
-__global__ __launch_bounds__(256) void k_adapter_prep(PrepDesc d) {
-    __shared__ uint16_t tile[64][66];
-    int b = blockIdx.x;
+__device__ __forceinline__ void prep_block(const PrepDesc& d, int b, unsigned char* lds) {
+    uint16_t (*const tile)[66] = reinterpret_cast<uint16_t (*)[66]>(lds);
     if (b < d.nA) {
         transpose_expand_tile(d.A, d.na_A, d.R, d.lam1, d.At_x, b % d.tilesA_a, b / d.tilesA_a, tile);
         return;
@@ -111,7 +110,7 @@ __global__ __launch_bounds__(256) void k_adapter_prep(PrepDesc d) {
     if (b < d.nS) {
         // 256 rows x 16 blocks per workgroup: rows are read along their (contiguous) blocks, written
         // per block along the 256 rows of the tile, through LDS
-        __shared__ float st[16][257];
+        float (*const st)[257] = reinterpret_cast<float (*)[257]>(lds);
         const int groups = (d.bpr + 15) / 16;
         const int rt = b / groups, blk0 = (b - rt * groups) * 16;
 #pragma unroll
@@ -165,6 +164,24 @@ __global__ __launch_bounds__(256) void k_adapter_prep(PrepDesc d) {
     }
 }
 
+constexpr int kPrepLds = 16 * 257 * 4;
+static_assert(kPrepLds >= 64 * 66 * 2, "both jobs' tiles");
+
+__global__ __launch_bounds__(256) void k_adapter_prep(PrepDesc d) {
+    __shared__ __align__(16) unsigned char lds[kPrepLds];
+    prep_block(d, blockIdx.x, lds);
+}
+
+// The re-layouts and, behind them, the weight itself in one launch: both are done before the narrow GEMM and the
+// contraction that wait for them, and the few workgroups of the first cost no launch of their own (4 to 5 us).
+template <bool BETA, int GEOM>
+__global__ __launch_bounds__(256) void k_prep_dequantize(PrepDesc p, DequantDesc q) {
+    __shared__ __align__(16) unsigned char lds[kPrepLds > kDequantLds ? kPrepLds : kDequantLds];
+    const int n = p.nA + p.nB + p.nS + p.nX;
+    if ((int)blockIdx.x < n) prep_block(p, blockIdx.x, lds);
+    else dequantize_block<BETA, GEOM>(q, blockIdx.x - n, *reinterpret_cast<DequantLds*>(lds));
+}
+
 // Expanded adapter operand for the alternative scale operators (Sec. 4.3 "The scale operators"):
 // every output element copies one source element or is zero.  Small (at most d x R elements), so one
 // element per thread is enough.
@@ -199,7 +216,7 @@ __global__ __launch_bounds__(256) void k_expand_op(ExpandDesc d) {
 
 int launch_adapter_prep(const qblora_bf16* A, const qblora_bf16* B, int d_in, int d_out, int R, int lam1,
                         int lam2, qblora_bf16* At_x, qblora_bf16* Bt, qblora_bf16* Bx, hipStream_t st,
-                        const ScaleTiling* sc) {
+                        const ScaleTiling* sc, const DequantDesc* dequant) {
     PrepDesc d{};
     if (sc && sc->out) {
         d.scales = sc->scales; d.scale_codes = sc->scale_codes; d.scale_step = sc->scale_step; d.scale_mid = sc->scale_mid;
@@ -213,9 +230,38 @@ int launch_adapter_prep(const qblora_bf16* A, const qblora_bf16* B, int d_in, in
     if (Bt) { d.tilesB_a = (R + 63) / 64; d.tilesB_b = (d.cols_B + 63) / 64; d.nB = d.tilesB_a * d.tilesB_b; }
     if (Bx) d.nX = (int)(((int64_t)R * d_out + 2047) / 2048);
     const int blocks = d.nA + d.nB + d.nS + d.nX;
+    if (dequant) {
+        if ((int64_t)blocks + dequant->blocks > 0x7fffffff) return QBLORA_ERR_UNSUPPORTED;
+        ProfileScope ev(QBLORA_PROFILE_DEQUANT, st);
+        with_form(*dequant, [&](auto beta, auto geom) {
+            hipLaunchKernelGGL((k_prep_dequantize<beta.value, geom.value>), dim3(blocks + dequant->blocks), dim3(256), 0, st, d, *dequant);
+        });
+        return launch_status();
+    }
     if (blocks == 0) return QBLORA_OK;
     hipLaunchKernelGGL(k_adapter_prep, dim3(blocks), dim3(256), 0, st, d);
     return launch_status();
+}
+
+// What is refused here is refused in front of a call's first launch.
+int describe_dequantize(const qblora_qweight& qw, qblora_bf16* Wop, DequantDesc* d) {
+    if (qw.d_in % 64 != 0 || qw.d_out % 64 != 0 || (reinterpret_cast<uintptr_t>(Wop) & 15)) return QBLORA_ERR_UNSUPPORTED;
+    if (qw.block_rows == 8 &&                             // four block parameters per 16-byte load
+        ((reinterpret_cast<uintptr_t>(qw.scales) & 15) || (reinterpret_cast<uintptr_t>(qw.beta) & 15)))
+        return QBLORA_ERR_UNSUPPORTED;
+    const int64_t blocks = (int64_t)(qw.d_out / 64) * ((qw.d_in + 127) / 128);
+    if (blocks > 0x7fffffff) return QBLORA_ERR_UNSUPPORTED;
+    const bool grouped = qw.scale_mode == QBLORA_SCALES_E4M3_GROUPED;
+    *d = DequantDesc{};
+    d->codes = qw.codes; d->scales = qw.scales; d->beta = qw.beta;
+    if (grouped) {
+        d->scale_codes = qw.scale_codes; d->scale_step = qw.scale_step; d->scale_mid = qw.scale_mid; d->scale_group = qw.scale_group;
+    }
+    for (int j = 0; j < 16; ++j) d->cb.c[j] = qw.codebook[j];
+    d->d_out = qw.d_out; d->d_in = qw.d_in; d->out = reinterpret_cast<uint4*>(Wop);
+    d->geom = qw.block_rows != 8 ? (grouped ? ROWS_GROUPED : ROWS) : qw.block == 64 ? EIGHT_BY_8 : EIGHT_BY_4;
+    d->blocks = (unsigned)blocks;
+    return QBLORA_OK;
 }
 
 int launch_expand_op(const qblora_bf16* in, int src_rows, int src_cols, int transpose, int out_rows, int out_cols,

@@ -422,183 +422,6 @@ __global__ __launch_bounds__(256) void k_dequantize_bf16(const uint32_t* __restr
     out[i] = o;
 }
 
-// The bf16 compute weight in MFMA operand order (see launch_dequantize_operand): the weight itself.
-// A workgroup owns 64 stored rows x 128 inputs.  A thread dequantizes 32 inputs of one stored row (16 bytes of
-// codes; four lanes read 64 contiguous bytes of a row) into four 16-byte chunks of an LDS tile [n][16 chunks], chunk
-// c of row n at position c ^ (n & 15); operand order only regroups whole chunks -- lane l = r + 16*g of the k slice
-// j takes chunk 4j + g of row r -- so each wave reads its pieces back with 16-byte LDS loads (16 consecutive rows of
-// one chunk lie in 16 different positions) and stores 1 KB per instruction, 4 KB contiguous per wave.  (The first form
-// let a lane load the 32 code bytes of its row's block, twice per row: both lanes of a row need every other dword;
-// it streamed at 0.60 of the HBM peak.)
-// BETA: offsets present; GEOM: 0 = 64-blocks, 1 = 8 x 8 blocks, 2 = blocks of 8 rows x 4 inputs -- compile-time, so that
-// a launch carries neither the other geometries' loads nor both of multiply and multiply-add with a select per weight
-// (380 -> 230 vector instructions per thread).
-template <bool BETA, int GEOM>
-__global__ __launch_bounds__(256) void k_dequantize_operand(const uint8_t* __restrict__ codes,
-                                                            const float* __restrict__ scales,
-                                                            const float* __restrict__ beta, Codebook cb,
-                                                            int d_out, int d_in,
-                                                            uint4* __restrict__ out) {
-    constexpr int block_rows = GEOM == 0 ? 1 : 8, block_cols = GEOM == 2 ? 4 : 8;
-    __shared__ float lut[16];
-    __shared__ __align__(16) uint4 tile[64][16];                // [n][chunk of 8 k], positions swizzled
-    const int t = threadIdx.x;
-    if (t < 16) lut[t] = cb.c[t];
-    __syncthreads();
-    const int n_tiles = (d_out + 63) / 64;                      // d_out is a multiple of 32 here
-    const int kt = blockIdx.x / n_tiles;                        // 128 inputs
-    const int nt = blockIdx.x % n_tiles;                        // 64 stored rows
-    {
-        const int row = t >> 2, piece = t & 3;                  // stored row in tile, 32 inputs
-        const int64_t n = min((int64_t)nt * 64 + row, (int64_t)d_out - 1);    // rows past the end: computed, never stored
-        const int k0 = kt * 128 + piece * 32;
-        u32x4_any cq = {0u, 0u, 0u, 0u};
-        float a1 = 0.0f, b1 = 0.0f;
-        float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f), b4 = make_float4(0.f, 0.f, 0.f, 0.f), a4b = a4, b4b = b4;
-        if (k0 < d_in) {                                        // d_in % 64 == 0: the last tile may be half
-            cq = *reinterpret_cast<const u32x4_any*>(codes + n * (d_in / 2) + k0 / 2);
-            if constexpr (block_rows == 8 && block_cols == 4) {  // eight block columns of 4 inputs
-                const int64_t blk = (n >> 3) * (int64_t)(d_in / 4) + k0 / 4;
-                a4 = *reinterpret_cast<const float4*>(scales + blk);
-                a4b = *reinterpret_cast<const float4*>(scales + blk + 4);
-                if constexpr (BETA) { b4 = *reinterpret_cast<const float4*>(beta + blk); b4b = *reinterpret_cast<const float4*>(beta + blk + 4); }
-            } else if constexpr (block_rows == 8) {              // four block columns of 8 inputs
-                const int64_t blk = (n >> 3) * (int64_t)(d_in / 8) + k0 / 8;
-                a4 = *reinterpret_cast<const float4*>(scales + blk);
-                if constexpr (BETA) b4 = *reinterpret_cast<const float4*>(beta + blk);
-            } else {
-                const int64_t blk = n * (int64_t)(d_in / kBlock) + k0 / kBlock;
-                a1 = scales[blk];
-                if constexpr (BETA) b1 = beta[blk];
-            }
-        }
-        const uint32_t cw[4] = {cq.x, cq.y, cq.z, cq.w};
-        const float as[8] = {a4.x, a4.y, a4.z, a4.w, a4b.x, a4b.y, a4b.z, a4b.w};
-        const float bs[8] = {b4.x, b4.y, b4.z, b4.w, b4b.x, b4b.y, b4b.z, b4b.w};
-        constexpr bool half = block_rows == 8 && block_cols == 4;   // two blocks per chunk of 8 inputs
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {                           // chunk 4*piece + c: 8 inputs
-            const float a = half ? as[2 * c] : block_rows == 8 ? as[c] : a1, be = half ? bs[2 * c] : block_rows == 8 ? bs[c] : b1;
-            const float a_hi = half ? as[2 * c + 1] : a, be_hi = half ? bs[2 * c + 1] : be;    // inputs 4 .. 7 of the chunk
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float cv = lut[(cw[c] >> (4 * j)) & 15];
-                v[j] = BETA ? __fmaf_rn(cv, j < 4 ? a : a_hi, j < 4 ? be : be_hi) : __fmul_rn(cv, j < 4 ? a : a_hi);
-            }
-            tile[row][(4 * piece + c) ^ (row & 15)] =
-                make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
-        }
-    }
-    __syncthreads();
-    {
-        const int w = t >> 6, lane = t & 63, row = 16 * w + (lane & 15), g = lane >> 4;
-        const int64_t rb = (int64_t)nt * 4 + w;                 // 16-row block of the weight
-        if (rb * 16 < d_out) {
-            const int64_t kb_count = d_in / 32;                 // 32-wide k slices of a row block
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int64_t js = (int64_t)kt * 4 + q;
-                const uint4 o = tile[row][(4 * q + g) ^ (row & 15)];
-                if (js < kb_count) out[(rb * kb_count + js) * 64 + lane] = o;
-            }
-        }
-    }
-}
-
-// The same for the transposed weight (operand rows = inputs k, contraction = stored rows n), which the
-// backward contraction reads.  A workgroup owns 64 stored rows x 128 inputs.  A thread dequantizes 32 inputs of
-// one stored row (16 bytes of codes; four lanes read 64 contiguous bytes of a row) and writes them as four
-// 16-byte chunks into an LDS tile in the stored orientation, [n][128 k] with 256-byte rows; the transposition is
-// left to the transposing LDS read ds_read_b64_tr_b16 (a group of 16 lanes that points at 4 rows x 16 columns
-// gets, lane i, column i of the four rows): two of them give a lane the 8 consecutive n of its k that the
-// operand order wants.  Logical chunk c of row n sits at chunk position c ^ ((n & 3) << 2) ^ ((n & 8) >> 2), so that
-// the four rows of a transposing read, and those of the neighbouring lane group eight rows on, lie in different
-// banks.  Each wave then stores 1 KB pieces (lane l = r + 16*g holds k = r, n = 8g .. + 7 of the slice).  (The first form read 4 bytes of codes per thread and wrote 2-byte elements
-// into a [k][n] tile: 57 % of its LDS cycles were bank conflicts and it streamed at 0.49 of the HBM peak.)
-typedef __attribute__((ext_vector_type(4))) short s16x4_t;
-template <bool BETA, int GEOM>
-__global__ __launch_bounds__(256) void k_dequantize_operand_t(const uint8_t* __restrict__ codes,
-                                                              const float* __restrict__ scales,
-                                                              const float* __restrict__ beta, Codebook cb,
-                                                              int d_out, int d_in,
-                                                              uint4* __restrict__ out) {
-    constexpr int block_rows = GEOM == 0 ? 1 : 8, block_cols = GEOM == 2 ? 4 : 8;
-    __shared__ float lut[16];
-    __shared__ __align__(16) unsigned char tile[64 * 256];      // [n][128 k] bf16, chunks swizzled
-    const int t = threadIdx.x;
-    if (t < 16) lut[t] = cb.c[t];
-    __syncthreads();
-    const int n_tiles = d_out / 64;                             // d_out is a multiple of 64 here
-    const int kt = blockIdx.x / n_tiles;                        // 128 inputs
-    const int nt = blockIdx.x % n_tiles;                        // 64 stored rows
-    {
-        const int row = t >> 2, piece = t & 3;                  // stored row in tile, 32 inputs
-        const int64_t n = (int64_t)nt * 64 + row;
-        const int k0 = kt * 128 + piece * 32;
-        u32x4_any cq = {0u, 0u, 0u, 0u};
-        float a1 = 0.0f, b1 = 0.0f;
-        float4 a4 = make_float4(0.f, 0.f, 0.f, 0.f), b4 = make_float4(0.f, 0.f, 0.f, 0.f), a4b = a4, b4b = b4;
-        if (k0 < d_in) {                                        // d_in % 64 == 0: the last tile may be half
-            cq = *reinterpret_cast<const u32x4_any*>(codes + n * (d_in / 2) + k0 / 2);
-            if constexpr (block_rows == 8 && block_cols == 4) {  // eight block columns of 4 inputs
-                const int64_t blk = (n >> 3) * (int64_t)(d_in / 4) + k0 / 4;
-                a4 = *reinterpret_cast<const float4*>(scales + blk);
-                a4b = *reinterpret_cast<const float4*>(scales + blk + 4);
-                if constexpr (BETA) { b4 = *reinterpret_cast<const float4*>(beta + blk); b4b = *reinterpret_cast<const float4*>(beta + blk + 4); }
-            } else if constexpr (block_rows == 8) {              // four block columns of 8 inputs
-                const int64_t blk = (n >> 3) * (int64_t)(d_in / 8) + k0 / 8;
-                a4 = *reinterpret_cast<const float4*>(scales + blk);
-                if constexpr (BETA) b4 = *reinterpret_cast<const float4*>(beta + blk);
-            } else {
-                const int64_t blk = n * (int64_t)(d_in / kBlock) + k0 / kBlock;
-                a1 = scales[blk];
-                if constexpr (BETA) b1 = beta[blk];
-            }
-        }
-        const uint32_t cw[4] = {cq.x, cq.y, cq.z, cq.w};
-        const float as[8] = {a4.x, a4.y, a4.z, a4.w, a4b.x, a4b.y, a4b.z, a4b.w};
-        const float bs[8] = {b4.x, b4.y, b4.z, b4.w, b4b.x, b4b.y, b4b.z, b4b.w};
-        constexpr bool half = block_rows == 8 && block_cols == 4;   // two blocks per chunk of 8 inputs
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {                           // chunk 4*piece + c: 8 inputs
-            const float a = half ? as[2 * c] : block_rows == 8 ? as[c] : a1, be = half ? bs[2 * c] : block_rows == 8 ? bs[c] : b1;
-            const float a_hi = half ? as[2 * c + 1] : a, be_hi = half ? bs[2 * c + 1] : be;    // inputs 4 .. 7 of the chunk
-            float v[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const float cv = lut[(cw[c] >> (4 * j)) & 15];
-                v[j] = BETA ? __fmaf_rn(cv, j < 4 ? a : a_hi, j < 4 ? be : be_hi) : __fmul_rn(cv, j < 4 ? a : a_hi);
-            }
-            const int pos = (4 * piece + c) ^ ((row & 3) << 2) ^ ((row & 8) >> 2);
-            *reinterpret_cast<uint4*>(tile + row * 256 + pos * 16) =
-                make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
-        }
-    }
-    __syncthreads();
-    {
-        const int w = t >> 6, lane = t & 63, g = lane >> 4, sl = lane & 15;
-        const int s = w >> 1;                                   // 32 stored rows of the tile
-        const int frow = 8 * g + (sl >> 2);                     // row inside the 32-row slice this lane points at
-        const int64_t kb_count = d_out / 32;                    // slices of the contraction (stored rows)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {                           // 16 inputs each
-            const int kb = 4 * (w & 1) + q, col = 16 * kb + 4 * (sl & 3);
-            const unsigned char* p = tile + (32 * s + frow) * 256 +
-                                     ((((col >> 3) ^ ((frow & 3) << 2) ^ ((frow & 8) >> 2)) & 15) << 4) + ((col >> 2) & 1) * 8;
-            const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p));
-            const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4_t*)(p + 4 * 256));
-            const int64_t kb16 = (int64_t)kt * 8 + kb;
-            if (kb16 * 16 < d_in) {
-                uint4 o;
-                o.x = __builtin_bit_cast(uint2, lo).x; o.y = __builtin_bit_cast(uint2, lo).y;
-                o.z = __builtin_bit_cast(uint2, hi).x; o.w = __builtin_bit_cast(uint2, hi).y;
-                out[(kb16 * kb_count + (int64_t)nt * 2 + s) * 64 + lane] = o;
-            }
-        }
-    }
-}
-
 // Nibbles of a code dword regrouped for the table-free decode: position p of the result holds input k(p),
 // k = 0, 2, 4, 6, 1, 3, 5, 7 -- the even inputs in the low half, the odd ones in the high half, so that
 // (w >> 4i) & 0x000F000F is the pair (input 2i, input 2i+1) in the low bits of two 16-bit lanes.
@@ -704,39 +527,6 @@ int launch_dequantize_bf16(const qblora_qweight& qw, const float* scales, qblora
                        reinterpret_cast<const uint32_t*>(qw.codes), scales, qw.beta, cb, n_words,
                        qw.block_rows == 8 ? qw.d_in / 8 : 0, qw.block_rows == 8 ? qw.block / 8 : 8,
                        reinterpret_cast<uint4*>(Wt));
-    return launch_status();
-}
-
-int launch_dequantize_operand(const qblora_qweight& qw, const float* scales, int transposed, qblora_bf16* Wop,
-                              hipStream_t st) {
-    if (qw.d_in % 64 != 0 || qw.d_out % 64 != 0 || (reinterpret_cast<uintptr_t>(Wop) & 15)) return QBLORA_ERR_UNSUPPORTED;
-    if (qw.block_rows == 8 &&                             // four block parameters per 16-byte load
-        ((reinterpret_cast<uintptr_t>(scales) & 15) || (reinterpret_cast<uintptr_t>(qw.beta) & 15)))
-        return QBLORA_ERR_UNSUPPORTED;
-    Codebook cb;
-    for (int j = 0; j < 16; ++j) cb.c[j] = qw.codebook[j];
-    const int br = qw.block_rows == 8 ? 8 : 1, bc = br == 8 ? qw.block / 8 : qw.block;
-    const int64_t blocks = transposed ? (int64_t)((qw.d_in + 127) / 128) * (qw.d_out / 64)
-                                      : (int64_t)((qw.d_out + 63) / 64) * ((qw.d_in + 127) / 128);
-    if (blocks > 0x7fffffff) return QBLORA_ERR_UNSUPPORTED;
-    auto go = [&](auto plain, auto trans) {
-        if (transposed)
-            hipLaunchKernelGGL(trans, dim3((unsigned)blocks), dim3(256), 0, st, qw.codes, scales, qw.beta, cb, qw.d_out, qw.d_in,
-                               reinterpret_cast<uint4*>(Wop));
-        else
-            hipLaunchKernelGGL(plain, dim3((unsigned)blocks), dim3(256), 0, st, qw.codes, scales, qw.beta, cb, qw.d_out, qw.d_in,
-                               reinterpret_cast<uint4*>(Wop));
-    };
-    const int geom = br == 1 ? 0 : bc == 8 ? 1 : 2;
-    if (qw.beta) {
-        if (geom == 0) go(k_dequantize_operand<true, 0>, k_dequantize_operand_t<true, 0>);
-        else if (geom == 1) go(k_dequantize_operand<true, 1>, k_dequantize_operand_t<true, 1>);
-        else go(k_dequantize_operand<true, 2>, k_dequantize_operand_t<true, 2>);
-    } else {
-        if (geom == 0) go(k_dequantize_operand<false, 0>, k_dequantize_operand_t<false, 0>);
-        else if (geom == 1) go(k_dequantize_operand<false, 1>, k_dequantize_operand_t<false, 1>);
-        else go(k_dequantize_operand<false, 2>, k_dequantize_operand_t<false, 2>);
-    }
     return launch_status();
 }
 
