@@ -193,6 +193,7 @@ struct GradDesc {
     int64_t T;
     float* part; int splits;
     float* out; int pool; float out_scale; int transpose_out;
+    float part_scale;                      // set by the launcher: factor of the sums in `part`
 };
 int grad_splits(int64_t T, int I, int J = 1);    // slices of the token range for an [I, J] gradient
 int launch_pool_rows(const qblora_bf16* in, int64_t T, int d, int lam, float scale, qblora_bf16* out,

@@ -2,7 +2,7 @@
 //
 //   C[M,N] = X1[M,K1] * W1^T  +  X2[M,K2] * W2[N/div2, K2]^T          (bf16 operands, fp32 accumulation)
 //
-// W1 is the 16-bit compute weight of Eq. 1 in MFMA operand order (launch_dequantize_operand): the 16 bytes lane l
+// W1 is the 16-bit compute weight of Eq. 1 in MFMA operand order (DequantDesc): the 16 bytes lane l
 // of a wave needs for rows 16i .. 16i+15 and the 32-wide k slice j sit at ((i*(K1/32) + j)*64 + l)*16, so a piece
 // of 1 KB is one copy instruction into LDS and one conflict-free ds_read_b128 out of it.  The second segment is
 // the adapter's K-extension (forward: X2 = s*U, W2 = B^T with output row n using row n/lambda2; backward: X2 =
