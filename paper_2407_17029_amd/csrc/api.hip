@@ -784,7 +784,7 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     if ((rc = launch_adapter_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, st, sct.out ? &sct : nullptr, dense ? &weight : nullptr)))
         return rc;
     // s * AvgPool_lambda1(X)
-    if ((rc = launch_pool_rows(X, T, qw->d_in, lambda1, s / (float)lambda1, ws.P, nullptr, st))) return rc;
+    if ((rc = launch_pool_rows(PoolDesc{X, T, qw->d_in, lambda1, s / (float)lambda1, ws.P, nullptr}, nullptr, st))) return rc;
 
     GemmDesc g{};
     g.qmode = 1;
@@ -829,10 +829,10 @@ int qablora_linear_bwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
 
     // (s/lambda1) * sum_lambda2(dY): operand of the dX K-extension and, rescaled by lambda1 at the end, of dH
     // (there with its bf16 residual, so that only the pooled input carries a bf16 rounding)
-    if ((rc = launch_pool_rows(dY, T, qw->d_out, lambda2, s / (float)lambda1, ws.dVs, dH ? ws.dVs_lo : nullptr, st)))
-        return rc;
+    const PoolDesc pool_dy{dY, T, qw->d_out, lambda2, s / (float)lambda1, ws.dVs, dH ? ws.dVs_lo : nullptr};
+    const PoolDesc pool_x{X, T, qw->d_in, lambda1, 1.0f / (float)lambda1, ws.P, nullptr};
+    if ((rc = launch_pool_rows(pool_dy, dH ? &pool_x : nullptr, st))) return rc;
     if (dH) {
-        if ((rc = launch_pool_rows(X, T, qw->d_in, lambda1, 1.0f / (float)lambda1, ws.P, nullptr, st))) return rc;
         GradDesc gh{};
         gh.L = ws.P; gh.ldl = I; gh.I = I; gh.S = ws.dVs; gh.S_lo = ws.dVs_lo; gh.lds = J; gh.J = J; gh.T = T;
         gh.part = ws.part; gh.splits = ws.splits; gh.out = dH; gh.pool = 1;

@@ -196,8 +196,9 @@ struct GradDesc {
     float part_scale;                      // set by the launcher: factor of the sums in `part`
 };
 int grad_splits(int64_t T, int I, int J = 1);    // slices of the token range for an [I, J] gradient
-int launch_pool_rows(const qblora_bf16* in, int64_t T, int d, int lam, float scale, qblora_bf16* out,
-                     qblora_bf16* out_lo, hipStream_t st);
+// out[t, m] = bf16(scale * sum of lam adjacent in[t, .]), out_lo (may be NULL) what that rounding took off; in: [T, d]
+struct PoolDesc { const qblora_bf16* in; int64_t T; int d, lam; float scale; qblora_bf16* out; qblora_bf16* out_lo; };
+int launch_pool_rows(const PoolDesc& a, const PoolDesc* b, hipStream_t st);     // b (may be NULL): in the same launch
 // `dequant` (may be NULL): the transposed weight, in the launch that reduces the partial sums
 int launch_grad(const GradDesc& d, hipStream_t st, const DequantDesc* dequant = nullptr);
 // two independent gradients whose partial buffers do not overlap: one launch for both where the shapes allow

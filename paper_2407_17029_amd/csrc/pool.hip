@@ -16,10 +16,8 @@ namespace qblora {
 namespace {
 
 template <int LAM>
-__global__ __launch_bounds__(256) void k_pool_rows8(const uint4* __restrict__ in, int64_t n_chunks, float scale,
-                                                    uint4* __restrict__ out, uint4* __restrict__ out_lo) {
-    const int64_t c = (int64_t)blockIdx.x * 256 + threadIdx.x;         // output chunk (8 values)
-    if (c >= n_chunks) return;
+__device__ __forceinline__ void pool_chunk(const uint4* __restrict__ in, int64_t c, float scale,
+                                           uint4* __restrict__ out, uint4* __restrict__ out_lo) {
     uint4 v[LAM];
 #pragma unroll
     for (int i = 0; i < LAM; ++i) v[i] = in[c * LAM + i];
@@ -51,6 +49,22 @@ __global__ __launch_bounds__(256) void k_pool_rows8(const uint4* __restrict__ in
             lw[q] = pack_bf16(o[2 * q] - bf16_bits_to_float(hw[q] & 0xffffu), o[2 * q + 1] - bf16_bits_to_float(hw[q] >> 16));
         out_lo[c] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
     }
+}
+
+// Two poolings in one launch: the first n_a workgroups work on `a`.  A layer's two (dY and X of a backward) take 5 us each
+// alone, most of it start and tail.
+struct PoolPair { PoolDesc a, b; int64_t chunks_a, chunks_b; unsigned n_a; };
+template <int LAM_A, int LAM_B>
+__global__ __launch_bounds__(256) void k_pool_rows8(PoolPair p) {
+    const bool second = blockIdx.x >= p.n_a;
+    const PoolDesc& d = second ? p.b : p.a;
+    const int64_t c = (int64_t)(blockIdx.x - (second ? p.n_a : 0)) * 256 + threadIdx.x;       // output chunk (8 values)
+    if (c >= (second ? p.chunks_b : p.chunks_a)) return;
+    const uint4* in = reinterpret_cast<const uint4*>(d.in);
+    uint4* out = reinterpret_cast<uint4*>(d.out);
+    uint4* out_lo = reinterpret_cast<uint4*>(d.out_lo);
+    if (LAM_A == LAM_B || !second) pool_chunk<LAM_A>(in, c, d.scale, out, out_lo);
+    else pool_chunk<LAM_B>(in, c, d.scale, out, out_lo);
 }
 
 __global__ __launch_bounds__(256) void k_pool_rows1(const uint16_t* __restrict__ in, int64_t n_out, int lam,
@@ -92,31 +106,51 @@ __global__ __launch_bounds__(256) void k_sample_rows(const uint16_t* __restrict_
 
 }  // namespace
 
-// in: bf16 [T, d] with d % lam == 0 (rows are contiguous, so the whole matrix is one run of groups of
-// lam values); out (and out_lo, or NULL): bf16 [T, d/lam].
-int launch_pool_rows(const qblora_bf16* in, int64_t T, int d, int lam, float scale, qblora_bf16* out,
-                     qblora_bf16* out_lo, hipStream_t st) {
-    const int64_t n_out = T * (int64_t)(d / lam);
-    if (n_out <= 0) return QBLORA_OK;
-    const bool aligned = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out) |
-                           reinterpret_cast<uintptr_t>(out_lo)) & 15) == 0;
-    if (aligned && n_out % 8 == 0 && (lam == 1 || lam == 2 || lam == 4 || lam == 8)) {
-        const int64_t n_chunks = n_out / 8;
-        const dim3 grid((unsigned)((n_chunks + 255) / 256));
-        const uint4* src = reinterpret_cast<const uint4*>(in);
-        uint4* dst = reinterpret_cast<uint4*>(out);
-        uint4* dlo = reinterpret_cast<uint4*>(out_lo);
-        switch (lam) {
-            case 1: hipLaunchKernelGGL(k_pool_rows8<1>, grid, dim3(256), 0, st, src, n_chunks, scale, dst, dlo); break;
-            case 2: hipLaunchKernelGGL(k_pool_rows8<2>, grid, dim3(256), 0, st, src, n_chunks, scale, dst, dlo); break;
-            case 4: hipLaunchKernelGGL(k_pool_rows8<4>, grid, dim3(256), 0, st, src, n_chunks, scale, dst, dlo); break;
-            default: hipLaunchKernelGGL(k_pool_rows8<8>, grid, dim3(256), 0, st, src, n_chunks, scale, dst, dlo); break;
-        }
-    } else {
-        hipLaunchKernelGGL(k_pool_rows1, dim3((unsigned)((n_out + 255) / 256)), dim3(256), 0, st,
-                           reinterpret_cast<const uint16_t*>(in), n_out, lam, scale, reinterpret_cast<uint16_t*>(out),
-                           reinterpret_cast<uint16_t*>(out_lo));
+namespace {
+
+int64_t outputs(const PoolDesc& d) { return d.T * (int64_t)(d.d / d.lam); }
+// whole chunks of 8 outputs: the matrix is one run of groups of lam values (rows are contiguous)
+bool in_chunks(const PoolDesc& d) {
+    const uintptr_t bits = reinterpret_cast<uintptr_t>(d.in) | reinterpret_cast<uintptr_t>(d.out) | reinterpret_cast<uintptr_t>(d.out_lo);
+    return (bits & 15) == 0 && outputs(d) % 8 == 0 && (d.lam == 1 || d.lam == 2 || d.lam == 4 || d.lam == 8);
+}
+unsigned chunk_blocks(const PoolDesc& d) { return (unsigned)((outputs(d) / 8 + 255) / 256); }
+
+template <int LAM_A>
+void launch_chunks(const PoolPair& p, unsigned blocks, int lam_b, hipStream_t st) {
+    switch (lam_b) {
+        case 1: hipLaunchKernelGGL((k_pool_rows8<LAM_A, 1>), dim3(blocks), dim3(256), 0, st, p); break;
+        case 2: hipLaunchKernelGGL((k_pool_rows8<LAM_A, 2>), dim3(blocks), dim3(256), 0, st, p); break;
+        case 4: hipLaunchKernelGGL((k_pool_rows8<LAM_A, 4>), dim3(blocks), dim3(256), 0, st, p); break;
+        default: hipLaunchKernelGGL((k_pool_rows8<LAM_A, 8>), dim3(blocks), dim3(256), 0, st, p); break;
     }
+}
+
+}  // namespace
+
+int launch_pool_rows(const PoolDesc& a, const PoolDesc* b, hipStream_t st) {
+    if (outputs(a) <= 0) return b ? launch_pool_rows(*b, nullptr, st) : QBLORA_OK;
+    if (b && (outputs(*b) <= 0 || !in_chunks(a) || !in_chunks(*b) || (int64_t)chunk_blocks(a) + chunk_blocks(*b) > 0x7fffffff)) {
+        const int rc = launch_pool_rows(a, nullptr, st);
+        return rc ? rc : launch_pool_rows(*b, nullptr, st);
+    }
+    if (in_chunks(a)) {
+        PoolPair p{};
+        p.a = a; p.n_a = chunk_blocks(a); p.chunks_a = outputs(a) / 8;
+        if (b) { p.b = *b; p.chunks_b = outputs(*b) / 8; }
+        const unsigned blocks = p.n_a + (b ? chunk_blocks(*b) : 0);
+        const int lam_b = b ? b->lam : a.lam;
+        switch (a.lam) {
+            case 1: launch_chunks<1>(p, blocks, lam_b, st); break;
+            case 2: launch_chunks<2>(p, blocks, lam_b, st); break;
+            case 4: launch_chunks<4>(p, blocks, lam_b, st); break;
+            default: launch_chunks<8>(p, blocks, lam_b, st); break;
+        }
+        return launch_status();
+    }
+    hipLaunchKernelGGL(k_pool_rows1, dim3((unsigned)((outputs(a) + 255) / 256)), dim3(256), 0, st,
+                       reinterpret_cast<const uint16_t*>(a.in), outputs(a), a.lam, a.scale, reinterpret_cast<uint16_t*>(a.out),
+                       reinterpret_cast<uint16_t*>(a.out_lo));
     return launch_status();
 }
 
