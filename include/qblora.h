@@ -404,7 +404,7 @@ int qblora_decode_pack(const qblora_qweight* qw, void* pack, void* stream);
  *   QBLORA_PROFILE_MERGE      the requantizing (or beta-shift) kernel of qablora_merge_quantize
  *   QBLORA_PROFILE_QUANTIZE   the code-selection kernel of qblora_quantize_blockwise
  *   QBLORA_PROFILE_ADAPTER_FWD    the narrow GEMM s*U = s * AvgPool(X) A of the forward
- *   QBLORA_PROFILE_ADAPTER_BWD    the narrow GEMM dU = dV B^T of the backward
+ *   QBLORA_PROFILE_ADAPTER_BWD    the narrow GEMM dU = dV B^T of the backward, with s*U where that is recomputed
  *   QBLORA_PROFILE_ADAPTER_GRADS  the token contractions behind dA and dB (partial sums, both in one launch)
  *   QBLORA_PROFILE_GRAD_REDUCE    the fixed-order reduction of those partial sums into dA and dB
  *   QBLORA_PROFILE_PREP           the per-call re-layout launch of the forward (adapter operands, block scales)

@@ -182,6 +182,8 @@ int skinny_splits(int64_t M, int N, int K, int64_t max_part_bytes);
 // no fewer rows of partial sums, slices x tokens, than any number of tokens up to M takes
 int64_t skinny_part_rows(int64_t M, int N, int K);
 int launch_skinny(const GemmDesc& d, hipStream_t st);
+// two of them, independent of each other, with partial sums of their own: one launch where they take the same form
+int launch_skinny_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t st);
 
 // Token-contraction GEMM with split-T partials:  part[z][i][j] = sum_{t in slice z} L[t,i] * S[t,j]
 // followed by the reduction  out = sum_z part, pooled over `pool` adjacent i (scaled by out_scale),

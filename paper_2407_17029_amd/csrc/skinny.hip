@@ -53,8 +53,14 @@ __device__ __forceinline__ uint32_t lds_address(const void* p) {
 // which halves the W stream from L2 and its LDS tile).  Only in the k-split form with two k-steps per
 // stage: the W columns of both k-steps are 128 contiguous bytes per row and form one tile per stage,
 // behind the stage's two X sub-tiles.
-template <int BM, int BN, int kStages, int kSub, bool kSplitK, int kDup = 1>
-__global__ __launch_bounds__(kThreads) void k_skinny(GemmDesc d) {
+// One GEMM, or two that do not depend on each other (a backward that recomputes s*U beside dU): the first n_a workgroups
+// work on `a`.  kPair is compile-time: the choice costs a lone GEMM 0.5 us of scalar loads before its first copy.
+struct SkinnyPair { GemmDesc a, b; unsigned n_a; };
+
+template <bool kPair, int BM, int BN, int kStages, int kSub, bool kSplitK, int kDup = 1>
+__global__ __launch_bounds__(kThreads) void k_skinny(SkinnyPair p) {
+    const bool second = kPair && blockIdx.x >= p.n_a;
+    const GemmDesc& d = second ? p.b : p.a;
     static_assert(!kSplitK || (BM == 64 && (BN == 64 || BN == 128)), "the k-split form is written for 64 x 64 and 64 x 128 tiles");
     static_assert(kDup == 1 || (kDup == 2 && kSplitK && kSub == 2), "column duplication: k-split form, two k-steps per stage");
     // a stage holds kSub consecutive k-steps (sub-tiles of 64 k each): one barrier per kSub * 64 k
@@ -81,7 +87,7 @@ __global__ __launch_bounds__(kThreads) void k_skinny(GemmDesc d) {
     // blockIdx.x % 8 is the XCD: the column tiles of one token tile are 8 apart
     const int tiles_n = (N + BN - 1) / BN;
     const int splits = d.splits > 1 ? d.splits : 1, all_steps = K / (kBK * kSub);
-    int z = 0, bid = blockIdx.x, step0 = 0, nsteps = all_steps;    // (unsliced calls spend no divisions on it: 0.3 us)
+    int z = 0, bid = blockIdx.x - (second ? p.n_a : 0), step0 = 0, nsteps = all_steps;    // (unsliced calls spend no divisions on it: 0.3 us)
     if (splits > 1) {
         z = bid % splits; bid /= splits;
         step0 = all_steps * z / splits;           // all_steps < 2^24
@@ -276,8 +282,11 @@ __global__ __launch_bounds__(kThreads) void k_skinny(GemmDesc d) {
 
 // The slices' partial tiles added in slice order, four columns of one token per thread; the same outputs as the
 // unsplit kernel's epilogue.
-__global__ __launch_bounds__(256) void k_skinny_reduce(GemmDesc d) {
-    const int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4, plane = d.M * d.N;
+template <bool kPair>
+__global__ __launch_bounds__(256) void k_skinny_reduce(SkinnyPair p) {
+    const bool second = kPair && blockIdx.x >= p.n_a;
+    const GemmDesc& d = second ? p.b : p.a;
+    const int64_t i = ((int64_t)(blockIdx.x - (second ? p.n_a : 0)) * 256 + threadIdx.x) * 4, plane = d.M * d.N;
     if (i >= plane) return;
     float4 sum = *reinterpret_cast<const float4*>(d.part + i);
     for (int z0 = 1; z0 < d.splits; z0 += 8) {
@@ -315,21 +324,35 @@ bool skinny_applies(const GemmDesc& d) {
            (int64_t)64 * d.ldx2 * 2 < (int64_t)1 << 31;
 }
 
-template <int BM, int BN, int kStages, int kSub, bool kSplitK, int kDup = 1>
-int launch_skinny_cfg(const GemmDesc& d, hipStream_t st) {
+template <bool kPair, int BM, int BN, int kStages, int kSub, bool kSplitK, int kDup>
+int launch_skinny_as(const GemmDesc& d, const GemmDesc* b, hipStream_t st) {
     constexpr size_t smem = kStages * kSub * (BM * 128 + BN * 128 / kDup);
-    auto kern = k_skinny<BM, BN, kStages, kSub, kSplitK, kDup>;
+    auto kern = k_skinny<kPair, BM, BN, kStages, kSub, kSplitK, kDup>;
     // set once per instantiation; the initialisation of a function-local static is thread safe
     static const bool attr_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem) == hipSuccess;
     if (!attr_ok) return QBLORA_ERR_LAUNCH;
-    const int64_t tiles_m = (d.M + BM - 1) / BM, tiles_n = (d.N + BN - 1) / BN;
-    const int splits = kSplitK && d.splits > 1 ? d.splits : 1;
-    dim3 grid((unsigned)((tiles_m + 7) / 8 * 8 * tiles_n * splits));
-    hipLaunchKernelGGL(kern, grid, dim3(kThreads), smem, st, d);
-    if (splits > 1)
-        hipLaunchKernelGGL(k_skinny_reduce, dim3((unsigned)((d.M * d.N / 4 + 255) / 256)), dim3(256), 0, st, d);
+    auto blocks = [](const GemmDesc& g) {
+        const int64_t tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
+        return (unsigned)((tiles_m + 7) / 8 * 8 * tiles_n * (kSplitK && g.splits > 1 ? g.splits : 1));
+    };
+    SkinnyPair p{};
+    p.a = d;
+    if (b) p.b = *b;
+    p.n_a = blocks(d);
+    hipLaunchKernelGGL(kern, dim3(p.n_a + (b ? blocks(*b) : 0)), dim3(kThreads), smem, st, p);
+    if (kSplitK && d.splits > 1) {
+        auto reduce_blocks = [](const GemmDesc& g) { return (unsigned)((g.M * g.N / 4 + 255) / 256); };
+        p.n_a = reduce_blocks(d);
+        hipLaunchKernelGGL(k_skinny_reduce<kPair>, dim3(p.n_a + (b ? reduce_blocks(*b) : 0)), dim3(256), 0, st, p);
+    }
     return launch_status();
+}
+
+template <int BM, int BN, int kStages, int kSub, bool kSplitK, int kDup = 1>
+int launch_skinny_cfg(const GemmDesc& d, const GemmDesc* b, hipStream_t st) {
+    return b ? launch_skinny_as<true, BM, BN, kStages, kSub, kSplitK, kDup>(d, b, st)
+             : launch_skinny_as<false, BM, BN, kStages, kSub, kSplitK, kDup>(d, b, st);
 }
 
 // A slice keeps at least four steps of 128 k (prologue and epilogue cost about five), and the split has to save twelve
@@ -346,27 +369,47 @@ int64_t skinny_part_rows(int64_t M, int N, int K) {
     return M <= 0 || N <= 0 ? 0 : std::min(M * std::max<int64_t>(most, 1), std::max<int64_t>(M, 64 * 256 / ((N + 63) / 64)));
 }
 
-int launch_skinny(const GemmDesc& d, hipStream_t st) {
+namespace {
+
+// `b` (may be NULL): a second one that takes the same form (same_form)
+int launch_forms(const GemmDesc& d, const GemmDesc* b, hipStream_t st) {
     // 64 x 128 tiles once they alone fill the chip twice over; below that 64 x 64 tiles with a deep
     // ring (a narrower output has nothing to split: 32-token tiles, 128 columns)
     const int64_t wgs = ((d.M + 63) / 64) * ((d.N + 127) / 128);
     if (d.splits > 1) {                                                            // see skinny_splits
-        if (d.dup2 == 2) return launch_skinny_cfg<64, 64, 3, 2, true, 2>(d, st);
-        return launch_skinny_cfg<64, 64, 4, 2, true>(d, st);
+        if (d.dup2 == 2) return launch_skinny_cfg<64, 64, 3, 2, true, 2>(d, b, st);
+        return launch_skinny_cfg<64, 64, 4, 2, true>(d, b, st);
     }
     if (d.dup2 == 2) {                                                             // see skinny_dup_applies
         // 128 columns per workgroup once that still puts a workgroup on every CU: the token tile is then fetched by
         // two workgroups instead of four (65B gate projection, inner rank 256: 2.16 -> 1.44 GB through the CUs,
         // backward 200 -> 157 us, forward 77 -> 62 us; three or four stages measure the same, two are slower)
-        if (d.N > 64 && wgs >= 256) return launch_skinny_cfg<64, 128, 3, 2, true, 2>(d, st);
-        return launch_skinny_cfg<64, 64, 5, 2, true, 2>(d, st);
+        if (d.N > 64 && wgs >= 256) return launch_skinny_cfg<64, 128, 3, 2, true, 2>(d, b, st);
+        return launch_skinny_cfg<64, 64, 5, 2, true, 2>(d, b, st);
     }
-    if (wgs >= 512) return launch_skinny_cfg<64, 128, 4, 1, false>(d, st);
+    if (wgs >= 512) return launch_skinny_cfg<64, 128, 4, 1, false>(d, b, st);
     if (d.N > 64) {
-        if (d.K2 % (2 * kBK) == 0) return launch_skinny_cfg<64, 64, 5, 2, true>(d, st);
-        return launch_skinny_cfg<64, 64, 9, 1, true>(d, st);
+        if (d.K2 % (2 * kBK) == 0) return launch_skinny_cfg<64, 64, 5, 2, true>(d, b, st);
+        return launch_skinny_cfg<64, 64, 9, 1, true>(d, b, st);
     }
-    return launch_skinny_cfg<32, 128, 6, 1, false>(d, st);
+    return launch_skinny_cfg<32, 128, 6, 1, false>(d, b, st);
+}
+
+// what launch_forms decides by
+bool same_form(const GemmDesc& a, const GemmDesc& b) {
+    return a.M == b.M && a.N == b.N && a.dup2 == b.dup2 && (a.splits > 1) == (b.splits > 1) &&
+           (a.K2 % (2 * kBK) == 0) == (b.K2 % (2 * kBK) == 0);
+}
+
+}  // namespace
+
+int launch_skinny(const GemmDesc& d, hipStream_t st) { return launch_forms(d, nullptr, st); }
+
+int launch_skinny_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t st) {
+    if (skinny_applies(a) && skinny_applies(b) && same_form(a, b) && (a.splits <= 1 || a.part != b.part))
+        return launch_forms(a, &b, st);
+    const int rc = launch_gemm(a, st);
+    return rc ? rc : launch_gemm(b, st);
 }
 
 }  // namespace qblora
