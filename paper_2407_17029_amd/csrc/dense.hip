@@ -10,16 +10,16 @@
 //
 // Bound: the matrix pipe.  A workgroup is 8 wave64 as 2 (tokens) x 4 (features), two waves to a SIMD; a wave owns
 // 32*MB tokens x 32*NB features.  The two waves of a SIMD belong to different halves of the workgroup (waves 0-3
-// and 4-7) that alternate strictly: while one half runs a compute phase (16 MFMAs, 256 cycles) the other runs a
-// memory phase (LDS fragment reads for its next compute phase, two to four copies into the ring, the waits), with
+// and 4-7) that alternate strictly: while one half runs a compute phase (16 or 32 MFMAs, 16 cycles each) the other runs a
+// memory phase (LDS fragment reads for its next compute phase, two to six copies into the ring, the waits), with
 // a barrier between phases.  The second half passes one extra barrier at the start, so a compute phase always has
 // a memory phase beside it: fragment reads, their latency and the refills hide under the other wave's MFMAs, and
 // the copies leave evenly spread instead of in a burst behind a barrier.
 //
 // All copies are direct (global_load_lds, 16 bytes a lane) in assembly statements without register outputs, in
 // program order, so the waits are exact counts: a part of a tile (16 KB, 2 copies a wave) is waited for at the end
-// of the memory phase in front of the one that reads it, with 12 younger copies (8 in the smallest tile) still in
-// flight.  A region of the ring is refilled from the memory phase behind the one that read it: reads complete
+// of the memory phase in front of the one that reads it, with 12 younger copies (8 in the smallest tile, 6 in the 128 x 256 one's long phases) still
+// in flight.  A region of the ring is refilled from the memory phase behind the one that read it: reads complete
 // (lgkmcnt(0)) in front of the barrier that ends their phase, and the other half's same phase ends one barrier
 // earlier than the refill starts.
 //
@@ -74,7 +74,8 @@ struct Ring {
     static constexpr int kLds = kStages * kStage > kEpilogue ? kStages * kStage : kEpilogue;
 };
 
-template <int MB, int NB>
+// WHOLE: a phase works on a whole step (128 x 256 tiles only)
+template <int MB, int NB, bool WHOLE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_dense(GemmDesc d) {
     using R = Ring<MB, NB>;
     constexpr int BM = 64 * MB, BN = 128 * NB, S = R::kStages;
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // reach the pipe as it drains (interval 292 -> 283 cycles against 256 of MFMAs).  The raised priority makes the
     // last MFMA issue ahead of the other half's; without it this half's next memory phase starts late (the whole
     // kernel 20 % slower with the barrier two MFMAs early).
-    auto compute = [&](int a, int p) __attribute__((always_inline)) {
+    auto compute = [&](int a, int p, auto ends_phase) __attribute__((always_inline)) {
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
@@ -216,7 +217,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    if (ks == 1 && h == 1 && b == 3) {
+                    if (ends_phase.value && ks == 1 && h == 1 && b == 3) {
                         __builtin_amdgcn_s_setprio(3);
                         end_compute();
                     }
@@ -224,7 +225,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                         __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[a][h][ks], xf[b][ks], acc[2 * a + h][4 * p + b], 0, 0, 0);
                 }
         __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_setprio(0);
+        if (ends_phase.value) __builtin_amdgcn_s_setprio(0);
     };
     auto slot_of = [&](int step) __attribute__((always_inline)) { return (uint32_t)(step % S) * (uint32_t)R::kStage; };
 
@@ -247,19 +248,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             read_x(0, cur);
             if constexpr (issue.value) issue_w(0, s + 2, cur);
             end_memory(w0);
-            compute(0, 0);
+            compute(0, 0, Int<1>{});
             read_w(1, cur);
             if constexpr (issue.value) issue_x(0, s + 2, cur);
             end_memory(w1);
-            compute(1, 0);
+            compute(1, 0, Int<1>{});
             read_x(1, cur);
             if constexpr (issue.value) issue_w(1, s + 2, cur);
             end_memory(w2);
-            compute(0, 1);
+            compute(0, 1, Int<1>{});
             if constexpr (!last.value) read_w(0, nxt);
             if constexpr (issue.value) issue_x(1, s + 2, cur);
             end_memory(w3);
-            compute(1, 1);
+            compute(1, 1, Int<1>{});
         };
         int s = 0;
         for (; s + 2 < n; ++s) step(s, Int<1>{}, Int<0>{}, Int<12>{}, Int<12>{}, Int<12>{}, Int<12>{});
@@ -268,7 +269,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             ++s;
         }
         step(s, Int<0>{}, Int<1>{}, Int<2>{}, Int<0>{}, Int<0>{}, Int<0>{});
-    } else if constexpr (MB == 2 && NB == 2) {
+    } else if constexpr (MB == 2 && NB == 2 && !WHOLE) {
         // 0: X -> (W0, X), W0(s+S) and W1(s+S-1);   1: W1, W0(s+1) -> (W1, X), X(s+S)
 #pragma unroll
         for (int q = 0; q < S; ++q)
@@ -288,16 +289,44 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             if constexpr (issue.value == 2) issue_w(0, s + S, cur);
             if constexpr (issue.value >= 1) issue_w(1, s + S - 1, slot_of(s + S - 1));
             end_memory(wait);
-            compute(0, 0);
+            compute(0, 0, Int<1>{});
             read_w(1, cur);
             if (issue.value == 2 || s + 1 < n) read_w(0, slot_of(s + 1));
             if constexpr (issue.value == 2) issue_x(0, s + S, cur);
             end_memory(wait);
-            compute(1, 0);
+            compute(1, 0, Int<1>{});
         };
         int s = 0;
         for (; s + S < n; ++s) step(s, Int<2>{}, Int<12>{});
         if (n >= S) step(s++, Int<1>{}, Int<0>{});
+        for (; s < n; ++s) step(s, Int<0>{}, Int<0>{});
+    } else if constexpr (MB == 2 && NB == 2) {
+        // One phase of 32 MFMAs a step: X, W0, W1 -> all four, copies of step s+2 into the stage read a step earlier (the
+        // other half's read of it ended one barrier ago).  Half as many barriers and waits for fragments as with a phase
+        // for each of W0 and W1: 80 tiles of 5120 inputs 65 -> 56 us, 220 tiles 79 -> 74.  (256 x 128 tiles read 20
+        // fragments for a step, and there the long phase is the slower one: 75.3 -> 77.9 us a call.)  Six copies instead
+        // of twelve are in flight, though, which costs 1 to 2 us where slices fill the chip (see launch_dense).
+        constexpr int kOps = 6;                                      // copies of a wave and step
+#pragma unroll
+        for (int q = 0; q < S - 1; ++q)
+            if (q < n) { issue_x(0, q, q * R::kStage); issue_w(0, q, q * R::kStage); issue_w(1, q, q * R::kStage); }
+        if (n >= S - 1) end_memory(Int<kOps * (S - 2)>{}); else end_memory(Int<0>{});
+        if (wm) end_compute();
+        auto step = [&](int s, auto issue, auto wait) __attribute__((always_inline)) {
+            const uint32_t cur = slot_of(s);
+            read_w(0, cur);
+            read_w(1, cur);
+            read_x(0, cur);
+            if constexpr (issue.value) {
+                const uint32_t to = slot_of(s + S - 1);
+                issue_x(0, s + S - 1, to); issue_w(0, s + S - 1, to); issue_w(1, s + S - 1, to);
+            }
+            end_memory(wait);
+            compute(0, 0, Int<0>{});
+            compute(1, 0, Int<1>{});
+        };
+        int s = 0;
+        for (; s + S - 1 < n; ++s) step(s, Int<1>{}, Int<kOps * (S - 2)>{});
         for (; s < n; ++s) step(s, Int<0>{}, Int<0>{});
     } else if constexpr (MB == 4 && NB == 1) {
         // 0: X part 0, W -> (W, X0), X1(s+S-1);   1: X part 1 -> (W, X1), X0(s+S) and W(s+S)
@@ -317,11 +346,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             read_x(0, cur);
             if constexpr (issue.value >= 1) issue_x(1, s + S - 1, slot_of(s + S - 1));
             end_memory(wait);
-            compute(0, 0);
+            compute(0, 0, Int<1>{});
             read_x(1, cur);
             if constexpr (issue.value == 2) { issue_x(0, s + S, cur); issue_w(0, s + S, cur); }
             end_memory(wait);
-            compute(0, 1);
+            compute(0, 1, Int<1>{});
         };
         int s = 0;
         for (; s + S < n; ++s) step(s, Int<2>{}, Int<12>{});
@@ -343,7 +372,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                 issue_x(0, s + S - 1, to); issue_w(0, s + S - 1, to);
             }
             end_memory(wait);
-            compute(0, 0);
+            compute(0, 0, Int<1>{});
         };
         int s = 0;
         for (; s + S - 1 < n; ++s) step(s, Int<1>{}, Int<4 * (S - 2)>{});
@@ -418,9 +447,9 @@ __global__ __launch_bounds__(256) void k_dense_reduce(GemmDesc d) {
                    pack_bf16(hi[0] * s, hi[1] * s), pack_bf16(hi[2] * s, hi[3] * s));
 }
 
-template <int MB, int NB>
+template <int MB, int NB, bool WHOLE = false>
 int launch_cfg(const GemmDesc& d, hipStream_t st) {
-    auto kern = k_dense<MB, NB>;
+    auto kern = k_dense<MB, NB, WHOLE>;
     constexpr int smem = Ring<MB, NB>::kLds;
     // set once per instantiation; the initialisation of a function-local static is thread safe
     static const bool attr_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
@@ -437,7 +466,8 @@ int launch_cfg(const GemmDesc& d, hipStream_t st) {
 
 // Tile shape (and slices) by the estimated time.  `full` is the measured time of a k-step with every CU busy, `few`
 // with a few (the clock is power-limited: 1.5-1.7 GHz with all matrix pipes busy, 2.4 with few), both in ns; a last
-// round of workgroups (256, one per CU) that is not full lies in between.  Larger tiles move fewer bytes per MFMA
+// round of workgroups (256, one per CU) that is not full lies in between.  (128 x 256 takes 690 and 870 since its phases
+// hold a whole step; the choices below were measured with the older figures, which stay.)  Larger tiles move fewer bytes per MFMA
 // (256 x 256 runs at 0.82-0.89 of the matrix pipe, 128 x 128 at 0.42: copies into LDS are its limit) and need more
 // tiles to fill the chip.  T x N x K, us for 256x256 / 128x256 / 256x128 / 128x128: 512 x 4096 x 11008 179 / 130 /
 // 131 / 87; 512 x 11008 x 4096 77 / 61 / 60 / 76; 1337 x 5120 x 5120 94 / 71 / 74 / 90; 2500 x 5120 x 13824 263 / 350 /
@@ -525,7 +555,9 @@ int launch_dense(const GemmDesc& d, hipStream_t st) {
     if (d.splits > 1 && p.splits != d.splits) return QBLORA_ERR_UNSUPPORTED;       // not what dense_splits said
     switch (p.shape) {
         case 0: return launch_cfg<4, 2>(d, st);
-        case 1: return launch_cfg<2, 2>(d, st);
+        // slices start far apart in both operands, and with a tile on every CU their copies take longer: 512 tokens of 4096 x
+        // 11008 in four slices 203.6 us a call with two phases a step, 205.6 with one; unsliced calls 10 to 5 % the other way
+        case 1: return d.splits > 1 ? launch_cfg<2, 2>(d, st) : launch_cfg<2, 2, true>(d, st);
         case 2: return launch_cfg<4, 1>(d, st);
         default: return launch_cfg<2, 1>(d, st);
     }
