@@ -183,13 +183,12 @@ BwdSpace carve_bwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T
         s.splits_a = grad_splits(T, qw->d_in);
         s.splits_b = grad_splits(T, qw->d_out);
         size_t pa = std::max(px, (size_t)s.splits_a * qw->d_in * ad->R);
-        // (the narrow GEMMs' partial sums share the buffers: they are added up before the gradients start)
+        // (the narrow GEMMs' partial sums share the buffer: they are added up before the gradients start)
         const int64_t narrow = query ? std::max(skinny_part_rows(T, ad->R, qw->d_in), skinny_part_rows(T, ad->R, qw->d_out))
                                      : T * std::max(su_splits(qw, ad, T), du_splits(qw, ad, T));
         pa = std::max(pa, (size_t)narrow * ad->R);
-        const size_t pb = std::max((size_t)s.splits_b * qw->d_out * ad->R, (size_t)narrow * ad->R);
         s.part = c.take<float>(pa);             // dA and dB are computed in one launch: a buffer each
-        s.part_b = c.take<float>(pb);
+        s.part_b = c.take<float>((size_t)s.splits_b * qw->d_out * ad->R);
         if (scale_op_of(ad)) s.A_op = c.take<qblora_bf16>((size_t)qw->d_in * ad->R);
         if (scale_op_of(ad) == QBLORA_OP_SAMPLE_ZEROFILL) {
             s.Xs = c.take<qblora_bf16>((size_t)T * (qw->d_in / ad->lambda1));
@@ -565,13 +564,15 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         const qblora_bf16* su = saved; const qblora_bf16* su_lo = saved ? saved + T * R : nullptr;
         {
             ScopedEvents ev(QBLORA_PROFILE_ADAPTER_BWD, st);
-            if (want_grads && !saved) {                       // s*U again from X, as the forward computed it, beside dU
+            if (want_grads && !saved) {                       // s*U again from X, as the forward computed it
                 GemmDesc u{};
                 u.qmode = 0;
                 u.X2 = X; u.ldx2 = qw->d_in; u.W2 = ws.At_x; u.ldw2 = qw->d_in; u.K2 = qw->d_in; u.div2 = 1;
                 if (dup_a) { u.ldw2 = qw->d_in / 2; u.dup2 = 2; }
                 u.C = ws.U; u.ldc = R; u.out_scale = op ? ad->s : ad->s / (float)ad->lambda1; u.M = T; u.N = R; u.C_lo = ws.U_lo;
-                u.part = ws.part_b; u.splits = su_splits(qw, ad, T);
+                // beside dU where its partial sums fit dB's (on all but outputs of a few hundred features), else behind it
+                u.splits = su_splits(qw, ad, T);
+                u.part = T * u.splits <= (int64_t)ws.splits_b * qw->d_out ? ws.part_b : ws.part;
                 rc = launch_skinny_pair(du, u, st);
                 su = ws.U; su_lo = ws.U_lo;
             } else {

@@ -78,3 +78,23 @@ def test_partial_sum_rows_are_the_most_of_any_count(rules, N, k1, k2):
         s = rules.dense_plan(T, N, k1, k2, 8).splits
         most = max(most, s * T if s > 1 else 0)
         assert rows(T, N, k1, k2) == most, T
+
+
+@pytest.mark.parametrize("T,d_out,d_in,R", [(1950, 64, 4672, 32), (4887, 64, 2368, 64), (14, 192, 17152, 8), (200, 64, 3072, 16),
+                                            (1337, 5120, 5120, 64)])
+def test_backward_needs_no_room_for_a_recomputed_activation(rules, T, d_out, d_in, R):
+    """s*U that is recomputed beside dU takes the room of the gradients: sizes that a program keeps stay enough."""
+    splits = rules.L["_ZN6qblora11grad_splitsElii"]
+    splits.argtypes, splits.restype = [C.c_int64, C.c_int, C.c_int], C.c_int
+    rows = {}
+    for name, sym in (("dense", "_ZN6qblora15dense_part_rowsEliii"), ("narrow", "_ZN6qblora16skinny_part_rowsElii")):
+        rows[name] = rules.L[sym]
+        rows[name].argtypes, rows[name].restype = [C.c_int64] + [C.c_int] * (3 if name == "dense" else 2), C.c_int64
+    q = _weight(rules.qb, d_out, d_in)
+    ad = rules.qb.CAdapter()
+    ad.lambda1, ad.lambda2, ad.R, ad.s, ad.A, ad.B = 2, 2, R, 1.0, 0x1000, 0x1000
+    part = max(4 * rows["dense"](T, d_in, d_out, R) * d_in, 4 * splits(T, d_in, 1) * d_in * R,
+               4 * R * max(rows["narrow"](T, R, d_in), rows["narrow"](T, R, d_out)))
+    buffers = [2 * d_out * d_in, 2 * R * d_in, 2 * R * d_out, *[2 * T * R] * 5, part, 4 * splits(T, d_out, 1) * d_out * R]
+    need = rules.L.qblora_linear_bwd_workspace_bytes(C.byref(q), C.byref(ad), T)
+    assert need == sum((b + 255) // 256 * 256 for b in buffers)

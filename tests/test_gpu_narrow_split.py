@@ -12,6 +12,7 @@ CASES = [
     (130, 2688, 2176, 24, 1),      # expanded operand, ragged tokens and columns
     (300, 4096, 2048, 136, 4),     # three column tiles; the forward's partial sums fill part of Y only
     (1, 2048, 3072, 8, 2),         # one token
+    (200, 64, 3072, 16, 2),        # more partial sums of s*U than dB has
 ]
 
 
