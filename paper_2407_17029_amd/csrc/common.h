@@ -235,6 +235,8 @@ int launch_tile_product(const qblora_bf16* A, const qblora_bf16* B, int rows, in
 // A quantized layer without adapter for 1 <= T <= 64 tokens (w4rows.hip): codes, scales and offsets row-major or in the
 // pack's order (tiled, with regrouped nibbles for INT4 models in 64-blocks)
 bool w4_rows_applies(int d_out, int d_in, int T);
+// its groups of 16 output rows per workgroup; table: codes are looked up in LDS (any codebook but packed or converted INT4)
+int w4_row_groups(int d_out, int d_in, int T, bool table);
 int launch_w4_rows(const uint8_t* codes, const float* scales, const float* beta, const Codebook& cb, int tiled, int d_out,
                    int d_in, const qblora_bf16* X, int T, qblora_bf16* Y, hipStream_t st, int block_rows = 1,
                    int regrouped = 0, int block_cols = 8);

@@ -17,7 +17,7 @@
 // with stages of its own, so that there is no barrier in the loop and no partial tile leaves the workgroup (slices of the
 // input dimension over workgroups cost a second launch and, at 48 tokens of 11008 x 4096, 34 MB of partial sums beside 30 MB
 // of model).  A stage is free as soon as its operands are in registers, so the next fetch goes out in front of the
-// arithmetic; kDepth blocks per wave are in flight.  4, 12 or 16 waves: the same times.  RG: see launch_w4_rows.
+// arithmetic; kDepth blocks per wave are in flight.  4, 12 or 16 waves: the same times.  RG: see w4_row_groups.
 //
 // us against the forms before (a streaming kernel up to 16 tokens, slices above), weights rotated through HBM:
 //   packed INT4      22016 x 8192   1 token  22.2 -> 19.7, 16 tokens 27.4 -> 21.6, 64 tokens 48.1 -> 36.8
@@ -36,7 +36,7 @@ namespace {
 
 constexpr int kWaves = 8;
 constexpr int kThreads = 64 * kWaves;
-constexpr int kTableReplicas = 8, kPairReplicas = 16;
+constexpr int kTableReplicas = 8, kPairReplicas = 16;      // two threads write a byte's
 constexpr int kSumTiles = 12;                   // 16 x 16 output tiles whose partial sums cross LDS together
 
 struct RowsDesc {
@@ -49,6 +49,7 @@ struct RowsDesc {
 };
 
 typedef __attribute__((ext_vector_type(2))) float f32x2;
+template <int V> struct Int { static constexpr int value = V; };
 
 __device__ __forceinline__ uint32_t lds_address(const void* p) {
     return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void*)p;
@@ -88,8 +89,13 @@ struct Stage {
     static constexpr int kTokens = kCopies ? 0 : kCodes + (kCodeChunks + 2 * kParamChunks) * 16;
     static constexpr int kBytes = kCodes + kGathers * 1024 + kGathers4 * 256;
     static constexpr int kOps = kCopies + kGathers + kGathers4;       // vector-memory operations
-    static constexpr int kStages = (160 * 1024 - TABLE) / (kWaves * kBytes);
-    static constexpr int kDepth = kStages > 4 ? 4 : kStages;               // blocks a wave has in flight
+    // Blocks a wave has in flight: up to four, but no more than leave a CU room for a second workgroup where that takes two
+    // or three.  A lone one hides neither its start nor its sum: 22016 x 4096 at 8 tokens, 3 KB a stage, 15.0 us with four
+    // in flight and 13.1 with three, 16384 x 8192 at 16 tokens 18.2 and 16.4; on at most 256 workgroups both are level.
+    static constexpr int kAlone = (160 * 1024 - TABLE) / (kWaves * kBytes), kPaired = (80 * 1024 - TABLE) / (kWaves * kBytes);
+    static constexpr int kStages = kPaired >= 2 ? kPaired : kAlone;
+    static constexpr int kDepth = kStages > 4 ? 4 : kStages;
+    static_assert(kPaired < 2 || kWaves * kDepth * kBytes + TABLE <= 80 * 1024, "two workgroups on a CU");
     static_assert(kDepth >= 1 && (kDepth - 1) * kOps < 64, "LDS; six bits of the wait counter");
 };
 
@@ -163,7 +169,7 @@ struct Feed {
         }
 #pragma unroll
         for (int j = 0; j < S::kGathers + S::kGathers4; ++j) {
-            src[j] += (uint64_t)step[j] * min(wave, blocks - 1);
+            src[j] += (uint64_t)step[j] * wave;
             step[j] *= kWaves;
         }
 #pragma unroll
@@ -172,19 +178,48 @@ struct Feed {
             x_off[j] = (uint32_t)((int64_t)min(row, d.T - 1) * d_in * 2 + chunk_in(row, lane & 7) * 16);
         }
     }
-    // fetches block i of the wave (i = 0, 1, 2, ... in turn) into a stage; past the end the last block again (never used)
+    // fetches block i of the wave (i = 0, 1, 2, ... in turn, below count) into a stage
     __device__ __forceinline__ void issue(int i, int stage) {
         const uint32_t to = lds + stage * S::kBytes;
 #pragma unroll
         for (int j = 0; j < S::kGathers; ++j) gather16_to_lds(src[j], to + S::kCodes + j * 1024);
 #pragma unroll
         for (int j = 0; j < S::kGathers4; ++j) gather4_to_lds(src[S::kGathers + j], to + S::kScales + j * 256);
-        if (i + 1 < count)
 #pragma unroll
-            for (int j = 0; j < S::kGathers + S::kGathers4; ++j) src[j] += step[j];
-        const int64_t b = min(wave + i * kWaves, blocks - 1);
+        for (int j = 0; j < S::kGathers + S::kGathers4; ++j) src[j] += step[j];
+        const int64_t b = wave + i * kWaves;
 #pragma unroll
         for (int j = 0; j < S::kCopies; ++j) copy16_to_lds(x + b * 128, x_off[j], to + j * 1024);
+    }
+    __device__ __forceinline__ void start() {
+#pragma unroll
+        for (int u = 0; u < S::kDepth; ++u)
+            if (u < count) issue(u, u);
+    }
+    // Walks the wave's blocks: block(stage, refill) reads a block's operands out of its stage, has it refilled and contracts
+    // them.  A block is in when only the operations of those fetched after it are outstanding; none is fetched past the end, which for short rows were
+    // more than all others (1024 inputs: two blocks a wave, four ahead of each).
+    template <typename Block>
+    __device__ __forceinline__ void walk(Block block) {
+        constexpr int D = S::kDepth;
+        int i = 0, stage = 0;
+        for (; i + D < count; ++i) {
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"((D - 1) * S::kOps) : "memory");
+            block(stage, [&]() __attribute__((always_inline)) { issue(i + D, stage); });
+            stage = stage + 1 == D ? 0 : stage + 1;
+        }
+        auto last = [&](auto left) __attribute__((always_inline)) {
+            if (count - i < left.value) return;
+            asm volatile("s_waitcnt vmcnt(%0)" :: "n"((left.value - 1) * S::kOps) : "memory");
+            block(stage, []() __attribute__((always_inline)) {});
+            stage = stage + 1 == D ? 0 : stage + 1;
+            ++i;
+        };
+        static_assert(D <= 4, "four calls");
+        if constexpr (D > 3) last(Int<4>{});
+        if constexpr (D > 2) last(Int<3>{});
+        if constexpr (D > 1) last(Int<2>{});
+        last(Int<1>{});
     }
 };
 
@@ -202,6 +237,18 @@ __device__ __forceinline__ f32x4 params_of(const unsigned char* p, int g, int r,
     }
 }
 
+// The two code values of byte v, out of scalar registers: a lookup in the kernel's arguments would be a vector load, and its
+// data are awaited behind all copies issued before it.
+__device__ __forceinline__ float2 codes_of(const Codebook& cb, int v) {
+    float2 e = make_float2(cb.c[0], cb.c[0]);
+#pragma unroll
+    for (int j = 1; j < 16; ++j) {
+        e.x = (v & 15) == j ? cb.c[j] : e.x;
+        e.y = (v >> 4) == j ? cb.c[j] : e.y;
+    }
+    return e;
+}
+
 // RG: groups of 16 output rows of a workgroup; TB: groups of 16 tokens, of which the first TX rows are there (TX <= 8:
 // one group); INT: the codebook is 0, 1, ..., 15 (and tile-ordered 64-blocks have their nibbles regrouped by the pack)
 template <int RG, int TX, int FORM, bool INT>
@@ -209,7 +256,6 @@ __global__ __launch_bounds__(kThreads) void k_w4_rows(RowsDesc d) {
     constexpr int TB = (TX + 15) / 16, kTable = INT ? 0 : 256 * kTableReplicas * (int)sizeof(float2);
     typedef Feed<RG, TX, FORM, kTable> F;
     typedef typename F::S S;
-    constexpr int DX = S::kDepth;
     extern __shared__ __align__(16) unsigned char smem[];
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int r = lane & 15, q = lane >> 4;
@@ -217,17 +263,19 @@ __global__ __launch_bounds__(kThreads) void k_w4_rows(RowsDesc d) {
     if (tile >= d.row_tiles) return;
     const int n0 = tile * (16 * RG);
 
-    float2* const sT = reinterpret_cast<float2*>(smem + kWaves * DX * S::kBytes);
-    if constexpr (!INT) {
-        for (int e = t; e < 256 * kTableReplicas; e += kThreads) {
-            const int v = e / kTableReplicas;
-            sT[e] = make_float2(d.cb.c[v & 15], d.cb.c[v >> 4]);
-        }
-    }
-    const float2* const my_table = sT + (lane & (kTableReplicas - 1));
-    unsigned char* const mine = smem + wave * DX * S::kBytes;
+    unsigned char* const mine = smem + wave * S::kDepth * S::kBytes;
     F feed;
     feed.init(d, n0, wave, lane, mine);
+    feed.start();
+    float2* const sT = reinterpret_cast<float2*>(smem + kWaves * S::kDepth * S::kBytes);
+    if constexpr (!INT) {                                                 // while the first blocks are on their way
+        const float2 e = codes_of(d.cb, t >> 1);
+        float4* const to = reinterpret_cast<float4*>(sT) + t * (kTableReplicas / 4);
+#pragma unroll
+        for (int u = 0; u < kTableReplicas / 4; ++u) to[u] = make_float4(e.x, e.y, e.x, e.y);
+        __syncthreads();
+    }
+    const float2* const my_table = sT + (lane & (kTableReplicas - 1));
     const int row = r & (TX - 1 < 15 ? TX - 1 : 15);                      // tokens past the end: any row (never stored)
     const int f_off = row * 128 + ((q ^ (row >> 1)) << 4);
 
@@ -267,12 +315,7 @@ __global__ __launch_bounds__(kThreads) void k_w4_rows(RowsDesc d) {
         for (int tb = 0; tb < TB; ++tb) acc[g][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     const bool has_beta = d.beta != nullptr;
-    if constexpr (!INT) __syncthreads();                                  // the table is complete
-#pragma unroll
-    for (int u = 0; u < DX; ++u) feed.issue(u, u);
-    int stage = 0;
-    for (int i = 0; i < feed.count; ++i) {
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((DX - 1) * S::kOps) : "memory");       // block i is in
+    feed.walk([&](int stage, auto refill) __attribute__((always_inline)) {
         const unsigned char* const in = mine + stage * S::kBytes;
         bf16x8 xf[2][TB];
         uint2 cw[RG];
@@ -289,8 +332,8 @@ __global__ __launch_bounds__(kThreads) void k_w4_rows(RowsDesc d) {
 #pragma unroll
             for (int tb = 0; tb < TB; ++tb) xf[m][tb] = *reinterpret_cast<const bf16x8*>(in + S::kTokens + tb * 2048 + (f_off ^ (m << 6)));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                // all of it is in registers: the stage is free
-        feed.issue(i + DX, stage);
-        stage = stage + 1 == DX ? 0 : stage + 1;
+        refill();
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int g = 0; g < RG; ++g)
 #pragma unroll
@@ -299,8 +342,7 @@ __global__ __launch_bounds__(kThreads) void k_w4_rows(RowsDesc d) {
 #pragma unroll
                 for (int tb = 0; tb < TB; ++tb) acc[g][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf, xf[m][tb], acc[g][tb], 0, 0, 0);
             }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                      // the look-ahead operations
+    });
 
     // ---- the waves' sums, added in wave order: the lane holds token 16 tb + r, rows 16 g + 4 q .. + 3 ------------------
     float* const red = reinterpret_cast<float*>(smem);
@@ -341,7 +383,6 @@ __global__ __launch_bounds__(kThreads) void k_w4_sums(RowsDesc d) {
     constexpr int NE = TX < 4 ? TX : 4;                                   // sums of the lane that belong to tokens
     typedef Feed<RG, TX, FORM, kTable> F;
     typedef typename F::S S;
-    constexpr int DX = S::kDepth;
     extern __shared__ __align__(16) unsigned char smem[];
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int r = lane & 15, q = lane >> 4;
@@ -349,17 +390,20 @@ __global__ __launch_bounds__(kThreads) void k_w4_sums(RowsDesc d) {
     if (tile >= d.row_tiles) return;
     const int n0 = tile * (16 * RG);
 
-    uint32_t* const sT = reinterpret_cast<uint32_t*>(smem + kWaves * DX * S::kBytes);
-    if constexpr (!REGROUPED) {
-        for (int e = t; e < 256 * kPairReplicas; e += kThreads) {
-            const int v = e / kPairReplicas;
-            sT[e] = pack_bf16(d.cb.c[v & 15], d.cb.c[v >> 4]);
-        }
-    }
-    const uint32_t* const my_table = sT + (lane & (kPairReplicas - 1));
-    unsigned char* const mine = smem + wave * DX * S::kBytes;
+    unsigned char* const mine = smem + wave * S::kDepth * S::kBytes;
     F feed;
     feed.init(d, n0, wave, lane, mine);
+    feed.start();
+    uint32_t* const sT = reinterpret_cast<uint32_t*>(smem + kWaves * S::kDepth * S::kBytes);
+    if constexpr (!REGROUPED) {                                           // while the first blocks are on their way
+        const float2 c = codes_of(d.cb, t >> 1);
+        const uint32_t e = pack_bf16(c.x, c.y);
+        uint4* const to = reinterpret_cast<uint4*>(sT) + t * (kPairReplicas / 8);
+#pragma unroll
+        for (int u = 0; u < kPairReplicas / 8; ++u) to[u] = make_uint4(e, e, e, e);
+        __syncthreads();
+    }
+    const uint32_t* const my_table = sT + (lane & (kPairReplicas - 1));
     const int row = r & (TX - 1);
     const int f_off = row * 128 + ((q ^ (row >> 1)) << 4);
     // in registers the compiler cannot see through: one and-or per operand dword (its encoding holds no two literals)
@@ -384,12 +428,7 @@ __global__ __launch_bounds__(kThreads) void k_w4_sums(RowsDesc d) {
 
     const bool has_beta = d.beta != nullptr;
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-    if constexpr (!REGROUPED) __syncthreads();                            // the table is complete
-#pragma unroll
-    for (int u = 0; u < DX; ++u) feed.issue(u, u);
-    int stage = 0;
-    for (int i = 0; i < feed.count; ++i) {
-        asm volatile("s_waitcnt vmcnt(%0)" :: "n"((DX - 1) * S::kOps) : "memory");       // block i is in
+    feed.walk([&](int stage, auto refill) __attribute__((always_inline)) {
         const unsigned char* const in = mine + stage * S::kBytes;
         bf16x8 xf[2];
         uint2 cw[RG];
@@ -404,8 +443,8 @@ __global__ __launch_bounds__(kThreads) void k_w4_sums(RowsDesc d) {
 #pragma unroll
         for (int m = 0; m < 2; ++m) xf[m] = *reinterpret_cast<const bf16x8*>(in + S::kTokens + (f_off ^ (m << 6)));
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");                // all of it is in registers: the stage is free
-        feed.issue(i + DX, stage);
-        stage = stage + 1 == DX ? 0 : stage + 1;
+        refill();
+        __builtin_amdgcn_sched_barrier(0);
         f32x4 xs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[0], ones, zero, 0, 0, 0);
         xs = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf[1], ones, xs, 0, 0, 0);
 #pragma unroll
@@ -416,8 +455,7 @@ __global__ __launch_bounds__(kThreads) void k_w4_sums(RowsDesc d) {
 #pragma unroll
             for (int e = 0; e < NE; ++e) acc[g][e] = __fmaf_rn(bs, xs[e], __fmaf_rn(a[g], s[e], acc[g][e]));
         }
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");                      // the look-ahead operations
+    });
 
     // ---- the waves' sums, added in wave order: the lane holds row 16 g + r, tokens 4 q .. + 3 ---------------------------
     float* const red = reinterpret_cast<float*>(smem);                    // [row group][wave][token of four][lane]
@@ -483,19 +521,27 @@ bool int_codebook(const Codebook& cb) {
 
 enum Blocks { BLOCKS_ROW64, BLOCKS_TILE64, BLOCKS_REGROUPED64, BLOCKS_8X8, BLOCKS_8X8_ANY, BLOCKS_8X4 };
 
+// (what row_groups never asks for is not built)
+template <int RG, int TX, int FORM>
+int launch_either(const RowsDesc& d, bool ints, hipStream_t st) {
+    if (ints) return launch_rows<RG, TX, FORM, true>(d, st);
+    if constexpr (RG < 6 || TX > 8) return launch_rows<RG, TX, FORM, false>(d, st);
+    return QBLORA_ERR_UNSUPPORTED;
+}
+
 template <int RG, int TX>
 int launch_rows_form(const RowsDesc& d, Blocks form, bool ints, hipStream_t st) {
     switch (form) {
-        case BLOCKS_8X4: return ints ? launch_rows<RG, TX, TILE84, true>(d, st) : launch_rows<RG, TX, TILE84, false>(d, st);
-        case BLOCKS_8X8: return ints ? launch_rows<RG, TX, TILE8, true>(d, st) : launch_rows<RG, TX, TILE8, false>(d, st);
+        case BLOCKS_8X4: return launch_either<RG, TX, TILE84>(d, ints, st);
+        case BLOCKS_8X8: return launch_either<RG, TX, TILE8>(d, ints, st);
         case BLOCKS_8X8_ANY:
-            if constexpr (TX <= 16) return ints ? launch_rows<RG, TX, TILE8_ANY, true>(d, st) : launch_rows<RG, TX, TILE8_ANY, false>(d, st);
+            if constexpr (TX <= 16) return launch_either<RG, TX, TILE8_ANY>(d, ints, st);
             else return QBLORA_ERR_SHAPE;
         default: break;
     }
     if constexpr (TX > 16) {
         switch (form) {
-            case BLOCKS_ROW64: return ints ? launch_rows<RG, TX, ROW64, true>(d, st) : launch_rows<RG, TX, ROW64, false>(d, st);
+            case BLOCKS_ROW64: return launch_either<RG, TX, ROW64>(d, ints, st);
             case BLOCKS_TILE64: return launch_rows<RG, TX, TILE64, false>(d, st);
             default: return launch_rows<RG, TX, TILE64, true>(d, st);
         }
@@ -505,11 +551,9 @@ int launch_rows_form(const RowsDesc& d, Blocks form, bool ints, hipStream_t st) 
 
 template <int RG, int TX>
 int launch_sums_form(const RowsDesc& d, Blocks form, hipStream_t st) {
-    switch (form) {
-        case BLOCKS_ROW64: return launch_sums<RG, TX, ROW64, false>(d, st);
-        case BLOCKS_TILE64: return launch_sums<RG, TX, TILE64, false>(d, st);
-        default: return launch_sums<RG, TX, TILE64, true>(d, st);
-    }
+    if (form == BLOCKS_REGROUPED64) return launch_sums<RG, TX, TILE64, true>(d, st);
+    if constexpr (RG < 6 || TX > 8) return form == BLOCKS_ROW64 ? launch_sums<RG, TX, ROW64, false>(d, st) : launch_sums<RG, TX, TILE64, false>(d, st);
+    return QBLORA_ERR_UNSUPPORTED;
 }
 
 template <int RG>
@@ -517,7 +561,8 @@ int launch_rg(const RowsDesc& d, Blocks form, hipStream_t st) {
     const bool ints = int_codebook(d.cb);
     const int T = d.T;
     if (T <= 16 && form <= BLOCKS_REGROUPED64) {
-        if (T == 1) return launch_sums_form<RG, 1>(d, form, st);
+        if constexpr (RG < 6)
+            if (T == 1) return launch_sums_form<RG, 1>(d, form, st);
         if (T <= 4) return launch_sums_form<RG, 4>(d, form, st);
         return T <= 8 ? launch_sums_form<RG, 8>(d, form, st) : launch_sums_form<RG, 16>(d, form, st);
     }
@@ -529,17 +574,26 @@ int launch_rg(const RowsDesc& d, Blocks form, hipStream_t st) {
 
 }  // namespace
 
-// Row groups of a workgroup: the fewest rounds of the chip, each as long as its rows (the arithmetic of 16 rows costs 1.5 us
-// per 4096 inputs) and its tokens (fetched once per workgroup).  us of 1 / 2 / 3 / 4 / 6 groups: 11008 x 4096 at 48 tokens
-// 27.4 / 21.7 / 14.1 / 15.4 / 18.6 (3: 230 workgroups), 4096 x 4096 8.7 / 9.3 / 10.6 / 12.4 / 16.4, 22016 x 8192 at 64 tokens
-// 81 / 50 / 41 / 48 / 37.  One token: stages are small enough for several workgroups on a CU, and six groups are not ahead
-// (22016 x 8192 19.1 / 19.9 / 19.7 / 23.8 / 21.3).
-static int row_groups(int d_out, int T) {
-    const int tokens = T <= 16 ? 1 : (T + 15) / 16;
+// Codes through the table in LDS rather than by conversion.
+static bool reads_table(const Codebook& cb, int tiled, int regrouped, int block_rows, int T) {
+    return block_rows != 8 && (tiled || T <= 16) ? !regrouped : !int_codebook(cb);
+}
+
+// Row groups of a workgroup: the fewest rows on the fullest CU, rounds of 256 workgroups times the rows of one, and of equal
+// ones the fewest rounds, since every round starts, fetches its tokens and sums once.  us of 1 / 2 / 3 / 4 / 6 groups, packed
+// INT4: 11008 x 4096 at 48 tokens 20.4 / 16.9 / 11.4 / 12.8 / 16.9 (3: 230 workgroups), 4096 x 4096 8.5 / 9.3 / 10.2 / 11.8 /
+// 16.5, 22016 x 8192 at 64 tokens 104 / 63 / 48 / 52 / 39.  What departs from it, up to 16 tokens:
+//   six groups, one workgroup on a CU, are behind on short rows (22016 rows at 8 tokens: 1024 inputs 7.4 / 6.7 / 6.0 / 6.5 / 6.6,
+//   4096 14.1 / 13.0 / 12.4 / 14.4 / 12.7, 13824 49.4 / 40.8 / 38.0 / 43.4 / 35.3), at one token (level: 22016 x 8192 22.8 / 22.3 /
+//   22.7 / 26.6 / 22.1) and, up to 8 tokens, beside a table in LDS (codebook 22016 x 8192 29.3 / 26.1 / 24.4 / 32.1 / 26.9);
+//   at one token many small workgroups hide the table (codebook 19200 x 4096 12.7 / 15.0 / 14.4 / 17.4 / 14.6; row-major 22016 x
+//   8192 28.4 / 32.3 / 35.5 / 43.9 / 36.3), unless rows are short (16384 x 1024 5.2 / 4.9 / 5.4 / 4.7 / 5.8).
+int w4_row_groups(int d_out, int d_in, int T, bool table) {
     int groups = 1, best = 0;
     for (const int c : {1, 2, 3, 4, 6}) {
-        if (T == 1 && c == 6) break;
-        const int cost = (((d_out + 16 * c - 1) / (16 * c) + 255) / 256) * (2 * c + 2 * tokens - 1);
+        if (c == 6 && T <= 16 && (T == 1 || (table ? T <= 8 : d_in <= 4096))) break;
+        const bool small = table && T == 1 && d_in > 2048;
+        const int cost = (((d_out + 16 * c - 1) / (16 * c) + 255) / 256) * (2 * c + (small ? 0 : 1));
         if (best == 0 || cost < best) { groups = c; best = cost; }
     }
     return groups;
@@ -552,7 +606,7 @@ static int row_groups(int d_out, int T) {
 bool w4_rows_applies(int d_out, int d_in, int T) {
     if (T > 64) return false;
     if (T <= 32) return true;
-    const int groups = row_groups(d_out, T);
+    const int groups = w4_row_groups(d_out, d_in, T, false);
     if (groups == 1) return (int64_t)(T <= 48 ? 48 : 64) * d_in <= 640 * 1024;
     return groups > 2 || T <= 48 || d_in <= 10 * 1024;
 }
@@ -571,7 +625,7 @@ int launch_w4_rows(const uint8_t* codes, const float* scales, const float* beta,
     const bool any = ((reinterpret_cast<uintptr_t>(scales) | reinterpret_cast<uintptr_t>(beta)) & 15) != 0;
     const Blocks form = block_rows == 8 ? (block_cols == 4 ? BLOCKS_8X4 : any ? BLOCKS_8X8_ANY : BLOCKS_8X8)
                         : regrouped ? BLOCKS_REGROUPED64 : tiled ? BLOCKS_TILE64 : BLOCKS_ROW64;
-    switch (row_groups(d_out, T)) {
+    switch (w4_row_groups(d_out, d_in, T, reads_table(cb, tiled, regrouped, block_rows, T))) {
         case 1: return launch_rg<1>(d, form, st);
         case 2: return launch_rg<2>(d, form, st);
         case 3: return launch_rg<3>(d, form, st);
