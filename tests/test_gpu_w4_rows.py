@@ -30,6 +30,9 @@ def _case(oracle, codebook, seed, T, d_out, d_in, fmt):
     (1, 8, 64), (1, 4104, 192), (2, 8200, 64), (4, 12296, 128), (5, 104, 576), (8, 16392, 64), (9, 24584, 64), (16, 40, 1024),
     (17, 4088, 192), (32, 4104, 64), (33, 8184, 64), (48, 8200, 448), (49, 12296, 64), (64, 16376, 64), (64, 16392, 128),
     (64, 72, 576), (40, 24568, 64),
+    # more blocks than a wave has in flight, a ragged number of them, in every number of row groups
+    (1, 4104, 2624), (2, 24584, 704), (8, 6152, 2624), (12, 18440, 1600), (16, 9224, 2368), (24, 4088, 2624), (32, 12296, 1600),
+    (48, 8200, 2112), (40, 12296, 1344), (33, 16392, 1088), (64, 16376, 1600), (64, 24584, 1088), (48, 20488, 1344),
 ])
 def test_edges(oracle, codebook, T, d_out, d_in, fmt):
     from gpu_util import assert_close_bf16
