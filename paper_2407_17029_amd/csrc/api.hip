@@ -1045,7 +1045,6 @@ int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblor
         return QBLORA_ERR_SHAPE;
     hipStream_t st = as_stream(stream);
     const bool mid = T > kDecodeMaxTokens || half_blocks(qw);   // contracts the bf16 compute weight whatever the block shape
-    const bool rows = w4_rows_applies(qw->d_out, qw->d_in, T);  // one launch that leaves the workspace's partial sums unused
     const size_t scale_bytes = qblora_linear_decode_workspace_bytes(qw);
     // the mid-batch kernel's token rows have 32-bit offsets: a batch of 4 GiB goes in two halves
     const int32_t chunk = (int64_t)T * qw->d_in * (int64_t)sizeof(qblora_bf16) >= (int64_t)1 << 32 ? kMidMaxTokens / 2 : kMidMaxTokens;
@@ -1063,6 +1062,8 @@ int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblor
     const float* scales = nullptr;
     const float* beta = qw->beta;
     const int regrouped = pack ? decode_regrouped(qw) : 0;
+    const bool table = w4_reads_table(codebook_of(qw), pack ? 1 : 0, regrouped, block_rows_of(qw), T);
+    const bool rows = w4_rows_applies(qw->d_out, qw->d_in, T, table, pack != nullptr);  // leaves the room for partial sums unused
     if (pack) {
         DecodePack p = carve_pack(qw, const_cast<void*>(pack));
         codes = p.codes; scales = p.scales; beta = p.beta;

@@ -234,13 +234,15 @@ int launch_merge_bf16(const MergeDesc& d, hipStream_t st);
 int launch_tile_product(const qblora_bf16* A, const qblora_bf16* B, int rows, int cols, int R, float* H, hipStream_t st);
 // A quantized layer without adapter for 1 <= T <= 64 tokens (w4rows.hip): codes, scales and offsets row-major or in the
 // pack's order (tiled, with regrouped nibbles for INT4 models in 64-blocks)
-bool w4_rows_applies(int d_out, int d_in, int T);
-// its groups of 16 output rows per workgroup; table: codes are looked up in LDS (any codebook but packed or converted INT4)
+bool w4_rows_applies(int d_out, int d_in, int T, bool table, bool tiled);
+// whether it looks codes up in LDS: any codebook but 0, 1, ..., 15 where those are converted
+bool w4_reads_table(const Codebook& cb, int tiled, int regrouped, int block_rows, int T);
+// its groups of 16 output rows per workgroup
 int w4_row_groups(int d_out, int d_in, int T, bool table);
 int launch_w4_rows(const uint8_t* codes, const float* scales, const float* beta, const Codebook& cb, int tiled, int d_out,
                    int d_in, const qblora_bf16* X, int T, qblora_bf16* Y, hipStream_t st, int block_rows = 1,
                    int regrouped = 0, int block_cols = 8);
-// The same layer for 33 <= T <= 256 tokens, in one launch, on the bf16 compute weight (w4mid.hip); `part` holds
+// The same layer for 17 <= T <= 256 tokens, in one launch, on the bf16 compute weight (w4mid.hip); `part` holds
 // w4_mid_part_bytes() bytes of split-K partial tiles (may be NULL when that is 0)
 int w4_mid_splits(int d_out, int d_in, int T);
 size_t w4_mid_part_bytes(int d_out, int d_in, int T);

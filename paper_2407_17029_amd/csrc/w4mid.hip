@@ -8,7 +8,7 @@
 // of codes + the block parameters per weight) sets the time and at 128 tokens the MFMAs do.  A token tile of
 // 256 (the training kernel) would waste most of its MFMAs here and, with one workgroup per 256 output rows,
 // leave most of the chip idle.  Here a workgroup of 4 waves owns 128 output rows (32 per wave), ALL tokens
-// (32 * TB of them, TB = 2 .. 8) and one slice of the input dimension; the slices of a row tile (split-K, as
+// (32 * TB of them, TB = 1 .. 8) and one slice of the input dimension; the slices of a row tile (split-K, as
 // many as one round of workgroups holds, see call_splits) write fp32 partial tiles that a second kernel adds in
 // slice order (deterministic).
 //
@@ -423,8 +423,9 @@ int launch_tb(const MidDesc& d, unsigned blocks, hipStream_t st, int form, int b
 namespace {
 
 // 32-token blocks of a workgroup: as many as there are (with two, four, six or eight of them alone 201 tokens of 5120 x
-// 13824 took 48.0 us instead of 45.1, 129 of 22016 x 8192 88.7 instead of 74.5)
-int token_blocks(int T) { return T <= 64 ? 2 : (T + 31) / 32; }
+// 13824 took 48.0 us instead of 45.1, 129 of 22016 x 8192 88.7 instead of 74.5; with two codebook weights of 19200 x 13824
+// take 49.2 at 17 tokens, with one 47.5)
+int token_blocks(int T) { return (T + 31) / 32; }
 
 // no empty slice, at least 4 steps each
 int slices_of(int want, int steps) {
@@ -479,6 +480,7 @@ int launch_w4_mid(const uint8_t* codes, const float* scales, const float* beta, 
     const unsigned blocks = (unsigned)(((d_out + kMidRows - 1) / kMidRows) * splits);
     int rc;
     switch (token_blocks(T)) {
+        case 1: rc = launch_tb<1>(d, blocks, st, form, block_rows, block_cols); break;
         case 2: rc = launch_tb<2>(d, blocks, st, form, block_rows, block_cols); break;
         case 3: rc = launch_tb<3>(d, blocks, st, form, block_rows, block_cols); break;
         case 4: rc = launch_tb<4>(d, blocks, st, form, block_rows, block_cols); break;

@@ -574,8 +574,7 @@ int launch_rg(const RowsDesc& d, Blocks form, hipStream_t st) {
 
 }  // namespace
 
-// Codes through the table in LDS rather than by conversion.
-static bool reads_table(const Codebook& cb, int tiled, int regrouped, int block_rows, int T) {
+bool w4_reads_table(const Codebook& cb, int tiled, int regrouped, int block_rows, int T) {
     return block_rows != 8 && (tiled || T <= 16) ? !regrouped : !int_codebook(cb);
 }
 
@@ -599,16 +598,25 @@ int w4_row_groups(int d_out, int d_in, int T, bool table) {
     return groups;
 }
 
-// Whether this form is the faster one: a workgroup fetches all tokens for its rows, so with few rows, many tokens and long
-// rows the sliced form with its 128-row workgroups (w4mid.hip) moves less.  us here / there: 64 tokens 4096 x 8192 17.6 / 18.9,
-// x 9728 20.1 / 19.5, x 13824 30.7 / 23.9; 5120 x 13824 34.3 / 31.5, 11008 x 13824 39.6 / 44.4; 33 tokens 4096 x 11008
-// 17.2 / 19.8, x 22016 32.8 / 28.2, 8192 x 22016 32.3 / 40.8; 17 tokens 4096 x 22016 23.1 / 24.8.
-bool w4_rows_applies(int d_out, int d_in, int T) {
+// Whether this form is the faster one.  A workgroup fetches all tokens for its rows, and their room in LDS is taken from the
+// codes in flight: with few rows to a workgroup, many tokens and long rows the sliced form (w4mid.hip), whose workgroups have 128
+// rows, is ahead, the earlier the further the weights come (from HBM, as layer after layer does; small layers that are called
+// again come from the memory-side cache).  us here / there from HBM, then from the cache: INT4 4096 x 8192 at 48 tokens 16.5 /
+// 15.8, 12.2 / 15.1, at 64 19.6 / 16.5, 14.4 / 16.0, 4096 x 13824 at 32 19.9 / 17.8, 14.9 / 17.0; 8192 x 13824 at 48 31.1 /
+// 29.9, 22.9 / 27.7, at 64 36.3 / 31.1, 26.9 / 29.1, 8192 x 22016 at 32 39.2 / 33.7, 38.7 / 33.4.  Codebooks hide more of it
+// behind their table (4096 x 13824 at 32 tokens 19.5 / 20.8, 15.6 / 20.2), but on tall layers in tile order the table itself is
+// the limit, which the sliced form reads once for 32 tokens and more: 19200 x 8192 at 17 tokens 34.2 / 30.1, 33.8 / 28.1, 19200 x
+// 13824 at 64 65.8 / 58.2, 66.9 / 58.3.  (Row-major codes: 19200 x 13824 at 17 tokens 71 / 69, all others ahead here.)  Of 6480
+// calls on 17 to 64 tokens from HBM, about 60 are left that the sliced form would serve more than 3 % faster, 12 % at most.
+bool w4_rows_applies(int d_out, int d_in, int T, bool table, bool tiled) {
     if (T > 64) return false;
-    if (T <= 32) return true;
-    const int groups = w4_row_groups(d_out, d_in, T, false);
-    if (groups == 1) return (int64_t)(T <= 48 ? 48 : 64) * d_in <= 640 * 1024;
-    return groups > 2 || T <= 48 || d_in <= 10 * 1024;
+    if (T <= 16) return true;
+    const int groups = w4_row_groups(d_out, d_in, T, table);
+    const int64_t tokens = (int64_t)(T <= 48 ? T : 64) * d_in;
+    if (groups == 1) return tokens <= (table ? 510 : 420) * 1024;
+    if (groups == 2) return tokens <= 680 * 1024;
+    if (!(table && tiled)) return true;
+    return groups == 6 && T <= 32 ? d_in < 4096 : (int64_t)groups * d_in < (T <= 32 ? 40 : 48) * 1024;
 }
 
 int launch_w4_rows(const uint8_t* codes, const float* scales, const float* beta, const Codebook& cb, int tiled, int d_out,
@@ -625,7 +633,7 @@ int launch_w4_rows(const uint8_t* codes, const float* scales, const float* beta,
     const bool any = ((reinterpret_cast<uintptr_t>(scales) | reinterpret_cast<uintptr_t>(beta)) & 15) != 0;
     const Blocks form = block_rows == 8 ? (block_cols == 4 ? BLOCKS_8X4 : any ? BLOCKS_8X8_ANY : BLOCKS_8X8)
                         : regrouped ? BLOCKS_REGROUPED64 : tiled ? BLOCKS_TILE64 : BLOCKS_ROW64;
-    switch (w4_row_groups(d_out, d_in, T, reads_table(cb, tiled, regrouped, block_rows, T))) {
+    switch (w4_row_groups(d_out, d_in, T, w4_reads_table(cb, tiled, regrouped, block_rows, T))) {
         case 1: return launch_rg<1>(d, form, st);
         case 2: return launch_rg<2>(d, form, st);
         case 3: return launch_rg<3>(d, form, st);

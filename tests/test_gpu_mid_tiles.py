@@ -1,5 +1,8 @@
-"""Inference on 65 to 256 tokens: every token tile at both of its ends, one to eight slices whose steps leave a remainder in
-the ring, ragged row tiles, and the three ways a code becomes a number (table, INT4, INT4 with regrouped nibbles)."""
+"""Inference on 65 to 256 tokens, and on fewer of few long rows: every token tile at both of its ends, one to eight slices whose
+steps leave a remainder in the ring, ragged row tiles, and the three ways a code becomes a number (table, INT4, INT4 with
+regrouped nibbles)."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -12,9 +15,13 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("T,d_out,d_in", [
     (65, 40, 64), (96, 136, 640), (97, 256, 1088), (128, 24, 2048), (129, 264, 448), (160, 8, 320), (161, 136, 192),
     (192, 128, 704), (193, 72, 2112), (224, 136, 256), (225, 40, 576), (256, 120, 832),
+    (17, 40, 40000), (32, 136, 21056), (33, 264, 21504), (50, 40, 14016), (64, 72, 13760),
 ])
-def test_token_tiles(oracle, codebook, T, d_out, d_in, fmt):
+def test_token_tiles(oracle, codebook, rules, T, d_out, d_in, fmt):
     from gpu_util import assert_close_bf16
+    rows = rules.L["_ZN6qblora15w4_rows_appliesEiiibb"]
+    rows.argtypes, rows.restype = [C.c_int, C.c_int, C.c_int, C.c_bool, C.c_bool], C.c_bool
+    assert not any(rows(d_out, d_in, T, table, True) for table in (False, True))
     print(f"case mid tiles T={T} {d_out}x{d_in} {fmt}", flush=True)
     qb, qw, X, ref = _case(oracle, codebook, 8200 + T + d_out, T, d_out, d_in, fmt)
     Y = torch.full((T + 1, d_out), 7.0, dtype=torch.bfloat16, device=X.device)
