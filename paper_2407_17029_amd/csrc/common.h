@@ -244,7 +244,8 @@ int launch_w4_rows(const uint8_t* codes, const float* scales, const float* beta,
                    int regrouped = 0, int block_cols = 8);
 // The same layer for 17 <= T <= 256 tokens, in one launch, on the bf16 compute weight (w4mid.hip); `part` holds
 // w4_mid_part_bytes() bytes of split-K partial tiles (may be NULL when that is 0)
-int w4_mid_splits(int d_out, int d_in, int T);
+int w4_mid_splits(int d_out, int d_in, int T);                    // the most slices of the input that a call takes
+int w4_mid_call_splits(int d_out, int d_in, int T, bool table);   // those that it takes
 size_t w4_mid_part_bytes(int d_out, int d_in, int T);
 int launch_w4_mid(const uint8_t* codes, const float* scales, const float* beta, const Codebook& cb, int tiled, int d_out,
                   int d_in, const qblora_bf16* X, int T, qblora_bf16* Y, float* part, hipStream_t st, int block_rows = 1,

@@ -9,7 +9,7 @@
 // 256 (the training kernel) would waste most of its MFMAs here and, with one workgroup per 256 output rows,
 // leave most of the chip idle.  Here a workgroup of 4 waves owns 128 output rows (32 per wave), ALL tokens
 // (32 * TB of them, TB = 1 .. 8) and one slice of the input dimension; the slices of a row tile (split-K, as
-// many as one round of workgroups holds, see call_splits) write fp32 partial tiles that a second kernel adds in
+// many as the chip takes at once, see w4_mid_call_splits) write fp32 partial tiles that a second kernel adds in
 // slice order (deterministic).
 //
 // A wave dequantizes its own MFMA operand in registers: lane l owns row (l & 31) and the 32 inputs
@@ -434,16 +434,6 @@ int slices_of(int want, int steps) {
     return (steps + per - 1) / per;
 }
 
-// The slices of a call.  A codebook in LDS wants two workgroups on a CU up to 128 tokens, which w4_mid_splits counts on;
-// without one a lone workgroup hides its expansion, and the partial tiles of more slices than one round of workgroups
-// holds only cost time.  us at 65 / 128 tokens with the slices for two workgroups and for one: 5120 x 13824 31.1 / 38.1
-// and 27.5 / 31.8, 8192 x 8192 28.8 / 36.2 and 23.6 / 30.1, 22016 x 8192 59.0 / 70.2 and 58.5 / 64.5; with the table
-// 22016 x 8192 57.6 / 69.1 and 68.1 / 71.4.
-int call_splits(int d_out, int d_in, int T, int form) {
-    const int tiles_n = (d_out + kMidRows - 1) / kMidRows;
-    return T > 64 && form != TABLE ? slices_of(256 / tiles_n, d_in / kBlock) : w4_mid_splits(d_out, d_in, T);
-}
-
 }  // namespace
 
 // The most slices of the input dimension.  Up to 128 tokens, measured over 2 / 3 / 4 waves per workgroup and 1 .. 8 slices
@@ -455,6 +445,25 @@ int call_splits(int d_out, int d_in, int T, int form) {
 int w4_mid_splits(int d_out, int d_in, int T) {
     const int tiles_n = (d_out + kMidRows - 1) / kMidRows, target = T > 64 ? 400 : 700;
     return slices_of(T > 128 ? 256 / tiles_n : (target + tiles_n / 2) / tiles_n, d_in / kBlock);
+}
+
+// The slices of a call.  A codebook in LDS wants two workgroups on a CU up to 128 tokens, which w4_mid_splits counts on.
+// Without one a lone workgroup hides its expansion nearly as well, so a step on two to a CU takes 1.6 times as long as on one,
+// and a slice costs its partial tiles, a step per 2000 outputs.  us of 1 / 2 / 3 / 4 / 5 / 6 slices, packed INT4: 8192 x 8192 at 65
+// tokens 54.9 / 34.1 / 26.9 / 23.3 / 27.2 / 26.3 (4: 256 workgroups), 5120 x 13824 88.7 / 50.3 / 36.3 / 29.8 / 26.2 / 24.1,
+// 11008 x 13824 91.2 / 54.3 / 57.6 / 48.1 / 43.7 / 50.5, 22016 x 13824 at 97 103.0 / 98.7 / 109.3 / 97.2 / 100.0 / 108.4.  The least
+// of this over the slices that the workspace counts on: over 1375 calls 0.7 % behind the best choice.
+int w4_mid_call_splits(int d_out, int d_in, int T, bool table) {
+    const int most = w4_mid_splits(d_out, d_in, T);
+    if (table || T <= 64 || T > 128) return most;
+    const int tiles_n = (d_out + kMidRows - 1) / kMidRows, steps = d_in / kBlock;
+    int splits = most, best = 0;
+    for (int want = 1; want <= most; ++want) {
+        const int s = slices_of(want, steps), per = (steps + s - 1) / s, blocks = tiles_n * s;
+        const int cost = per * (blocks <= 256 ? 10 : 16 * ((blocks + 511) / 512)) + (s > 1 ? s * d_out / 200 : 0);
+        if (best == 0 || cost < best) { splits = s; best = cost; }
+    }
+    return splits;
 }
 
 size_t w4_mid_part_bytes(int d_out, int d_in, int T) {
@@ -474,7 +483,7 @@ int launch_w4_mid(const uint8_t* codes, const float* scales, const float* beta, 
     bool whole_numbers = beta != nullptr;
     for (int j = 0; j < 16; ++j) whole_numbers &= cb.c[j] == (float)j;
     const int form = regrouped ? REGROUPED : whole_numbers ? INT4 : TABLE;
-    const int splits = call_splits(d_out, d_in, T, form), steps = d_in / kBlock;
+    const int splits = w4_mid_call_splits(d_out, d_in, T, form == TABLE), steps = d_in / kBlock;
     if (splits > 1 && !part) return QBLORA_ERR_WORKSPACE;
     MidDesc d{codes, scales, beta, cb, tiled, d_out, d_in, X, T, Y, part, splits, (steps + splits - 1) / splits};
     const unsigned blocks = (unsigned)(((d_out + kMidRows - 1) / kMidRows) * splits);

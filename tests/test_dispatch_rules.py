@@ -124,3 +124,22 @@ def test_form_of_up_to_64_tokens(rules, d_out, d_in, T, table, tiled, rows):
     f = rules.L["_ZN6qblora15w4_rows_appliesEiiibb"]
     f.argtypes, f.restype = [C.c_int, C.c_int, C.c_int, C.c_bool, C.c_bool], C.c_bool
     assert f(d_out, d_in, T, table, tiled) == rows
+
+
+@pytest.mark.parametrize("d_out,d_in,T,slices", [(8192, 8192, 96, 4), (11008, 13824, 65, 5), (22016, 13824, 97, 2), (11008, 4096, 65, 2)])
+def test_slices_of_65_to_128_tokens(rules, d_out, d_in, T, slices):
+    """INT4 11008 x 13824 at 65 tokens: 54.3 us in two slices, which one round of workgroups holds, 43.7 in five."""
+    call = rules.L["_ZN6qblora18w4_mid_call_splitsEiiib"]
+    call.argtypes, call.restype = [C.c_int, C.c_int, C.c_int, C.c_bool], C.c_int
+    assert call(d_out, d_in, T, False) == slices
+
+
+def test_no_call_takes_more_slices_than_its_workspace_counts_on(rules):
+    call, most = rules.L["_ZN6qblora18w4_mid_call_splitsEiiib"], rules.L["_ZN6qblora13w4_mid_splitsEiii"]
+    call.argtypes, call.restype = [C.c_int, C.c_int, C.c_int, C.c_bool], C.c_int
+    most.argtypes, most.restype = [C.c_int] * 3, C.c_int
+    for d_out in [8, 64, 1000, 4096, 8192, 11008, 16384, 22016, 50000]:
+        for d_in in [64, 192, 1024, 4096, 13824, 22016]:
+            for T in [17, 32, 64, 65, 96, 97, 128, 129, 192, 256]:
+                for table in (False, True):
+                    assert 1 <= call(d_out, d_in, T, table) <= most(d_out, d_in, T)
