@@ -69,6 +69,18 @@ def measured_valu(workload: str, kernel: str):
     return None
 
 
+def side_launches(ms, once):
+    """Adapter launches and passes over the weight of a projection, ms each, from the mean times of the event slots: {launch: ms}.
+    A pass over the weight shares its launch with the adapter's re-layouts (forward) or the reduction of the gradients' partial
+    sums (backward); the slots then bracket that same launch, which counts once and as the pass."""
+    adapter = {k: ms[k] for k in ("adapter_fwd", "adapter_bwd", "adapter_grads")}
+    passes = {k: ms[k] for k in ("dequant_fwd", "dequant_bwd") if once[k]}
+    for k, with_pass in (("prep", "dequant_fwd"), ("grad_reduce", "dequant_bwd")):
+        if not once[with_pass]:
+            adapter[k] = ms[k]
+    return adapter, passes
+
+
 class Stack:
     """Device state of one workload: per-projection weights, adapters, outputs; shared activations and scratch."""
 
@@ -311,6 +323,8 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
     fwd_flops = 2.0 * T * bp.d_in * bp.d_out + 2.0 * T * R * bp.d_out / lam
     bwd_flops = 2.0 * T * bp.d_in * bp.d_out + 2.0 * T * R * bp.d_in / lam
     n_w = bp.d_in * bp.d_out
+    adapter_elems = R * (bp.d_in + bp.d_out) / lam
+    scale_bytes = ((1 + 8 / 256) if wl.scale_mode else 4) / 64          # per weight, as the pass reads them
     quant_bytes = n_w * (4 + 0.5 + 4 / 64)
     merge_batch_bytes = sum(S.merge_bytes(st["p"]) for st in S.proj)
     achieved = fwd_flops / (gemm_ms("fwd_gemm") * 1e-3) / 1e12
@@ -347,16 +361,18 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
                          "achieved": round(bwd_flops / (gemm_ms("bwd_gemm") * 1e-3) / 1e12, 2), "unit": "TFLOP/s",
                          "frac": round(bwd_flops / (gemm_ms("bwd_gemm") * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4)},
             "quantize": hbm("quantize", quant_bytes),
-            "dequantize_once_fwd": (hbm("dequant_fwd", n_w * (0.5 + 4 / 64 + 2), "codes + scales -> bf16 weight in the workspace")
+            "dequantize_once_fwd": (hbm("dequant_fwd", n_w * (0.5 + scale_bytes + 2) + 4.0 * adapter_elems,
+                                        "codes + scales -> bf16 weight in the workspace, and A, B re-laid, in one launch")
                                     if once["dequant_fwd"] else None),
-            "dequantize_once_bwd": (hbm("dequant_bwd", n_w * (0.5 + 4 / 64 + 2), "the same, transposed, for the backward contraction")
+            "dequantize_once_bwd": ({"event_overhead_included": True, "ms": stats(raw["dequant_bwd"]),
+                                     "note": "the same, transposed, and the reduction of the gradients' partial sums, in one launch"}
                                     if once["dequant_bwd"] else None),
             "adapter_fwd_skinny": hbm("adapter_fwd", 2.0 * T * bp.d_in + 2.0 * T * R * 2, "s*U = (s/lambda) X A_x^T; reads X once"),
             "adapter_bwd_skinny": hbm("adapter_bwd", 2.0 * T * bp.d_out + 2.0 * T * R * 3, "dU = s dY B_x^T; reads dY once"),
             "adapter_grads": hbm("adapter_grads", 2.0 * T * (bp.d_in + bp.d_out) + 8.0 * T * R,
                                  "token contractions behind dA and dB, one launch; partial-sum writes not counted"),
-            "grad_reduce": {"ms": stats(raw["grad_reduce"])},
-            "prep": {"ms": stats(raw["prep"])},
+            "grad_reduce": None if once["dequant_bwd"] else {"ms": stats(raw["grad_reduce"])},
+            "prep": None if once["dequant_fwd"] else {"ms": stats(raw["prep"])},
             "merge_requant_batch": hbm("merge", merge_batch_bytes,
                                        f"the requantizing merge of all {len(S.proj)} projections of the layer, one launch"),
             "tile_products": {"ms": stats(raw["tile_product"]),
@@ -372,10 +388,10 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
         v = measured_valu(wl.name, k)
         if v and out["kernels"].get(key):
             out["kernels"][key].update(v)
-    adapter_ms = sum(float(np.mean(raw[k])) for k in ("adapter_fwd", "adapter_bwd", "adapter_grads", "grad_reduce", "prep"))
-    dq_ms = float(np.mean(raw["dequant_fwd"])) + float(np.mean(raw["dequant_bwd"]))
-    proj_ms = adapter_ms + gemm_ms("fwd_gemm") + gemm_ms("bwd_gemm") + float(np.mean(raw["quantize"])) + dq_ms
-    # the contraction with its share of the one-off dequantize pass, as one figure per direction
+    adapter, passes = side_launches({k: float(np.mean(v)) for k, v in raw.items()}, once)
+    adapter_ms = sum(adapter.values())
+    proj_ms = adapter_ms + gemm_ms("fwd_gemm") + gemm_ms("bwd_gemm") + float(np.mean(raw["quantize"])) + sum(passes.values())
+    # the contraction with the launch of the one-off dequantize pass, as one figure per direction
     for key, gk, dk, fl in (("fwd_gemm_with_dequantize", "fwd_gemm", "dequant_fwd", fwd_flops),
                             ("bwd_gemm_with_dequantize", "bwd_gemm", "dequant_bwd", bwd_flops)):
         ms = gemm_ms(gk) + float(np.mean(raw[dk]))
