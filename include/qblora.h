@@ -84,8 +84,8 @@ enum { QBLORA_MERGE_BETA_SHIFT = 0, QBLORA_MERGE_REQUANT_MINMAX = 1 };
  *              i*(d_in/4) + j.  Taken by the quantizers, qblora_dequantize_bf16, the forward / backward calls of both
  *              adapter forms at any token count (they dequantize the weight once per call into the workspace, as
  *              calls on many tokens do -- the workspace sizes say so), the three merges (offset shift: 4 | lambda1
- *              and 8 | lambda2) and qblora_linear_decode (at every token count the kernel of the mid-batch form,
- *              i.e. bf16(fma(c, alpha, beta)) contracted; workspace from qblora_linear_decode_tokens_workspace_bytes).
+ *              and 8 | lambda2) and qblora_linear_decode (at every token count bf16(fma(c, alpha, beta)) contracted;
+ *              workspace from qblora_linear_decode_tokens_workspace_bytes).
  *              qblora_linear_fwd_noalloc returns QBLORA_ERR_UNSUPPORTED for them.
  *   codes_tiled optional second copy of the codes (NULL = absent) in the order the forward kernel
  *              streams them, qblora_codes_tiled_bytes() bytes: output rows in tiles of 256, and for
@@ -360,15 +360,18 @@ int qblora_merge_bf16(const qblora_qweight* base, const float* H, int32_t lambda
  * 16 < T <= 256 (mid batch: prefill chunks, batched decode):
  *   Y[t,n] = sum_k X[t,k] * bf16( c[code[n,k]] * alpha (+ beta) ),
  * the arithmetic of qblora_linear_fwd without adapter (Eq. 1 rounded once to the bf16 compute weight, fp32
- * accumulation), on token tiles of 32 / 64 / 128 / 192 / 256 with the input dimension split over workgroups; the fp32
- * partial tiles of the splits are added in a fixed order (reproducible bit for bit).
+ * accumulation).  Up to 64 tokens a workgroup mostly walks its rows' whole input; otherwise the input dimension is split
+ * over workgroups, on token tiles in steps of 32, and the fp32 partial tiles are added in a fixed order.  A repeated call
+ * repeats its bits.
  *   X bf16 [T, d_in], 16-byte aligned; Y bf16 [T, d_out], fully overwritten.
  *   workspace: T <= 16: qblora_linear_decode_workspace_bytes() bytes (non-zero only for grouped scales, and
  *   not needed with a pack); T > 16: qblora_linear_decode_tokens_workspace_bytes(qw, T) bytes, 16-byte aligned
  *   (the former plus the partial tiles; the size for T serves every smaller batch of the weight too).
+ *   The sizes hold for every form that a call of so many tokens may take; one that needs no partial tiles asks for
+ *   them all the same.
  * T = 0 is a no-op; T > 256 is QBLORA_ERR_SHAPE (use qblora_linear_fwd).  With T <= 16 a weight whose codes take
- * 2 GB or more (d_out rounded up to 256, times d_in / 2) is QBLORA_ERR_UNSUPPORTED: the kernel addresses them with
- * 32-bit offsets.
+ * 2 GB or more (d_out rounded up to 256, times d_in / 2) is QBLORA_ERR_UNSUPPORTED, a limit that is kept although the
+ * kernel has 64-bit addresses.
  */
 size_t qblora_linear_decode_workspace_bytes(const qblora_qweight* qw);
 size_t qblora_linear_decode_tokens_workspace_bytes(const qblora_qweight* qw, int32_t T);
@@ -381,7 +384,7 @@ int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblor
  * fp32 block scales (grouped scales are reconstructed) and the offsets in tile order (rows in tiles of
  * 256; the values of one block for the rows of a tile are adjacent), so that a wave's load of one block
  * for 16 rows touches 5 cache lines instead of 32.  qblora_linear_decode with pack = NULL reads the
- * row-major arrays of `qw` (the same sums, 2-3 times slower on large layers); with a pack a call of at most
+ * row-major arrays of `qw` (the same sums, 1.2 to 2.4 times slower on large layers); with a pack a call of at most
  * 16 tokens needs no workspace.
  * A pack belongs to the description it was made from: pass the same `qw` (codebook, offsets, block shape)
  * to qblora_linear_decode.  For an INT4 model -- codebook exactly 0, 1, ..., 15 with offsets, 64-blocks, the

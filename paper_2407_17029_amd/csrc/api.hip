@@ -46,8 +46,8 @@ int op_map(int op) { return op == QBLORA_OP_TRUNCATE_PAD0 ? MAP_FRONT : op == QB
 int block_rows_of(const qblora_qweight* qw) { return qw->block_rows == 8 ? 8 : 1; }
 // inputs per block: 64 (row segments), or with 8-row blocks 8 (block size 64) or 4 (block size 32)
 int block_cols_of(const qblora_qweight* qw) { return qw->block_rows == 8 ? qw->block / 8 : qw->block; }
-// Blocks of 8 rows x 4 inputs: the kernels that rebuild weights inside a contraction (training calls on few tokens,
-// the inference kernels) do not know this shape; every training call takes the dequantize-once form instead.
+// Blocks of 8 rows x 4 inputs: the kernels of the training calls that rebuild weights inside a contraction do not know
+// this shape; every training call takes the dequantize-once form instead.
 bool half_blocks(const qblora_qweight* qw) { return qw->block_rows == 8 && qw->block == 32; }
 
 int check_qweight(const qblora_qweight* qw, bool need_codes, bool allow_tile8 = false) {
@@ -136,7 +136,7 @@ FwdSpace carve_fwd(const qblora_qweight* qw, const qblora_adapter* ad, int64_t T
     FwdSpace s{};
     if (dense) {
         s.W16 = c.take<qblora_bf16>((size_t)qw->d_out * qw->d_in);
-        if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));   // reconstructed
+        if (qw->scale_mode == QBLORA_SCALES_E4M3_GROUPED) s.scales = c.take<float>(n_blocks(qw));   // kept in the sizes; unused
     } else {
         s.scales = c.take<float>((size_t)((qw->d_out + 255) / 256) * 256 * (qw->d_in / qw->block));   // tile-ordered
     }
@@ -1023,14 +1023,14 @@ size_t qblora_linear_decode_workspace_bytes(const qblora_qweight* qw) {
 }
 size_t qblora_linear_decode_tokens_workspace_bytes(const qblora_qweight* qw, int32_t T) {
     if (check_qweight(qw, false, true)) return 0;
-    // The size covers every smaller batch too: the slices depend on the token tile, and the largest batch of a smaller
-    // tile may have more partial sums (22016 x 8192: none from 129 tokens on, 22 MB at 128).  Queries beyond the largest
+    // The size covers every smaller batch too: the slices change above 64 and above 128 tokens, and the largest batch below
+    // may have more partial sums (22016 x 8192: none from 129 tokens on, 22 MB at 128).  Queries beyond the largest
     // batch answer for the largest.
     const bool mid = T > kDecodeMaxTokens || (T > 0 && half_blocks(qw));
     size_t part = 0;
     if (mid)
-        for (const int32_t tile : {32, 64, 128, 192, kMidMaxTokens})
-            part = std::max(part, w4_mid_part_bytes(qw->d_out, qw->d_in, std::min(T, tile)));
+        for (const int32_t most : {64, 128, kMidMaxTokens})
+            part = std::max(part, w4_mid_part_bytes(qw->d_out, qw->d_in, std::min(T, most)));
     return qblora_linear_decode_workspace_bytes(qw) + align_up(part);
 }
 int qblora_linear_decode(const qblora_qweight* qw, const void* pack, const qblora_bf16* X, int32_t T, qblora_bf16* Y,

@@ -149,7 +149,7 @@ def test_workspace_sizes(qb):
     fwd_many = L.qblora_linear_fwd_workspace_bytes(C.byref(qw), C.byref(ad), many)
     assert fwd_many == dense_w + 2 * (128 * 4096 + 2048 * 128 + many * 128)
     assert L.qblora_linear_bwd_workspace_bytes(C.byref(qw), C.byref(ad), many) > dense_w
-    # double-quantized scales: the one-off pass reads reconstructed fp32 scales from the workspace
+    # double-quantized scales: room for reconstructed fp32 ones (the one-off pass itself reads them in place)
     qw.scale_mode, qw.scale_group = 1, 256
     qw.scale_codes = qw.scale_step = qw.scale_mid = 0x1000
     assert L.qblora_linear_fwd_workspace_bytes(C.byref(qw), None, many) == dense_w + 4 * 4096 * 64

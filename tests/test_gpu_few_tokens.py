@@ -113,8 +113,7 @@ def test_mid_batch_of_four_gibibytes(codebook):
 
 @pytest.mark.parametrize("T,d_out,d_in", [(8, 40, 4160), (5, 4096, 8128), (8, 256, 6080)])
 def test_sixteen_wave_decode_of_a_packed_model(oracle, codebook, T, d_out, d_in):
-    """Packed INT4 model whose activations exceed the LDS copy, few rows: sixteen waves share a row group, with
-    block counts (65, 127, 95) that no wave count divides."""
+    """Packed INT4 model, few long rows: block counts (65, 127, 95) that the waves of a workgroup do not divide."""
     from paper_2407_17029_amd import binding as qb
     from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
     print(f"case sixteen waves T={T} {d_out}x{d_in}", flush=True)

@@ -203,16 +203,15 @@ def _inference_on_sampled_rows(qb, oracle, d_out, d_in, tokens, seed):
 
 
 def test_small_batch_inference_at_the_measured_shape(qb, oracle):
-    """The decode kernel on the 65B up-projection shape bench.py times among its side measurements (22016 x 8192, INT4 with
-    offsets, tile-ordered pack): one token (all of X in LDS, two row groups per workgroup), 2 .. 16 (activations staged per
-    wave, two row groups), and the mid-batch form at 32, 128 and 200 tokens."""
+    """The 65B up-projection shape bench.py times among its side measurements (22016 x 8192, INT4 with offsets, tile-ordered
+    pack): scales on block sums up to 16 tokens (three row groups at one, six above), whole rows of the rounded weight at 32,
+    slices of the input at 128 and 200."""
     _inference_on_sampled_rows(qb, oracle, 22016, 8192, (1, 2, 3, 7, 16, 32, 128, 200), 4242)
 
 
 @pytest.mark.parametrize("d_out,d_in", [(8192, 22016), (8192, 8192)])
 def test_small_batch_inference_short_layers(qb, oracle, d_out, d_in):
-    """The 65B down and attention projections: at most two workgroups per CU, so the forms with eight waves per workgroup
-    (one token; up to three at 8192 inputs) and the staged form with one row group."""
+    """The 65B down and attention projections: two row groups, one workgroup per CU."""
     _inference_on_sampled_rows(qb, oracle, d_out, d_in, (1, 2, 3, 4, 9, 16), 4243)
 
 
