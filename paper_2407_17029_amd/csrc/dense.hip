@@ -468,8 +468,8 @@ int launch_cfg(const GemmDesc& d, hipStream_t st) {
 // with a few (the clock is power-limited: 1.5-1.7 GHz with all matrix pipes busy, 2.4 with few), both in ns; a last
 // round of workgroups (256, one per CU) that is not full lies in between.  (128 x 256 takes 690 and 870 since its phases
 // hold a whole step; the choices below were measured with the older figures, which stay.)  Larger tiles move fewer bytes per MFMA
-// (256 x 256 runs at 0.82-0.89 of the matrix pipe, 128 x 128 at 0.42: copies into LDS are its limit) and need more
-// tiles to fill the chip.  T x N x K, us for 256x256 / 128x256 / 256x128 / 128x128: 512 x 4096 x 11008 179 / 130 /
+// (256 x 256 runs at 0.82-0.89 of the matrix pipe, 128 x 256 at 0.61, 128 x 128 at 0.40, where waves wait 0.42 of the time, LDS
+// reads take 0.31 and copies 25 bytes a cycle) and need more tiles to fill the chip.  T x N x K, us for 256x256 / 128x256 / 256x128 / 128x128: 512 x 4096 x 11008 179 / 130 /
 // 131 / 87; 512 x 11008 x 4096 77 / 61 / 60 / 76; 1337 x 5120 x 5120 94 / 71 / 74 / 90; 2500 x 5120 x 13824 263 / 350 /
 // 358 / 439; 8192 x 4096 x 4096 192 / 233 / 238 / 285.  A slice adds its fp32 partial tile, written and read once, and
 // all of them the second launch: 512 x 4096 x 11008 91 -> 54 + 7 us (128 x 256, four slices), 300 x 2048 x 6144 51 ->
@@ -522,7 +522,8 @@ int64_t dense_part_rows(int64_t M, int N, int k1, int k2) {
 }
 
 // The one-off pass takes 0.46 us per million weights and a launch, which the forward's kernel from the codes does not
-// spend; that one wins on wide layers with few tokens.  us from the codes / dequantized first: 512 x 22016 x 8192 190 / 265,
+// spend (the launch is the re-layouts' by now, which both have; the line was measured with one of its own); that one wins on
+// wide layers with few tokens.  us from the codes / dequantized first: 512 x 22016 x 8192 190 / 265,
 // 512 x 16384 x 8192 138 / 194, 512 x 11008 x 4096 72 / 77, 1024 x 16384 x 8192 233 / 257, 512 x 4096 x 4096 70 / 46,
 // 2048 x 22016 x 8192 632 / 610.  The margin of 5 % is for the estimates' errors: without it 72 of 1134 measured calls
 // lose up to 9 % of their time, with it three lose 3 % (and 207 gain 17 % on average).

@@ -27,7 +27,7 @@
 //   8 x 8 blocks      4096 x 11008  8 tokens 13.5 -> 9.3; 22016 x 8192 28.1 -> 25.6
 // An empty launch with this prologue and the sum of the waves takes 3.3 us of each.  48 tokens, 11008 x 4096: 11.5 us
 // without the fetches of the tokens, 10.9 without those of the weight, 14.1 without arithmetic: what is left is the path
-// into LDS (64 bytes a cycle in, 128 out).
+// into LDS.
 #include "common.h"
 
 namespace qblora {
@@ -197,8 +197,8 @@ struct Feed {
             if (u < count) issue(u, u);
     }
     // Walks the wave's blocks: block(stage, refill) reads a block's operands out of its stage, has it refilled and contracts
-    // them.  A block is in when only the operations of those fetched after it are outstanding; none is fetched past the end, which for short rows were
-    // more than all others (1024 inputs: two blocks a wave, four ahead of each).
+    // them.  A block is in when only the operations of those fetched after it are outstanding; none is fetched past the end,
+    // which for short rows were more than all others (1024 inputs: two blocks a wave, four ahead of each).
     template <typename Block>
     __device__ __forceinline__ void walk(Block block) {
         constexpr int D = S::kDepth;
