@@ -1,5 +1,7 @@
 """Inference on at most 64 tokens (a workgroup walks the whole input dimension) at the edges of its tiles: token counts on
 both sides of every form, 1, 2, 3, 4 and 6 row groups with ragged last workgroups, fewer blocks than waves."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
@@ -33,9 +35,13 @@ def _case(oracle, codebook, seed, T, d_out, d_in, fmt):
     # more blocks than a wave has in flight, a ragged number of them, in every number of row groups
     (1, 4104, 2624), (2, 24584, 704), (8, 6152, 2624), (12, 18440, 1600), (16, 9224, 2368), (24, 4088, 2624), (32, 12296, 1600),
     (48, 8200, 2112), (40, 12296, 1344), (33, 16392, 1088), (64, 16376, 1600), (64, 24584, 1088), (48, 20488, 1344),
+    (48, 40, 2624), (64, 72, 2624), (40, 8184, 1600), (64, 8184, 1600), (49, 11000, 1600), (64, 16392, 1216),
 ])
-def test_edges(oracle, codebook, T, d_out, d_in, fmt):
+def test_edges(oracle, codebook, rules, T, d_out, d_in, fmt):
     from gpu_util import assert_close_bf16
+    rows = rules.L["_ZN6qblora15w4_rows_appliesEiiibb"]
+    rows.argtypes, rows.restype = [C.c_int, C.c_int, C.c_int, C.c_bool, C.c_bool], C.c_bool
+    assert all(rows(d_out, d_in, T, table, tiled) for table in (False, True) for tiled in (False, True))
     print(f"case w4 rows T={T} {d_out}x{d_in} {fmt}", flush=True)
     qb, qw, X, ref = _case(oracle, codebook, 8000 + T + d_out, T, d_out, d_in, fmt)
     Y = torch.full((T + 1, d_out), 7.0, dtype=torch.bfloat16, device=X.device)
