@@ -81,6 +81,38 @@ __device__ __forceinline__ float pair_max(float v) {
     return fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0xB1, 0xf, 0xf, false)));
 }
 
+// Stages the deltas of a tile in LDS: delta = (s*H)/lambda1, a division unless lambda1 is one of the powers of two with a
+// code path of their own, where multiplying by the (exact) reciprocal gives the same bits.
+template <int L1>
+__device__ __forceinline__ void stage_deltas(const MergeDesc& d, const TileGeom& g, int stride, int sh2, float* dl) {
+    const int t = threadIdx.x, ldH = div_by(d.d_out, d.lam2, sh2);
+    const float lam1f = (float)d.lam1;
+    auto delta_of = [&](float h) __attribute__((always_inline)) {
+        const float sh = __fmul_rn(d.s, h);
+        if constexpr (L1 > 0) return __fmul_rn(sh, 1.0f / (float)L1);
+        else return __fdiv_rn(sh, lam1f);
+    };
+    const int hc4 = g.hcols >> 2;
+    if ((g.hcols & 3) == 0 && (hc4 & (hc4 - 1)) == 0 && (ldH & 3) == 0 && (g.hcol0 & 3) == 0 &&
+        (reinterpret_cast<uintptr_t>(d.H) & 15) == 0) {
+        // whole tiles of power-of-two lambdas: 16-byte loads along n, no division in the index
+        const int sh = 31 - __builtin_clz(hc4);
+        for (int idx = t; idx < g.hrows * hc4; idx += kMergeThreads) {
+            const int r = idx >> sh, c = (idx & (hc4 - 1)) << 2;
+            const float4 h = *reinterpret_cast<const float4*>(d.H + (int64_t)(g.hrow0 + r) * ldH + g.hcol0 + c);
+            dl[delta_pos<L1>(c, r, stride)] = delta_of(h.x);
+            dl[delta_pos<L1>(c + 1, r, stride)] = delta_of(h.y);
+            dl[delta_pos<L1>(c + 2, r, stride)] = delta_of(h.z);
+            dl[delta_pos<L1>(c + 3, r, stride)] = delta_of(h.w);
+        }
+    } else {
+        for (int idx = t; idx < g.hrows * g.hcols; idx += kMergeThreads) {
+            const int r = idx / g.hcols, c = idx - r * g.hcols;
+            dl[delta_pos<L1>(c, r, stride)] = delta_of(d.H[(int64_t)(g.hrow0 + r) * ldH + g.hcol0 + c]);
+        }
+    }
+}
+
 // OUT16: write the shifted weights themselves as bf16 (the 16-bit merge) instead of requantizing them.
 template <bool GROUPED, bool BETA, int L1, bool OUT16>
 __device__ __forceinline__ void merge_requant_tile(const MergeDesc& d, const unsigned wg) {
@@ -123,38 +155,11 @@ __device__ __forceinline__ void merge_requant_tile(const MergeDesc& d, const uns
         if constexpr (BETA) b = d.beta[blk];
     }
 
-    // stage the deltas of the tile: delta = (s*H)/lambda1, a division unless lambda1 is one of the
-    // powers of two with a code path of their own, where multiplying by the (exact) reciprocal gives
-    // the same bits
     const int sh2 = shift_of(d.lam2);
     const TileGeom g = tile_geom<L1>(d, n0, k0, sh2);
-    const int ldH = div_by(d.d_out, d.lam2, sh2), stride = delta_stride<L1>(d.lam1);
+    const int stride = delta_stride<L1>(d.lam1);
     if (t < 16) lut[t] = d.cb.c[t];
-    const float lam1f = (float)d.lam1;
-    auto delta_of = [&](float h) __attribute__((always_inline)) {
-        const float sh = __fmul_rn(d.s, h);
-        if constexpr (L1 > 0) return __fmul_rn(sh, 1.0f / (float)L1);
-        else return __fdiv_rn(sh, lam1f);
-    };
-    const int hc4 = g.hcols >> 2;
-    if ((g.hcols & 3) == 0 && (hc4 & (hc4 - 1)) == 0 && (ldH & 3) == 0 && (g.hcol0 & 3) == 0 &&
-        (reinterpret_cast<uintptr_t>(d.H) & 15) == 0) {
-        // whole tiles of power-of-two lambdas: 16-byte loads along n, no division in the index
-        const int sh = 31 - __builtin_clz(hc4);
-        for (int idx = t; idx < g.hrows * hc4; idx += kMergeThreads) {
-            const int r = idx >> sh, c = (idx & (hc4 - 1)) << 2;
-            const float4 h = *reinterpret_cast<const float4*>(d.H + (int64_t)(g.hrow0 + r) * ldH + g.hcol0 + c);
-            dl[delta_pos<L1>(c, r, stride)] = delta_of(h.x);
-            dl[delta_pos<L1>(c + 1, r, stride)] = delta_of(h.y);
-            dl[delta_pos<L1>(c + 2, r, stride)] = delta_of(h.z);
-            dl[delta_pos<L1>(c + 3, r, stride)] = delta_of(h.w);
-        }
-    } else {
-        for (int idx = t; idx < g.hrows * g.hcols; idx += kMergeThreads) {
-            const int r = idx / g.hcols, c = idx - r * g.hcols;
-            dl[delta_pos<L1>(c, r, stride)] = delta_of(d.H[(int64_t)(g.hrow0 + r) * ldH + g.hcol0 + c]);
-        }
-    }
+    stage_deltas<L1>(d, g, stride, sh2, dl);
     __syncthreads();
     if (!live) return;
 
@@ -274,75 +279,116 @@ __global__ __launch_bounds__(256) void k_merge_beta_shift_tile8(MergeDesc d) {
 }
 
 // Requantizing merge and 16-bit merge on 8 x 8 blocks (any lambdas; with 8 | lambda1 and 8 | lambda2 the offset
-// shift above is the exact and cheaper way).  A thread owns one block: eight code dwords, one per row, the lanes
-// of a wave along the block columns (256 contiguous bytes per row and load), its scale and offset; the shift of
-// element (n, k) is read from H where it is (the 64 elements see at most (8/lambda1 + 1)(8/lambda2 + 1) entries,
-// served by the cache).  Same arithmetic as on 64-blocks: fp32 w~ = fma(c, alpha, beta) or c * alpha, + delta,
-// then the min-max quantizer of Eq. 1 over the block, or one rounding to bf16.
-// BC = 4: blocks of 8 rows x 4 inputs (two code bytes per row).
-template <bool BETA, bool OUT16, int BC>
-__global__ __launch_bounds__(256) void k_merge_tile8(MergeDesc d) {
+// shift above is the exact and cheaper way) and on blocks of 8 rows x 4 inputs (BC = 4).  Same arithmetic as on 64-blocks:
+// fp32 w~ = fma(c, alpha, beta) or c * alpha, + delta, then the min-max quantizer of Eq. 1 over the block, or one rounding
+// to bf16.
+//
+// A workgroup owns 64 rows x 256 inputs, as on 64-blocks, with the deltas of the tile staged in the same way: H is read
+// along its rows, once.  (A thread per block that read H where it is touched a line of H per lane and load, and divided 64
+// times: before / now, us, 2048 x 5248 at lambda 4 to 16 bits 44.4 / 8.3, 8192 x 8192 at lambda 2 to 16 bits 245 / 41,
+// two of 8192 x 8192 requantized 501 / 67 in one launch, 4.5 TB/s.)  Bound: HBM.  A wave owns one row of blocks; two lanes
+// share a block, rows 4*sub .. +3 of eight inputs each, so a load of codes covers 128 bytes of two rows and a 16-bit store
+// 512.  A tile's block parameters are whole 128-byte lines, so the tiles need no order for their sake; tiles that are
+// neighbours along the rows share lines of H where lambda2 > 2 and are consecutive on one XCD.
+template <bool BETA, int L1, bool OUT16, int BC>
+__device__ __forceinline__ void merge_tile8(const MergeDesc& d, const unsigned wg) {
     __shared__ float lut[16];
-    if (threadIdx.x < 16) lut[threadIdx.x] = d.cb.c[threadIdx.x];
+    extern __shared__ __align__(16) float dl[];          // deltas, [hcols][stride]
+    constexpr int NBLK = 8 / BC;                         // blocks of a lane's eight inputs
+    const int t = threadIdx.x;
+    const unsigned ntiles = (unsigned)(d.d_out + NT - 1) / NT, tiles = (unsigned)(d.d_in + KT - 1) / KT * ntiles;
+    const unsigned tile = (wg & 7) * ((tiles + 7) >> 3) + (wg >> 3);
+    if ((wg >> 3) >= ((tiles + 7) >> 3) || tile >= tiles) return;
+    const int kt = (int)(tile / ntiles), k0 = kt * KT, n0 = (int)(tile - (unsigned)kt * ntiles) * NT;
+    const int sub = t & 1, n = n0 + 8 * (t >> 6) + 4 * sub, k = k0 + 8 * ((t >> 1) & 31);
+    const bool live = n < d.d_out && k < d.d_in;         // the same for the two lanes of a block: d_out % 8 == 0
+    const int64_t blk = (int64_t)(n >> 3) * (d.d_in / BC) + k / BC, at = ((int64_t)n * d.d_in + k) / 2;
+
+    uint32_t cw[4] = {0, 0, 0, 0};
+    float a[NBLK], b[NBLK];
+#pragma unroll
+    for (int u = 0; u < NBLK; ++u) a[u] = b[u] = 0.0f;
+    if (live) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) cw[i] = *reinterpret_cast<const u32_any*>(d.codes + at + (int64_t)i * (d.d_in / 2));
+#pragma unroll
+        for (int u = 0; u < NBLK; ++u) {
+            a[u] = d.scales[blk + u];
+            if constexpr (BETA) b[u] = d.beta[blk + u];
+        }
+    }
+    const int sh2 = shift_of(d.lam2);
+    const TileGeom g = tile_geom<L1>(d, n0, k0, sh2);
+    const int stride = delta_stride<L1>(d.lam1);
+    if (t < 16) lut[t] = d.cb.c[t];
+    stage_deltas<L1>(d, g, stride, sh2, dl);
     __syncthreads();
-    const int nbc = d.d_in / BC;
-    const int64_t total = (int64_t)(d.d_out / 8) * nbc;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
-    const int bi = (int)(idx / nbc), bj = (int)(idx - (int64_t)bi * nbc);
-    const int n0 = 8 * bi, k0 = BC * bj;
-    const float a = d.scales[idx], b = BETA ? d.beta[idx] : 0.0f;
-    const int ldH = d.d_out / d.lam2;
-    const float lam1f = (float)d.lam1;
-    float w[8][BC];
+    if (!live) return;
+
+    float w[4][8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const uint8_t* cp = d.codes + ((int64_t)(n0 + i) * d.d_in + k0) / 2;
-        const uint32_t cw = BC == 8 ? *reinterpret_cast<const uint32_t*>(cp) : (uint32_t)*reinterpret_cast<const uint16_t*>(cp);
-        const float* hrow = d.H + (n0 + i) / d.lam2;
+    for (int i = 0; i < 4; ++i) {
+        const int c = div_by(n + i, d.lam2, sh2) - g.hcol0;
+        float de[8];
+        if constexpr (L1 > 0) {
+            const float* const dq = dl + delta_pos<L1>(c, (k - k0) / L1, stride);      // inside one run
 #pragma unroll
-        for (int j = 0; j < BC; ++j) {
-            const float cv = lut[(cw >> (4 * j)) & 15];
-            const float wt = BETA ? __fmaf_rn(cv, a, b) : __fmul_rn(cv, a);
-            const float delta = __fdiv_rn(__fmul_rn(d.s, hrow[(int64_t)((k0 + j) / d.lam1) * ldH]), lam1f);
-            w[i][j] = __fadd_rn(wt, delta);
+            for (int v = 0; v < 8 / L1; ++v) de[v] = dq[v];
+        } else {
+#pragma unroll
+            for (int j = 0; j < 8; ++j) de[j] = dl[c * stride + (k + j) / d.lam1 - g.hrow0];
+        }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float cv = lut[(cw[i] >> (4 * j)) & 15];
+            const float wt = BETA ? __fmaf_rn(cv, a[j / BC], b[j / BC]) : __fmul_rn(cv, a[j / BC]);
+            w[i][j] = __fadd_rn(wt, de[L1 > 0 ? j / (L1 > 0 ? L1 : 1) : j]);
         }
     }
     if constexpr (OUT16) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            qblora_bf16* wp = d.w16_out + (int64_t)(n0 + i) * d.d_in + k0;
-            if constexpr (BC == 8)
-                *reinterpret_cast<uint4*>(wp) = make_uint4(pack_bf16(w[i][0], w[i][1]), pack_bf16(w[i][2], w[i][3]),
-                                                           pack_bf16(w[i][4], w[i][5]), pack_bf16(w[i][6], w[i][7]));
-            else
-                *reinterpret_cast<uint2*>(wp) = make_uint2(pack_bf16(w[i][0], w[i][1]), pack_bf16(w[i][2], w[i][3]));
+        for (int i = 0; i < 4; ++i) {
+            const u32x4_any o = {pack_bf16(w[i][0], w[i][1]), pack_bf16(w[i][2], w[i][3]), pack_bf16(w[i][4], w[i][5]),
+                                 pack_bf16(w[i][6], w[i][7])};
+            *reinterpret_cast<u32x4_any*>(d.w16_out + (int64_t)(n + i) * d.d_in + k) = o;
         }
         return;
     }
-    float lo = w[0][0], hi = w[0][0];
+    uint32_t p[4] = {0, 0, 0, 0};
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int u = 0; u < NBLK; ++u) {
+        float lo = w[0][BC * u], hi = lo;
 #pragma unroll
-        for (int j = 0; j < BC; ++j) { lo = fminf(lo, w[i][j]); hi = fmaxf(hi, w[i][j]); }
-    const float range = __fsub_rn(hi, lo);
-    const float al = __fdiv_rn(range, 15.0f);
-    const float inv = al != 0.0f ? __fdiv_rn(15.0f, range) : 0.0f;     // a flat block gets codes 0
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        uint32_t p = 0;
+            for (int j = BC * u; j < BC * (u + 1); ++j) { lo = fminf(lo, w[i][j]); hi = fmaxf(hi, w[i][j]); }
+        lo = pair_min(lo); hi = pair_max(hi);
+        const float range = __fsub_rn(hi, lo);
+        const float al = __fdiv_rn(range, 15.0f);
+        const float inv = al != 0.0f ? __fdiv_rn(15.0f, range) : 0.0f;     // a flat block gets codes 0
 #pragma unroll
-        for (int j = 0; j < BC; ++j) {
-            // (w-lo)*inv lies in [0, 15*(1+2^-23)]: rint() of it is already a code
-            const float q = rintf(__fmul_rn(__fsub_rn(w[i][j], lo), inv));
-            p |= (uint32_t)q << (4 * j);
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = BC * u; j < BC * (u + 1); ++j) {
+                // (w-lo)*inv lies in [0, 15*(1+2^-23)]: rint() of it is already a code
+                p[i] |= (uint32_t)rintf(__fmul_rn(__fsub_rn(w[i][j], lo), inv)) << (4 * j);
+            }
+        if (sub == 0) {
+            d.alpha_out[blk + u] = al;
+            d.beta_out[blk + u] = lo;
         }
-        uint8_t* op = d.codes_out + ((int64_t)(n0 + i) * d.d_in + k0) / 2;
-        if constexpr (BC == 8) *reinterpret_cast<uint32_t*>(op) = p;
-        else *reinterpret_cast<uint16_t*>(op) = (uint16_t)p;
     }
-    d.alpha_out[idx] = al;
-    d.beta_out[idx] = lo;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) *reinterpret_cast<u32_any*>(d.codes_out + at + (int64_t)i * (d.d_in / 2)) = p[i];
+}
+
+template <bool BETA, int L1, bool OUT16, int BC>
+__global__ __launch_bounds__(kMergeThreads) void k_merge_tile8(MergeBatch b) {
+    int m = 0;
+#pragma unroll
+    for (int i = 1; i < kMergeBatchMax; ++i)
+        if (i < b.count && blockIdx.x >= b.first[i]) m = i;
+    merge_tile8<BETA, L1, OUT16, BC>(b.d[m], blockIdx.x - b.first[m]);
 }
 
 }  // namespace
@@ -409,14 +455,77 @@ int launch_requant_batch_l1(const MergeDesc* ds, int count, hipStream_t st) {
     return ds[0].beta ? launch(k_merge_requant_batch<false, true, L1>) : launch(k_merge_requant_batch<false, false, L1>);
 }
 
-// One launch for `count` (2 .. 8) row-segment weights that share lambdas, scale format and the presence of offsets;
+// One launch for 1 .. 8 weights in blocks of 8 rows that share lambdas, block width and the presence of offsets.
+template <int L1, bool OUT16>
+int launch_tile8_l1(const MergeDesc* ds, int count, hipStream_t st) {
+    MergeBatch b{};
+    b.count = count;
+    int64_t total = 0;
+    for (int m = 0; m < count; ++m) {
+        b.d[m] = ds[m];
+        b.first[m] = (unsigned)total;
+        total += ((int64_t)((ds[m].d_in + KT - 1) / KT) * ((ds[m].d_out + NT - 1) / NT) + 7) / 8 * 8;
+        if (total > 0x7fffffff) return QBLORA_ERR_UNSUPPORTED;
+    }
+    b.first[count] = (unsigned)total;
+    const size_t smem = sizeof(float) * (size_t)delta_stride<L1>(ds[0].lam1) * (NT / ds[0].lam2 + 2);
+    auto launch = [&](auto kern) -> int {
+        if (smem > 48 * 1024 &&
+            hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                (int)smem) != hipSuccess)
+            return QBLORA_ERR_LAUNCH;
+        hipLaunchKernelGGL(kern, dim3((unsigned)total), dim3(kMergeThreads), smem, st, b);
+        return launch_status();
+    };
+    if (ds[0].block_cols == 4) return ds[0].beta ? launch(k_merge_tile8<true, L1, OUT16, 4>) : launch(k_merge_tile8<false, L1, OUT16, 4>);
+    return ds[0].beta ? launch(k_merge_tile8<true, L1, OUT16, 8>) : launch(k_merge_tile8<false, L1, OUT16, 8>);
+}
+
+template <bool OUT16>
+int launch_tile8(const MergeDesc* ds, int count, hipStream_t st) {
+    for (int m = 0; m < count; ++m)
+        if (ds[m].scale_codes || ds[m].d_out % 8 != 0 || ds[m].d_in % 8 != 0 || (ds[m].block_cols != 8 && ds[m].block_cols != 4))
+            return QBLORA_ERR_UNSUPPORTED;
+    switch (ds[0].lam1) {
+        case 1: return launch_tile8_l1<1, OUT16>(ds, count, st);
+        case 2: return launch_tile8_l1<2, OUT16>(ds, count, st);
+        case 4: return launch_tile8_l1<4, OUT16>(ds, count, st);
+        case 8: return launch_tile8_l1<8, OUT16>(ds, count, st);
+        default: return launch_tile8_l1<0, OUT16>(ds, count, st);
+    }
+}
+
+// Whether no weight's output lies in another's base or output (a chain of merges runs one after the other).
+bool independent(const MergeDesc* ds, int count) {
+    auto overlap = [](const void* p, size_t np, const void* q, size_t nq) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
+        return p && q && a < b + nq && b < a + np;
+    };
+    for (int m = 0; m < count; ++m)
+        for (int q = 0; q < count; ++q) {
+            if (m == q) continue;
+            auto blocks = [](const MergeDesc& d) { return sizeof(float) * (size_t)(d.d_out / 8) * (d.d_in / d.block_cols); };
+            const MergeDesc &x = ds[m], &y = ds[q];
+            const size_t cx = (size_t)x.d_out * x.d_in / 2, cy = (size_t)y.d_out * y.d_in / 2;
+            const struct { const void* p; size_t n; } out[3] = {{x.codes_out, cx}, {x.alpha_out, blocks(x)}, {x.beta_out, blocks(x)}},
+                in[6] = {{y.codes, cy}, {y.scales, blocks(y)}, {y.beta, blocks(y)}, {y.codes_out, cy}, {y.alpha_out, blocks(y)}, {y.beta_out, blocks(y)}};
+            for (const auto& o : out)
+                for (const auto& i : in)
+                    if (overlap(o.p, o.n, i.p, i.n)) return false;
+        }
+    return true;
+}
+
+// One launch for `count` (2 .. 8) weights that share lambdas, block shape, scale format and the presence of offsets;
 // QBLORA_ERR_UNSUPPORTED (nothing launched) when they do not -- the caller then merges them one by one.
 int launch_merge_requant_batch(const MergeDesc* ds, int count, hipStream_t st) {
     if (count < 2 || count > kMergeBatchMax) return QBLORA_ERR_UNSUPPORTED;
     for (int m = 0; m < count; ++m)
-        if (ds[m].block_rows == 8 || ds[m].lam1 != ds[0].lam1 || ds[m].lam2 != ds[0].lam2 ||
-            (ds[m].scale_codes == nullptr) != (ds[0].scale_codes == nullptr) || (ds[m].beta == nullptr) != (ds[0].beta == nullptr))
+        if (ds[m].block_rows != ds[0].block_rows || ds[m].block_cols != ds[0].block_cols || ds[m].lam1 != ds[0].lam1 ||
+            ds[m].lam2 != ds[0].lam2 || (ds[m].scale_codes == nullptr) != (ds[0].scale_codes == nullptr) ||
+            (ds[m].beta == nullptr) != (ds[0].beta == nullptr))
             return QBLORA_ERR_UNSUPPORTED;
+    if (ds[0].block_rows == 8) return independent(ds, count) ? launch_tile8<false>(ds, count, st) : QBLORA_ERR_UNSUPPORTED;
     switch (ds[0].lam1) {
         case 1: return launch_requant_batch_l1<1>(ds, count, st);
         case 2: return launch_requant_batch_l1<2>(ds, count, st);
@@ -428,20 +537,7 @@ int launch_merge_requant_batch(const MergeDesc* ds, int count, hipStream_t st) {
 
 template <bool OUT16>
 int launch_merge_elementwise(const MergeDesc& d, hipStream_t st) {
-    if (d.block_rows == 8) {
-        if (d.scale_codes || d.d_out % 8 != 0 || d.d_in % 8 != 0 || (d.block_cols != 8 && d.block_cols != 4))
-            return QBLORA_ERR_UNSUPPORTED;
-        const int64_t total = (int64_t)(d.d_out / 8) * (d.d_in / d.block_cols);
-        const dim3 grid((unsigned)((total + 255) / 256));
-        if (d.block_cols == 4) {
-            if (d.beta) hipLaunchKernelGGL((k_merge_tile8<true, OUT16, 4>), grid, dim3(256), 0, st, d);
-            else hipLaunchKernelGGL((k_merge_tile8<false, OUT16, 4>), grid, dim3(256), 0, st, d);
-        } else {
-            if (d.beta) hipLaunchKernelGGL((k_merge_tile8<true, OUT16, 8>), grid, dim3(256), 0, st, d);
-            else hipLaunchKernelGGL((k_merge_tile8<false, OUT16, 8>), grid, dim3(256), 0, st, d);
-        }
-        return launch_status();
-    }
+    if (d.block_rows == 8) return launch_tile8<OUT16>(&d, 1, st);
     switch (d.lam1) {
         case 1: return launch_requant_l1<1, OUT16>(d, st);
         case 2: return launch_requant_l1<2, OUT16>(d, st);

@@ -208,6 +208,37 @@ def test_requantizing_and_16bit_merge_on_8x8_blocks(qb, oracle, codebook, d_out,
     assert_close_bf16(Ym, oracle.forward(Wm, L.X, None, None, 1, 1, 0.0), "Y (merged, 8x8)")
 
 
+@pytest.mark.parametrize("lam1,lam2,block_cols", [(2, 2, 8), (8, 8, 8), (4, 1, 8), (16, 4, 8), (3, 2, 8), (1, 8, 4), (2, 2, 4), (6, 3, 4)])
+def test_batched_merge_on_blocks_of_eight_rows(qb, oracle, lam1, lam2, block_cols):
+    """One launch for several weights: a single block row, ragged last tiles in both dimensions and whole ones, lambdas with
+    and without a code path of their own, bit for bit; and a chain, whose second weight is the first one's output."""
+    from gpu_util import f32_to_dev, to_np, OracleWeight
+    s, unit = 0.75, 24 if lam2 == 3 else 8
+    shapes = [(unit, 192), (72 + unit, 384), (9 * unit, 960), (192, 768)]
+    bits = lambda a: np.ascontiguousarray(a).view(np.uint32).reshape(-1)
+    weights = [synth.base_weight(1860 + i, 0, *sh) for i, sh in enumerate(shapes)]
+    bases = [qb.qblora_quantize_blockwise(f32_to_dev(W), 8 * block_cols, qb.QUANT_MINMAX_INT4, block_rows=8) for W in weights]
+    Hs = [synth.normal_f32(1870 + i, 1, (d_in // lam1, d_out // lam2), 0.01) for i, (d_out, d_in) in enumerate(shapes)]
+    outs = qb.qablora_merge_quantize_batch(bases, [f32_to_dev(H) for H in Hs], lam1, lam2, s, qb.MERGE_REQUANT_MINMAX)
+    W16 = [qb.qblora_merge_bf16(b, f32_to_dev(H), lam1, lam2, s) for b, H in zip(bases, Hs)]
+    torch.cuda.synchronize()
+    for W, b, H, o, w in zip(weights, bases, Hs, outs, W16):
+        ow = OracleWeight(oracle, W, None, True, block_rows=8, block_cols=block_cols).assert_same(b)
+        args = ow.codes, ow.scales, ow.beta, ow.cb, H, 8, block_cols, lam1, lam2, s
+        co, ao, bo = oracle.merge_requant_tile(*args)
+        assert np.array_equal(to_np(o.codes), co)
+        assert np.array_equal(bits(to_np(o.scales)), bits(ao)) and np.array_equal(bits(to_np(o.beta)), bits(bo))
+        assert np.array_equal(to_np(w.view(torch.int16)).view(np.uint16), oracle.merge_bf16_tile(*args))
+    like = lambda b: qb.QWeight(b.d_out, b.d_in, b.block, b.codebook, torch.zeros_like(b.codes), torch.zeros_like(b.scales),
+                                torch.zeros_like(b.scales), block_rows=8)
+    first, second, H = like(bases[3]), like(bases[3]), f32_to_dev(Hs[3])
+    qb.qablora_merge_quantize_batch([bases[3], first], [H, H], lam1, lam2, s, qb.MERGE_REQUANT_MINMAX, outs=[first, second])
+    want = qb.qablora_merge_quantize(outs[3], H, lam1, lam2, s, qb.MERGE_REQUANT_MINMAX)
+    torch.cuda.synchronize()
+    assert torch.equal(first.codes, outs[3].codes) and torch.equal(second.codes, want.codes)
+    assert torch.equal(second.beta.view(torch.int32), want.beta.view(torch.int32))
+
+
 # ---- blocks of 8 output rows x 4 inputs (block size 32; the other block shape of Sec. 3.3) ------------------------
 
 def _layer84(qb, oracle, codebook, seed, T, d_out, d_in, R, lam1, lam2, minmax):
