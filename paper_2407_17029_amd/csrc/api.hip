@@ -26,9 +26,19 @@ struct Carver {
 };
 
 bool has_adapter(const qblora_adapter* ad) { return ad && ad->A && ad->B && ad->R > 0; }
-// Whether the narrow GEMM over `width` features takes the unexpanded adapter operand (pool / repeat factor 2)
-bool pooled_pair_operand(int R, int width, int lam) {
-    return lam == 2 && skinny_dup_applies(R, width, width / 2);
+// How the narrow GEMM over `width` features, pooled or repeated in groups of lam, takes its adapter operand
+struct NarrowOperand {
+    bool in_place;             // as it lies: lam is 1 or 2, the kernel uses each stored value for lam adjacent features
+    int dup;                   // features per stored value of what the kernel reads
+    int expand;                // ... which is a copy expanded by this factor where it is not read in place
+};
+NarrowOperand narrow_operand(const qblora_bf16* stored, int R, int width, int lam) {
+    NarrowOperand o{false, 1, lam};
+    if (width >= 1 << 23) return o;                           // 32-bit offsets of the kernel's copies (skinny_applies)
+    o.dup = lam % 2 == 0 && skinny_dup_applies(R, width, width / 2) ? 2 : 1;
+    o.expand = lam / o.dup;
+    o.in_place = o.expand == 1 && skinny_dup_applies(R, width, width / o.dup) && (reinterpret_cast<uintptr_t>(stored) & 15) == 0;
+    return o;
 }
 // Slices of s*U = s*X*At_x.  The partial sums of the forward live in Y, which the contraction behind them overwrites,
 // so that the call needs no further scratch; the backward that recomputes s*U takes the same number for the same bits.
@@ -448,16 +458,28 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     }
     const int op = scale_op_of(ad);
     const bool prep_adapter = adapted && op == QBLORA_OP_AVGPOOL_REPEAT;
-    // lambda1 = 2: A^T stays unexpanded and the narrow GEMM uses each of its columns for two adjacent k
-    const bool dup_a = prep_adapter && pooled_pair_operand(ad->R, qw->d_in, ad->lambda1);
+    const NarrowOperand na = prep_adapter ? narrow_operand(ad->A, ad->R, qw->d_in, ad->lambda1) : NarrowOperand{false, 1, 1};
+    const PrepDesc prep = describe_prep(prep_adapter ? ad->A : nullptr, prep_adapter ? ad->B : nullptr, qw->d_in / na.dup,
+                                        qw->d_out, adapted ? ad->R : 0, adapted ? na.expand : 1, adapted ? ad->lambda2 : 1,
+                                        na.in_place ? nullptr : ws.At_x, ws.Bt, nullptr, sct.out ? &sct : nullptr);
+    // s*U = (s/lambda1) * X * expand(A): average pool folded into the contraction
+    GemmDesc u{};
+    if (adapted) {
+        u.X2 = X; u.ldx2 = qw->d_in; u.W2 = ws.At_x; u.ldw2 = qw->d_in / na.dup; u.K2 = qw->d_in; u.div2 = 1; u.dup2 = na.dup;
+        if (na.in_place) { u.W2 = ad->A; u.ldw2 = ad->R; u.by_k = 1; }
+        qblora_bf16* su = saved ? saved : ws.U;               // kept for the backward: high part, then residual
+        u.C = su; u.C_lo = saved ? saved + T * ad->R : nullptr;
+        u.ldc = ad->R; u.out_scale = op ? ad->s : ad->s / (float)ad->lambda1; u.M = T; u.N = ad->R;
+        u.part = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(Y) + 15) & ~(uintptr_t)15); u.splits = su_splits(qw, ad, T);
+    }
+    // Where the narrow GEMM does not wait for the re-layouts they share its launch, and a weight that is dequantized once
+    // that of its sums: a launch (4 to 5 us) less.  Otherwise they go first, the weight with them: beside the narrow GEMM itself
+    // it would have one or two workgroups on a CU, whose LDS the GEMM's ring takes.
+    const bool together = adapted && skinny_shares(u) && (!dense || u.splits > 1);
     {
         ScopedEvents ev(QBLORA_PROFILE_PREP, st);
-        rc = launch_adapter_prep(prep_adapter ? ad->A : nullptr, prep_adapter ? ad->B : nullptr,
-                                 dup_a ? qw->d_in / 2 : qw->d_in, qw->d_out,
-                                 adapted ? ad->R : 0, adapted ? (dup_a ? 1 : ad->lambda1) : 1, adapted ? ad->lambda2 : 1,
-                                 ws.At_x, ws.Bt, nullptr, st, sct.out ? &sct : nullptr, dense ? &weight : nullptr);
+        if (!together && (rc = launch_prep(prep, st, dense ? &weight : nullptr))) return rc;
     }
-    if (rc) return rc;
     if (adapted && op != QBLORA_OP_AVGPOOL_REPEAT) {
         // At_x[j][k] = A[C-map(k)][j] and Bt[n][j] = B[j][E-map(n)], zero where the operator drops the index
         const int na = qw->d_in / ad->lambda1, nb = qw->d_out / ad->lambda2;
@@ -467,21 +489,12 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
             return rc;
     }
     if (adapted) {
-        // s*U = (s/lambda1) * X * expand(A): average pool folded into the contraction
-        GemmDesc u{};
-        u.qmode = 0;
-        u.X2 = X; u.ldx2 = qw->d_in; u.W2 = ws.At_x; u.ldw2 = qw->d_in; u.K2 = qw->d_in; u.div2 = 1;
-        if (dup_a) { u.ldw2 = qw->d_in / 2; u.dup2 = 2; }
-        qblora_bf16* su = saved ? saved : ws.U;               // kept for the backward: high part, then residual
-        u.C = su; u.C_lo = saved ? saved + T * ad->R : nullptr;
-        u.ldc = ad->R; u.out_scale = op ? ad->s : ad->s / (float)ad->lambda1; u.M = T; u.N = ad->R;
-        u.part = reinterpret_cast<float*>((reinterpret_cast<uintptr_t>(Y) + 15) & ~(uintptr_t)15); u.splits = su_splits(qw, ad, T);
         {
             ScopedEvents ev(QBLORA_PROFILE_ADAPTER_FWD, st);
-            rc = launch_gemm(u, st);
+            rc = together ? launch_skinny_with(u, prep, dense ? &weight : nullptr, st) : launch_gemm(u, st);
         }
         if (rc) return rc;
-        g.X2 = su; g.ldx2 = ad->R; g.W2 = ws.Bt; g.ldw2 = ad->R; g.K2 = ad->R; g.div2 = op ? 1 : ad->lambda2;
+        g.X2 = reinterpret_cast<const qblora_bf16*>(u.C); g.ldx2 = ad->R; g.W2 = ws.Bt; g.ldw2 = ad->R; g.K2 = ad->R; g.div2 = op ? 1 : ad->lambda2;
     } else {
         g.K2 = 0; g.div2 = 1;
     }
@@ -534,14 +547,12 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         const int R = ad->R;
         const int op = scale_op_of(ad);
         const int na = qw->d_in / ad->lambda1, nb = qw->d_out / ad->lambda2;
-        // lambda = 2: the narrow GEMMs read B (and A^T) unexpanded, each column serving two adjacent features
-        const bool dup_b = op == QBLORA_OP_AVGPOOL_REPEAT && pooled_pair_operand(R, qw->d_out, ad->lambda2) &&
-                           (reinterpret_cast<uintptr_t>(ad->B) & 15) == 0;      // B is copied in 16-byte chunks
-        const bool dup_a = op == QBLORA_OP_AVGPOOL_REPEAT && pooled_pair_operand(R, qw->d_in, ad->lambda1);
+        const NarrowOperand oa = op ? NarrowOperand{false, 1, 1} : narrow_operand(ad->A, R, qw->d_in, ad->lambda1);
+        const NarrowOperand ob = op ? NarrowOperand{false, 1, 1} : narrow_operand(ad->B, R, qw->d_out, ad->lambda2);
         if (op == QBLORA_OP_AVGPOOL_REPEAT) {
-            if ((rc = launch_adapter_prep(ad->A, ad->B, dup_a ? qw->d_in / 2 : qw->d_in, qw->d_out, R,
-                                          dup_a ? 1 : ad->lambda1, ad->lambda2,
-                                          (want_grads && !saved) ? ws.At_x : nullptr, nullptr, dup_b ? nullptr : ws.Bx, st)))
+            if ((rc = launch_prep(describe_prep(ad->A, ad->B, qw->d_in / oa.dup, qw->d_out / ob.dup, R, oa.expand, ob.expand,
+                                                want_grads && !saved && !oa.in_place ? ws.At_x : nullptr, nullptr,
+                                                ob.in_place ? nullptr : ws.Bx), st)))
                 return rc;
         } else {
             // Bx[j][n] = B[j][E-map(n)], A_op[k][j] = A[C-map(k)][j] (and At_x as in the forward), zeros elsewhere
@@ -556,8 +567,8 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
         // dU = s * dY * expand(B)^T (sum pool over lambda2 folded into the contraction); dUs = dU/lambda1
         GemmDesc du{};
         du.qmode = 0;
-        du.X2 = dY; du.ldx2 = qw->d_out; du.W2 = ws.Bx; du.ldw2 = qw->d_out; du.K2 = qw->d_out; du.div2 = 1;
-        if (dup_b) { du.W2 = ad->B; du.ldw2 = nb; du.dup2 = 2; }
+        du.X2 = dY; du.ldx2 = qw->d_out; du.W2 = ob.in_place ? ad->B : ws.Bx; du.ldw2 = qw->d_out / ob.dup;
+        du.K2 = qw->d_out; du.div2 = 1; du.dup2 = ob.dup; du.in_place = ob.in_place;
         du.C = ws.dU; du.ldc = R; du.out_scale = ad->s; du.C2 = ws.dUs; du.c2_scale = op ? 1.0f : 1.0f / (float)ad->lambda1;
         du.C_lo = want_grads ? ws.dU_lo : nullptr;
         du.M = T; du.N = R; du.part = ws.part; du.splits = du_splits(qw, ad, T);
@@ -566,9 +577,8 @@ int linear_bwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
             ScopedEvents ev(QBLORA_PROFILE_ADAPTER_BWD, st);
             if (want_grads && !saved) {                       // s*U again from X, as the forward computed it
                 GemmDesc u{};
-                u.qmode = 0;
-                u.X2 = X; u.ldx2 = qw->d_in; u.W2 = ws.At_x; u.ldw2 = qw->d_in; u.K2 = qw->d_in; u.div2 = 1;
-                if (dup_a) { u.ldw2 = qw->d_in / 2; u.dup2 = 2; }
+                u.X2 = X; u.ldx2 = qw->d_in; u.W2 = ws.At_x; u.ldw2 = qw->d_in / oa.dup; u.K2 = qw->d_in; u.div2 = 1; u.dup2 = oa.dup;
+                if (oa.in_place) { u.W2 = ad->A; u.ldw2 = R; u.by_k = 1; }
                 u.C = ws.U; u.ldc = R; u.out_scale = op ? ad->s : ad->s / (float)ad->lambda1; u.M = T; u.N = R; u.C_lo = ws.U_lo;
                 // beside dU where its partial sums fit dB's (on all but outputs of a few hundred features), else behind it
                 u.splits = su_splits(qw, ad, T);
@@ -783,7 +793,7 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     if (tile8 || dense || few) sct.out = nullptr;
     DequantDesc weight;
     if (dense && (rc = describe_dequantize(*qw, ws.W16, &weight))) return rc;
-    if ((rc = launch_adapter_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, st, sct.out ? &sct : nullptr, dense ? &weight : nullptr)))
+    if ((rc = launch_prep(describe_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, sct.out ? &sct : nullptr), st, dense ? &weight : nullptr)))
         return rc;
     // s * AvgPool_lambda1(X)
     if ((rc = launch_pool_rows(PoolDesc{X, T, qw->d_in, lambda1, s / (float)lambda1, ws.P, nullptr}, nullptr, st))) return rc;
@@ -880,7 +890,7 @@ int qblora_tile_product(const qblora_adapter* ad, int32_t d_in, int32_t d_out, f
     int rc = launch_tile_product(ad->A, ad->B, rows, cols, ad->R, H, st);
     if (rc != QBLORA_ERR_UNSUPPORTED) return rc;
     qblora_bf16* Bt = static_cast<qblora_bf16*>(workspace);
-    rc = launch_adapter_prep(ad->A, ad->B, d_in, d_out, ad->R, ad->lambda1, ad->lambda2, nullptr, Bt, nullptr, st);
+    rc = launch_prep(describe_prep(ad->A, ad->B, d_in, d_out, ad->R, ad->lambda1, ad->lambda2, nullptr, Bt, nullptr), st);
     if (rc) return rc;
     GemmDesc g{};
     g.qmode = 0;
@@ -1006,12 +1016,12 @@ int qblora_decode_pack(const qblora_qweight* qw, void* pack, void* stream) {
     sct.scales = grouped ? nullptr : qw->scales;
     if (grouped) { sct.scale_codes = qw->scale_codes; sct.scale_step = qw->scale_step; sct.scale_mid = qw->scale_mid; }
     sct.scale_group = qw->scale_group; sct.d_out = qw->d_out; sct.d_in = qw->d_in; sct.out = p.scales;
-    if ((rc = launch_adapter_prep(nullptr, nullptr, qw->d_in, qw->d_out, 0, 1, 1, nullptr, nullptr, nullptr, st, &sct)))
+    if ((rc = launch_prep(describe_prep(nullptr, nullptr, qw->d_in, qw->d_out, 0, 1, 1, nullptr, nullptr, nullptr, &sct), st)))
         return rc;
     if (qw->beta) {
         ScaleTiling bt{};
         bt.scales = qw->beta; bt.d_out = qw->d_out; bt.d_in = qw->d_in; bt.out = p.beta;
-        if ((rc = launch_adapter_prep(nullptr, nullptr, qw->d_in, qw->d_out, 0, 1, 1, nullptr, nullptr, nullptr, st, &bt)))
+        if ((rc = launch_prep(describe_prep(nullptr, nullptr, qw->d_in, qw->d_out, 0, 1, 1, nullptr, nullptr, nullptr, &bt), st)))
             return rc;
     }
     return QBLORA_OK;

@@ -123,9 +123,23 @@ struct ScaleTiling {
     int scale_group, d_out, d_in;
     float* out;
 };
-int launch_adapter_prep(const qblora_bf16* A, const qblora_bf16* B, int d_in, int d_out, int R, int lam1,
-                        int lam2, qblora_bf16* At_x, qblora_bf16* Bt, qblora_bf16* Bx, hipStream_t st,
-                        const ScaleTiling* sc = nullptr, const DequantDesc* dequant = nullptr);   // the weight in the same launch
+struct PrepDesc {
+    const uint16_t* A; const uint16_t* B;
+    int na_A, R, lam1;          // A is [na_A, R]
+    int cols_B, lam2;           // B is [R, cols_B]
+    uint16_t* At_x; uint16_t* Bt; uint16_t* Bx;
+    int tilesA_a, tilesA_b, nA;     // tile grid of the A job and its block count (0 when skipped)
+    int tilesB_a, tilesB_b, nB;     // tile grid of the B-transpose job
+    int nX;                         // blocks of the column-expansion job (2048 outputs each)
+    // block scales in the order the forward kernel streams them: [row tile of 256][64-block][row in tile]
+    const float* scales; const uint8_t* scale_codes; const float* scale_step; const float* scale_mid;
+    int scale_group, d_out, bpr;
+    float* scales_tiled; int nS;    // blocks of this job (256 rows x 16 blocks each)
+    __host__ __device__ int blocks() const { return nA + nB + nS + nX; }
+};
+PrepDesc describe_prep(const qblora_bf16* A, const qblora_bf16* B, int d_in, int d_out, int R, int lam1, int lam2,
+                       qblora_bf16* At_x, qblora_bf16* Bt, qblora_bf16* Bx, const ScaleTiling* sc = nullptr);
+int launch_prep(const PrepDesc& d, hipStream_t st, const DequantDesc* dequant = nullptr);   // the weight in the same launch
 
 // One GEMM launch description.  C[M,N] = out_scale1 * ( X1[M,K1] * Wq^T  +  X2[M,K2] * W2[N/div2, K2]^T )
 // "token" operands X1/X2 are bf16 row-major; the quantized segment is optional (qmode 0).
@@ -149,6 +163,8 @@ struct GemmDesc {
     int64_t M; int N;
     int block_rows;            // rows of a quantization block: 0/1 = 64 inputs of one row, 8 = 8 rows x 8 inputs
     int dup2;                  // qmode 0, narrow form only: 2 = W2 has K2/2 columns, column m serves k = 2m, 2m+1
+    int by_k;                  // qmode 0, narrow form only: W2 is stored the other way round, [K2 or K2/2 rows][N]
+    int in_place;              // qmode 0, narrow form only: W2 is the adapter's own matrix
     float* part; int splits;   // qmode 0 (narrow form) and 3: splits > 1 = the contraction in that many workgroup slices,
                                // fp32 [splits][M][N] partial sums in `part` (skinny_splits, dense_splits; 16-byte aligned)
 };
@@ -182,6 +198,10 @@ int skinny_splits(int64_t M, int N, int K, int64_t max_part_bytes);
 // no fewer rows of partial sums, slices x tokens, than any number of tokens up to M takes
 int64_t skinny_part_rows(int64_t M, int N, int K);
 int launch_skinny(const GemmDesc& d, hipStream_t st);
+// a GEMM whose W2 is stored by k, with re-layouts that it does not wait for in the same launch and, where it is sliced, the
+// weight (may be NULL) in the launch of the sums
+bool skinny_shares(const GemmDesc& d);
+int launch_skinny_with(const GemmDesc& d, const PrepDesc& prep, const DequantDesc* weight, hipStream_t st);
 // two of them, independent of each other, with partial sums of their own: one launch where they take the same form
 int launch_skinny_pair(const GemmDesc& a, const GemmDesc& b, hipStream_t st);
 

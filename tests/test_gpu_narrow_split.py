@@ -69,3 +69,39 @@ def test_sliced_narrow_gemms_of_the_other_operators(oracle, codebook, rules, T, 
     assert_close_bf16(dX, rX, "dX")
     assert_close_f32(dA, rA, "dA")
     assert_close_f32(dB, rB, "dB")
+
+
+@pytest.mark.parametrize("T,d_out,d_in,R,lam", [
+    (77, 2112, 2880, 8, 1),        # an odd number of 64-wide steps both ways: half a stage at the end of the last slice
+    (70, 2368, 2752, 40, 2),       # the same with one stored value for two features
+    (33, 2880, 2112, 72, 8),       # expanded by four, two column tiles
+    (129, 2496, 2880, 24, 6),      # expanded by three
+    (65, 64, 192, 8, 1), (5, 192, 64, 16, 2), (300, 320, 448, 136, 2),     # not sliced: one, two, four stages, one half
+    (129, 448, 320, 200, 1),       # four column tiles of A as it lies
+    (8200, 192, 320, 96, 2),       # 128-column tiles; the last column tile ends inside one
+    (8200, 320, 192, 136, 1),      # the same, one stored value a feature
+])
+def test_narrow_gemms_on_operands_as_they_lie(oracle, codebook, T, d_out, d_in, R, lam):
+    """Kept and recomputed s*U and the forward on the library's own scratch included (same bits)."""
+    test_sliced_narrow_gemms(oracle, codebook, T, d_out, d_in, R, lam)
+
+
+@pytest.mark.parametrize("lam", [1, 2])
+def test_operands_off_16_bytes_take_a_copy(oracle, codebook, lam):
+    """A and B at any address: copies of them are read then, with the same bits."""
+    from paper_2407_17029_amd import binding as qb
+    from gpu_util import f32_to_dev, bf16_to_dev
+    T, d_out, d_in, R = 90, 2240, 2368, 24
+    L = synth.make_layer(6300 + lam, T, d_out, d_in, R, lam, lam)
+    qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook)
+    A, B, X, dY = (bf16_to_dev(t) for t in (L.A, L.B, L.X, L.dY))
+
+    def off(t):
+        return torch.cat([t.new_zeros(1), t.reshape(-1)])[1:].view(t.shape)
+
+    res = []
+    for a, b in ((A, B), (off(A), off(B))):
+        ad = qb.Adapter(a, b, lam, lam, 0.5)
+        res.append((qb.qblora_linear_fwd(qw, ad, X), *qb.qblora_linear_bwd(qw, ad, X, dY)))
+    torch.cuda.synchronize()
+    assert off(A).data_ptr() % 16 and all(torch.equal(x, y) for x, y in zip(*res))
