@@ -9,6 +9,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+import struct
 
 import numpy as np
 import torch
@@ -50,6 +51,13 @@ class CQWeight(C.Structure):
 class CAdapter(C.Structure):
     _fields_ = [("lambda1", C.c_int32), ("lambda2", C.c_int32), ("R", C.c_int32), ("s", C.c_float),
                 ("A", C.c_void_p), ("B", C.c_void_p), ("scale_op", C.c_int32)]
+
+
+# The same layouts for struct.pack: one call instead of a descriptor access per field (a description of a weight took 9 us
+# of the 10 that a small inference call spent in Python, now 2).
+_QWEIGHT, _ADAPTER = struct.Struct("=5i64s4x7Qi4x"), struct.Struct("=3if2Qi4x")
+_FLOAT32 = np.dtype(np.float32)
+assert _QWEIGHT.size == C.sizeof(CQWeight) and _ADAPTER.size == C.sizeof(CAdapter)
 
 
 class QBLoRAError(RuntimeError):
@@ -190,11 +198,16 @@ def _check(code: int, where: str) -> None:
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)      # without a torch.cuda.Stream object around it
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 class QWeight:
@@ -210,7 +223,22 @@ class QWeight:
         self.scale_codes, self.scale_step, self.scale_mid = scale_codes, scale_step, scale_mid
         self.codes_tiled = codes_tiled          # optional tile-ordered copy of the codes (forward fast path)
 
+    def c_bytes(self) -> bytes:
+        """The C struct as an immutable argument for calls that only read it; describes the object as it is now."""
+        try:
+            cb = self.codebook
+            raw = cb.tobytes() if cb.dtype is _FLOAT32 and cb.shape == (16,) else bytes(self._c_struct())[20:84]
+            return _QWEIGHT.pack(self.d_out, self.d_in, self.block, self.scale_mode, self.scale_group, raw, *[
+                0 if t is None else t.data_ptr()
+                for t in (self.codes, self.scales, self.beta, self.scale_codes, self.scale_step, self.scale_mid,
+                          self.codes_tiled)], self.block_rows)
+        except (struct.error, AttributeError):            # numbers and codebooks that only the fields themselves convert
+            return bytes(self._c_struct())
+
     def c_struct(self) -> CQWeight:
+        return CQWeight.from_buffer_copy(self.c_bytes())
+
+    def _c_struct(self) -> CQWeight:
         s = CQWeight()
         s.d_out, s.d_in, s.block = self.d_out, self.d_in, self.block
         s.scale_mode, s.scale_group = self.scale_mode, self.scale_group
@@ -226,7 +254,7 @@ class QWeight:
         """Take back the scalar fields the library filled in."""
         self.d_out, self.d_in, self.block = s.d_out, s.d_in, s.block
         self.scale_mode, self.scale_group = s.scale_mode, s.scale_group
-        self.codebook = np.array([s.codebook[j] for j in range(16)], np.float32)
+        self.codebook = np.array(s.codebook, np.float32)
         if not s.beta:
             self.beta = None
 
@@ -239,6 +267,14 @@ class Adapter:
         self.R = 0 if A is None else int(A.shape[1])
         self.scale_op = int(scale_op)        # OP_*: the scale operators of the ablation (Sec. 4.3)
 
+    def c_bytes(self) -> bytes:
+        """The C struct as an immutable argument, as of now."""
+        try:
+            return _ADAPTER.pack(self.lambda1, self.lambda2, self.R, self.s, 0 if self.A is None else self.A.data_ptr(),
+                                 0 if self.B is None else self.B.data_ptr(), self.scale_op)
+        except (struct.error, OverflowError):             # numbers that only the fields themselves convert
+            return bytes(self.c_struct())
+
     def c_struct(self) -> CAdapter:
         a = CAdapter()
         a.lambda1, a.lambda2, a.R, a.s = self.lambda1, self.lambda2, self.R, self.s
@@ -248,11 +284,8 @@ class Adapter:
         return a
 
 
-def _adapter_ref(ad):
-    if ad is None:
-        return None, None
-    s = ad.c_struct()
-    return s, C.byref(s)
+def _adapter(ad):
+    return None if ad is None else ad.c_bytes()
 
 
 def qblora_codes_tiled_bytes(d_out: int, d_in: int) -> int:
@@ -264,8 +297,7 @@ def qblora_prepack_codes(qw: QWeight) -> QWeight:
     if qw.codes_tiled is None:
         qw.codes_tiled = torch.empty(qblora_codes_tiled_bytes(qw.d_out, qw.d_in), dtype=torch.uint8,
                                      device=qw.codes.device)
-    s = qw.c_struct()
-    _check(lib().qblora_prepack_codes(C.byref(s), _stream()), "qblora_prepack_codes")
+    _check(lib().qblora_prepack_codes(qw.c_bytes(), _stream()), "qblora_prepack_codes")
     return qw
 
 
@@ -314,21 +346,16 @@ def qblora_quantize_blockwise(W: torch.Tensor, block: int = 64, quantizer: int =
 
 def qblora_dequantize_bf16(qw: QWeight) -> torch.Tensor:
     Wt = torch.empty((qw.d_out, qw.d_in), dtype=torch.bfloat16, device=qw.codes.device)
-    s = qw.c_struct()
-    _check(lib().qblora_dequantize_bf16(C.byref(s), _ptr(Wt), _stream()), "qblora_dequantize_bf16")
+    _check(lib().qblora_dequantize_bf16(qw.c_bytes(), _ptr(Wt), _stream()), "qblora_dequantize_bf16")
     return Wt
 
 
 def qblora_linear_fwd_workspace_bytes(qw: QWeight, ad, T: int) -> int:
-    s = qw.c_struct()
-    a, aref = _adapter_ref(ad)
-    return int(lib().qblora_linear_fwd_workspace_bytes(C.byref(s), aref, T))
+    return int(lib().qblora_linear_fwd_workspace_bytes(qw.c_bytes(), _adapter(ad), T))
 
 
 def qblora_linear_bwd_workspace_bytes(qw: QWeight, ad, T: int) -> int:
-    s = qw.c_struct()
-    a, aref = _adapter_ref(ad)
-    return int(lib().qblora_linear_bwd_workspace_bytes(C.byref(s), aref, T))
+    return int(lib().qblora_linear_bwd_workspace_bytes(qw.c_bytes(), _adapter(ad), T))
 
 
 def _workspace(nbytes, device, workspace):
@@ -339,8 +366,7 @@ def _workspace(nbytes, device, workspace):
 
 
 def qblora_saved_bytes(ad, T: int) -> int:
-    a, aref = _adapter_ref(ad)
-    return int(lib().qblora_saved_bytes(aref, T))
+    return int(lib().qblora_saved_bytes(_adapter(ad), T))
 
 
 def qblora_linear_fwd(qw: QWeight, ad, X: torch.Tensor, Y: torch.Tensor = None, workspace: torch.Tensor = None,
@@ -351,14 +377,13 @@ def qblora_linear_fwd(qw: QWeight, ad, X: torch.Tensor, Y: torch.Tensor = None, 
     if Y is None:
         Y = torch.empty((T, qw.d_out), dtype=torch.bfloat16, device=X.device)
     ws = _workspace(lambda: qblora_linear_fwd_workspace_bytes(qw, ad, T), X.device, workspace)
-    s = qw.c_struct()
-    a, aref = _adapter_ref(ad)
+    s, a = qw.c_bytes(), _adapter(ad)
     if saved is None:
-        rc = lib().qblora_linear_fwd(C.byref(s), aref, _ptr(X), T, _ptr(Y), _ptr(ws), ws.numel(), _stream())
+        rc = lib().qblora_linear_fwd(s, a, _ptr(X), T, _ptr(Y), _ptr(ws), ws.numel(), _stream())
         _check(rc, "qblora_linear_fwd")
     else:
-        assert saved.is_cuda and saved.numel() * saved.element_size() >= qblora_saved_bytes(ad, T)
-        rc = lib().qblora_linear_fwd_save(C.byref(s), aref, _ptr(X), T, _ptr(Y), _ptr(saved), _ptr(ws), ws.numel(),
+        assert saved.is_cuda and saved.numel() * saved.element_size() >= lib().qblora_saved_bytes(a, T)
+        rc = lib().qblora_linear_fwd_save(s, a, _ptr(X), T, _ptr(Y), _ptr(saved), _ptr(ws), ws.numel(),
                                           _stream())
         _check(rc, "qblora_linear_fwd_save")
     return Y
@@ -376,9 +401,7 @@ def qblora_linear_fwd_noalloc(qw: QWeight, ad, X: torch.Tensor, Y: torch.Tensor)
     """qblora_linear_fwd on the library's own scratch array: the caller passes inputs and the output only."""
     assert X.is_cuda and X.dtype == torch.bfloat16 and X.is_contiguous() and X.shape[1] == qw.d_in
     assert Y.is_cuda and Y.dtype == torch.bfloat16 and Y.is_contiguous() and tuple(Y.shape) == (X.shape[0], qw.d_out)
-    s = qw.c_struct()
-    a, aref = _adapter_ref(ad)
-    _check(lib().qblora_linear_fwd_noalloc(C.byref(s), aref, _ptr(X), X.shape[0], _ptr(Y), _stream()),
+    _check(lib().qblora_linear_fwd_noalloc(qw.c_bytes(), _adapter(ad), _ptr(X), X.shape[0], _ptr(Y), _stream()),
            "qblora_linear_fwd_noalloc")
     return Y
 
@@ -398,14 +421,13 @@ def qblora_linear_bwd(qw: QWeight, ad, X: torch.Tensor, dY: torch.Tensor, need_d
         if dB is None:
             dB = torch.empty((ad.R, qw.d_out // ad.lambda2), dtype=torch.float32, device=dev)
     ws = _workspace(lambda: qblora_linear_bwd_workspace_bytes(qw, ad, T), dev, workspace)
-    s = qw.c_struct()
-    a, aref = _adapter_ref(ad)
+    s, a = qw.c_bytes(), _adapter(ad)
     if saved is None:
-        rc = lib().qblora_linear_bwd(C.byref(s), aref, _ptr(X), _ptr(dY), T, _ptr(dX), _ptr(dA), _ptr(dB), _ptr(ws),
+        rc = lib().qblora_linear_bwd(s, a, _ptr(X), _ptr(dY), T, _ptr(dX), _ptr(dA), _ptr(dB), _ptr(ws),
                                      ws.numel(), _stream())
         _check(rc, "qblora_linear_bwd")
     else:
-        rc = lib().qblora_linear_bwd_saved(C.byref(s), aref, _ptr(X), _ptr(dY), T, _ptr(saved), _ptr(dX), _ptr(dA),
+        rc = lib().qblora_linear_bwd_saved(s, a, _ptr(X), _ptr(dY), T, _ptr(saved), _ptr(dX), _ptr(dA),
                                            _ptr(dB), _ptr(ws), ws.numel(), _stream())
         _check(rc, "qblora_linear_bwd_saved")
     return dX, dA, dB
@@ -420,9 +442,9 @@ def qablora_linear_fwd(qw: QWeight, H: torch.Tensor, lambda1: int, lambda2: int,
     T = X.shape[0]
     if Y is None:
         Y = torch.empty((T, qw.d_out), dtype=torch.bfloat16, device=X.device)
-    q = qw.c_struct()
-    ws = _workspace(lambda: lib().qablora_linear_fwd_workspace_bytes(C.byref(q), lambda1, lambda2, T), X.device, workspace)
-    rc = lib().qablora_linear_fwd(C.byref(q), _ptr(H), lambda1, lambda2, s, _ptr(X), T, _ptr(Y), _ptr(ws), ws.numel(),
+    q = qw.c_bytes()
+    ws = _workspace(lambda: lib().qablora_linear_fwd_workspace_bytes(q, lambda1, lambda2, T), X.device, workspace)
+    rc = lib().qablora_linear_fwd(q, _ptr(H), lambda1, lambda2, s, _ptr(X), T, _ptr(Y), _ptr(ws), ws.numel(),
                                   _stream())
     _check(rc, "qablora_linear_fwd")
     return Y
@@ -439,9 +461,9 @@ def qablora_linear_bwd(qw: QWeight, H: torch.Tensor, lambda1: int, lambda2: int,
         dX = torch.empty((T, qw.d_in), dtype=torch.bfloat16, device=dev)
     if need_dh and dH is None:
         dH = torch.empty((qw.d_in // lambda1, qw.d_out // lambda2), dtype=torch.float32, device=dev)
-    q = qw.c_struct()
-    ws = _workspace(lambda: lib().qablora_linear_bwd_workspace_bytes(C.byref(q), lambda1, lambda2, T), dev, workspace)
-    rc = lib().qablora_linear_bwd(C.byref(q), _ptr(H), lambda1, lambda2, s, _ptr(X), _ptr(dY), T,
+    q = qw.c_bytes()
+    ws = _workspace(lambda: lib().qablora_linear_bwd_workspace_bytes(q, lambda1, lambda2, T), dev, workspace)
+    rc = lib().qablora_linear_bwd(q, _ptr(H), lambda1, lambda2, s, _ptr(X), _ptr(dY), T,
                                   _ptr(dX if need_dx else None), _ptr(dH if need_dh else None), _ptr(ws), ws.numel(),
                                   _stream())
     _check(rc, "qablora_linear_bwd")
@@ -452,9 +474,9 @@ def qblora_tile_product(ad: Adapter, d_in: int, d_out: int, H: torch.Tensor = No
     dev = ad.A.device
     if H is None:
         H = torch.empty((d_in // ad.lambda1, d_out // ad.lambda2), dtype=torch.float32, device=dev)
-    a = ad.c_struct()
-    ws = _workspace(lambda: lib().qblora_tile_product_workspace_bytes(C.byref(a), d_in, d_out), dev, workspace)
-    rc = lib().qblora_tile_product(C.byref(a), d_in, d_out, _ptr(H), _ptr(ws), ws.numel(), _stream())
+    a = ad.c_bytes()
+    ws = _workspace(lambda: lib().qblora_tile_product_workspace_bytes(a, d_in, d_out), dev, workspace)
+    rc = lib().qblora_tile_product(a, d_in, d_out, _ptr(H), _ptr(ws), ws.numel(), _stream())
     _check(rc, "qblora_tile_product")
     return H
 
@@ -469,9 +491,8 @@ def qablora_merge_quantize(base: QWeight, H: torch.Tensor, lambda1: int, lambda2
                       torch.empty(tuple(base.scales.shape), dtype=torch.float32, device=dev),
                       torch.empty(tuple(base.scales.shape), dtype=torch.float32, device=dev),
                       block_rows=base.block_rows)
-    b = base.c_struct()
     o = out.c_struct()
-    rc = lib().qablora_merge_quantize(C.byref(b), _ptr(H), lambda1, lambda2, s, mode, C.byref(o), _stream())
+    rc = lib().qablora_merge_quantize(base.c_bytes(), _ptr(H), lambda1, lambda2, s, mode, C.byref(o), _stream())
     _check(rc, "qablora_merge_quantize")
     beta_keep = out.beta
     out.absorb(o)
@@ -490,11 +511,9 @@ def qablora_merge_quantize_batch(bases, Hs, lambda1: int, lambda2: int, s: float
                         torch.empty(tuple(b.scales.shape), dtype=torch.float32, device=b.codes.device),
                         torch.empty(tuple(b.scales.shape), dtype=torch.float32, device=b.codes.device),
                         block_rows=b.block_rows) for b in bases]
-    bs = [b.c_struct() for b in bases]
-    os_ = [o.c_struct() for o in outs]
-    Pq = C.POINTER(CQWeight)
-    barr = (Pq * n)(*[C.pointer(x) for x in bs])
-    oarr = (Pq * n)(*[C.pointer(x) for x in os_])
+    bs = (CQWeight * n).from_buffer_copy(b"".join([b.c_bytes() for b in bases]))
+    os_ = (CQWeight * n).from_buffer_copy(b"".join([o.c_bytes() for o in outs]))
+    barr, oarr = ((C.c_void_p * n)(*[C.addressof(a) + i * _QWEIGHT.size for i in range(n)]) for a in (bs, os_))
     harr = (C.c_void_p * n)(*[_ptr(H) for H in Hs])
     rc = lib().qablora_merge_quantize_batch(n, barr, harr, lambda1, lambda2, C.c_float(s), mode, oarr, _stream())
     _check(rc, "qablora_merge_quantize_batch")
@@ -513,17 +532,16 @@ def qblora_merge_bf16(base: QWeight, H: torch.Tensor, lambda1: int, lambda2: int
     assert H.is_cuda and H.dtype == torch.float32 and H.is_contiguous()
     if W16 is None:
         W16 = torch.empty((base.d_out, base.d_in), dtype=torch.bfloat16, device=H.device)
-    b = base.c_struct()
-    rc = lib().qblora_merge_bf16(C.byref(b), _ptr(H), lambda1, lambda2, s, _ptr(W16), _stream())
+    rc = lib().qblora_merge_bf16(base.c_bytes(), _ptr(H), lambda1, lambda2, s, _ptr(W16), _stream())
     _check(rc, "qblora_merge_bf16")
     return W16
 
 
 def qblora_decode_pack(qw: QWeight) -> torch.Tensor:
     """One-off tile-ordered copy of codes / scales / offsets for qblora_linear_decode."""
-    q = qw.c_struct()
-    pack = torch.empty(int(lib().qblora_decode_pack_bytes(C.byref(q))), dtype=torch.uint8, device=qw.codes.device)
-    _check(lib().qblora_decode_pack(C.byref(q), _ptr(pack), _stream()), "qblora_decode_pack")
+    q = qw.c_bytes()
+    pack = torch.empty(int(lib().qblora_decode_pack_bytes(q)), dtype=torch.uint8, device=qw.codes.device)
+    _check(lib().qblora_decode_pack(q, _ptr(pack), _stream()), "qblora_decode_pack")
     return pack
 
 
@@ -534,8 +552,8 @@ def qblora_linear_decode(qw: QWeight, X: torch.Tensor, Y: torch.Tensor = None, w
     T = X.shape[0]
     if Y is None:
         Y = torch.empty((T, qw.d_out), dtype=torch.bfloat16, device=X.device)
-    q = qw.c_struct()
-    ws = _workspace(lambda: lib().qblora_linear_decode_tokens_workspace_bytes(C.byref(q), T), X.device, workspace)
-    rc = lib().qblora_linear_decode(C.byref(q), _ptr(pack), _ptr(X), T, _ptr(Y), _ptr(ws), ws.numel(), _stream())
+    q = qw.c_bytes()
+    ws = _workspace(lambda: lib().qblora_linear_decode_tokens_workspace_bytes(q, T), X.device, workspace)
+    rc = lib().qblora_linear_decode(q, _ptr(pack), _ptr(X), T, _ptr(Y), _ptr(ws), ws.numel(), _stream())
     _check(rc, "qblora_linear_decode")
     return Y

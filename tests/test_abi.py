@@ -153,3 +153,31 @@ def test_workspace_sizes(qb):
     qw.scale_mode, qw.scale_group = 1, 256
     qw.scale_codes = qw.scale_step = qw.scale_mid = 0x1000
     assert L.qblora_linear_fwd_workspace_bytes(C.byref(qw), None, many) == dense_w + 4 * 4096 * 64
+
+
+def test_descriptions_are_packed_as_their_fields_say(qb):
+    """The packed form of a weight's and an adapter's description, and what it does with values that struct.pack refuses;
+    both follow the object as it is when they are made."""
+    import numpy as np
+    import torch
+    t = [torch.zeros(4) for _ in range(7)]
+    w = qb.QWeight(24, 128, 64, np.arange(16) / 7.0, t[0], t[1], t[2], qb.SCALES_E4M3_GROUPED, t[3], t[4], t[5], 512, t[6], 8)
+    a = qb.Adapter(torch.zeros(3, 8), torch.zeros(8, 5), 2, 3, 0.1, scale_op=2)
+    for change in (lambda: None, lambda: setattr(w, "d_out", np.int64(72)), lambda: w.codebook.__setitem__(3, -2.5),
+                   lambda: setattr(w, "beta", None), lambda: setattr(w, "codebook", list(range(16))),
+                   lambda: setattr(w, "codebook", np.arange(16, dtype=np.float64)), lambda: setattr(w, "d_in", 2**31 + 64),
+                   lambda: setattr(a, "A", None), lambda: setattr(a, "s", 1e300)):
+        change()
+        got, want = w.c_struct(), w._c_struct()
+        assert w.c_bytes() == bytes(got)
+        for name, _ in qb.CQWeight._fields_:
+            x, y = getattr(got, name), getattr(want, name)
+            assert (list(x) == list(y)) if name == "codebook" else (x == y)
+        got, want = qb.CAdapter.from_buffer_copy(a.c_bytes()), a.c_struct()
+        assert all(getattr(got, n) == getattr(want, n) for n, _ in qb.CAdapter._fields_)
+    s = qb.CQWeight.from_buffer_copy(w.c_bytes())
+    s.codebook[5] = 9.25
+    w.absorb(s)
+    assert w.codebook.dtype == np.float32 and w.codebook.shape == (16,) and w.codebook[5] == 9.25
+    s.codebook[5] = 0.0
+    assert w.codebook[5] == 9.25                          # a copy of its own
