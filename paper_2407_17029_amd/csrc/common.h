@@ -179,9 +179,11 @@ bool few_applies(int64_t M, int N, int K);
 int launch_few(const GemmDesc& d, hipStream_t st);
 // the contraction on a weight dequantized beforehand (qmode 3); called by launch_gemm
 int launch_dense(const GemmDesc& d, hipStream_t st);
-// its tile shape (0 .. 3: 256 x 256, 128 x 256, 256 x 128, 128 x 128 tokens x features), slices and estimated time
+// The tile shape (0 .. 6: 256 x 256, 128 x 256, 256 x 128, 128 x 128, 128 x 192, 192 x 128, 192 x 192 tokens x features), slices and
+// estimated time that bound a call's (0 .. 3 only; no call takes more slices), and those that it takes
 struct DensePlan { int shape, splits; int64_t ns; };
 DensePlan dense_plan(int64_t M, int N, int k1, int k2, int max_splits);
+DensePlan dense_call_plan(int64_t M, int N, int k1, int k2, int max_splits);
 // whether dequantizing the weight first is faster than contracting straight from the codes (qmode 3 against qmode 1)
 bool dense_pays(int64_t M, int N, int k1, int k2);
 // the same for the transposed weight (qmode 3, in slices where they pay, against qmode 4)

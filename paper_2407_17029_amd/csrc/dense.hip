@@ -8,23 +8,30 @@
 // the adapter's K-extension (forward: X2 = s*U, W2 = B^T with output row n using row n/lambda2; backward: X2 =
 // dU/lambda1, W2 = A with row k/lambda1): its steps run through the same ring, W2's rows gathered by the copies.
 //
-// Bound: the matrix pipe.  A workgroup is 8 wave64 as 2 (tokens) x 4 (features), two waves to a SIMD; a wave owns
-// 32*MB tokens x 32*NB features.  The two waves of a SIMD belong to different halves of the workgroup (waves 0-3
-// and 4-7) that alternate strictly: while one half runs a compute phase (16 or 32 MFMAs, 16 cycles each) the other runs a
-// memory phase (LDS fragment reads for its next compute phase, two to six copies into the ring, the waits), with
-// a barrier between phases.  The second half passes one extra barrier at the start, so a compute phase always has
-// a memory phase beside it: fragment reads, their latency and the refills hide under the other wave's MFMAs, and
-// the copies leave evenly spread instead of in a burst behind a barrier.
+// Bound: the matrix pipe.  Two kernels, by the size of the tile:
 //
-// All copies are direct (global_load_lds, 16 bytes a lane) in assembly statements without register outputs, in
-// program order, so the waits are exact counts: a part of a tile (16 KB, 2 copies a wave) is waited for at the end
-// of the memory phase in front of the one that reads it, with 12 younger copies (8 in the smallest tile, 6 in the 128 x 256 one's long phases) still
-// in flight.  A region of the ring is refilled from the memory phase behind the one that read it: reads complete
-// (lgkmcnt(0)) in front of the barrier that ends their phase, and the other half's same phase ends one barrier
-// earlier than the refill starts.
+// k_dense, 256 x 256 tiles, for calls that fill rounds of the chip with them (1450 to 1510 TFLOP/s at 1.6-1.7 GHz, where the
+// part is power-limited).  A workgroup is 8 wave64 as 2 (tokens) x 4 (features), two waves to a SIMD; a wave owns 128 tokens x
+// 64 features.  The two waves of a SIMD belong to different halves of the workgroup (waves 0-3 and 4-7) that alternate
+// strictly: while one half runs a compute phase (16 MFMAs, 16 cycles each) the other runs a memory phase (LDS fragment reads
+// for its next compute phase, two copies into the ring, the waits), with a barrier between phases.  The second half passes one
+// extra barrier at the start, so a compute phase always has a memory phase beside it: fragment reads, their latency and the
+// refills hide under the other wave's MFMAs, and the copies leave evenly spread instead of in a burst behind a barrier.  The
+// waits are exact counts: a part of a tile (16 KB, 2 copies a wave) is waited for at the end of the memory phase in front of
+// the one that reads it, with 12 younger copies still in flight.  A region of the ring is refilled from the memory phase
+// behind the one that read it: reads complete (lgkmcnt(0)) in front of the barrier that ends their phase, and the other half's
+// same phase ends one barrier earlier than the refill starts.
 //
+// k_flow, smaller tiles, for all other calls.  Eight waves contract, four others, one to a SIMD, do nothing but copy: a copy
+// instruction holds up the wave that issues it, and among the MFMAs that cost a quarter of the time.  The fragments of the next
+// 64 or 32 wide step are read between the MFMAs of this one; one barrier a step says that the next stage is in and that the
+// last one is free.  us in the phased form (which smaller tiles had too) / with the copies among the MFMAs / here: 1337 x 5120 x
+// 5184 in 128 x 256 tiles 71 / 72 / 60, 1024 x 4096 x 4608 in 128 x 128 42.4 / 38.1 / 33.9 (without any copies: 28.6), 334 x 4224
+// x 8064 64 / 52 / 45, 512 x 4096 x 11136 in four slices of 128 x 256 51 / 51 / 47.
+//
+// All copies are direct (global_load_lds, 16 bytes a lane) in assembly statements without register outputs, in program order.
 // k is accumulated in ascending order by v_mfma_f32_16x16x32_bf16, as in the kernel that contracts from the codes
-// (qlinear.hip), so both give the same bits where this one is not sliced.
+// (qlinear.hip), so all of them give the same bits where they are not sliced.
 #include <algorithm>
 #include <type_traits>
 
@@ -65,25 +72,24 @@ __device__ __forceinline__ void end_compute() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int MB, int NB>
+// 256 x 256 tiles
+constexpr int MB = 4, NB = 2;                                               // a wave's 32-row blocks of tokens and features
 struct Ring {
-    static constexpr int kStages = MB == 4 && NB == 2 ? 2 : MB == 2 && NB == 1 ? 4 : 3;
+    static constexpr int kStages = 2;
     static constexpr int kX = MB * 8192, kW = NB * kPart, kStage = kX + kW;     // bytes
     static constexpr int kPitch = NB * 64 + 16;                                 // epilogue: output row of a wave in LDS
     static constexpr int kEpilogue = 8 * MB * 32 * kPitch;
     static constexpr int kLds = kStages * kStage > kEpilogue ? kStages * kStage : kEpilogue;
 };
 
-// WHOLE: a phase works on a whole step (128 x 256 tiles only)
-template <int MB, int NB, bool WHOLE>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_dense(GemmDesc d) {
-    using R = Ring<MB, NB>;
+    using R = Ring;
     constexpr int BM = 64 * MB, BN = 128 * NB, S = R::kStages;
     extern __shared__ __align__(16) unsigned char smem[];
 
     const int64_t M = d.M;
     const int N = d.N, K2 = d.K2, div2 = d.div2;
-    const int all_steps = d.K1 / kBK + (K2 + kBK - 1) / kBK;
+    const int n = d.K1 / kBK + (K2 + kBK - 1) / kBK, steps1 = d.K1 / kBK;     // steps1 of them belong to the first segment
     const int64_t ldx2 = d.ldx2, ldw2 = d.ldw2;
     const qblora_bf16* const X2 = d.X2;
     const qblora_bf16* const W2 = d.W2;
@@ -96,21 +102,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // Tile assignment: workgroup ids go to the XCDs round-robin; each XCD gets a contiguous range of tiles, grouped
     // along tokens so that the tiles it runs at a time share token and weight panels in its L2.
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN, ntiles = tiles_m * tiles_n;
-    const int splits = d.splits > 1 ? d.splits : 1;
     int L;
     {
-        const int units = ntiles * splits, xcd = blockIdx.x & 7, q = units >> 3, rem = units & 7;
+        const int xcd = blockIdx.x & 7, q = ntiles >> 3, rem = ntiles & 7;
         L = xcd * q + min(xcd, rem) + (blockIdx.x >> 3);
     }
-    // slice z of the contraction (all tiles of a slice are neighbours): n steps from step0 on, at least one
-    int z = 0, step0 = 0, n = all_steps;
-    if (splits > 1) {
-        z = L / ntiles;
-        step0 = all_steps * z / splits;
-        n = all_steps * (z + 1) / splits - step0;
-        L -= z * ntiles;
-    }
-    const int steps1 = d.K1 / kBK - step0;        // steps from here on that belong to the first segment (may be negative)
     constexpr int GM = 4;
     const int in_group = GM * tiles_n, first_m = (L / in_group) * GM, gsize = min(tiles_m - first_m, GM);
     const int64_t m0 = (int64_t)(first_m + (L % in_group) % gsize) * BM;
@@ -125,7 +121,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // collide in pairs: 19 % of the kernel's cycles.)
     uint32_t xoff[MB / 2][2];
     int xchunk[2];
-    const qblora_bf16* const x_tile = d.X1 + m0 * d.ldx1 + (int64_t)step0 * kBK;
+    const qblora_bf16* const x_tile = d.X1 + m0 * d.ldx1;
 #pragma unroll
     for (int i = 0; i < 2; ++i) xchunk[i] = (lane & 7) ^ (4 * i + (lane >> 4));
     auto token_row = [&](int p, int i) __attribute__((always_inline)) {          // tile row, clamped to the last token
@@ -143,7 +139,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int a = 0; a < NB; ++a) {
         wblk[a] = min(n0 / 32 + (wave >> 1) * NB + a, blocks32 - 1);    // rows past N: any block, results never stored
-        wbase[a] = reinterpret_cast<const unsigned char*>(d.W1) + (int64_t)(2 * wblk[a] + (wave & 1)) * (d.K1 / 32) * 1024 + (int64_t)step0 * 2048;
+        wbase[a] = reinterpret_cast<const unsigned char*>(d.W1) + (int64_t)(2 * wblk[a] + (wave & 1)) * (d.K1 / 32) * 1024;
     }
     const uint32_t lane16 = (uint32_t)lane * 16u;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
@@ -209,7 +205,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // reach the pipe as it drains (interval 292 -> 283 cycles against 256 of MFMAs).  The raised priority makes the
     // last MFMA issue ahead of the other half's; without it this half's next memory phase starts late (the whole
     // kernel 20 % slower with the barrier two MFMAs early).
-    auto compute = [&](int a, int p, auto ends_phase) __attribute__((always_inline)) {
+    auto compute = [&](int a, int p) __attribute__((always_inline)) {
         __builtin_amdgcn_s_setprio(1);
 #pragma unroll
         for (int ks = 0; ks < 2; ++ks)
@@ -217,7 +213,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
             for (int h = 0; h < 2; ++h)
 #pragma unroll
                 for (int b = 0; b < 4; ++b) {
-                    if (ends_phase.value && ks == 1 && h == 1 && b == 3) {
+                    if (ks == 1 && h == 1 && b == 3) {
                         __builtin_amdgcn_s_setprio(3);
                         end_compute();
                     }
@@ -225,176 +221,53 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
                         __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[a][h][ks], xf[b][ks], acc[2 * a + h][4 * p + b], 0, 0, 0);
                 }
         __builtin_amdgcn_sched_barrier(0);
-        if (ends_phase.value) __builtin_amdgcn_s_setprio(0);
+        __builtin_amdgcn_s_setprio(0);
     };
     auto slot_of = [&](int step) __attribute__((always_inline)) { return (uint32_t)(step % S) * (uint32_t)R::kStage; };
 
-    if constexpr (MB == 4 && NB == 2) {
-        // Phases of step s (reads -> MFMAs; copies for step s+2 into the region read one phase earlier):
-        //   0: X part 0 -> (W0, X0), W0(s+2);   1: W1 -> (W1, X0), X0(s+2);
-        //   2: X part 1 -> (W0, X1), W1(s+2);   3: W0(s+1) -> (W1, X1), X1(s+2)
-        issue_w(0, 0, 0); issue_x(0, 0, 0); issue_w(1, 0, 0); issue_x(1, 0, 0);
-        if (n > 1) {
-            issue_w(0, 1, R::kStage); issue_x(0, 1, R::kStage); issue_w(1, 1, R::kStage); issue_x(1, 1, R::kStage);
-            end_memory(Int<12>{});
-        } else {
-            end_memory(Int<0>{});
-        }
-        read_w(0, 0);
+    // Phases of step s (reads -> MFMAs; copies for step s+2 into the region read one phase earlier):
+    //   0: X part 0 -> (W0, X0), W0(s+2);   1: W1 -> (W1, X0), X0(s+2);
+    //   2: X part 1 -> (W0, X1), W1(s+2);   3: W0(s+1) -> (W1, X1), X1(s+2)
+    issue_w(0, 0, 0); issue_x(0, 0, 0); issue_w(1, 0, 0); issue_x(1, 0, 0);
+    if (n > 1) {
+        issue_w(0, 1, R::kStage); issue_x(0, 1, R::kStage); issue_w(1, 1, R::kStage); issue_x(1, 1, R::kStage);
         end_memory(Int<12>{});
-        if (wm) end_compute();                                       // the second half runs one phase behind
-        auto step = [&](int s, auto issue, auto last, auto w0, auto w1, auto w2, auto w3) __attribute__((always_inline)) {
-            const uint32_t cur = slot_of(s), nxt = (uint32_t)R::kStage - cur;
-            read_x(0, cur);
-            if constexpr (issue.value) issue_w(0, s + 2, cur);
-            end_memory(w0);
-            compute(0, 0, Int<1>{});
-            read_w(1, cur);
-            if constexpr (issue.value) issue_x(0, s + 2, cur);
-            end_memory(w1);
-            compute(1, 0, Int<1>{});
-            read_x(1, cur);
-            if constexpr (issue.value) issue_w(1, s + 2, cur);
-            end_memory(w2);
-            compute(0, 1, Int<1>{});
-            if constexpr (!last.value) read_w(0, nxt);
-            if constexpr (issue.value) issue_x(1, s + 2, cur);
-            end_memory(w3);
-            compute(1, 1, Int<1>{});
-        };
-        int s = 0;
-        for (; s + 2 < n; ++s) step(s, Int<1>{}, Int<0>{}, Int<12>{}, Int<12>{}, Int<12>{}, Int<12>{});
-        if (s + 1 < n) {
-            step(s, Int<0>{}, Int<0>{}, Int<10>{}, Int<8>{}, Int<6>{}, Int<4>{});
-            ++s;
-        }
-        step(s, Int<0>{}, Int<1>{}, Int<2>{}, Int<0>{}, Int<0>{}, Int<0>{});
-    } else if constexpr (MB == 2 && NB == 2 && !WHOLE) {
-        // 0: X -> (W0, X), W0(s+S) and W1(s+S-1);   1: W1, W0(s+1) -> (W1, X), X(s+S)
-#pragma unroll
-        for (int q = 0; q < S; ++q)
-            if (q < n) {
-                issue_w(0, q, q * R::kStage);
-                if (q > 0) issue_w(1, q - 1, (q - 1) * R::kStage);
-                issue_x(0, q, q * R::kStage);
-            }
-        if (n >= S) end_memory(Int<12>{});
-        else { issue_w(1, n - 1, (n - 1) * R::kStage); end_memory(Int<0>{}); }
-        read_w(0, 0);
-        end_memory(Int<12>{});
-        if (wm) end_compute();
-        auto step = [&](int s, auto issue, auto wait) __attribute__((always_inline)) {
-            const uint32_t cur = slot_of(s);
-            read_x(0, cur);
-            if constexpr (issue.value == 2) issue_w(0, s + S, cur);
-            if constexpr (issue.value >= 1) issue_w(1, s + S - 1, slot_of(s + S - 1));
-            end_memory(wait);
-            compute(0, 0, Int<1>{});
-            read_w(1, cur);
-            if (issue.value == 2 || s + 1 < n) read_w(0, slot_of(s + 1));
-            if constexpr (issue.value == 2) issue_x(0, s + S, cur);
-            end_memory(wait);
-            compute(1, 0, Int<1>{});
-        };
-        int s = 0;
-        for (; s + S < n; ++s) step(s, Int<2>{}, Int<12>{});
-        if (n >= S) step(s++, Int<1>{}, Int<0>{});
-        for (; s < n; ++s) step(s, Int<0>{}, Int<0>{});
-    } else if constexpr (MB == 2 && NB == 2) {
-        // One phase of 32 MFMAs a step: X, W0, W1 -> all four, copies of step s+2 into the stage read a step earlier (the
-        // other half's read of it ended one barrier ago).  Half as many barriers and waits for fragments as with a phase
-        // for each of W0 and W1: 80 tiles of 5120 inputs 65 -> 56 us, 220 tiles 79 -> 74.  (256 x 128 tiles read 20
-        // fragments for a step, and there the long phase is the slower one: 75.3 -> 77.9 us a call.)  Six copies instead
-        // of twelve are in flight, though, which costs 1 to 2 us where slices fill the chip (see launch_dense).
-        constexpr int kOps = 6;                                      // copies of a wave and step
-#pragma unroll
-        for (int q = 0; q < S - 1; ++q)
-            if (q < n) { issue_x(0, q, q * R::kStage); issue_w(0, q, q * R::kStage); issue_w(1, q, q * R::kStage); }
-        if (n >= S - 1) end_memory(Int<kOps * (S - 2)>{}); else end_memory(Int<0>{});
-        if (wm) end_compute();
-        auto step = [&](int s, auto issue, auto wait) __attribute__((always_inline)) {
-            const uint32_t cur = slot_of(s);
-            read_w(0, cur);
-            read_w(1, cur);
-            read_x(0, cur);
-            if constexpr (issue.value) {
-                const uint32_t to = slot_of(s + S - 1);
-                issue_x(0, s + S - 1, to); issue_w(0, s + S - 1, to); issue_w(1, s + S - 1, to);
-            }
-            end_memory(wait);
-            compute(0, 0, Int<0>{});
-            compute(1, 0, Int<1>{});
-        };
-        int s = 0;
-        for (; s + S - 1 < n; ++s) step(s, Int<1>{}, Int<kOps * (S - 2)>{});
-        for (; s < n; ++s) step(s, Int<0>{}, Int<0>{});
-    } else if constexpr (MB == 4 && NB == 1) {
-        // 0: X part 0, W -> (W, X0), X1(s+S-1);   1: X part 1 -> (W, X1), X0(s+S) and W(s+S)
-#pragma unroll
-        for (int q = 0; q < S; ++q)
-            if (q < n) {
-                if (q > 0) issue_x(1, q - 1, (q - 1) * R::kStage);
-                issue_x(0, q, q * R::kStage);
-                issue_w(0, q, q * R::kStage);
-            }
-        if (n >= S) end_memory(Int<12>{});
-        else { issue_x(1, n - 1, (n - 1) * R::kStage); end_memory(Int<0>{}); }
-        if (wm) end_compute();
-        auto step = [&](int s, auto issue, auto wait) __attribute__((always_inline)) {
-            const uint32_t cur = slot_of(s);
-            read_w(0, cur);
-            read_x(0, cur);
-            if constexpr (issue.value >= 1) issue_x(1, s + S - 1, slot_of(s + S - 1));
-            end_memory(wait);
-            compute(0, 0, Int<1>{});
-            read_x(1, cur);
-            if constexpr (issue.value == 2) { issue_x(0, s + S, cur); issue_w(0, s + S, cur); }
-            end_memory(wait);
-            compute(0, 1, Int<1>{});
-        };
-        int s = 0;
-        for (; s + S < n; ++s) step(s, Int<2>{}, Int<12>{});
-        if (n >= S) step(s++, Int<1>{}, Int<0>{});
-        for (; s < n; ++s) step(s, Int<0>{}, Int<0>{});
     } else {
-        // one phase a step: X, W -> MFMAs, copies of step s+S-1
-#pragma unroll
-        for (int q = 0; q < S - 1; ++q)
-            if (q < n) { issue_x(0, q, q * R::kStage); issue_w(0, q, q * R::kStage); }
-        if (n >= S - 1) end_memory(Int<4 * (S - 2)>{}); else end_memory(Int<0>{});
-        if (wm) end_compute();
-        auto step = [&](int s, auto issue, auto wait) __attribute__((always_inline)) {
-            const uint32_t cur = slot_of(s);
-            read_w(0, cur);
-            read_x(0, cur);
-            if constexpr (issue.value) {
-                const uint32_t to = slot_of(s + S - 1);
-                issue_x(0, s + S - 1, to); issue_w(0, s + S - 1, to);
-            }
-            end_memory(wait);
-            compute(0, 0, Int<1>{});
-        };
-        int s = 0;
-        for (; s + S - 1 < n; ++s) step(s, Int<1>{}, Int<4 * (S - 2)>{});
-        for (; s < n; ++s) step(s, Int<0>{}, Int<0>{});
+        end_memory(Int<0>{});
     }
+    read_w(0, 0);
+    end_memory(Int<12>{});
+    if (wm) end_compute();                                       // the second half runs one phase behind
+    auto step = [&](int s, auto issue, auto last, auto w0, auto w1, auto w2, auto w3) __attribute__((always_inline)) {
+        const uint32_t cur = slot_of(s), nxt = (uint32_t)R::kStage - cur;
+        read_x(0, cur);
+        if constexpr (issue.value) issue_w(0, s + 2, cur);
+        end_memory(w0);
+        compute(0, 0);
+        read_w(1, cur);
+        if constexpr (issue.value) issue_x(0, s + 2, cur);
+        end_memory(w1);
+        compute(1, 0);
+        read_x(1, cur);
+        if constexpr (issue.value) issue_w(1, s + 2, cur);
+        end_memory(w2);
+        compute(0, 1);
+        if constexpr (!last.value) read_w(0, nxt);
+        if constexpr (issue.value) issue_x(1, s + 2, cur);
+        end_memory(w3);
+        compute(1, 1);
+    };
+    int s = 0;
+    for (; s + 2 < n; ++s) step(s, Int<1>{}, Int<0>{}, Int<12>{}, Int<12>{}, Int<12>{}, Int<12>{});
+    if (s + 1 < n) {
+        step(s, Int<0>{}, Int<0>{}, Int<10>{}, Int<8>{}, Int<6>{}, Int<4>{});
+        ++s;
+    }
+    step(s, Int<0>{}, Int<1>{}, Int<2>{}, Int<0>{}, Int<0>{}, Int<0>{});
     if (!wm) end_compute();                                          // barriers even out
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // LDS is free: no copy under way, no wave reading
 
     // ---- epilogue -----------------------------------------------------------------------------------------
-    if (splits > 1) {                                                // partial sums: 4 features of one token per lane
-        float* const part = d.part + (int64_t)z * M * N;
-#pragma unroll
-        for (int b = 0; b < 2 * MB; ++b) {
-            const int64_t m = m0 + wm * 32 * MB + 16 * b + r;
-#pragma unroll
-            for (int a = 0; a < 2 * NB; ++a) {
-                const int nn = n0 + wn * 32 * NB + 16 * a + 4 * g;
-                if (m < M && nn < N) *reinterpret_cast<f32x4*>(part + m * N + nn) = acc[a][b];
-            }
-        }
-        return;
-    }
     // A lane holds features n..n+3 of one token per accumulator.  The wave lays its part out in LDS as bf16
     // rows and reads it back 16 bytes a lane, so that a store instruction writes whole row segments.
     {
@@ -417,6 +290,229 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
         for (int i = 0; i < MB * 32 / kRows; ++i) {
             const int row = i * kRows + erow;
             const int64_t m = m0 + wm * 32 * MB + row;
+            typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(eb + row * kPitch + echunk * 16);
+            if (m < M && nn < N) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(C + m * d.ldc + nn));
+        }
+    }
+}
+
+// Smaller tiles: BM tokens x BN features, WN of the eight contracting waves along the features.  A stage of the ring holds the
+// token rows of a step, 128 bytes each, swizzled as above, and behind them the weight's pieces, 1 KB per 16 rows and 32-wide
+// slice.  HALF: a fragment set is a 32-wide slice, and the barrier stands between a step's two; else a whole step (128 x 128
+// tiles, whose eight MFMAs a slice would not cover the reads' latency: 34.8 -> 33.9 us).
+template <int BM, int BN, int WN>
+struct Flow {
+    static constexpr int WM = 8 / WN, TB = BM / WM / 16, FB = BN / WN / 16;    // 16-row blocks of a wave
+    static constexpr int kX = BM * 128, kStage = kX + BN * 128;                 // bytes
+    static constexpr int kStages = 160 * 1024 / kStage;
+    static constexpr int PX = BM / 32, PW = BN / 32, kOps = PX + PW;            // copies of a copying wave and step
+    static constexpr int kPitch = FB * 32 + 16;
+    static constexpr int kEpilogue = 8 * TB * 16 * kPitch;
+    static constexpr int kLds = kStages * kStage > kEpilogue ? kStages * kStage : kEpilogue;
+};
+
+constexpr int kFlowThreads = 768;                                               // eight waves contract, four copy
+template <int BM, int BN, int WN, bool HALF>
+__global__ __launch_bounds__(kFlowThreads) __attribute__((amdgpu_waves_per_eu(3, 3))) void k_flow(GemmDesc d) {
+    using F = Flow<BM, BN, WN>;
+    constexpr int TB = F::TB, FB = F::FB, S = F::kStages, PX = F::PX, PW = F::PW;
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int64_t M = d.M;
+    const int N = d.N, K2 = d.K2, div2 = d.div2;
+    const int all_steps = d.K1 / kBK + (K2 + kBK - 1) / kBK;
+    const int64_t ldx2 = d.ldx2, ldw2 = d.ldw2;
+    const qblora_bf16* const X2 = d.X2;
+    const qblora_bf16* const W2 = d.W2;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    const int r = lane & 15, g = lane >> 4;
+
+    const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN, ntiles = tiles_m * tiles_n;
+    const int splits = d.splits > 1 ? d.splits : 1;
+    int L;
+    {
+        const int units = ntiles * splits, xcd = blockIdx.x & 7, q = units >> 3, rem = units & 7;
+        L = xcd * q + min(xcd, rem) + (blockIdx.x >> 3);
+    }
+    int z = 0, step0 = 0, n = all_steps;
+    if (splits > 1) {
+        z = L / ntiles;
+        step0 = all_steps * z / splits;
+        n = all_steps * (z + 1) / splits - step0;
+        L -= z * ntiles;
+    }
+    const int steps1 = d.K1 / kBK - step0;
+    constexpr int GM = 4;
+    const int in_group = GM * tiles_n, first_m = (L / in_group) * GM, gsize = min(tiles_m - first_m, GM);
+    const int64_t m0 = (int64_t)(first_m + (L % in_group) % gsize) * BM;
+    const int n0 = (L % in_group) / gsize * BN;
+
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
+    if (wave >= 8) {
+        // copying wave c fills token rows 8*(PX*c + i) .. +7 and the weight pieces PW*c + i (16-row block p >> 1, 32-wide
+        // slice p & 1)
+        const int c = wave - 8;
+        uint32_t xoff[PX];
+        const qblora_bf16* const x_tile = d.X1 + m0 * d.ldx1 + (int64_t)step0 * kBK;
+        auto token_row = [&](int i) __attribute__((always_inline)) {
+            const int row = 8 * (PX * c + i) + (lane >> 3);
+            return m0 + row > M - 1 ? (int)(M - 1 - m0) : row;
+        };
+        auto chunk_of = [&](int i) __attribute__((always_inline)) { return (lane & 7) ^ (4 * ((PX * c + i) & 1) + (lane >> 4)); };
+#pragma unroll
+        for (int i = 0; i < PX; ++i) xoff[i] = (uint32_t)(token_row(i) * d.ldx1 * 2) + (uint32_t)(chunk_of(i) << 4);
+        int wblk[PW], wpiece[PW];                                       // 1 KB pieces from the weight's first: below 2^31
+#pragma unroll
+        for (int i = 0; i < PW; ++i) {
+            const int p = PW * c + i;
+            wblk[i] = min(n0 / 16 + (p >> 1), N / 16 - 1);              // rows past N: any block, results never stored
+            wpiece[i] = __builtin_amdgcn_readfirstlane(wblk[i] * (d.K1 / 32) + step0 * 2 + (p & 1));
+        }
+        const unsigned char* const W1 = reinterpret_cast<const unsigned char*>(d.W1);
+        const uint32_t lane16 = (uint32_t)lane * 16u;
+        const uint32_t lds_x = lds0 + (uint32_t)c * (PX * 1024), lds_w = lds0 + F::kX + (uint32_t)c * (PW * 1024);
+        auto issue = [&](int step, uint32_t slot) __attribute__((always_inline)) {
+            if (step < steps1) {
+#pragma unroll
+                for (int i = 0; i < PX; ++i) copy16_to_lds(x_tile + step * kBK, xoff[i], lds_x + slot + i * 1024);
+#pragma unroll
+                for (int i = 0; i < PW; ++i) copy16_to_lds(W1 + (int64_t)(wpiece[i] + 2 * step) * 1024, lane16, lds_w + slot + i * 1024);
+                return;
+            }
+            const int k0 = (step - steps1) * kBK;                       // chunks at or beyond K2 are zeros
+#pragma unroll
+            for (int i = 0; i < PX; ++i) {
+                const int k = k0 + chunk_of(i) * 8;
+                const qblora_bf16* src = X2 + (m0 + token_row(i)) * ldx2 + k;
+                copy16_to_lds(k < K2 ? src : reinterpret_cast<const qblora_bf16*>(g_zero_chunk), lds_x + slot + i * 1024);
+            }
+#pragma unroll
+            for (int i = 0; i < PW; ++i) {
+                const qblora_bf16* src = W2 + (int64_t)((uint32_t)(wblk[i] * 16 + r) / (uint32_t)div2) * ldw2;
+                const int k = k0 + ((PW * c + i) & 1) * 32 + g * 8;
+                copy16_to_lds(k < K2 ? src + k : reinterpret_cast<const qblora_bf16*>(g_zero_chunk), lds_w + slot + i * 1024);
+            }
+        };
+        // until at most `left` whole steps of this wave's copies are in flight
+        auto landed = [&](int left) __attribute__((always_inline)) {
+            if (left >= S - 2) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S - 2) * F::kOps) : "memory");
+            else if (S > 3 && left == S - 3) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S > 3 ? S - 3 : 0) * F::kOps) : "memory");
+            else if (S > 4 && left == S - 4) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S > 4 ? S - 4 : 0) * F::kOps) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        };
+#pragma unroll 1
+        for (int q = 0; q < S && q < n; ++q) issue(q, q * F::kStage);
+        if (n >= S) asm volatile("s_waitcnt vmcnt(%0)" :: "n"((S - 1) * F::kOps) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        asm volatile("s_barrier" ::: "memory");                         // step 0 is in
+        uint32_t slot = 0;
+#pragma unroll 1
+        for (int s = 0; s + 1 < n; ++s) {
+            landed(n - 2 - s);
+            asm volatile("s_barrier" ::: "memory");                     // step s + 1 is in, the stage of step s is free
+            if (s + S < n) issue(s + S, slot);
+            slot = slot + F::kStage == S * F::kStage ? 0u : slot + (uint32_t)F::kStage;
+        }
+        asm volatile("s_barrier" ::: "memory");
+        return;
+    }
+
+    f32x4 acc[FB][TB];
+#pragma unroll
+    for (int a = 0; a < FB; ++a)
+#pragma unroll
+        for (int b = 0; b < TB; ++b) acc[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int KS = HALF ? 1 : 2;                                 // 32-wide slices of a fragment set
+    struct Frags { bf16x8 x[KS][TB], w[KS][FB]; };
+    const uint32_t xa = (uint32_t)((wm * 16 * TB + r) * 128 + ((g ^ (r >> 1)) << 4));
+    const uint32_t wa = (uint32_t)(F::kX + wn * FB * 2048 + lane * 16);
+    constexpr int NR = KS * (TB + FB), NM = KS * TB * FB;
+    auto read = [&](Frags& f, int i, int ks0, uint32_t slot) __attribute__((always_inline)) {        // fragment i of NR
+        const int q = i / (TB + FB), ks = ks0 + q, j = i % (TB + FB);
+        if (j < FB) f.w[q][j] = *reinterpret_cast<const bf16x8*>(smem + (wa + slot) + j * 2048 + ks * 1024);
+        else f.x[q][j - FB] = *reinterpret_cast<const bf16x8*>(smem + ((xa ^ (uint32_t)(ks << 6)) + slot) + (j - FB) * 2048);
+    };
+    auto top = [&]() __attribute__((always_inline)) {                // this wave's reads are done; the next step is in
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // the MFMAs of a set, and between them the reads of the next set
+    auto contract = [&](const Frags& now, Frags& next, auto reads, int ks_next, uint32_t from) __attribute__((always_inline)) {
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const int q = m / (TB * FB), a = m / TB % FB, b = m % TB;
+            acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(now.w[q][a], now.x[q][b], acc[a][b], 0, 0, 0);
+            if constexpr (reads.value) {
+#pragma unroll
+                for (int i = m * NR / NM; i < (m + 1) * NR / NM; ++i) read(next, i, ks_next, from);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    uint32_t slot = 0;                                               // stage of the step in work
+    auto next_slot = [&]() __attribute__((always_inline)) { return slot + F::kStage == S * F::kStage ? 0u : slot + (uint32_t)F::kStage; };
+    asm volatile("s_barrier" ::: "memory");                          // step 0 is in
+    Frags f0, f1;
+#pragma unroll
+    for (int i = 0; i < NR; ++i) read(f0, i, 0, 0);
+    int s = 0;
+    if constexpr (HALF) {
+        // first slice: its MFMAs beside the reads of the second; the barrier; second slice beside the next step's first
+        for (; s + 1 < n; ++s) {
+            contract(f0, f1, Int<1>{}, 1, slot);
+            top();
+            contract(f1, f0, Int<1>{}, 0, next_slot());
+            slot = next_slot();
+        }
+        contract(f0, f1, Int<1>{}, 1, slot);
+        contract(f1, f0, Int<0>{}, 0, 0);
+    } else {
+        auto step = [&](const Frags& now, Frags& next) __attribute__((always_inline)) {
+            top();
+            contract(now, next, Int<1>{}, 0, next_slot());
+            slot = next_slot();
+        };
+        for (; s + 2 < n; s += 2) { step(f0, f1); step(f1, f0); }
+        if (s + 1 < n) { step(f0, f1); f0 = f1; }
+        contract(f0, f1, Int<0>{}, 0, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // LDS is free: no copy under way, no wave reading
+
+    if (splits > 1) {                                                // partial sums: 4 features of one token per lane
+        float* const part = d.part + (int64_t)z * M * N;
+#pragma unroll
+        for (int b = 0; b < TB; ++b) {
+            const int64_t m = m0 + wm * 16 * TB + 16 * b + r;
+#pragma unroll
+            for (int a = 0; a < FB; ++a) {
+                const int nn = n0 + wn * 16 * FB + 16 * a + 4 * g;
+                if (m < M && nn < N) *reinterpret_cast<f32x4*>(part + m * N + nn) = acc[a][b];
+            }
+        }
+        return;
+    }
+    {
+        constexpr int kPitch = F::kPitch, kChunks = FB * 2, kTotal = TB * 16 * kChunks;
+        qblora_bf16* const C = reinterpret_cast<qblora_bf16*>(d.C);
+        const float out_scale = d.out_scale;
+        unsigned char* eb = smem + wave * (TB * 16 * kPitch);
+#pragma unroll
+        for (int a = 0; a < FB; ++a)
+#pragma unroll
+            for (int b = 0; b < TB; ++b) {
+                uint2 o;
+                o.x = pack_bf16(acc[a][b][0] * out_scale, acc[a][b][1] * out_scale);
+                o.y = pack_bf16(acc[a][b][2] * out_scale, acc[a][b][3] * out_scale);
+                *reinterpret_cast<uint2*>(eb + (b * 16 + r) * kPitch + (a * 16 + g * 4) * 2) = o;
+            }
+#pragma unroll 8
+        for (int i = lane; i < kTotal; i += 64) {
+            const int row = i / kChunks, echunk = i % kChunks;
+            const int nn = n0 + wn * 16 * FB + echunk * 8;
+            const int64_t m = m0 + wm * 16 * TB + row;
             typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
             const u32x4 v = *reinterpret_cast<const u32x4*>(eb + row * kPitch + echunk * 16);
             if (m < M && nn < N) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(C + m * d.ldc + nn));
@@ -447,33 +543,41 @@ __global__ __launch_bounds__(256) void k_dense_reduce(GemmDesc d) {
                    pack_bf16(hi[0] * s, hi[1] * s), pack_bf16(hi[2] * s, hi[3] * s));
 }
 
-template <int MB, int NB, bool WHOLE = false>
-int launch_cfg(const GemmDesc& d, hipStream_t st) {
-    auto kern = k_dense<MB, NB, WHOLE>;
-    constexpr int smem = Ring<MB, NB>::kLds;
-    // set once per instantiation; the initialisation of a function-local static is thread safe
-    static const bool attr_ok = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                                    hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
-    if (!attr_ok) return QBLORA_ERR_LAUNCH;
-    const int64_t tiles = ((d.M + 64 * MB - 1) / (64 * MB)) * ((d.N + 128 * NB - 1) / (128 * NB));
-    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * (d.splits > 1 ? d.splits : 1))), dim3(kThreads), smem, st, d);
+template <typename K>
+int launch_tiles(K kern, bool lds_ok, int smem, int threads, int bm, int bn, const GemmDesc& d, hipStream_t st) {
+    if (!lds_ok) return QBLORA_ERR_LAUNCH;
+    const int64_t tiles = ((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(tiles * (d.splits > 1 ? d.splits : 1))), dim3(threads), smem, st, d);
     if (d.splits > 1)
         hipLaunchKernelGGL(k_dense_reduce, dim3((unsigned)((d.M * d.N / 8 + 255) / 256)), dim3(256), 0, st, d);
     return launch_status();
 }
 
+// set once per kernel; callers keep the result in a function-local static, whose initialisation is thread safe
+template <typename K>
+bool set_lds(K kern, int smem) {
+    return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
+}
+
+int launch_large(const GemmDesc& d, hipStream_t st) {
+    static const bool ok = set_lds(k_dense, Ring::kLds);
+    return launch_tiles(k_dense, ok, Ring::kLds, kThreads, 64 * MB, 128 * NB, d, st);
+}
+
+template <int BM, int BN, int WN, bool HALF>
+int launch_flow(const GemmDesc& d, hipStream_t st) {
+    constexpr int smem = Flow<BM, BN, WN>::kLds;
+    static const bool ok = set_lds(k_flow<BM, BN, WN, HALF>, smem);
+    return launch_tiles(k_flow<BM, BN, WN, HALF>, ok, smem, kFlowThreads, BM, BN, d, st);
+}
+
 }  // namespace
 
-// Tile shape (and slices) by the estimated time.  `full` is the measured time of a k-step with every CU busy, `few`
-// with a few (the clock is power-limited: 1.5-1.7 GHz with all matrix pipes busy, 2.4 with few), both in ns; a last
-// round of workgroups (256, one per CU) that is not full lies in between.  (128 x 256 takes 690 and 870 since its phases
-// hold a whole step; the choices below were measured with the older figures, which stay.)  Larger tiles move fewer bytes per MFMA
-// (256 x 256 runs at 0.82-0.89 of the matrix pipe, 128 x 256 at 0.61, 128 x 128 at 0.40, where waves wait 0.42 of the time, LDS
-// reads take 0.31 and copies 25 bytes a cycle) and need more tiles to fill the chip.  T x N x K, us for 256x256 / 128x256 / 256x128 / 128x128: 512 x 4096 x 11008 179 / 130 /
-// 131 / 87; 512 x 11008 x 4096 77 / 61 / 60 / 76; 1337 x 5120 x 5120 94 / 71 / 74 / 90; 2500 x 5120 x 13824 263 / 350 /
-// 358 / 439; 8192 x 4096 x 4096 192 / 233 / 238 / 285.  A slice adds its fp32 partial tile, written and read once, and
-// all of them the second launch: 512 x 4096 x 11008 91 -> 54 + 7 us (128 x 256, four slices), 300 x 2048 x 6144 51 ->
-// 19 + 4 (five), 128 x 4096 x 4096 35 -> 14 + 5 (five).
+// The most slices of a call, which workspaces count on, and the line between this form and the one from the codes on large
+// weights: estimates by the times of the kernels that these were measured with, 256 x 256, 128 x 256, 256 x 128 and 128 x 128
+// tiles.  `full` is the time of a k-step with every CU busy, `few` with a few, both in ns; a last round of workgroups (256, one
+// per CU) that is not full lies in between.  A slice adds its fp32 partial tile, written and read once, and all of them the
+// second launch.  What a call takes: dense_call_plan.
 DensePlan dense_plan(int64_t M, int N, int k1, int k2, int max_splits) {
     struct Shape { int bm, bn; int64_t few, full; };
     static constexpr Shape shapes[4] = {{256, 256, 940, 1460}, {128, 256, 800, 920}, {256, 128, 800, 930}, {128, 128, 490, 570}};
@@ -494,12 +598,43 @@ DensePlan dense_plan(int64_t M, int N, int k1, int k2, int max_splits) {
     return best;
 }
 
+// The tile and the slices of a call, by the present kernels' times: as above, but a last round of f of the 256 workgroups lies
+// f^2 of the way from few to full (the clock holds to about half of them), and a round starts and ends in 3 us.  Larger tiles
+// move fewer bytes per MFMA, 256 x 256 ones nearly reach the power limit and pay where they fill rounds (in slices they are
+// never the fastest); the others are there
+// for their sizes: a round of 232 tiles of 128 x 192 beats two thirds of one of 128 x 256.  us for 256 x 256 / 128 x 256 / 128 x
+// 192 / 192 x 192 / 128 x 128 tiles (256 x 128 and 192 x 128 take as long as 128 x 256 and 128 x 192): 1337 x 5120 x 5184 99 / 60 /
+// 86 / 59 / 71; 512 x 11008 x 4224 71 / 42 / 39 / 46 / 54; 1024 x 4096 x 4608 79 / 43 / 38 / 48 / 34; 334 x 4224 x 8064 128 / 67 / 53 /
+// 75 / 45; 2048 x 4096 x 4224 81 / 53 / 71 / 58 / 61; 8192 x 5120 x 5184 315 / 313 / 346 / 330 / -; 8192 x 22016 x 8448 2032 / 2380 /
+// 2592 / 2341 / -.
+DensePlan dense_call_plan(int64_t M, int N, int k1, int k2, int max_splits) {
+    struct Shape { int bm, bn; int64_t few, full; };
+    static constexpr Shape shapes[7] = {{256, 256, 1000, 1450}, {128, 256, 500, 775}, {256, 128, 500, 775}, {128, 128, 330, 440},
+                                        {128, 192, 400, 585}, {192, 128, 400, 585}, {192, 192, 560, 835}};
+    const int64_t steps = k1 / kBK + (k2 + kBK - 1) / kBK;
+    const int most = max_splits > 1 ? dense_plan(M, N, k1, k2, max_splits).splits : 1;
+    DensePlan best{0, 1, INT64_MAX};
+    for (int i = 0; i < 7; ++i) {
+        const int64_t tiles = ((M + shapes[i].bm - 1) / shapes[i].bm) * ((N + shapes[i].bn - 1) / shapes[i].bn);
+        for (int s = 1; s <= (i == 0 ? 1 : most) && (s == 1 || (tiles * s <= 256 && steps >= 4 * s)); ++s) {
+            const int64_t units = tiles * s, last = units % 256;
+            const int64_t step_ns = units / 256 * shapes[i].full +
+                                    (last ? shapes[i].few + (shapes[i].full - shapes[i].few) * last * last / 65536 : 0);
+            int64_t t = step_ns * ((steps + s - 1) / s) + 3000 * ((units + 255) / 256);
+            // (slices start far apart in both operands; their partial tiles stay in the caches: 8 TB/s)
+            if (s > 1) t += t / 10 + 5000 + M * N * 8 * s / 8000;
+            if (t < best.ns) best = DensePlan{i, s, t};
+        }
+    }
+    return best;
+}
+
 // Tiles are counted in 128 or 256 tokens, so between two multiples of 128 every form's time is linear in M, with a slope
 // that grows with its slices: the cheapest form's slices do not increase with M there, and each run of the same number
 // has its most rows at its end.
 int64_t dense_part_rows(int64_t M, int N, int k1, int k2) {
     if (M <= 0 || N <= 0) return 0;
-    auto splits = [&](int64_t m) { return (int64_t)dense_splits(m, N, k1, k2); };
+    auto splits = [&](int64_t m) { return N % 8 != 0 ? 1 : (int64_t)dense_plan(m, N, k1, k2, 8).splits; };
     int64_t top = 0;                                             // the largest M whose tiles leave room for two slices
     for (const int bm : {128, 256})
         for (const int bn : {128, 256}) top = std::max<int64_t>(top, (int64_t)bm * (128 / ((N + bn - 1) / bn)));
@@ -521,29 +656,41 @@ int64_t dense_part_rows(int64_t M, int N, int k1, int k2) {
     return rows;
 }
 
-// The one-off pass takes 0.46 us per million weights and a launch, which the forward's kernel from the codes does not
-// spend (the launch is the re-layouts' by now, which both have; the line was measured with one of its own); that one wins on
-// wide layers with few tokens.  us from the codes / dequantized first: 512 x 22016 x 8192 190 / 265,
-// 512 x 16384 x 8192 138 / 194, 512 x 11008 x 4096 72 / 77, 1024 x 16384 x 8192 233 / 257, 512 x 4096 x 4096 70 / 46,
-// 2048 x 22016 x 8192 632 / 610.  The margin of 5 % is for the estimates' errors: without it 72 of 1134 measured calls
-// lose up to 9 % of their time, with it three lose 3 % (and 207 gain 17 % on average).
+namespace {
+
+// The 16-bit weight stays in the 256 MB memory-side cache between the pass and the contraction
+bool weight_stays(int64_t N, int k1) { return N * k1 * 2 < (int64_t)256 << 20; }
+
+}  // namespace
+
+// The one-off pass takes 0.46 to 0.5 us per million weights, in a launch that both forms have (the re-layouts' or the narrow
+// GEMM's sums'); the kernel from the codes wins on wide layers with few tokens.  us from the codes / dequantized first: 512 x
+// 22016 x 8192 190 / 265, 512 x 16384 x 8192 138 / 194, 1024 x 16384 x 8192 233 / 257, 512 x 4096 x 4096 70 / 46, 2048 x 22016 x
+// 8192 632 / 610, and with the present tiles 512 x 11008 x 4096 86 / 72 (with the narrow GEMM and what
+// shares its launches).  On weights whose 16-bit form outgrows the memory-side cache
+// the first line stands, measured with the figures of dense_plan (a margin of 5 % for the estimates' errors: without it 72 of
+// 1134 measured calls lose up to 9 % of their time, with it three lose 3 % and 207 gain 17 % on average).
 bool dense_pays(int64_t M, int N, int k1, int k2) {
-    const int64_t first = dense_plan(M, N, k1, k2, 1).ns + (int64_t)N * k1 * 46 / 100000 + 2000;
-    return qlinear_ns(M, N, k1 + (k2 + kBK - 1) / kBK * kBK) + 2000 >= first - first * 5 / 100;
+    const int64_t codes = qlinear_ns(M, N, k1 + (k2 + kBK - 1) / kBK * kBK), weights = (int64_t)N * k1;
+    const int64_t first = dense_plan(M, N, k1, k2, 1).ns + weights * 46 / 100000 + 2000;
+    if (codes + 2000 >= first - first * 5 / 100) return true;
+    return weight_stays(N, k1) && codes >= dense_call_plan(M, N, k1, k2, 1).ns + weights * 50 / 100000;
 }
 
-// The transposed weight's pass is the same; its contraction may be sliced, which the one from the codes is not.  us from
-// the codes / dequantized first, 8192 x 22016: 64 tokens 122 / 185, 256 122 / 223, 512 195 / 275, 700 376 / 401; 4096 x 11008
-// at 512 67 / 76; 8192 x 8192 at 700 131 / 124.  A margin of 10 %: the slices' time is the less certain (with 5 % two of
-// 480 measured calls lose 6 and 10 %, with 10 % none).
+// The transposed weight's pass takes 0.62 us per million weights with the gradients' sums, and its contraction may be sliced,
+// which the one from the codes is not.  us from the codes / dequantized first, 8192 x 22016: 64 tokens 122 / 185, 256 122 / 223,
+// 512 195 / 275, 700 376 / 401; 8192 x 8192 at 700 131 / 124.  On large weights a margin of 10 %: the slices' time is the less
+// certain (with 5 % two of 480 measured calls lose 6 and 10 %, with 10 % none).
 bool dense_pays_t(int64_t M, int N, int k1, int k2) {
-    const int64_t first = dense_plan(M, N, k1, k2, 8).ns + (int64_t)N * k1 * 46 / 100000 + 2000;
-    return qlinear_ns(M, N, k1 + (k2 + kBK - 1) / kBK * kBK) + 2000 >= first - first * 10 / 100;
+    const int64_t codes = qlinear_ns(M, N, k1 + (k2 + kBK - 1) / kBK * kBK), weights = (int64_t)N * k1;
+    const int64_t first = dense_plan(M, N, k1, k2, 8).ns + weights * 46 / 100000 + 2000;
+    if (codes + 2000 >= first - first * 10 / 100) return true;
+    return weight_stays(N, k1) && codes >= dense_call_plan(M, N, k1, k2, 8).ns + weights * 62 / 100000;
 }
 
 int dense_splits(int64_t M, int N, int k1, int k2) {
     if (M <= 0 || N <= 0 || N % 8 != 0) return 1;
-    return dense_plan(M, N, k1, k2, 8).splits;
+    return dense_call_plan(M, N, k1, k2, 8).splits;
 }
 
 int launch_dense(const GemmDesc& d, hipStream_t st) {
@@ -552,15 +699,16 @@ int launch_dense(const GemmDesc& d, hipStream_t st) {
     if (d.out_f32 || d.C2 || d.C_lo || !d.W1 || d.K1 <= 0 || d.K1 % kBK != 0 || d.N % 32 != 0 ||
         (reinterpret_cast<uintptr_t>(d.W1) & 15))
         return QBLORA_ERR_UNSUPPORTED;
-    const DensePlan p = dense_plan(d.M, d.N, d.K1, d.K2, d.splits > 1 ? 8 : 1);
+    const DensePlan p = dense_call_plan(d.M, d.N, d.K1, d.K2, d.splits > 1 ? 8 : 1);
     if (d.splits > 1 && p.splits != d.splits) return QBLORA_ERR_UNSUPPORTED;       // not what dense_splits said
     switch (p.shape) {
-        case 0: return launch_cfg<4, 2>(d, st);
-        // slices start far apart in both operands, and with a tile on every CU their copies take longer: 512 tokens of 4096 x
-        // 11008 in four slices 203.6 us a call with two phases a step, 205.6 with one; unsliced calls 10 to 5 % the other way
-        case 1: return d.splits > 1 ? launch_cfg<2, 2>(d, st) : launch_cfg<2, 2, true>(d, st);
-        case 2: return launch_cfg<4, 1>(d, st);
-        default: return launch_cfg<2, 1>(d, st);
+        case 0: return launch_large(d, st);
+        case 1: return launch_flow<128, 256, 4, true>(d, st);
+        case 2: return launch_flow<256, 128, 2, true>(d, st);
+        case 3: return launch_flow<128, 128, 4, false>(d, st);
+        case 4: return launch_flow<128, 192, 4, true>(d, st);
+        case 5: return launch_flow<192, 128, 2, true>(d, st);
+        default: return launch_flow<192, 192, 4, true>(d, st);
     }
 }
 

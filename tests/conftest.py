@@ -41,6 +41,9 @@ def rules():
     pays_t.argtypes, pays_t.restype = [C.c_int64, C.c_int, C.c_int, C.c_int], C.c_bool
     plan = L["_ZN6qblora10dense_planEliiii"]
     plan.argtypes, plan.restype = [C.c_int64, C.c_int, C.c_int, C.c_int, C.c_int], DensePlan
+    call_plan = L["_ZN6qblora15dense_call_planEliiii"]
+    call_plan.argtypes, call_plan.restype = plan.argtypes, DensePlan
     few = L["_ZN6qblora11few_appliesElii"]
     few.argtypes, few.restype = [C.c_int64, C.c_int, C.c_int], C.c_bool
-    return type("Rules", (), dict(qb=qb, L=L, dense_pays=pays, dense_pays_t=pays_t, dense_plan=plan, few_applies=few))
+    return type("Rules", (), dict(qb=qb, L=L, dense_pays=pays, dense_pays_t=pays_t, dense_plan=plan, dense_call_plan=call_plan,
+                                   few_applies=few))

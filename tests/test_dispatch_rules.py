@@ -46,6 +46,7 @@ def test_inference_workspace_serves_smaller_batches(rules, d_out, d_in, kind):
     assert need[256] == need[299]
 
 
+TILES = ["256 x 256", "128 x 256", "256 x 128", "128 x 128", "128 x 192", "192 x 128", "192 x 192"]
 TOKENS = sorted({*range(1, 400), *range(400, 3300, 13), 511, 512, 513, 767, 768, 769, 1024, 2047, 2048, 4096, 8192})
 
 
@@ -78,6 +79,24 @@ def test_partial_sum_rows_are_the_most_of_any_count(rules, N, k1, k2):
         s = rules.dense_plan(T, N, k1, k2, 8).splits
         most = max(most, s * T if s > 1 else 0)
         assert rows(T, N, k1, k2) == most, T
+
+
+@pytest.mark.parametrize("N,k1,k2", [(512, 512, 0), (4096, 11008, 128), (4160, 448, 8), (11008, 4096, 1376), (64, 22016, 0)])
+def test_no_contraction_takes_more_slices_than_workspaces_count_on(rules, N, k1, k2):
+    for T in [*range(1, 700, 7), 768, 769, 1024, 1337, 2048, 8192]:
+        call = rules.dense_call_plan(T, N, k1, k2, 8)
+        assert 1 <= call.splits <= rules.dense_plan(T, N, k1, k2, 8).splits
+        assert rules.dense_call_plan(T, N, k1, k2, 1).splits == 1
+
+
+@pytest.mark.parametrize("T,N,k1,k2,shape", [
+    (8192, 22016, 8192, 256, "256 x 256"), (8192, 4096, 4096, 128, "256 x 256"), (2048, 4096, 4096, 128, "128 x 256"),
+    (3000, 8192, 3072, 64, "128 x 256"), (1024, 4096, 4096, 512, "128 x 128"), (334, 4224, 8000, 64, "128 x 128"),
+    (512, 11008, 4096, 128, "128 x 192"), (260, 14336, 2560, 32, "192 x 128"), (1337, 5120, 5120, 64, "128 x 256"), (1337, 5760, 5760, 64, "192 x 192"),
+])
+def test_tiles_of_a_contraction(rules, T, N, k1, k2, shape):
+    """512 x 11008 x 4224: 39 us in 128 x 192 tiles, 42 in 128 x 256, 54 in 128 x 128."""
+    assert TILES[rules.dense_call_plan(T, N, k1, k2, 1).shape] == shape
 
 
 @pytest.mark.parametrize("T,d_out,d_in,R", [(1950, 64, 4672, 32), (4887, 64, 2368, 64), (14, 192, 17152, 8), (200, 64, 3072, 16),

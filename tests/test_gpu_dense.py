@@ -84,6 +84,38 @@ def test_slices_of_every_tile(oracle, codebook, rules, T, d_out, d_in, R, shape,
     assert_close_bf16(dX, oracle.backward(Wt, L.X, L.dY, A, B, 2, 2, s)[0], "dX")
 
 
+TILES = [*SHAPES, "128 x 192", "192 x 128", "192 x 192"]
+
+
+@pytest.mark.parametrize("T,d_out,d_in,R,tile", [
+    (2049, 4480, 64, 8, "256 x 256"),       # one step and the extension; one token and half a tile past
+    (1025, 5440, 64, 0, "128 x 256"),       # a single step
+    (1025, 5440, 192, 72, "128 x 256"),     # as many steps as stages, and a ragged extension
+    (1930, 3200, 128, 72, "256 x 128"),     # one more
+    (257, 640, 64, 0, "128 x 128"),         # a single step
+    (300, 640, 256, 72, "128 x 128"),       # one step more than stages
+    (257, 640, 1024, 8, "128 x 128"),
+    (769, 4800, 64, 0, "128 x 192"), (769, 4800, 320, 72, "128 x 192"),      # one token past; whole feature tiles
+    (769, 4672, 128, 8, "128 x 192"),      # 64 features in the last tile
+    (900, 4160, 64, 0, "192 x 128"), (700, 5440, 256, 72, "192 x 128"),      # partial tiles both ways
+    (1337, 5440, 64, 0, "192 x 192"), (1337, 5440, 192, 72, "192 x 192"),    # 64 features in the last tile
+    (577, 2112, 704, 0, "128 x 128"),       # an odd number of steps
+])
+def test_tiles_that_calls_take(oracle, codebook, rules, T, d_out, d_in, R, tile):
+    assert TILES[rules.dense_call_plan(T, d_out, d_in, R, 1).shape] == tile
+    test_tiles_and_stages(oracle, codebook, T, d_out, d_in, R)
+
+
+@pytest.mark.parametrize("T,d_out,d_in,R,tile,slices", [
+    (65, 2112, 320, 72, "128 x 128", 7), (129, 4096, 5504, 72, "192 x 128", 5), (65, 8192, 8384, 72, "128 x 192", 5),
+    (257, 8192, 4352, 72, "128 x 256", 5), (385, 8192, 3200, 72, "256 x 128", 5), (257, 8192, 4160, 72, "192 x 192", 5),
+])
+def test_slices_that_calls_take(oracle, codebook, rules, T, d_out, d_in, R, tile, slices):
+    plan = rules.dense_call_plan(T, d_in, d_out, R, 8)
+    assert rules.dense_pays_t(T, d_in, d_out, R) and (TILES[plan.shape], plan.splits) == (tile, slices)
+    test_tiles_and_stages(oracle, codebook, T, d_out, d_in, R)
+
+
 def test_slices_with_a_single_matrix_adapter(oracle, codebook, rules):
     """dX's extension is H^T here, d_out / lambda2 wide: its steps lie in the last slices."""
     from paper_2407_17029_amd import binding as qb
