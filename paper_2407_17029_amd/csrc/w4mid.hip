@@ -31,6 +31,7 @@
 // A lane ends up with 4 consecutive output rows of one token per accumulator quad and stores them as one
 // 8-byte word (bf16) or one 16-byte word (fp32 partials).
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
@@ -59,6 +60,7 @@ __device__ __forceinline__ void copy16_to_lds(const void* uniform_base, uint32_t
 }
 // The data of these loads arrive asynchronously: a destination may only be used behind a wait_slot that names it.
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+typedef __attribute__((ext_vector_type(2))) float f32x2;
 __device__ __forceinline__ void load16(u32x4& v, uint32_t lane_offset, const void* uniform_base) {
     asm volatile("global_load_dwordx4 %0, %1, %2" : "=&v"(v) : "v"(lane_offset), "s"(uniform_base) : "memory");
 }
@@ -100,6 +102,29 @@ __device__ __forceinline__ void wait_slot(Slot<BR>& s) {
 // How a code becomes a number: any codebook through a table of byte pairs in LDS, the codebook 0, 1, ..., 15 by byte
 // conversions, and the same with the nibbles of every code dword regrouped by the decode pack (64-blocks).
 enum { TABLE, INT4, REGROUPED };
+
+// Rows nb .. nb + 3 of token `tok`: a slice's partial sums, or the output
+__device__ __forceinline__ void store_four(const MidDesc& d, int z, int nb, int tok, const f32x4& v) {
+    const int d_out = d.d_out;
+    if (tok >= d.T || nb >= d_out) return;
+    const bool whole = (d_out & 3) == 0;
+    if (d.splits > 1) {
+        float* p = d.part + ((int64_t)z * d.T + tok) * d_out + nb;
+        if (whole) { *reinterpret_cast<f32x4*>(p) = v; return; }
+        p[0] = v[0];
+        if (nb + 1 < d_out) p[1] = v[1];
+        if (nb + 2 < d_out) p[2] = v[2];
+        if (nb + 3 < d_out) p[3] = v[3];
+    } else {
+        uint16_t* p = reinterpret_cast<uint16_t*>(d.Y) + (int64_t)tok * d_out + nb;
+        const uint32_t lo = pack_bf16(v[0], v[1]), hi = pack_bf16(v[2], v[3]);
+        if (whole) { *reinterpret_cast<uint2*>(p) = make_uint2(lo, hi); return; }
+        p[0] = (uint16_t)(lo & 0xffffu);
+        if (nb + 1 < d_out) p[1] = (uint16_t)(lo >> 16);
+        if (nb + 2 < d_out) p[2] = (uint16_t)(hi & 0xffffu);
+        if (nb + 3 < d_out) p[3] = (uint16_t)(hi >> 16);
+    }
+}
 
 // TB: 32-token blocks; BETA: offsets present; BR: 1 (64 inputs of one row), 8 (8 rows x 8 inputs) or 84 (8 rows x 4 inputs)
 template <int TB, bool BETA, int BR, int CODES>
@@ -328,34 +353,312 @@ __global__ __launch_bounds__(kMidThreads) void k_w4_mid(MidDesc d) {
     for (int u = 0; u < kStages; ++u) wait_slot<0, BR, BETA>(slot[u]);     // the redirected look-ahead operations
 
     // ---- store: lane = token 32*tb + r; registers 4q .. 4q+3 = rows 8q + 4h .. +3 of the wave's 32 ----------
-    const bool whole = (d_out & 3) == 0;
 #pragma unroll
-    for (int tb = 0; tb < TB; ++tb) {
-        const int tok = 32 * tb + r;
-        if (tok >= T) continue;
+    for (int tb = 0; tb < TB; ++tb)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int nb = n0 + 8 * q + 4 * h;
-            if (nb >= d_out) continue;
-            const float v0 = acc[tb][4 * q], v1 = acc[tb][4 * q + 1], v2 = acc[tb][4 * q + 2], v3 = acc[tb][4 * q + 3];
-            if (d.splits > 1) {
-                float* p = d.part + ((int64_t)z * T + tok) * d_out + nb;
-                if (whole) { *reinterpret_cast<float4*>(p) = make_float4(v0, v1, v2, v3); continue; }
-                p[0] = v0;
-                if (nb + 1 < d_out) p[1] = v1;
-                if (nb + 2 < d_out) p[2] = v2;
-                if (nb + 3 < d_out) p[3] = v3;
-            } else {
-                uint16_t* p = reinterpret_cast<uint16_t*>(d.Y) + (int64_t)tok * d_out + nb;
-                const uint32_t lo = pack_bf16(v0, v1), hi = pack_bf16(v2, v3);
-                if (whole) { *reinterpret_cast<uint2*>(p) = make_uint2(lo, hi); continue; }
-                p[0] = (uint16_t)(lo & 0xffffu);
-                if (nb + 1 < d_out) p[1] = (uint16_t)(lo >> 16);
-                if (nb + 2 < d_out) p[2] = (uint16_t)(hi & 0xffffu);
-                if (nb + 3 < d_out) p[3] = (uint16_t)(hi >> 16);
-            }
+        for (int q = 0; q < 4; ++q)
+            store_four(d, z, n0 + 8 * q + 4 * h, 32 * tb + r, f32x4{acc[tb][4 * q], acc[tb][4 * q + 1], acc[tb][4 * q + 2], acc[tb][4 * q + 3]});
+}
+
+// The same layer on 161 to 256 tokens (TB = 6 .. 8).  A copy instruction holds up the wave that issues it, and one wave per SIMD
+// contracts by v_mfma_f32_32x32x16_bf16 at little more than half of the pipe's rate, by 16x16x32 at nearly all of it.  Here four
+// waves do nothing but copy, three the token tiles into a ring of four stages and one the codes, scales and offsets into a
+// ring of its own, deeper because they come from HBM (waits are in order: beside tokens in one wave's queue they could not be).
+// The other four read all of it from LDS and contract in 16 x 16 blocks; codes of INT4 models become floats two at a time.  One
+// barrier a step.  Kernel us in the form above / here: 201 tokens of 5120 x 13824 INT4 40.4 / 37.3, 256 of 22016 x 8192 123 / 111,
+// 256 of 4096 x 4096 20.2 / 18.3; codebooks 200 of 8192 x 8192 39.4 / 36.0, row-major 256 of 5120 x 13824 50.6 / 45.4; 161 of 11008 x
+// 4096 in 8 x 8 blocks 30.9 / 30.0; 129 tokens of 22016 x 8192 79 / 81, so that five token blocks stay above.  What bounds it: LDS
+// (128 KB of fragments and 37 KB of copies a step of 256 tokens) and the expansion, 300 cycles beside 1024 of MFMAs, that only
+// partly hides: without it 256 of 22016 x 8192 take 106, without MFMAs 55.  (Eight waves that share the rows and halve the tokens
+// expand twice: 134.)
+template <int TB, int CODES, int BR>
+struct Wide {
+    static constexpr int kTokens = TB * 32 * 128;
+    static constexpr int kParams = BR == 84 ? 1024 : 512;      // scales of 128 rows and a step, and again offsets
+    static constexpr int kCodes = 4096 + 2 * kParams;
+    static constexpr int kReplicas = TB == 8 ? 4 : kTableReplicas;
+    static constexpr int kTable = CODES == TABLE ? 256 * kReplicas * (int)sizeof(float2) : 0;
+    static constexpr int kRoom = (160 * 1024 - kStages * kTokens - kTable) / kCodes;
+    static constexpr int kCodeStages = kRoom < 8 ? kRoom : 8;
+    static constexpr int kXOps = (4 * TB + 2) / 3;             // copies of a token wave and step
+    static constexpr int kLds = kStages * kTokens + kCodeStages * kCodes + kTable;
+    static_assert(kCodeStages >= 4, "codes in flight");
+};
+
+__device__ __forceinline__ void gather16_to_lds(const unsigned char* p, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" :: "s"(lds_base), "v"(p) : "memory");
+}
+__device__ __forceinline__ void gather4_to_lds(const unsigned char* p, uint32_t lds_base) {
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, off" :: "s"(lds_base), "v"(p) : "memory");
+}
+
+constexpr int kWideThreads = 512;
+
+template <int TB, bool BETA, int BR, int CODES>
+__global__ __launch_bounds__(kWideThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_w4_wide(MidDesc d) {
+    static_assert(CODES != REGROUPED || (BETA && BR == 1), "regrouped codes belong to INT4 models in 64-blocks");
+    typedef Wide<TB, CODES, BR> G;
+    constexpr int CS = G::kCodeStages;
+    extern __shared__ __align__(16) unsigned char smem[];
+    unsigned char* const sC = smem + kStages * G::kTokens;                       // codes and block parameters
+    float2* const sT = reinterpret_cast<float2*>(sC + CS * G::kCodes);           // byte -> (c[lo], c[hi]), replicated
+
+    const int d_out = d.d_out, d_in = d.d_in, T = d.T;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int r = lane & 15, g = lane >> 4;
+    const int tiles_n = (d_out + kMidRows - 1) / kMidRows;
+    const int nt = blockIdx.x % tiles_n, z = blockIdx.x / tiles_n;
+    const int steps_total = d_in / kBlock;
+    const int s_begin = z * d.steps_per_split;
+    const int n = min(steps_total, s_begin + d.steps_per_split) - s_begin;       // steps of this slice, at least one
+
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
+    // Copying waves: steps past the slice are redirected to its last one (fetched, never used), so that the counts stay.
+    if (wave >= 5) {
+        // ---- tokens: wave c fetches eight rows with each of its copies c, c + 3, ... (some the last ones again) --------------
+        constexpr int kXOps = G::kXOps;
+        const int c = wave - 5;
+        uint32_t x_off[kXOps];
+#pragma unroll
+        for (int i = 0; i < kXOps; ++i) {
+            const int row = 8 * min(c + 3 * i, 4 * TB - 1) + (lane >> 3);
+            // chunk c of a row sits at (4*(c & 1) + (c >> 1)) ^ (row >> 1 & 7): the sixteen rows of a fragment touch every bank
+            // once, and a lane's two chunks of a step are neighbours in the row, like its codes
+            const int v = (lane & 7) ^ ((row >> 1) & 7), chunk = 2 * (v & 3) + (v >> 2);
+            x_off[i] = (uint32_t)((int64_t)min(row, T - 1) * d_in * 2 + chunk * 16);
         }
+        const unsigned char* const xbase = reinterpret_cast<const unsigned char*>(d.X) + (int64_t)s_begin * 128;
+        auto issue = [&](int s) __attribute__((always_inline)) {
+            const int64_t at = min(s, n - 1);
+#pragma unroll
+            for (int i = 0; i < kXOps; ++i)
+                copy16_to_lds(xbase + at * 128, x_off[i], lds0 + (s % kStages) * G::kTokens + min(c + 3 * i, 4 * TB - 1) * 1024);
+        };
+#pragma unroll
+        for (int u = 0; u < kStages - 1; ++u) issue(u);
+        asm volatile("s_barrier" ::: "memory");                // (the codes)
+#pragma unroll 1
+        for (int s = 0; s < n; ++s) {
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((kStages - 2) * kXOps) : "memory");   // step s is in, all are past s - 1
+            issue(s + kStages - 1);
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // nothing may arrive behind the workgroup's end
+        return;
     }
+    if (wave == 4) {
+        // ---- codes and block parameters of the 128 rows; rows past the end are computed, never stored ----------------------
+        const int row0 = nt * kMidRows;
+        const int64_t bpr = steps_total, bstep = d.tiled ? 256 : 1;
+        auto block_of = [&](int row) { return d.tiled ? ((int64_t)(row >> 8) * bpr) * 256 + (row & 255) : (int64_t)row * bpr; };
+        const unsigned char* codes[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            codes[i] = d.codes + (block_of(min(row0 + 32 * i + (lane >> 1), d_out - 1)) + s_begin * bstep) * 32 + 16 * (lane & 1);
+        // 16 bytes a lane, scales then offsets; row-major 64-blocks: 4 bytes
+        constexpr int kP = BR == 84 ? 2 : BR == 1 ? 4 : 1;
+        constexpr int per = BR == 84 ? 4 : 2, cols = BR == 84 ? 4 : 8;         // 16-byte pieces of a block row and step; inputs a block
+        const unsigned char* params[kP];
+#pragma unroll
+        for (int i = 0; i < kP; ++i) {
+            int64_t at;
+            bool scales;
+            if constexpr (BR == 1) {
+                scales = d.tiled ? lane < 32 : i < 2;
+                at = (d.tiled ? block_of(min(row0 + 4 * (lane & 31), (d_out - 1) & ~3)) : block_of(min(row0 + 64 * (i & 1) + lane, d_out - 1))) + s_begin * bstep;
+            } else {
+                const int u = (64 * i + lane) % (16 * per);
+                scales = 64 * i + lane < 16 * per;
+                at = (int64_t)min((row0 >> 3) + u / per, (d_out >> 3) - 1) * (d_in / cols) + 4 * (u % per) + (int64_t)s_begin * (64 / cols);
+            }
+            params[i] = reinterpret_cast<const unsigned char*>((scales || !BETA ? d.scales : d.beta) + at);
+        }
+        const int64_t p_step = BR == 1 ? bstep * 4 : 64 / cols * 4;
+        const uint32_t lds_c = lds0 + kStages * G::kTokens;
+        auto run = [&](auto four) __attribute__((always_inline)) {             // four: 4-byte fetches
+            constexpr bool kFour = BR == 1 && four.value;
+            constexpr int kParamOps = kFour ? 4 : BR == 84 ? 2 : 1, kOps = 4 + kParamOps;
+            static_assert((CS - 1) * kOps < 64, "six bits of the wait counter");
+            auto issue = [&](int s, int slot) __attribute__((always_inline)) {
+                const int64_t at = min(s, n - 1);
+                const uint32_t to = lds_c + slot * G::kCodes;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) gather16_to_lds(codes[i] + at * bstep * 32, to + i * 1024);
+#pragma unroll
+                for (int i = 0; i < kParamOps; ++i) {
+                    if constexpr (kFour) gather4_to_lds(params[i] + at * p_step, to + 4096 + i * 256);
+                    else gather16_to_lds(params[i] + at * p_step, to + 4096 + i * 1024);
+                }
+            };
+#pragma unroll 1
+            for (int u = 0; u < CS; ++u) issue(u, u);
+            asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((CS - 1) * kOps) : "memory");      // the first are in
+            int slot = 0;
+#pragma unroll 1
+            for (int s = 0; s < n; ++s) {
+                asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" :: "n"((CS - 2) * kOps) : "memory");  // those of step s + 1 are
+                issue(s + CS, slot);                           // the codes of step s were expanded a step ago
+                slot = slot + 1 == CS ? 0 : slot + 1;
+            }
+        };
+        if (BR == 1 && !d.tiled) run(std::true_type{}); else run(std::false_type{});
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        return;
+    }
+
+    if constexpr (CODES == TABLE) {
+        const float2 e = make_float2(d.cb.c[t & 15], d.cb.c[t >> 4]);
+#pragma unroll
+        for (int q = 0; q < G::kReplicas; ++q) sT[t * G::kReplicas + q] = e;
+    }
+    const float2* const my_table = sT + (lane & (G::kReplicas - 1));
+    // fragment of 16 tokens and a slice ks of 32 inputs: lane (r, g) reads chunk 2g + ks of token r
+    const uint32_t x_at = (uint32_t)(r * 128 + ((g ^ (r >> 1)) << 4));
+    constexpr int NT = 2 * TB;                                 // 16-token blocks
+    f32x4 acc[2][NT];
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int tb = 0; tb < NT; ++tb) acc[b][tb] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // codes of the lane's 16 inputs (16g .. +15 of the step) of rows r and 16 + r, and their scales and offsets
+    struct Params { uint2 cw[2]; f32x4 a[2], b[2]; };
+    auto load_params = [&](int slot) __attribute__((always_inline)) {
+        const unsigned char* const p = sC + slot * G::kCodes + wave * 1024;
+        const unsigned char* const q = sC + slot * G::kCodes + 4096 + wave * (G::kParams / 4);
+        Params v;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) {
+            const int row = 16 * b + r;
+            v.cw[b] = *reinterpret_cast<const uint2*>(p + row * 32 + 8 * g);
+            auto values = [&](const unsigned char* at) __attribute__((always_inline)) {
+                f32x4 f = {0.f, 0.f, 0.f, 0.f};
+                if constexpr (BR == 1) {
+                    f[0] = *reinterpret_cast<const float*>(at + row * 4);
+                } else if constexpr (BR == 8) {
+                    const float2 two = *reinterpret_cast<const float2*>(at + (row >> 3) * 32 + 8 * g);
+                    f[0] = two.x; f[1] = two.y;
+                } else {
+                    f = *reinterpret_cast<const f32x4*>(at + (row >> 3) * 64 + 16 * g);
+                }
+                return f;
+            };
+            v.a[b] = values(q);
+            if constexpr (BETA) v.b[b] = values(q + G::kParams); else v.b[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        return v;
+    };
+    // unit k = 8b + 4ks + i: dword i (inputs 2i, 2i + 1 of eight) of the operand of rows 16b .. and slice ks
+    auto word_of = [&](const Params& p, int k) __attribute__((always_inline)) { return (k >> 2) & 1 ? p.cw[k >> 3].y : p.cw[k >> 3].x; };
+    auto unit_a = [&](const Params& p, int k, float2& tv) __attribute__((always_inline)) {
+        if constexpr (CODES == TABLE) tv = my_table[((word_of(p, k) >> (8 * (k & 3))) & 0xffu) * G::kReplicas];
+    };
+    f32x2 f_lo[2], f_hi[2];                                    // converted codes of units under way
+    auto unit_b = [&](const Params& p, int k, const float2& tv) __attribute__((always_inline)) {
+        const int b = k >> 3, ks = (k >> 2) & 1, i = k & 3;
+        const uint32_t w = word_of(p, k);
+        float lo, hi;
+        if constexpr (CODES == TABLE) {
+            lo = tv.x; hi = tv.y;
+        } else {
+            // a nibble as an E4M3 number is the code times 2^-9: two codes a conversion, exact.  Of the eight nibbles, low
+            // ones first in each byte: inputs 0, 1, 2, ..., or regrouped 0, 2, 4, 6, 1, 3, 5, 7.
+            constexpr bool kPairs = CODES == REGROUPED;        // a byte pair gives the low or high inputs of two units
+            if (kPairs ? i < 2 : i % 2 == 0) {
+                if constexpr (kPairs) {
+                    const uint32_t v = (w >> (4 * i)) & 0x0F0F0F0Fu;
+                    f_lo[i] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(v, 512.0f, false);
+                    f_hi[i] = __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(v, 512.0f, true);
+                } else {
+                    const uint32_t e = w & 0x0F0F0F0Fu, q = (w >> 4) & 0x0F0F0F0Fu;
+                    f_lo[0] = i ? __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(e, 512.0f, true) : __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(e, 512.0f, false);
+                    f_hi[0] = i ? __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(q, 512.0f, true) : __builtin_amdgcn_cvt_scalef32_pk_f32_fp8(q, 512.0f, false);
+                }
+            }
+            const int at = kPairs ? i & 1 : 0, el = kPairs ? i >> 1 : i & 1;
+            lo = f_lo[at][el]; hi = f_hi[at][el];
+        }
+        const int e = BR == 84 ? 2 * ks + (i >> 1) : BR == 8 ? ks : 0;
+        const float sc = p.a[b][e], of = p.b[b][e];
+        return BETA ? pack_bf16(__fmaf_rn(lo, sc, of), __fmaf_rn(hi, sc, of)) : pack_bf16(__fmul_rn(lo, sc), __fmul_rn(hi, sc));
+    };
+    auto operands = [&](const uint32_t (&o)[16], bf16x8 (&wf)[4]) __attribute__((always_inline)) {      // wf[2b + ks]
+#pragma unroll
+        for (int j = 0; j < 4; ++j) wf[j] = __builtin_bit_cast(bf16x8, make_uint4(o[4 * j], o[4 * j + 1], o[4 * j + 2], o[4 * j + 3]));
+    };
+    // One step: the MFMAs on operands `wf`, and between them the next step's operands `wn` from code stage `slot`; written in
+    // issue order and fenced, LDS reads ahead of their use, as in k_w4_mid.  A fragment serves both row blocks.
+    auto step = [&](const bf16x8 (&wf)[4], int stage, int slot, bf16x8 (&wn)[4]) __attribute__((always_inline)) {
+        constexpr int M = 4 * NT, kAhead = 3;
+        const unsigned char* xs = smem + stage * G::kTokens;
+        auto read_x = [&](int f) __attribute__((always_inline)) {             // fragment f = ks * NT + tb
+            return *reinterpret_cast<const bf16x8*>(xs + (x_at ^ (uint32_t)((f / NT) << 6)) + (f % NT) * 2048);
+        };
+        const Params p = load_params(slot);
+        bf16x8 xf[kAhead + 1];
+#pragma unroll
+        for (int f = 0; f < kAhead; ++f) xf[f] = read_x(f);
+        uint32_t o[16];
+        float2 tv[2] = {make_float2(0.f, 0.f), make_float2(0.f, 0.f)};
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+            const int f = m / 2, b = m & 1, ks = f / NT, tb = f % NT;
+            acc[b][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[2 * b + ks], xf[f % (kAhead + 1)], acc[b][tb], 0, 0, 0);
+            if (b == 0 && f + kAhead < M / 2) xf[(f + kAhead) % (kAhead + 1)] = read_x(f + kAhead);
+            // the first MFMAs cover the reads of the codes: the sixteen units sit behind the others
+            constexpr int kSkip = 6;
+            const int k0 = m < kSkip ? 0 : (m - kSkip) * 16 / (M - kSkip), k1 = m < kSkip ? 0 : (m - kSkip + 1) * 16 / (M - kSkip);
+            if (m == kSkip - 1) unit_a(p, 0, tv[0]);
+#pragma unroll
+            for (int k = k0; k < k1; ++k) {
+                if (k + 1 < 16) unit_a(p, k + 1, tv[(k + 1) & 1]);
+                o[k] = unit_b(p, k, tv[k & 1]);
+                asm volatile("" : "+v"(o[k]));                  // computed here
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        operands(o, wn);
+    };
+    auto top = [&]() __attribute__((always_inline)) {          // this wave's reads are done; what the step needs is in
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+
+    bf16x8 wf[2][4];
+    top();                                                     // the table is complete, the first codes are in
+    {
+        const Params p = load_params(0);
+        uint32_t o[16];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) { float2 tv = make_float2(0.f, 0.f); unit_a(p, k, tv); o[k] = unit_b(p, k, tv); }
+        operands(o, wf[0]);
+    }
+    int stage = 0, slot = 1;                                   // of the step's tokens and the next step's codes
+    auto advance = [&]() __attribute__((always_inline)) {
+        stage = (stage + 1) % kStages;
+        slot = slot + 1 == CS ? 0 : slot + 1;
+    };
+    int s = 0;
+    for (; s + 1 < n; s += 2) {
+        top();
+        step(wf[0], stage, slot, wf[1]);
+        advance();
+        top();
+        step(wf[1], stage, slot, wf[0]);
+        advance();
+    }
+    if (s < n) {
+        top();
+        step(wf[0], stage, slot, wf[1]);
+    }
+
+    // ---- store: the lane holds token 16*tb + r, rows 16*b + 4*g .. +3 of the wave's 32 ---------------------------------
+    const int n0 = nt * kMidRows + wave * 32;
+#pragma unroll
+    for (int tb = 0; tb < NT; ++tb)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) store_four(d, z, n0 + 16 * b + 4 * g, 16 * tb + r, acc[b][tb]);
 }
 
 // Y = bf16( sum_z part[z] ), slices added in ascending order, four outputs per thread (Y is 8-byte aligned)
@@ -396,10 +699,17 @@ bool set_lds(K kernel, size_t smem) {
 
 template <int TB, bool BETA, int BR, int CODES>
 int launch_one(const MidDesc& d, unsigned blocks, hipStream_t st) {
-    constexpr size_t smem = mid_lds<TB>(CODES);
-    static const bool ok = set_lds(k_w4_mid<TB, BETA, BR, CODES>, smem);
-    if (!ok) return QBLORA_ERR_LAUNCH;
-    hipLaunchKernelGGL((k_w4_mid<TB, BETA, BR, CODES>), dim3(blocks), dim3(kMidThreads), smem, st, d);
+    if constexpr (TB > 5) {
+        constexpr size_t smem = Wide<TB, CODES, BR>::kLds;
+        static const bool ok = set_lds(k_w4_wide<TB, BETA, BR, CODES>, smem);
+        if (!ok) return QBLORA_ERR_LAUNCH;
+        hipLaunchKernelGGL((k_w4_wide<TB, BETA, BR, CODES>), dim3(blocks), dim3(kWideThreads), smem, st, d);
+    } else {
+        constexpr size_t smem = mid_lds<TB>(CODES);
+        static const bool ok = set_lds(k_w4_mid<TB, BETA, BR, CODES>, smem);
+        if (!ok) return QBLORA_ERR_LAUNCH;
+        hipLaunchKernelGGL((k_w4_mid<TB, BETA, BR, CODES>), dim3(blocks), dim3(kMidThreads), smem, st, d);
+    }
     return launch_status();
 }
 
