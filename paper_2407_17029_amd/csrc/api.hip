@@ -793,10 +793,10 @@ int qablora_linear_fwd(const qblora_qweight* qw, const qblora_bf16* H, int32_t l
     if (tile8 || dense || few) sct.out = nullptr;
     DequantDesc weight;
     if (dense && (rc = describe_dequantize(*qw, ws.W16, &weight))) return rc;
-    if ((rc = launch_prep(describe_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, sct.out ? &sct : nullptr), st, dense ? &weight : nullptr)))
+    // ... with s * AvgPool_lambda1(X) and a weight that is dequantized once
+    if ((rc = launch_prep_pool(describe_prep(H, H, I, J, J, 1, 1, ws.Ht, nullptr, nullptr, sct.out ? &sct : nullptr),
+                               PoolDesc{X, T, qw->d_in, lambda1, s / (float)lambda1, ws.P, nullptr}, dense ? &weight : nullptr, st)))
         return rc;
-    // s * AvgPool_lambda1(X)
-    if ((rc = launch_pool_rows(PoolDesc{X, T, qw->d_in, lambda1, s / (float)lambda1, ws.P, nullptr}, nullptr, st))) return rc;
 
     GemmDesc g{};
     g.qmode = 1;

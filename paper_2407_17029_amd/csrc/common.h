@@ -223,6 +223,8 @@ int grad_splits(int64_t T, int I, int J = 1);    // slices of the token range fo
 // out[t, m] = bf16(scale * sum of lam adjacent in[t, .]), out_lo (may be NULL) what that rounding took off; in: [T, d]
 struct PoolDesc { const qblora_bf16* in; int64_t T; int d, lam; float scale; qblora_bf16* out; qblora_bf16* out_lo; };
 int launch_pool_rows(const PoolDesc& a, const PoolDesc* b, hipStream_t st);     // b (may be NULL): in the same launch
+// a pooling without residual beside re-layouts and, where it is given, the weight: one launch where it goes in whole chunks
+int launch_prep_pool(const PrepDesc& d, const PoolDesc& pool, const DequantDesc* dequant, hipStream_t st);
 // `dequant` (may be NULL): the transposed weight, in the launch that reduces the partial sums
 int launch_grad(const GradDesc& d, hipStream_t st, const DequantDesc* dequant = nullptr);
 // two independent gradients whose partial buffers do not overlap: one launch for both where the shapes allow

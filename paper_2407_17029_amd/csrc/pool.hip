@@ -1,59 +1,10 @@
-// Row pooling for the single-matrix adapter (QA-BLoRA, Sec. 3.3, Alg. 2): the compressed input
-// AvgPool_lambda1(X) and the compressed output gradient sum_lambda2(dY) are materialised once per call
-// as bf16 operands of the K-extension of the dequantize-and-contract kernel and of the dH contraction,
-//
-//   out[t, m] = bf16( scale * sum_{i < lam} in[t, lam*m + i] )      (sum and product in fp32)
-//
-// and optionally the bf16 residual out_lo = bf16(value - out), which the dH contraction adds as a
-// second operand part so that only one of its two operands carries a bf16 rounding.
-//
-// Streaming, HBM-bound: a thread produces 8 consecutive outputs (one 16-byte store) from 8*lam
-// consecutive inputs (lam 16-byte loads) when rows are whole chunks, one output otherwise.
-#include "common.h"
+// Launches of the row poolings of pool.h, and interval sampling.
+#include "pool.h"
 
 namespace qblora {
 
 namespace {
 
-template <int LAM>
-__device__ __forceinline__ void pool_chunk(const uint4* __restrict__ in, int64_t c, float scale,
-                                           uint4* __restrict__ out, uint4* __restrict__ out_lo) {
-    uint4 v[LAM];
-#pragma unroll
-    for (int i = 0; i < LAM; ++i) v[i] = in[c * LAM + i];
-    float x[8 * LAM];
-#pragma unroll
-    for (int i = 0; i < LAM; ++i) {
-        const uint32_t w[4] = {v[i].x, v[i].y, v[i].z, v[i].w};
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            x[8 * i + 2 * q] = bf16_bits_to_float(w[q] & 0xffffu);
-            x[8 * i + 2 * q + 1] = bf16_bits_to_float(w[q] >> 16);
-        }
-    }
-    float o[8];
-#pragma unroll
-    for (int m = 0; m < 8; ++m) {
-        float acc = x[LAM * m];
-#pragma unroll
-        for (int i = 1; i < LAM; ++i) acc += x[LAM * m + i];
-        o[m] = acc * scale;
-    }
-    const uint4 h = make_uint4(pack_bf16(o[0], o[1]), pack_bf16(o[2], o[3]), pack_bf16(o[4], o[5]), pack_bf16(o[6], o[7]));
-    out[c] = h;
-    if (out_lo) {
-        const uint32_t hw[4] = {h.x, h.y, h.z, h.w};
-        uint32_t lw[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            lw[q] = pack_bf16(o[2 * q] - bf16_bits_to_float(hw[q] & 0xffffu), o[2 * q + 1] - bf16_bits_to_float(hw[q] >> 16));
-        out_lo[c] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
-    }
-}
-
-// Two poolings in one launch: the first n_a workgroups work on `a`.  A layer's two (dY and X of a backward) take 5 us each
-// alone, most of it start and tail.
-struct PoolPair { PoolDesc a, b; int64_t chunks_a, chunks_b; unsigned n_a; };
 template <int LAM_A, int LAM_B>
 __global__ __launch_bounds__(256) void k_pool_rows8(PoolPair p) {
     const bool second = blockIdx.x >= p.n_a;
@@ -108,14 +59,6 @@ __global__ __launch_bounds__(256) void k_sample_rows(const uint16_t* __restrict_
 
 namespace {
 
-int64_t outputs(const PoolDesc& d) { return d.T * (int64_t)(d.d / d.lam); }
-// whole chunks of 8 outputs: the matrix is one run of groups of lam values (rows are contiguous)
-bool in_chunks(const PoolDesc& d) {
-    const uintptr_t bits = reinterpret_cast<uintptr_t>(d.in) | reinterpret_cast<uintptr_t>(d.out) | reinterpret_cast<uintptr_t>(d.out_lo);
-    return (bits & 15) == 0 && outputs(d) % 8 == 0 && (d.lam == 1 || d.lam == 2 || d.lam == 4 || d.lam == 8);
-}
-unsigned chunk_blocks(const PoolDesc& d) { return (unsigned)((outputs(d) / 8 + 255) / 256); }
-
 template <int LAM_A>
 void launch_chunks(const PoolPair& p, unsigned blocks, int lam_b, hipStream_t st) {
     switch (lam_b) {
@@ -129,16 +72,16 @@ void launch_chunks(const PoolPair& p, unsigned blocks, int lam_b, hipStream_t st
 }  // namespace
 
 int launch_pool_rows(const PoolDesc& a, const PoolDesc* b, hipStream_t st) {
-    if (outputs(a) <= 0) return b ? launch_pool_rows(*b, nullptr, st) : QBLORA_OK;
-    if (b && (outputs(*b) <= 0 || !in_chunks(a) || !in_chunks(*b) || (int64_t)chunk_blocks(a) + chunk_blocks(*b) > 0x7fffffff)) {
+    if (pool_outputs(a) <= 0) return b ? launch_pool_rows(*b, nullptr, st) : QBLORA_OK;
+    if (b && (pool_outputs(*b) <= 0 || !pool_in_chunks(a) || !pool_in_chunks(*b) || (int64_t)pool_blocks(a) + pool_blocks(*b) > 0x7fffffff)) {
         const int rc = launch_pool_rows(a, nullptr, st);
         return rc ? rc : launch_pool_rows(*b, nullptr, st);
     }
-    if (in_chunks(a)) {
+    if (pool_in_chunks(a)) {
         PoolPair p{};
-        p.a = a; p.n_a = chunk_blocks(a); p.chunks_a = outputs(a) / 8;
-        if (b) { p.b = *b; p.chunks_b = outputs(*b) / 8; }
-        const unsigned blocks = p.n_a + (b ? chunk_blocks(*b) : 0);
+        p.a = a; p.n_a = pool_blocks(a); p.chunks_a = pool_outputs(a) / 8;
+        if (b) { p.b = *b; p.chunks_b = pool_outputs(*b) / 8; }
+        const unsigned blocks = p.n_a + (b ? pool_blocks(*b) : 0);
         const int lam_b = b ? b->lam : a.lam;
         switch (a.lam) {
             case 1: launch_chunks<1>(p, blocks, lam_b, st); break;
@@ -148,8 +91,8 @@ int launch_pool_rows(const PoolDesc& a, const PoolDesc* b, hipStream_t st) {
         }
         return launch_status();
     }
-    hipLaunchKernelGGL(k_pool_rows1, dim3((unsigned)((outputs(a) + 255) / 256)), dim3(256), 0, st,
-                       reinterpret_cast<const uint16_t*>(a.in), outputs(a), a.lam, a.scale, reinterpret_cast<uint16_t*>(a.out),
+    hipLaunchKernelGGL(k_pool_rows1, dim3((unsigned)((pool_outputs(a) + 255) / 256)), dim3(256), 0, st,
+                       reinterpret_cast<const uint16_t*>(a.in), pool_outputs(a), a.lam, a.scale, reinterpret_cast<uint16_t*>(a.out),
                        reinterpret_cast<uint16_t*>(a.out_lo));
     return launch_status();
 }

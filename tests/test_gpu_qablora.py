@@ -54,6 +54,18 @@ def test_forward_parity(qb, oracle, codebook, T, d_out, d_in, lam1, lam2, s):
     assert_close_bf16(Y, oracle.qa_forward(Wt, L.X, Hb, lam1, lam2, s), "Y")
 
 
+@pytest.mark.parametrize("T,d_out,d_in,lam1,lam2", [
+    (1, 64, 64, 8, 8),                       # one chunk of eight pooled values
+    (65, 192, 256, 8, 2),                    # 260 chunks: the second workgroup of the pooling is nearly empty
+    (64, 192, 256, 8, 2),                    # 256: exactly one
+    (97, 128, 320, 1, 4), (33, 320, 192, 2, 1), (300, 128, 448, 4, 2),
+    (9, 192, 384, 16, 4), (7, 64, 512, 64, 1),     # 16 and 64 features a value: pooled in a launch of their own
+    (520, 512, 1024, 4, 2), (520, 512, 1024, 32, 8),       # with the weight dequantized in the same launch, or beside its own
+])
+def test_forward_pooled_beside_the_layouts(qb, oracle, codebook, T, d_out, d_in, lam1, lam2):
+    test_forward_parity(qb, oracle, codebook, T, d_out, d_in, lam1, lam2, 0.5)
+
+
 @pytest.mark.parametrize("T,d_out,d_in,lam1,lam2,s", CASES)
 def test_backward_parity(qb, oracle, codebook, T, d_out, d_in, lam1, lam2, s):
     from gpu_util import assert_close_bf16, assert_close_f32
