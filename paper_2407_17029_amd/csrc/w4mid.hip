@@ -8,7 +8,7 @@
 // of codes + the block parameters per weight) sets the time and at 128 tokens the MFMAs do.  A token tile of
 // 256 (the training kernel) would waste most of its MFMAs here and, with one workgroup per 256 output rows,
 // leave most of the chip idle.  Here a workgroup of 4 waves owns 128 output rows (32 per wave), ALL tokens
-// (32 * TB of them, TB = 1 .. 8) and one slice of the input dimension; the slices of a row tile (split-K, as
+// (32 * TB of them, TB = 1 .. 5, to 8 in k_w4_wide) and one slice of the input dimension; the slices of a row tile (split-K, as
 // many as the chip takes at once, see w4_mid_call_splits) write fp32 partial tiles that a second kernel adds in
 // slice order (deterministic).
 //
@@ -23,9 +23,9 @@
 // hand (the compiler would tie every LDS access to them): a step waits until only the two youngest batches (the codes
 // and the token tile of a step each) are outstanding.  The operands of step s+1 are built between the MFMAs of step s.
 //
-// Above 128 tokens one launch reads and dequantizes every weight once for all of them; two chunks of 128 did it twice (201
+// From 161 tokens four waves copy and four contract (k_w4_wide).  Above 128 tokens one launch reads and dequantizes every weight once for all of them; two chunks of 128 did it twice (201
 // tokens of 5120 x 13824 63 + 10 us for the contraction and the sum of the slices, one launch 47 + 5).  What bounds it: the
-// partial tiles (256 workgroups of 128 rows x 256 tokens write and read 34 MB, about 14 us of 4096 x 4096's 25), then the
+// partial tiles (256 workgroups of 128 rows x 256 tokens write and read 34 MB, about 14 us of 4096 x 4096's 23), then the
 // matrix pipe at half to two thirds of its rate.
 //
 // A lane ends up with 4 consecutive output rows of one token per accumulator quad and stores them as one
