@@ -31,3 +31,12 @@ def test_token_tiles(oracle, codebook, rules, T, d_out, d_in, fmt):
     assert_close_bf16(Y[:T], ref, "Y")
     assert torch.equal(Y[:T], Yp)                        # the same weight, contracted in the same order
     assert torch.all(Y[T:] == 7.0)                       # nothing is written past the last token
+
+
+@pytest.mark.parametrize("fmt", list(FORMATS))
+@pytest.mark.parametrize("T,d_out,d_in", [
+    (161, 40, 64), (256, 264, 64), (200, 136, 128), (225, 8, 192), (256, 40, 256),          # one to four steps: fewer than the rings hold
+    (192, 264, 512), (224, 128, 576),                                                   # two slices of four, of four and five
+])
+def test_copying_waves_on_short_slices(oracle, codebook, rules, T, d_out, d_in, fmt):
+    test_token_tiles(oracle, codebook, rules, T, d_out, d_in, fmt)
