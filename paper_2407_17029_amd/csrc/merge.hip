@@ -495,29 +495,39 @@ int launch_tile8(const MergeDesc* ds, int count, hipStream_t st) {
     }
 }
 
-// Whether no weight's output lies in another's base or output (a chain of merges runs one after the other).
+// Whether no weight's output lies in what another reads or writes (a chain of merges runs one after the other).
 bool independent(const MergeDesc* ds, int count) {
-    auto overlap = [](const void* p, size_t np, const void* q, size_t nq) {
-        const uintptr_t a = reinterpret_cast<uintptr_t>(p), b = reinterpret_cast<uintptr_t>(q);
-        return p && q && a < b + nq && b < a + np;
+    struct Range { const void* p; size_t n; };
+    auto overlap = [](const Range& x, const Range& y) {
+        const uintptr_t a = reinterpret_cast<uintptr_t>(x.p), b = reinterpret_cast<uintptr_t>(y.p);
+        return x.p && y.p && a < b + y.n && b < a + x.n;
     };
-    for (int m = 0; m < count; ++m)
+    auto blocks = [](const MergeDesc& d) {
+        return d.block_rows == 8 ? (size_t)(d.d_out / 8) * (d.d_in / d.block_cols) : (size_t)d.d_out * (d.d_in / kBlock);
+    };
+    auto codes = [](const MergeDesc& d) { return (size_t)d.d_out * d.d_in / 2; };
+    for (int m = 0; m < count; ++m) {
+        const MergeDesc& x = ds[m];
+        const size_t params = sizeof(float) * blocks(x);
+        const Range out[3] = {{x.codes_out, codes(x)}, {x.alpha_out, params}, {x.beta_out, params}};
         for (int q = 0; q < count; ++q) {
             if (m == q) continue;
-            auto blocks = [](const MergeDesc& d) { return sizeof(float) * (size_t)(d.d_out / 8) * (d.d_in / d.block_cols); };
-            const MergeDesc &x = ds[m], &y = ds[q];
-            const size_t cx = (size_t)x.d_out * x.d_in / 2, cy = (size_t)y.d_out * y.d_in / 2;
-            const struct { const void* p; size_t n; } out[3] = {{x.codes_out, cx}, {x.alpha_out, blocks(x)}, {x.beta_out, blocks(x)}},
-                in[6] = {{y.codes, cy}, {y.scales, blocks(y)}, {y.beta, blocks(y)}, {y.codes_out, cy}, {y.alpha_out, blocks(y)}, {y.beta_out, blocks(y)}};
-            for (const auto& o : out)
-                for (const auto& i : in)
-                    if (overlap(o.p, o.n, i.p, i.n)) return false;
+            const MergeDesc& y = ds[q];
+            const size_t nb = blocks(y), f = sizeof(float), groups = y.scale_codes ? (nb + y.scale_group - 1) / y.scale_group : 0;
+            const Range in[10] = {{y.codes, codes(y)}, {y.scale_codes ? nullptr : y.scales, f * nb}, {y.beta, f * nb},
+                                  {y.scale_codes, nb}, {y.scale_step, f * groups}, {y.scale_mid, f * groups},
+                                  {y.H, f * (size_t)(y.d_in / y.lam1) * (y.d_out / y.lam2)},
+                                  {y.codes_out, codes(y)}, {y.alpha_out, f * nb}, {y.beta_out, f * nb}};
+            for (const Range& o : out)
+                for (const Range& i : in)
+                    if (overlap(o, i)) return false;
         }
+    }
     return true;
 }
 
-// One launch for `count` (2 .. 8) weights that share lambdas, block shape, scale format and the presence of offsets;
-// QBLORA_ERR_UNSUPPORTED (nothing launched) when they do not -- the caller then merges them one by one.
+// One launch for `count` (2 .. 8) weights that share lambdas, block shape, scale format and the presence of offsets and do
+// not wait for each other; else QBLORA_ERR_UNSUPPORTED (nothing launched), and the caller merges them one by one.
 int launch_merge_requant_batch(const MergeDesc* ds, int count, hipStream_t st) {
     if (count < 2 || count > kMergeBatchMax) return QBLORA_ERR_UNSUPPORTED;
     for (int m = 0; m < count; ++m)
@@ -525,7 +535,8 @@ int launch_merge_requant_batch(const MergeDesc* ds, int count, hipStream_t st) {
             ds[m].lam2 != ds[0].lam2 || (ds[m].scale_codes == nullptr) != (ds[0].scale_codes == nullptr) ||
             (ds[m].beta == nullptr) != (ds[0].beta == nullptr))
             return QBLORA_ERR_UNSUPPORTED;
-    if (ds[0].block_rows == 8) return independent(ds, count) ? launch_tile8<false>(ds, count, st) : QBLORA_ERR_UNSUPPORTED;
+    if (!independent(ds, count)) return QBLORA_ERR_UNSUPPORTED;
+    if (ds[0].block_rows == 8) return launch_tile8<false>(ds, count, st);
     switch (ds[0].lam1) {
         case 1: return launch_requant_batch_l1<1>(ds, count, st);
         case 2: return launch_requant_batch_l1<2>(ds, count, st);

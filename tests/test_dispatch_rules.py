@@ -162,3 +162,57 @@ def test_no_call_takes_more_slices_than_its_workspace_counts_on(rules):
             for T in [17, 32, 64, 65, 96, 97, 128, 129, 192, 256]:
                 for table in (False, True):
                     assert 1 <= call(d_out, d_in, T, table) <= most(d_out, d_in, T)
+
+
+class MergeDesc(C.Structure):
+    """The library's description of one weight's merge (csrc/common.h)."""
+    _fields_ = [*[(n, C.c_void_p) for n in ("codes", "scales", "beta", "scale_codes", "scale_step", "scale_mid")],
+                ("scale_group", C.c_int), ("codebook", C.c_float * 16), ("d_out", C.c_int), ("d_in", C.c_int),
+                ("H", C.c_void_p), ("lam1", C.c_int), ("lam2", C.c_int), ("s", C.c_float),
+                *[(n, C.c_void_p) for n in ("codes_out", "alpha_out", "beta_out", "w16_out")],
+                ("block_rows", C.c_int), ("block_cols", C.c_int), ("magic", C.c_uint32)]
+
+
+@pytest.mark.parametrize("kind", ["absmax", "int4", "grouped", "8x8", "8x4"])
+def test_merges_that_wait_for_each_other_share_no_launch(rules, kind):
+    """No output of one weight may lie in what another reads or writes, up to its last byte: the weights of a launch run side
+    by side.  The addresses are made up; nothing is launched where the rule says so."""
+    rule, launch = rules.L["_ZN6qblora11independentEPKNS_9MergeDescEi"], rules.L["_ZN6qblora26launch_merge_requant_batchEPKNS_9MergeDescEiP12ihipStream_t"]
+    rule.argtypes, rule.restype = [C.c_void_p, C.c_int], C.c_bool
+    launch.argtypes, launch.restype = [C.c_void_p, C.c_int, C.c_void_p], C.c_int
+    d_out, d_in, lam1, lam2, group = 24, 192, 2, 4, 7
+    blocks = d_out * d_in // {"8x4": 32}.get(kind, 64)
+    groups = -(-blocks // group)
+    sizes = {"codes": d_out * d_in // 2, "scales": 4 * blocks, "beta": 4 * blocks, "scale_codes": blocks, "scale_step": 4 * groups,
+             "scale_mid": 4 * groups, "H": 4 * (d_in // lam1) * (d_out // lam2), "codes_out": d_out * d_in // 2,
+             "alpha_out": 4 * blocks, "beta_out": 4 * blocks}
+    names = [n for n in sizes if not (n.startswith("scale_") and kind != "grouped") and (n, kind) not in
+             {("scales", "grouped"), ("beta", "absmax"), ("beta", "grouped")}]
+
+    def pair():
+        ds, at = (MergeDesc * 2)(), 1 << 20
+        for d in ds:
+            for n in names:
+                setattr(d, n, at)
+                at += -(-sizes[n] // 4) * 4                                    # one right behind the other
+            d.scale_group, d.d_out, d.d_in, d.lam1, d.lam2, d.s = group, d_out, d_in, lam1, lam2, 1.0
+            d.block_rows, d.block_cols = (8, int(kind[2])) if kind[0] == "8" else (1, 64)
+        return ds
+
+    assert rule(pair(), 2)
+    ds = pair()
+    for n in names[:-3]:
+        setattr(ds[1], n, getattr(ds[0], n))                                   # what is only read may be shared
+    ds[0].codes_out, ds[0].alpha_out = ds[0].codes, ds[0].scales or ds[0].alpha_out
+    ds[1].codes = ds[1].codes_out
+    if kind != "grouped":
+        ds[1].scales = ds[1].alpha_out
+    assert rule(ds, 2)                                                         # each in place
+    for x, y in ((0, 1), (1, 0)):
+        for out in ("codes_out", "alpha_out", "beta_out"):
+            for n in names:
+                for at in (0, sizes[n] - 1, 1 - sizes[out]):
+                    ds = pair()
+                    setattr(ds[x], out, getattr(ds[y], n) + at)
+                    assert not rule(ds, 2), (x, out, n, at)
+                    assert launch(ds, 2, None) == -3           # QBLORA_ERR_UNSUPPORTED

@@ -195,3 +195,20 @@ def test_batched_merge_offset_shift_and_errors(qb, oracle, codebook):
     assert qb.qablora_merge_quantize_batch([], [], 2, 2, 1.0, qb.MERGE_REQUANT_MINMAX) == []
     with pytest.raises(qb.QBLoRAError):                      # one misaligned weight rejects the whole call
         qb.qablora_merge_quantize_batch(bases, Hs, 2, 2, s, qb.MERGE_BETA_SHIFT)
+
+
+@pytest.mark.parametrize("d_out,d_in,lam1,lam2", [(64, 256, 2, 2), (1024, 2048, 2, 2), (100, 192, 3, 5), (520, 4096, 64, 8)])
+def test_chain_of_merges_in_one_call(qb, d_out, d_in, lam1, lam2):
+    """A batch whose second weight is the first one's output: merged one after the other, the bits of single calls."""
+    from gpu_util import f32_to_dev
+    base = qb.qblora_quantize_blockwise(f32_to_dev(synth.base_weight(895, 0, d_out, d_in)), 64, qb.QUANT_MINMAX_INT4)
+    H = f32_to_dev(synth.normal_f32(896, 1, (d_in // lam1, d_out // lam2), 0.01))
+    first, second = (qb.QWeight(d_out, d_in, 64, base.codebook, torch.zeros_like(base.codes), torch.zeros_like(base.scales),
+                                torch.zeros_like(base.scales)) for _ in range(2))
+    qb.qablora_merge_quantize_batch([base, first], [H, H], lam1, lam2, 0.75, qb.MERGE_REQUANT_MINMAX, outs=[first, second])
+    want = qb.qablora_merge_quantize(base, H, lam1, lam2, 0.75, qb.MERGE_REQUANT_MINMAX)
+    again = qb.qablora_merge_quantize(want, H, lam1, lam2, 0.75, qb.MERGE_REQUANT_MINMAX)
+    torch.cuda.synchronize()
+    for got, ref in ((first, want), (second, again)):
+        assert torch.equal(got.codes, ref.codes) and torch.equal(got.scales.view(torch.int32), ref.scales.view(torch.int32))
+        assert torch.equal(got.beta.view(torch.int32), ref.beta.view(torch.int32))
