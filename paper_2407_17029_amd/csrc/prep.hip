@@ -124,11 +124,12 @@ int launch_prep_pool(const PrepDesc& d, const PoolDesc& pool, const DequantDesc*
         return rc ? rc : launch_pool_rows(pool, nullptr, st);
     }
     const PoolJob j{pool, pool_outputs(pool) / 8, pool_blocks(pool)};
-    if (dequant)
+    if (dequant) {
+        ProfileScope ev(QBLORA_PROFILE_DEQUANT, st);
         with_form(*dequant, [&](auto beta, auto geom) {
             hipLaunchKernelGGL((k_prep_pool_dequantize<beta.value, geom.value>), dim3((unsigned)blocks), dim3(256), 0, st, d, j, *dequant);
         });
-    else hipLaunchKernelGGL(k_prep_pool, dim3((unsigned)blocks), dim3(256), 0, st, d, j);
+    } else hipLaunchKernelGGL(k_prep_pool, dim3((unsigned)blocks), dim3(256), 0, st, d, j);
     return launch_status();
 }
 
