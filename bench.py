@@ -69,15 +69,19 @@ def measured_valu(workload: str, kernel: str):
     return None
 
 
-def side_launches(ms, once):
+def side_launches(ms, once, in_narrow=()):
     """Adapter launches and passes over the weight of a projection, ms each, from the mean times of the event slots: {launch: ms}.
     A pass over the weight shares its launch with the adapter's re-layouts (forward) or the reduction of the gradients' partial
-    sums (backward); the slots then bracket that same launch, which counts once and as the pass."""
+    sums (backward); the slots then bracket that same launch, which counts once and as the pass.  `in_narrow`: which of "prep" and
+    "dequant_fwd" are launches of the forward's narrow GEMM, between the events of adapter_fwd: the re-layouts count as that GEMM,
+    the pass over the weight, in the launch of the slices' sums, as the pass."""
     adapter = {k: ms[k] for k in ("adapter_fwd", "adapter_bwd", "adapter_grads")}
     passes = {k: ms[k] for k in ("dequant_fwd", "dequant_bwd") if once[k]}
     for k, with_pass in (("prep", "dequant_fwd"), ("grad_reduce", "dequant_bwd")):
-        if not once[with_pass]:
+        if not once[with_pass] and k not in in_narrow:
             adapter[k] = ms[k]
+    if once["dequant_fwd"] and "dequant_fwd" in in_narrow:
+        adapter["adapter_fwd"] -= ms["dequant_fwd"]
     return adapter, passes
 
 
@@ -320,6 +324,13 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
         if not ran:
             raw[k] = [0.0]
 
+    def between(k, outer):                  # whether k's events lie between those of `outer`
+        return all(o[0].elapsed_time(e[0]) >= 0 and e[1].elapsed_time(o[1]) >= 0
+                   for e, o in zip(events[k], events[outer]))
+
+    # What the forward's narrow GEMM does not wait for shares its launches
+    in_narrow = [k for k in ("prep", "dequant_fwd") if once.get(k, True) and between(k, "adapter_fwd")]
+
     fwd_flops = 2.0 * T * bp.d_in * bp.d_out + 2.0 * T * R * bp.d_out / lam
     bwd_flops = 2.0 * T * bp.d_in * bp.d_out + 2.0 * T * R * bp.d_in / lam
     n_w = bp.d_in * bp.d_out
@@ -341,7 +352,7 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
         return d
 
     proj_name = f"{bp.name} [{bp.d_out}x{bp.d_in}]"
-    kname = ("k_dense (forward contraction on the weight dequantized once per call)" if once["dequant_fwd"]
+    kname = ("k_dense, or k_flow in tiles below 256 x 256 (forward contraction on the weight dequantized once per call)" if once["dequant_fwd"]
              else "k_qlinear, or k_few up to 256 tokens (forward contraction from the 4-bit codes)")
     out = {
         "value": round(value, 2), "unit": "TFLOP/s", "steps": steps, "warmup": warmup,
@@ -362,17 +373,19 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
                          "frac": round(bwd_flops / (gemm_ms("bwd_gemm") * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, 4)},
             "quantize": hbm("quantize", quant_bytes),
             "dequantize_once_fwd": (hbm("dequant_fwd", n_w * (0.5 + scale_bytes + 2) + 4.0 * adapter_elems,
-                                        "codes + scales -> bf16 weight in the workspace, and A, B re-laid, in one launch")
+                                        "codes + scales -> bf16 weight in the workspace, in one launch with " +
+                                        ("the sums of the narrow GEMM's slices" if "dequant_fwd" in in_narrow else "A, B re-laid"))
                                     if once["dequant_fwd"] else None),
             "dequantize_once_bwd": ({"event_overhead_included": True, "ms": stats(raw["dequant_bwd"]),
                                      "note": "the same, transposed, and the reduction of the gradients' partial sums, in one launch"}
                                     if once["dequant_bwd"] else None),
-            "adapter_fwd_skinny": hbm("adapter_fwd", 2.0 * T * bp.d_in + 2.0 * T * R * 2, "s*U = (s/lambda) X A_x^T; reads X once"),
+            "adapter_fwd_skinny": hbm("adapter_fwd", 2.0 * T * bp.d_in + 2.0 * T * R * 2, "s*U = (s/lambda) X A_x^T; reads X once" +
+                                      "".join(f"; with {k} in its launches" for k in in_narrow)),
             "adapter_bwd_skinny": hbm("adapter_bwd", 2.0 * T * bp.d_out + 2.0 * T * R * 3, "dU = s dY B_x^T; reads dY once"),
             "adapter_grads": hbm("adapter_grads", 2.0 * T * (bp.d_in + bp.d_out) + 8.0 * T * R,
                                  "token contractions behind dA and dB, one launch; partial-sum writes not counted"),
             "grad_reduce": None if once["dequant_bwd"] else {"ms": stats(raw["grad_reduce"])},
-            "prep": None if once["dequant_fwd"] else {"ms": stats(raw["prep"])},
+            "prep": None if once["dequant_fwd"] or "prep" in in_narrow else {"ms": stats(raw["prep"])},
             "merge_requant_batch": hbm("merge", merge_batch_bytes,
                                        f"the requantizing merge of all {len(S.proj)} projections of the layer, one launch"),
             "tile_products": {"ms": stats(raw["tile_product"]),
@@ -388,7 +401,7 @@ def measure(S, steps, warmup, side_steps, plain_events=False, calibration_copy=F
         v = measured_valu(wl.name, k)
         if v and out["kernels"].get(key):
             out["kernels"][key].update(v)
-    adapter, passes = side_launches({k: float(np.mean(v)) for k, v in raw.items()}, once)
+    adapter, passes = side_launches({k: float(np.mean(v)) for k, v in raw.items()}, once, in_narrow)
     adapter_ms = sum(adapter.values())
     proj_ms = adapter_ms + gemm_ms("fwd_gemm") + gemm_ms("bwd_gemm") + float(np.mean(raw["quantize"])) + sum(passes.values())
     # the contraction with the launch of the one-off dequantize pass, as one figure per direction

@@ -401,7 +401,7 @@ int qblora_decode_pack(const qblora_qweight* qw, void* pack, void* stream);
  * Measurement hook.  Registers a pair of caller-created hipEvent_t (passed as void*) that the next
  * calls record on their stream immediately before and after ONE part of the work, so that a
  * benchmark can time that part alone while running the whole path.  It is one kernel launch, except that a
- * contraction that is cut into slices is bracketed together with the launch that adds them:
+ * contraction that is cut into slices (the narrow GEMMs among them) is bracketed together with the launch that adds them:
  *   QBLORA_PROFILE_FWD_GEMM   the base contraction of qblora_linear_fwd, adapter term included, from the codes or on the
  *                             weight dequantized once (whose pass is then QBLORA_PROFILE_DEQUANT)
  *   QBLORA_PROFILE_BWD_GEMM   the same on the transposed weight: dX of qblora_linear_bwd
@@ -411,11 +411,13 @@ int qblora_decode_pack(const qblora_qweight* qw, void* pack, void* stream);
  *   QBLORA_PROFILE_ADAPTER_BWD    the narrow GEMM dU = dV B^T of the backward, with s*U where that is recomputed
  *   QBLORA_PROFILE_ADAPTER_GRADS  the token contractions behind dA and dB (partial sums, both in one launch)
  *   QBLORA_PROFILE_GRAD_REDUCE    the fixed-order reduction of those partial sums into dA and dB
- *   QBLORA_PROFILE_PREP           the per-call re-layout launch of the forward (adapter operands, block scales)
+ *   QBLORA_PROFILE_PREP           the launch with the per-call re-layouts of qblora_linear_fwd (adapter operands, block
+ *                                 scales): its own, or that of the narrow GEMM, which is then inside the ADAPTER_FWD pair
  *   QBLORA_PROFILE_TILE_PRODUCT   the kernel of qblora_tile_product
- *   QBLORA_PROFILE_DEQUANT        the launch with the one-off dequantize pass of a forward / backward call, which the
- *                                 re-layouts (PREP) or the reduction (GRAD_REDUCE) share (not recorded by calls that
- *                                 contract from the codes)
+ *   QBLORA_PROFILE_DEQUANT        the launch with the one-off dequantize pass of a forward / backward call (not recorded by
+ *                                 calls that contract from the codes).  Others share it: the forward's re-layouts (it is
+ *                                 inside the PREP pair, if there is one) or, where these go with the narrow GEMM, the sums
+ *                                 of that GEMM's slices (inside ADAPTER_FWD); the backward's gradient reduction
  * Passing NULL for both events unregisters the slot.  The registration is per host thread: it applies to
  * calls made by the thread that registered it, so concurrent callers do not see each other's events.  Has
  * no effect on results.

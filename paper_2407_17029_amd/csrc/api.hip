@@ -476,9 +476,9 @@ int linear_fwd_impl(const qblora_qweight* qw, const qblora_adapter* ad, const qb
     // that of its sums: a launch (4 to 5 us) less.  Otherwise they go first, the weight with them: beside the narrow GEMM itself
     // it would have one or two workgroups on a CU, whose LDS the GEMM's ring takes.
     const bool together = adapted && skinny_shares(u) && (!dense || u.splits > 1);
-    {
+    if (!together) {
         ScopedEvents ev(QBLORA_PROFILE_PREP, st);
-        if (!together && (rc = launch_prep(prep, st, dense ? &weight : nullptr))) return rc;
+        if ((rc = launch_prep(prep, st, dense ? &weight : nullptr))) return rc;
     }
     if (adapted && op != QBLORA_OP_AVGPOOL_REPEAT) {
         // At_x[j][k] = A[C-map(k)][j] and Bt[n][j] = B[j][E-map(n)], zero where the operator drops the index

@@ -442,6 +442,7 @@ int launch_cfg(const Call& c, hipStream_t st) {
             auto kern = k_skinny_prep<BM, BN, kStages, kSub, kSplitK, kDup, kByK>;
             static const bool ok = set_lds(kern, smem);
             if (!ok) return QBLORA_ERR_LAUNCH;
+            ProfileScope ev(QBLORA_PROFILE_PREP, st);
             hipLaunchKernelGGL(kern, dim3(n + (unsigned)c.prep->blocks()), dim3(kThreads), smem, st, SkinnyPrep{d, *c.prep, n});
         }
     } else {
