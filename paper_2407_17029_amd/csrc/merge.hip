@@ -495,35 +495,30 @@ int launch_tile8(const MergeDesc* ds, int count, hipStream_t st) {
     }
 }
 
-// Whether no weight's output lies in what another reads or writes (a chain of merges runs one after the other).
+// Whether no weight's output lies in what another reads or writes (a chain of merges runs one after the other); at most
+// kMergeBatchMax weights.
 bool independent(const MergeDesc* ds, int count) {
-    struct Range { const void* p; size_t n; };
-    auto overlap = [](const Range& x, const Range& y) {
-        const uintptr_t a = reinterpret_cast<uintptr_t>(x.p), b = reinterpret_cast<uintptr_t>(y.p);
-        return x.p && y.p && a < b + y.n && b < a + x.n;
-    };
-    auto blocks = [](const MergeDesc& d) {
-        return d.block_rows == 8 ? (size_t)(d.d_out / 8) * (d.d_in / d.block_cols) : (size_t)d.d_out * (d.d_in / kBlock);
-    };
-    auto codes = [](const MergeDesc& d) { return (size_t)d.d_out * d.d_in / 2; };
+    constexpr int kOut = 3, kAll = 10;                       // a weight's outputs, and behind them what it reads
+    uintptr_t lo[kMergeBatchMax][kAll], hi[kMergeBatchMax][kAll];
     for (int m = 0; m < count; ++m) {
-        const MergeDesc& x = ds[m];
-        const size_t params = sizeof(float) * blocks(x);
-        const Range out[3] = {{x.codes_out, codes(x)}, {x.alpha_out, params}, {x.beta_out, params}};
-        for (int q = 0; q < count; ++q) {
-            if (m == q) continue;
-            const MergeDesc& y = ds[q];
-            const size_t nb = blocks(y), f = sizeof(float), groups = y.scale_codes ? (nb + y.scale_group - 1) / y.scale_group : 0;
-            const Range in[10] = {{y.codes, codes(y)}, {y.scale_codes ? nullptr : y.scales, f * nb}, {y.beta, f * nb},
-                                  {y.scale_codes, nb}, {y.scale_step, f * groups}, {y.scale_mid, f * groups},
-                                  {y.H, f * (size_t)(y.d_in / y.lam1) * (y.d_out / y.lam2)},
-                                  {y.codes_out, codes(y)}, {y.alpha_out, f * nb}, {y.beta_out, f * nb}};
-            for (const Range& o : out)
-                for (const Range& i : in)
-                    if (overlap(o, i)) return false;
+        const MergeDesc& d = ds[m];
+        const size_t n = d.block_rows == 8 ? (size_t)(d.d_out / 8) * (d.d_in / d.block_cols) : (size_t)d.d_out * (d.d_in / kBlock);
+        const size_t codes = (size_t)d.d_out * d.d_in / 2, f = sizeof(float), groups = d.scale_codes ? (n + d.scale_group - 1) / d.scale_group : 0;
+        const struct { const void* p; size_t bytes; } ranges[kAll] = {
+            {d.codes_out, codes}, {d.alpha_out, f * n}, {d.beta_out, f * n}, {d.codes, codes}, {d.scale_codes ? nullptr : d.scales, f * n},
+            {d.beta, f * n}, {d.scale_codes, n}, {d.scale_step, f * groups}, {d.scale_mid, f * groups},
+            {d.H, f * (size_t)(d.d_in / d.lam1) * (d.d_out / d.lam2)}};
+        for (int i = 0; i < kAll; ++i) {
+            lo[m][i] = reinterpret_cast<uintptr_t>(ranges[i].p);
+            hi[m][i] = ranges[i].p ? lo[m][i] + ranges[i].bytes : 0;
         }
     }
-    return true;
+    bool overlap = false;
+    for (int m = 0; m < count; ++m)
+        for (int q = 0; q < count; ++q)
+            for (int o = 0; o < kOut && m != q; ++o)
+                for (int i = 0; i < kAll; ++i) overlap |= (lo[m][o] < hi[q][i]) & (lo[q][i] < hi[m][o]);
+    return !overlap;
 }
 
 // One launch for `count` (2 .. 8) weights that share lambdas, block shape, scale format and the presence of offsets and do
