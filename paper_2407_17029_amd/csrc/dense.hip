@@ -11,7 +11,7 @@
 // Bound: the matrix pipe.  Two kernels, by the size of the tile:
 //
 // k_dense, 256 x 256 tiles, for calls that fill rounds of the chip with them (1450 to 1510 TFLOP/s at 1.6-1.7 GHz, where the
-// part is power-limited).  A workgroup is 8 wave64 as 2 (tokens) x 4 (features), two waves to a SIMD; a wave owns 128 tokens x
+// part is power-limited), sliced too, and for operands that outgrow the memory-side cache (dense_call_plan).  A workgroup is 8 wave64 as 2 (tokens) x 4 (features), two waves to a SIMD; a wave owns 128 tokens x
 // 64 features.  The two waves of a SIMD belong to different halves of the workgroup (waves 0-3 and 4-7) that alternate
 // strictly: while one half runs a compute phase (16 MFMAs, 16 cycles each) the other runs a memory phase (LDS fragment reads
 // for its next compute phase, two copies into the ring, the waits), with a barrier between phases.  The second half passes one
@@ -22,7 +22,7 @@
 // behind the one that read it: reads complete (lgkmcnt(0)) in front of the barrier that ends their phase, and the other half's
 // same phase ends one barrier earlier than the refill starts.
 //
-// k_flow, smaller tiles, for all other calls.  Eight waves contract, four others, one to a SIMD, do nothing but copy: a copy
+// k_flow, smaller tiles.  Eight waves contract, four others, one to a SIMD, do nothing but copy: a copy
 // instruction holds up the wave that issues it, and among the MFMAs that cost a quarter of the time.  The fragments of the next
 // 64 or 32 wide step are read between the MFMAs of this one; one barrier a step says that the next stage is in and that the
 // last one is free.  us in the phased form (which smaller tiles had too) / with the copies among the MFMAs / here: 1337 x 5120 x
@@ -82,6 +82,7 @@ struct Ring {
     static constexpr int kLds = kStages * kStage > kEpilogue ? kStages * kStage : kEpilogue;
 };
 
+template <bool SLICED>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_dense(GemmDesc d) {
     using R = Ring;
     constexpr int BM = 64 * MB, BN = 128 * NB, S = R::kStages;
@@ -89,7 +90,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 
     const int64_t M = d.M;
     const int N = d.N, K2 = d.K2, div2 = d.div2;
-    const int n = d.K1 / kBK + (K2 + kBK - 1) / kBK, steps1 = d.K1 / kBK;     // steps1 of them belong to the first segment
+    const int all_steps = d.K1 / kBK + (K2 + kBK - 1) / kBK;
     const int64_t ldx2 = d.ldx2, ldw2 = d.ldw2;
     const qblora_bf16* const X2 = d.X2;
     const qblora_bf16* const W2 = d.W2;
@@ -102,11 +103,21 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // Tile assignment: workgroup ids go to the XCDs round-robin; each XCD gets a contiguous range of tiles, grouped
     // along tokens so that the tiles it runs at a time share token and weight panels in its L2.
     const int tiles_m = (int)((M + BM - 1) / BM), tiles_n = (N + BN - 1) / BN, ntiles = tiles_m * tiles_n;
+    const int splits = SLICED ? d.splits : 1;
     int L;
     {
-        const int xcd = blockIdx.x & 7, q = ntiles >> 3, rem = ntiles & 7;
+        const int units = ntiles * splits, xcd = blockIdx.x & 7, q = units >> 3, rem = units & 7;
         L = xcd * q + min(xcd, rem) + (blockIdx.x >> 3);
     }
+    // slice z of the contraction (all tiles of a slice are neighbours): n steps from step0 on, at least one
+    int z = 0, step0 = 0, n = all_steps;
+    if constexpr (SLICED) {
+        z = L / ntiles;
+        step0 = all_steps * z / splits;
+        n = all_steps * (z + 1) / splits - step0;
+        L -= z * ntiles;
+    }
+    const int steps1 = d.K1 / kBK - step0;        // steps from here on that belong to the first segment (may be negative)
     constexpr int GM = 4;
     const int in_group = GM * tiles_n, first_m = (L / in_group) * GM, gsize = min(tiles_m - first_m, GM);
     const int64_t m0 = (int64_t)(first_m + (L % in_group) % gsize) * BM;
@@ -121,7 +132,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     // collide in pairs: 19 % of the kernel's cycles.)
     uint32_t xoff[MB / 2][2];
     int xchunk[2];
-    const qblora_bf16* const x_tile = d.X1 + m0 * d.ldx1;
+    const qblora_bf16* const x_tile = d.X1 + m0 * d.ldx1 + (int64_t)step0 * kBK;
 #pragma unroll
     for (int i = 0; i < 2; ++i) xchunk[i] = (lane & 7) ^ (4 * i + (lane >> 4));
     auto token_row = [&](int p, int i) __attribute__((always_inline)) {          // tile row, clamped to the last token
@@ -139,7 +150,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
 #pragma unroll
     for (int a = 0; a < NB; ++a) {
         wblk[a] = min(n0 / 32 + (wave >> 1) * NB + a, blocks32 - 1);    // rows past N: any block, results never stored
-        wbase[a] = reinterpret_cast<const unsigned char*>(d.W1) + (int64_t)(2 * wblk[a] + (wave & 1)) * (d.K1 / 32) * 1024;
+        wbase[a] = reinterpret_cast<const unsigned char*>(d.W1) + (int64_t)(2 * wblk[a] + (wave & 1)) * (d.K1 / 32) * 1024 + (int64_t)step0 * 2048;
     }
     const uint32_t lane16 = (uint32_t)lane * 16u;
     const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(smem));
@@ -268,6 +279,19 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");   // LDS is free: no copy under way, no wave reading
 
     // ---- epilogue -----------------------------------------------------------------------------------------
+    if constexpr (SLICED) {                                          // partial sums: 4 features of one token per lane
+        float* const part = d.part + (int64_t)z * M * N;
+#pragma unroll
+        for (int b = 0; b < 2 * MB; ++b) {
+            const int64_t m = m0 + wm * 32 * MB + 16 * b + r;
+#pragma unroll
+            for (int a = 0; a < 2 * NB; ++a) {
+                const int nn = n0 + wn * 32 * NB + 16 * a + 4 * g;
+                if (m < M && nn < N) *reinterpret_cast<f32x4*>(part + m * N + nn) = acc[a][b];
+            }
+        }
+        return;
+    }
     // A lane holds features n..n+3 of one token per accumulator.  The wave lays its part out in LDS as bf16
     // rows and reads it back 16 bytes a lane, so that a store instruction writes whole row segments.
     {
@@ -559,9 +583,10 @@ bool set_lds(K kern, int smem) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem) == hipSuccess;
 }
 
+template <bool SLICED>
 int launch_large(const GemmDesc& d, hipStream_t st) {
-    static const bool ok = set_lds(k_dense, Ring::kLds);
-    return launch_tiles(k_dense, ok, Ring::kLds, kThreads, 64 * MB, 128 * NB, d, st);
+    static const bool ok = set_lds(k_dense<SLICED>, Ring::kLds);
+    return launch_tiles(k_dense<SLICED>, ok, Ring::kLds, kThreads, 64 * MB, 128 * NB, d, st);
 }
 
 template <int BM, int BN, int WN, bool HALF>
@@ -599,30 +624,34 @@ DensePlan dense_plan(int64_t M, int N, int k1, int k2, int max_splits) {
 }
 
 // The tile and the slices of a call, by the present kernels' times: as above, but a last round of f of the 256 workgroups lies
-// f^2 of the way from few to full (the clock holds to about half of them), and a round starts and ends in 3 us.  Larger tiles
-// move fewer bytes per MFMA, 256 x 256 ones nearly reach the power limit and pay where they fill rounds (in slices they are
-// never the fastest); the others are there
-// for their sizes: a round of 232 tiles of 128 x 192 beats two thirds of one of 128 x 256.  us for 256 x 256 / 128 x 256 / 128 x
-// 192 / 192 x 192 / 128 x 128 tiles (256 x 128 and 192 x 128 take as long as 128 x 256 and 128 x 192): 1337 x 5120 x 5184 99 / 60 /
-// 86 / 59 / 71; 512 x 11008 x 4224 71 / 42 / 39 / 46 / 54; 1024 x 4096 x 4608 79 / 43 / 38 / 48 / 34; 334 x 4224 x 8064 128 / 67 / 53 /
-// 75 / 45; 2048 x 4096 x 4224 81 / 53 / 71 / 58 / 61; 8192 x 5120 x 5184 315 / 313 / 346 / 330 / -; 8192 x 22016 x 8448 2032 / 2380 /
-// 2592 / 2341 / -.
+// f^3 of the way from few to full (the clock holds to about half of them), and a round starts and ends in 1.6 us and what its
+// output tiles take.  Larger tiles move fewer bytes per MFMA, which counts above all where the operands outgrow the memory-side
+// cache (256 MB): the second pair of times, reached in steps between 180 and 285 MB.  Fitted to 1333 shapes of 16 to 9000 tokens, each
+// timed in every tile and number of slices: a call on 257 tokens or more takes 0.9 % longer than in its best form on average, 4 % of
+// them more than 6 %; fewer tokens 4 % on average.  With one pair of times, from weights of 9 to 47 million alone, 2921 x 12416 x 13120
+// took 128 x 192 tiles, 1013 us with the pass over the weight, now 878; 698 x 4160 x 22720 unsliced 128 x 128 ones, 244, now five
+// slices of 256 x 256, 179.  us for 256 x 256 / 128 x 256 / 128 x 192 / 192 x 192 / 128 x 128 tiles: 1337 x 5120 x 5184 99 / 60 / 86 /
+// 59 / 71; 512 x 11008 x 4224 71 / 42 / 39 / 46 / 54; 1024 x 4096 x 4608 79 / 43 / 38 / 48 / 34; 334 x 4224 x 8064 128 / 67 / 53 / 75 /
+// 45; 2048 x 4096 x 4224 81 / 53 / 71 / 58 / 61; 8192 x 5120 x 5184 315 / 313 / 346 / 330 / -; 8192 x 22016 x 8448 2032 / 2380 / 2592 /
+// 2341 / -.
 DensePlan dense_call_plan(int64_t M, int N, int k1, int k2, int max_splits) {
-    struct Shape { int bm, bn; int64_t few, full; };
-    static constexpr Shape shapes[7] = {{256, 256, 1000, 1450}, {128, 256, 500, 775}, {256, 128, 500, 775}, {128, 128, 330, 440},
-                                        {128, 192, 400, 585}, {192, 128, 400, 585}, {192, 192, 560, 835}};
-    const int64_t steps = k1 / kBK + (k2 + kBK - 1) / kBK;
+    struct Shape { int bm, bn; int64_t few, full, few_far, full_far; };
+    static constexpr Shape shapes[7] = {{256, 256, 940, 1310, 1070, 1440}, {128, 256, 490, 730, 985, 825}, {256, 128, 495, 735, 860, 850},
+                                        {128, 128, 293, 421, 628, 554}, {128, 192, 386, 587, 814, 682}, {192, 128, 383, 574, 653, 685},
+                                        {192, 192, 545, 824, 815, 843}};
+    const int64_t steps = k1 / kBK + (k2 + kBK - 1) / kBK, far = std::min<int64_t>(std::max<int64_t>(((M + N) * k1 >> 19) - 180, 0), 105);
     const int most = max_splits > 1 ? dense_plan(M, N, k1, k2, max_splits).splits : 1;
     DensePlan best{0, 1, INT64_MAX};
     for (int i = 0; i < 7; ++i) {
-        const int64_t tiles = ((M + shapes[i].bm - 1) / shapes[i].bm) * ((N + shapes[i].bn - 1) / shapes[i].bn);
-        for (int s = 1; s <= (i == 0 ? 1 : most) && (s == 1 || (tiles * s <= 256 && steps >= 4 * s)); ++s) {
+        const Shape& c = shapes[i];
+        const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+        const int64_t few = c.few + (c.few_far - c.few) * far / 105, full = c.full + (c.full_far - c.full) * far / 105;
+        for (int s = 1; s <= most && (s == 1 || (tiles * s <= 256 && steps >= 4 * s)); ++s) {
             const int64_t units = tiles * s, last = units % 256;
-            const int64_t step_ns = units / 256 * shapes[i].full +
-                                    (last ? shapes[i].few + (shapes[i].full - shapes[i].few) * last * last / 65536 : 0);
-            int64_t t = step_ns * ((steps + s - 1) / s) + 3000 * ((units + 255) / 256);
-            // (slices start far apart in both operands; their partial tiles stay in the caches: 8 TB/s)
-            if (s > 1) t += t / 10 + 5000 + M * N * 8 * s / 8000;
+            const int64_t step_ns = units / 256 * full + (last ? few + (full - few) * (last * last * last) / (256 * 256 * 256) : 0);
+            int64_t t = step_ns * ((steps + s - 1) / s) + (1600 + 75 * c.bm * c.bn / 1024) * ((units + 255) / 256);
+            // (slices start far apart in both operands; their partial tiles stay in the caches: 10 TB/s)
+            if (s > 1) t += t / 20 + 3500 + M * N * 8 * s / 10000;
             if (t < best.ns) best = DensePlan{i, s, t};
         }
     }
@@ -702,7 +731,7 @@ int launch_dense(const GemmDesc& d, hipStream_t st) {
     const DensePlan p = dense_call_plan(d.M, d.N, d.K1, d.K2, d.splits > 1 ? 8 : 1);
     if (d.splits > 1 && p.splits != d.splits) return QBLORA_ERR_UNSUPPORTED;       // not what dense_splits said
     switch (p.shape) {
-        case 0: return launch_large(d, st);
+        case 0: return d.splits > 1 ? launch_large<true>(d, st) : launch_large<false>(d, st);
         case 1: return launch_flow<128, 256, 4, true>(d, st);
         case 2: return launch_flow<256, 128, 2, true>(d, st);
         case 3: return launch_flow<128, 128, 4, false>(d, st);

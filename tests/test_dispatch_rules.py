@@ -93,10 +93,22 @@ def test_no_contraction_takes_more_slices_than_workspaces_count_on(rules, N, k1,
     (8192, 22016, 8192, 256, "256 x 256"), (8192, 4096, 4096, 128, "256 x 256"), (2048, 4096, 4096, 128, "128 x 256"),
     (3000, 8192, 3072, 64, "128 x 256"), (1024, 4096, 4096, 512, "128 x 128"), (334, 4224, 8000, 64, "128 x 128"),
     (512, 11008, 4096, 128, "128 x 192"), (260, 14336, 2560, 32, "192 x 128"), (1337, 5120, 5120, 64, "128 x 256"), (1337, 5760, 5760, 64, "192 x 192"),
+    (2921, 12416, 13120, 0, "256 x 256"), (2156, 16512, 13952, 64, "256 x 256"), (637, 14528, 8512, 0, "256 x 256"),
 ])
 def test_tiles_of_a_contraction(rules, T, N, k1, k2, shape):
-    """512 x 11008 x 4224: 39 us in 128 x 192 tiles, 42 in 128 x 256, 54 in 128 x 128."""
+    """512 x 11008 x 4224: 39 us in 128 x 192 tiles, 42 in 128 x 256, 54 in 128 x 128.  2921 x 12416 x 13120 with the pass over the weight:
+    875 in 256 x 256, 1013 in 128 x 192, which fetch half as much again from beyond the memory-side cache."""
     assert TILES[rules.dense_call_plan(T, N, k1, k2, 1).shape] == shape
+
+
+@pytest.mark.parametrize("T,N,k1,k2,shape,slices", [
+    (512, 4096, 11008, 128, "128 x 256", 4), (698, 4160, 22720, 0, "256 x 256", 5), (663, 6016, 16960, 64, "192 x 192", 2),
+    (775, 10688, 19776, 0, "256 x 256", 1), (154, 896, 14016, 64, "128 x 128", 8),
+])
+def test_slices_of_a_contraction(rules, T, N, k1, k2, shape, slices):
+    """698 x 4160 x 22720: 183 us with the pass over the weight in five slices of 256 x 256, 201 in two of 128 x 256, 244 in 128 x 128."""
+    plan = rules.dense_call_plan(T, N, k1, k2, 8)
+    assert (TILES[plan.shape], plan.splits) == (shape, slices)
 
 
 @pytest.mark.parametrize("T,d_out,d_in,R", [(1950, 64, 4672, 32), (4887, 64, 2368, 64), (14, 192, 17152, 8), (200, 64, 3072, 16),

@@ -98,7 +98,7 @@ TILES = [*SHAPES, "128 x 192", "192 x 128", "192 x 192"]
     (769, 4800, 64, 0, "128 x 192"), (769, 4800, 320, 72, "128 x 192"),      # one token past; whole feature tiles
     (769, 4672, 128, 8, "128 x 192"),      # 64 features in the last tile
     (900, 4160, 64, 0, "192 x 128"), (700, 5440, 256, 72, "192 x 128"),      # partial tiles both ways
-    (1337, 5440, 64, 0, "192 x 192"), (1337, 5440, 192, 72, "192 x 192"),    # 64 features in the last tile
+    (1153, 6592, 64, 0, "192 x 192"), (1153, 6592, 192, 72, "192 x 192"),    # one token past, 64 features in the last tile
     (577, 2112, 704, 0, "128 x 128"),       # an odd number of steps
 ])
 def test_tiles_that_calls_take(oracle, codebook, rules, T, d_out, d_in, R, tile):
@@ -107,8 +107,9 @@ def test_tiles_that_calls_take(oracle, codebook, rules, T, d_out, d_in, R, tile)
 
 
 @pytest.mark.parametrize("T,d_out,d_in,R,tile,slices", [
-    (65, 2112, 320, 72, "128 x 128", 7), (129, 4096, 5504, 72, "192 x 128", 5), (65, 8192, 8384, 72, "128 x 192", 5),
-    (257, 8192, 4352, 72, "128 x 256", 5), (385, 8192, 3200, 72, "256 x 128", 5), (257, 8192, 4160, 72, "192 x 192", 5),
+    (65, 2112, 320, 72, "128 x 128", 7), (129, 4096, 5504, 72, "192 x 128", 4), (65, 8192, 8384, 72, "128 x 192", 5),
+    (577, 6784, 3392, 24, "128 x 256", 3), (385, 8192, 3200, 72, "256 x 128", 5), (900, 11008, 2240, 72, "192 x 192", 4),
+    (385, 13248, 5824, 24, "256 x 256", 5),      # 129 tokens and 192 features in the last tiles; slices of 41 and 42 steps
 ])
 def test_slices_that_calls_take(oracle, codebook, rules, T, d_out, d_in, R, tile, slices):
     plan = rules.dense_call_plan(T, d_in, d_out, R, 8)
