@@ -81,12 +81,18 @@ def test_partial_sum_rows_are_the_most_of_any_count(rules, N, k1, k2):
         assert rows(T, N, k1, k2) == most, T
 
 
-@pytest.mark.parametrize("N,k1,k2", [(512, 512, 0), (4096, 11008, 128), (4160, 448, 8), (11008, 4096, 1376), (64, 22016, 0)])
+@pytest.mark.parametrize("N,k1,k2", [(512, 512, 0), (4096, 11008, 128), (4160, 448, 8), (11008, 4096, 1376), (64, 22016, 0), (4160, 22720, 24)])
 def test_no_contraction_takes_more_slices_than_workspaces_count_on(rules, N, k1, k2):
-    for T in [*range(1, 700, 7), 768, 769, 1024, 1337, 2048, 8192]:
+    """The rows of partial sums of every number of tokens, against what the workspace query reserves for it and for any larger one."""
+    rows = rules.L["_ZN6qblora15dense_part_rowsEliii"]
+    rows.argtypes, rows.restype = [C.c_int64, C.c_int, C.c_int, C.c_int], C.c_int64
+    taken = reserved = 0
+    for T in [*range(1, 1500), 2048, 8192]:
         call = rules.dense_call_plan(T, N, k1, k2, 8)
-        assert 1 <= call.splits <= rules.dense_plan(T, N, k1, k2, 8).splits
-        assert rules.dense_call_plan(T, N, k1, k2, 1).splits == 1
+        assert call.splits >= 1 and rules.dense_call_plan(T, N, k1, k2, 1).splits == 1
+        taken = max(taken, call.splits * T if call.splits > 1 else 0)
+        assert taken <= rows(T, N, k1, k2), T
+        assert reserved <= (reserved := rows(T, N, k1, k2))
 
 
 @pytest.mark.parametrize("T,N,k1,k2,shape", [

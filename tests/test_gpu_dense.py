@@ -7,14 +7,14 @@ from paper_2407_17029_amd import synth
 
 pytestmark = pytest.mark.gpu
 
-# T, d_out, d_in, R: the tile shape follows from T and the output width (256 x 256, 128 x 256, 256 x 128 and 128 x 128
-# tokens x features; forward and backward differ), the number of 64-wide steps from the other width (one step up to
-# more than the ring holds), R adds none, one partial or two steps of the K-extension.  Backward contractions of few
-# output tiles are sliced, most of these in 128 x 128 tiles; the other tiles in slices are below.
+# T, d_out, d_in, R: the tiles (tokens x features; forward and backward differ) follow from T and the output width, the number of
+# 64-wide steps from the other width (one step up to more than the ring holds), R adds none, one partial or two steps of the
+# K-extension.  Backward contractions of few output tiles are sliced, in 128 x 128 tiles here; the other tiles in slices are
+# below.
 CASES = [
-    (4100, 4096, 64, 0),       # 256 x 256, one step; backward 128 x 128, 64 steps
-    (4100, 4096, 128, 72),     # 256 x 256, two steps and a ragged extension
-    (4097, 4160, 192, 8),      # 256 x 256, one token and 64 features past a tile, three steps
+    (4100, 4096, 64, 0),       # 192 x 192, one step; backward 128 x 128, 64 steps
+    (4100, 4096, 128, 72),     # 192 x 192, two steps and a ragged extension
+    (4097, 4160, 192, 8),      # 192 x 192, three steps, partial tiles on both sides
     (2048, 4096, 64, 8),       # 128 x 256, one step
     (1930, 4032, 256, 0),      # 128 x 256, partial tiles on both sides, as many steps as stages and one more
     (1270, 6528, 64, 0),       # 256 x 128, one step
@@ -23,8 +23,9 @@ CASES = [
     (300, 320, 64, 24),        # 128 x 128, fewer steps than stages
     (1, 448, 128, 16),         # backward of one token; forward few
     (200, 2112, 192, 72),      # backward in slices of 128 x 128 tiles, the last one with the ragged extension; forward few
-    (1000, 4160, 448, 0),      # backward in slices, no adapter, partial tiles on both sides
-    (513, 8256, 2048, 8),      # backward in slices of 128 x 128 tiles; forward from the codes
+    (1000, 4160, 448, 0),      # backward in slices, no adapter, partial tiles on both sides; forward 128 x 192
+    (513, 8256, 2048, 8),      # backward in slices of 128 x 128 tiles; forward 192 x 128, 64 features in the last
+    (700, 8256, 1024, 8),      # forward from the codes
 ]
 
 
@@ -52,27 +53,29 @@ def test_tiles_and_stages(oracle, codebook, T, d_out, d_in, R):
     assert_close_bf16(Y, oracle.forward(Wt, L.X, A, B, 2, 2, s), "Y")
     assert_close_bf16(dX, oracle.backward(Wt, L.X, L.dY, A, B, 2, 2, s)[0], "dX")
     # the form that rebuilds weight tiles in LDS adds in the same order (of 1 and 200 tokens both take the one for few,
-    # of 513 both take this one)
+    # of 700 both take this one)
     Y2 = torch.empty_like(Y)
     qb.qblora_linear_fwd_noalloc(qw, ad, X, Y2)
     torch.cuda.synchronize()
     assert torch.equal(Y.view(torch.int16), Y2.view(torch.int16))
 
 
-SHAPES = ["256 x 256", "128 x 256", "256 x 128", "128 x 128"]
+TILES = ["256 x 256", "128 x 256", "256 x 128", "128 x 128", "128 x 192", "192 x 128", "192 x 192"]
 
 
-@pytest.mark.parametrize("T,d_out,d_in,R,shape,slices", [
-    (513, 4096, 6592, 72, "256 x 256", 3),     # one token past two tiles, 192 features in the last
-    (257, 4096, 5440, 0, "128 x 256", 3),      # one token past two tiles, 64 features in the last
-    (385, 6144, 3136, 24, "256 x 128", 5),     # steps that do not divide evenly
+@pytest.mark.parametrize("T,d_out,d_in,R,tile,slices", [
+    (577, 6784, 3392, 24, "128 x 256", 3),     # 65 tokens and 64 features in the last tiles; steps that do not divide evenly
+    (700, 7168, 2880, 24, "256 x 128", 3),     # 188 and 64, uneven
+    (257, 3904, 3648, 72, "192 x 128", 4),     # 65 and 64, uneven, a ragged extension of two steps
+    (385, 4672, 2752, 72, "128 x 192", 4),     # one token past three tiles, 64, uneven
+    (65, 1024, 64, 72, "128 x 128", 4),        # half a tile both ways, 18 steps
 ])
-def test_slices_of_every_tile(oracle, codebook, rules, T, d_out, d_in, R, shape, slices):
+def test_slices_of_partial_tiles(oracle, codebook, rules, T, d_out, d_in, R, tile, slices):
     from paper_2407_17029_amd import binding as qb
     from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, OracleWeight
     print(f"case dense slices T={T} {d_out}x{d_in} R={R}", flush=True)
-    plan = rules.dense_plan(T, d_in, d_out, R, 8)
-    assert rules.dense_pays_t(T, d_in, d_out, R) and (SHAPES[plan.shape], plan.splits) == (shape, slices)
+    plan = rules.dense_call_plan(T, d_in, d_out, R, 8)
+    assert rules.dense_pays_t(T, d_in, d_out, R) and (TILES[plan.shape], plan.splits) == (tile, slices)
     L = synth.make_layer(5200 + T, T, d_out, d_in, max(R, 8), 2, 2, b_std=0.05)
     qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook, tiled=False)
     Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)
@@ -84,11 +87,11 @@ def test_slices_of_every_tile(oracle, codebook, rules, T, d_out, d_in, R, shape,
     assert_close_bf16(dX, oracle.backward(Wt, L.X, L.dY, A, B, 2, 2, s)[0], "dX")
 
 
-TILES = [*SHAPES, "128 x 192", "192 x 128", "192 x 192"]
-
-
 @pytest.mark.parametrize("T,d_out,d_in,R,tile", [
     (2049, 4480, 64, 8, "256 x 256"),       # one step and the extension; one token and half a tile past
+    (8193, 1088, 64, 0, "256 x 256"),       # a single step; one token and 64 features past
+    (7000, 1216, 64, 0, "256 x 256"), (7000, 1216, 192, 0, "256 x 256"),     # one and three steps; 88 tokens, 192 features in the last
+    (7000, 1216, 128, 72, "256 x 256"),     # two steps and a ragged extension of two
     (1025, 5440, 64, 0, "128 x 256"),       # a single step
     (1025, 5440, 192, 72, "128 x 256"),     # as many steps as stages, and a ragged extension
     (1930, 3200, 128, 72, "256 x 128"),     # one more
@@ -123,7 +126,7 @@ def test_slices_with_a_single_matrix_adapter(oracle, codebook, rules):
     from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, assert_close_f32, OracleWeight
     T, d_out, d_in, lam = 300, 2112, 1088, 8
     print(f"case dense slices, single matrix T={T} {d_out}x{d_in}", flush=True)
-    assert rules.dense_pays_t(T, d_in, d_out, d_out // lam) and rules.dense_plan(T, d_in, d_out, d_out // lam, 8).splits > 1
+    assert rules.dense_pays_t(T, d_in, d_out, d_out // lam) and rules.dense_call_plan(T, d_in, d_out, d_out // lam, 8).splits > 1
     L = synth.make_layer(5300, T, d_out, d_in, 8, lam, lam)
     qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook, tiled=False)
     Wt = OracleWeight(oracle, L.W, codebook).assert_same(qw).dequantize(oracle, 2)

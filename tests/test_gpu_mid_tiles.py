@@ -40,3 +40,13 @@ def test_token_tiles(oracle, codebook, rules, T, d_out, d_in, fmt):
 ])
 def test_copying_waves_on_short_slices(oracle, codebook, rules, T, d_out, d_in, fmt):
     test_token_tiles(oracle, codebook, rules, T, d_out, d_in, fmt)
+
+
+@pytest.mark.parametrize("fmt", [f for f in FORMATS if "8x" not in f])
+@pytest.mark.parametrize("T,d_out,d_in", [
+    (161, 37, 64), (201, 130, 256), (255, 257, 448),           # one slice: odd rows, pairs of rows, one row past two tiles
+    (161, 130, 2048), (201, 37, 832), (255, 257, 1088), (193, 2, 576), (256, 1, 1024),     # slices whose sums are no whole words
+])
+def test_copying_waves_on_odd_outputs(oracle, codebook, rules, T, d_out, d_in, fmt):
+    """Outputs in 64-blocks may be any number: single stores, block parameters up to the last row, the sums' scalar path."""
+    test_token_tiles(oracle, codebook, rules, T, d_out, d_in, fmt)

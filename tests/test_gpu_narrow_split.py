@@ -54,7 +54,7 @@ def test_sliced_narrow_gemms_of_the_other_operators(oracle, codebook, rules, T, 
     from paper_2407_17029_amd import binding as qb
     from gpu_util import f32_to_dev, bf16_to_dev, assert_close_bf16, assert_close_f32, OracleWeight
     print(f"case narrow split op={op} T={T} {d_out}x{d_in} R={R} lam={lam}", flush=True)
-    assert rules.dense_pays_t(T, d_in, d_out, R) and rules.dense_plan(T, d_in, d_out, R, 8).splits > 1
+    assert rules.dense_pays_t(T, d_in, d_out, R) and rules.dense_call_plan(T, d_in, d_out, R, 8).splits > 1
     L = synth.make_layer(6200 + T + R, T, d_out, d_in, R, lam, lam)
     qw = qb.qblora_quantize_blockwise(f32_to_dev(L.W), 64, qb.QUANT_ABSMAX_CODEBOOK, codebook)
     torch.cuda.synchronize()
