@@ -693,12 +693,12 @@ bool weight_stays(int64_t N, int k1) { return N * k1 * 2 < (int64_t)256 << 20; }
 }  // namespace
 
 // The one-off pass takes 0.46 to 0.5 us per million weights, in a launch that both forms have (the re-layouts' or the narrow
-// GEMM's sums'); the kernel from the codes wins on wide layers with few tokens.  us from the codes / dequantized first: 512 x
-// 22016 x 8192 190 / 265, 512 x 16384 x 8192 138 / 194, 1024 x 16384 x 8192 233 / 257, 512 x 4096 x 4096 70 / 46, 2048 x 22016 x
-// 8192 632 / 610, and with the present tiles 512 x 11008 x 4096 86 / 72 (with the narrow GEMM and what
-// shares its launches).  On weights whose 16-bit form outgrows the memory-side cache
-// the first line stands, measured with the figures of dense_plan (a margin of 5 % for the estimates' errors: without it 72 of
-// 1134 measured calls lose up to 9 % of their time, with it three lose 3 % and 207 gain 17 % on average).
+// GEMM's sums'); the kernel from the codes wins on wide layers with few tokens.  us from the codes / dequantized first, without
+// adapter: 512 x 22016 x 8192 223 / 264, 512 x 16384 x 8192 150 / 201, 1024 x 16384 x 8192 249 / 251, 650 x 8192 x 22016 363 / 361, 512 x
+// 4096 x 4096 72 / 37, 512 x 11008 x 4096 77 / 64, 2048 x 22016 x 8192 680 / 616.  On weights whose 16-bit form outgrows the memory-side
+// cache the first line stands alone, with the figures of dense_plan: those of dense_call_plan would send 560 to 740 x 8192 x 22016
+// the other way (337 to 363 / 361 to 370), though 560 x 28672 x 8192 rightly (415 / 365).  Over 314 shapes near the line a call takes
+// 0.8 % longer than the faster way on average, 1.0 % on those weights.
 bool dense_pays(int64_t M, int N, int k1, int k2) {
     const int64_t codes = qlinear_ns(M, N, k1 + (k2 + kBK - 1) / kBK * kBK), weights = (int64_t)N * k1;
     const int64_t first = dense_plan(M, N, k1, k2, 1).ns + weights * 46 / 100000 + 2000;
@@ -707,9 +707,11 @@ bool dense_pays(int64_t M, int N, int k1, int k2) {
 }
 
 // The transposed weight's pass takes 0.62 us per million weights with the gradients' sums, and its contraction may be sliced,
-// which the one from the codes is not.  us from the codes / dequantized first, 8192 x 22016: 64 tokens 122 / 185, 256 122 / 223,
-// 512 195 / 275, 700 376 / 401; 8192 x 8192 at 700 131 / 124.  On large weights a margin of 10 %: the slices' time is the less
-// certain (with 5 % two of 480 measured calls lose 6 and 10 %, with 10 % none).
+// which the one from the codes is not.  us from the codes / dequantized first, M x N x K, without adapter: 64 x 22016 x 8192 127 / 176,
+// 256 123 / 209, 512 198 / 268, 700 406 / 317; 700 x 8192 x 8192 142 / 108; 512 x 4096 x 11008 169 / 73; 512 x 11008 x 4096 72 / 61.  On
+// large weights a margin of 10 %: with the slices' times of dense_plan, 5 % lost 6 and 10 % on two of 480 measured calls, 10 % on
+// none.  Over 86 shapes near the line a call takes 2.1 % longer than the faster way on average, mostly for few tokens of wide
+// layers (126 x 17280 x 9664 151 / 181, and dequantized first).
 bool dense_pays_t(int64_t M, int N, int k1, int k2) {
     const int64_t codes = qlinear_ns(M, N, k1 + (k2 + kBK - 1) / kBK * kBK), weights = (int64_t)N * k1;
     const int64_t first = dense_plan(M, N, k1, k2, 8).ns + weights * 46 / 100000 + 2000;

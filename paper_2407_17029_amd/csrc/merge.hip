@@ -288,8 +288,9 @@ __global__ __launch_bounds__(256) void k_merge_beta_shift_tile8(MergeDesc d) {
 // times: before / now, us, 2048 x 5248 at lambda 4 to 16 bits 44.4 / 8.3, 8192 x 8192 at lambda 2 to 16 bits 245 / 41,
 // two of 8192 x 8192 requantized 501 / 67 in one launch, 4.5 TB/s.)  Bound: HBM.  A wave owns one row of blocks; two lanes
 // share a block, rows 4*sub .. +3 of eight inputs each, so a load of codes covers 128 bytes of two rows and a 16-bit store
-// 512.  A tile's block parameters are whole 128-byte lines, so the tiles need no order for their sake; tiles that are
-// neighbours along the rows share lines of H where lambda2 > 2 and are consecutive on one XCD.
+// 512.  A tile's block parameters are 128 bytes of a row of blocks (256 in blocks of four), whole lines where d_in is a multiple of
+// 256 (128), so the tiles need no order for their sake; tiles that are neighbours along the rows share lines of H where
+// lambda2 > 2 and are consecutive on one XCD.
 template <bool BETA, int L1, bool OUT16, int BC>
 __device__ __forceinline__ void merge_tile8(const MergeDesc& d, const unsigned wg) {
     __shared__ float lut[16];

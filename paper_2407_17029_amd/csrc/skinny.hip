@@ -429,13 +429,10 @@ int launch_cfg(const Call& c, hipStream_t st) {
     };
     const unsigned n = blocks(d);
     if (c.b) {
-        if constexpr (kByK && !kSplitK) return QBLORA_ERR_UNSUPPORTED;
-        else {
-            auto kern = k_skinny_pair<BM, BN, kStages, kSub, kSplitK, kDup, kByK>;
-            static const bool ok = set_lds(kern, smem);
-            if (!ok) return QBLORA_ERR_LAUNCH;
-            hipLaunchKernelGGL(kern, dim3(n + blocks(*c.b)), dim3(kThreads), smem, st, SkinnyPair{d, *c.b, n});
-        }
+        auto kern = k_skinny_pair<BM, BN, kStages, kSub, kSplitK, kDup, kByK>;
+        static const bool ok = set_lds(kern, smem);
+        if (!ok) return QBLORA_ERR_LAUNCH;
+        hipLaunchKernelGGL(kern, dim3(n + blocks(*c.b)), dim3(kThreads), smem, st, SkinnyPair{d, *c.b, n});
     } else if (c.prep && kByK) {
         if constexpr (kByK) {
             static_assert(smem >= (size_t)kPrepLds, "both jobs share the LDS");

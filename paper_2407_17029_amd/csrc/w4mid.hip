@@ -751,7 +751,8 @@ int slices_of(int want, int steps) {
 // (the weight stream wants loads in flight), about 400 at 128 (two resident per CU; more slices only add partial
 // tiles) -- while 64- or 96-row workgroups differ from 128-row ones by a few percent at most; one slice per row tile,
 // which the balance of matrix work alone would choose at 128 tokens, is 20 % slower than two.  Above 128 tokens a
-// workgroup's ring of token tiles takes a CU's LDS: as many slices as one round of 256 workgroups holds.
+// workgroup's ring of token tiles takes a CU's LDS: as many slices as one round of 256 workgroups holds (measured with
+// k_w4_mid, not again with k_w4_wide).
 int w4_mid_splits(int d_out, int d_in, int T) {
     const int tiles_n = (d_out + kMidRows - 1) / kMidRows, target = T > 64 ? 400 : 700;
     return slices_of(T > 128 ? 256 / tiles_n : (target + tiles_n / 2) / tiles_n, d_in / kBlock);
